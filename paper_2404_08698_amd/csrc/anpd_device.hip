@@ -732,29 +732,42 @@ int32_t run_step_mega(anpd_model *m, anpd_kv *kv, const int32_t *window, int M, 
 // ---- prompt processing on the matrix cores ------------------------------------
 
 template <int EPI, int TN>
-int32_t launch_prefill_gemm_tn(const PrefillArgs &a, int n_bt, int n_br, hipStream_t st)
+int32_t launch_prefill_gemm_tn(const PrefillArgs &a, hipStream_t st)
 {
     static bool attr_set = false;   // per instantiation
     if (!attr_set) {
-        HIP_TRY(hipFuncSetAttribute((const void *)prefill_gemm_kernel<EPI, TN>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPgLdsBytes));
+        HIP_TRY(hipFuncSetAttribute((const void *)prefill_gemm_kernel<EPI, TN>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pg_lds_bytes(TN)));
         attr_set = true;
     }
-    hipLaunchKernelGGL((prefill_gemm_kernel<EPI, TN>), dim3((unsigned)(n_bt * a.S * n_br)), dim3(kPgThreads), kPgLdsBytes, st, a);
+    const int blocks = (a.n_tiles + 4 * TN - 1) / (4 * TN) * a.S * ((a.G + 7) / 8);
+    hipLaunchKernelGGL((prefill_gemm_kernel<EPI, TN>), dim3((unsigned)blocks), dim3(kPgThreads), pg_lds_bytes(TN), st, a);
     HIP_TRY(hipGetLastError());
     return ANPD_OK;
 }
 
-// Blocks of 256 or of 192 output features, whichever takes fewer rounds of the chip's compute units, a
-// round of the smaller block counted as kPfSmallBlock of the larger one's (measured at the 7B shape: 0.85 - 0.89).
-constexpr double kPfSmallBlock = 0.87;
+// Blocks of 64 TN features: the TN whose grid takes the least time, counted in rounds of the chip's compute
+// units times the measured time of one round (us at K = 4096; the same within 3 % at one round of 512 rows and
+// at 4 to 19 rounds of 3584 rows).  Wider blocks read less per MFMA, narrower ones leave fewer compute units idle
+// in the last round: 512 rows of the 7B shape take TN 6 for gate/up (158 us; TN 2 / 3 / 4: 191 / 180 / 204), 3 for
+// QKV (97; 2 / 4 / 6: 128 / 108 / 144) and 4 for O and down; 205 rows of the ChatGLM3 shape take 2 for all but gate/up.
+constexpr double kPgRound[7] = {0, 0, 66, 90, 106, 126, 150};
 template <int EPI>
 int32_t launch_prefill_gemm(const PrefillArgs &a, int n_cu, hipStream_t st)
 {
-    const int n_br = (a.G + 7) / 8;
-    const int bt4 = (a.n_tiles + 15) / 16, bt3 = (a.n_tiles + 11) / 12;
-    const int rounds4 = (bt4 * a.S * n_br + n_cu - 1) / n_cu, rounds3 = (bt3 * a.S * n_br + n_cu - 1) / n_cu;
-    const bool small = kPfSmallBlock * rounds3 < (double)rounds4;
-    return small ? launch_prefill_gemm_tn<EPI, 3>(a, bt3, n_br, st) : launch_prefill_gemm_tn<EPI, 4>(a, bt4, n_br, st);
+    int best = 0;
+    double least = 0;
+    for (int tn = 6; tn >= 2; --tn) {
+        const long long blocks = (long long)((a.n_tiles + 4 * tn - 1) / (4 * tn)) * a.S * ((a.G + 7) / 8);
+        const double t = kPgRound[tn] * (double)((blocks + n_cu - 1) / n_cu);
+        if (best == 0 || t < least) { least = t; best = tn; }
+    }
+    switch (best) {
+    case 2: return launch_prefill_gemm_tn<EPI, 2>(a, st);
+    case 3: return launch_prefill_gemm_tn<EPI, 3>(a, st);
+    case 4: return launch_prefill_gemm_tn<EPI, 4>(a, st);
+    case 5: return launch_prefill_gemm_tn<EPI, 5>(a, st);
+    default: return launch_prefill_gemm_tn<EPI, 6>(a, st);
+    }
 }
 
 // All P rows at once; per layer norm -> QKV(+RoPE, cache write) -> attention -> O(+residual) -> norm ->

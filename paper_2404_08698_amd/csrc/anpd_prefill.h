@@ -4,7 +4,7 @@
 // Algorithm 1: before any drafting the LLM reads the prompt once, which fills
 // the (k, v) cache and yields the first generated token.  With hundreds of
 // rows the GEMMs are bound by the matrix cores, not by weight streaming, so
-// they get a form of their own: every wave owns a 64-feature x 64-row output
+// they get a form of their own: every wave owns a 16 TN-feature x 64-row output
 // tile, a weight fragment meets 4 row groups (each as hi and lo term) instead
 // of one, and the eight waves of a block share their fragments through LDS.
 //
@@ -24,17 +24,15 @@
 // lane holding columns 32 ks + 8 kg .. + 8 of row m: the B fragment of
 // v_mfma_f32_16x16x32_bf16, loaded with one coalesced 1 KiB read.
 #pragma once
+#include <utility>
+
 #include "anpd_fast.h"
 
 namespace anpd {
 
 constexpr int kPgThreads = 512;       // GEMM block: 8 waves, 4 (features) x 2 (rows)
-constexpr int kPfTN = 4, kPfTM = 4;   // wave tile: 4 weight tiles x 4 row groups
-constexpr int kPgStages = 4;          // LDS ring of k-steps
-constexpr int kPgLead = 2;            // k-steps per block barrier (a round); the next round is requested one round ahead
-constexpr int kPgUnits = 32;          // 1 KiB fragments per k-step: 16 weight tiles, 8 row groups x (hi, lo)
+constexpr int kPfTM = 4;              // row groups per wave
 constexpr int kPgSplit = 4;           // K splits of the residual GEMMs
-constexpr size_t kPgLdsBytes = (size_t)kPgStages * kPgUnits * 1024;
 
 struct PrefillArgs {
     const uint4 *Wp;      // packed weights [n_tiles][nks][64]
@@ -225,25 +223,35 @@ __device__ __forceinline__ void prefill_epilogue(const PrefillArgs &a, int tile,
 // -------------------------------------------------------------------- GEMM
 //
 // Y^T[features][rows] = W X^T with hi and lo terms of X accumulated into the
-// same tile.  Block = 4 x 2 waves, 256 features x 128 rows, each wave a
-// 64 x 64 tile (4 weight fragments x 4 row groups).  Per k-step the block
-// needs 16 weight fragments and 16 activation fragments of 1 KiB; each wave
-// requests four of them straight into LDS (buffer loads with the LDS bit:
-// lane i's 16 bytes land at base + 16 i, the fragment order itself; absent
-// tiles and row groups read zeros and fetch nothing), one round of two k-steps
-// ahead of the matrix cores through a ring of four stages, and every wave then
-// reads its 12 fragments per k-step from LDS.  A fragment thus crosses the
-// L2 -> CU path once per block instead of once per wave that uses it.
-// One block barrier per round of two k-steps: it publishes the two stages
-// whose loads the waves have just waited for, and frees the two stages read in
-// the previous round for the requests that follow it (one barrier per k-step
-// with three stages in flight measured 2 % slower).
+// same tile.  Block = 4 x 2 waves, 64 TN features x 128 rows, each wave
+// TN weight fragments x 4 row groups.  Per k-step the block needs 4 TN weight
+// fragments and 16 activation fragments of 1 KiB; each wave requests its share
+// of them straight into LDS (buffer loads with the LDS bit: lane i's 16 bytes
+// land at base + 16 i, the fragment order itself; absent tiles, row groups and
+// k-steps read zeros and fetch nothing) through a ring of k-steps, and every wave
+// then reads its TN + 8 fragments per k-step from LDS.  A fragment thus crosses
+// the L2 -> CU path once per block instead of once per wave that uses it.
+//
+// Three things take about the same time here - the matrix cores (8 TN MFMAs per wave and k-step), the LDS
+// reads (TN + 8 fragments per wave) and the L2 -> CU traffic (4 TN + 16 fragments per block; 85 GB/s per
+// compute unit at most) - so they have to run side by side: a wave holds the fragments of k-step i in one
+// set of registers while it reads those of k-step i + 1 into the other, one every few MFMAs, and the three
+// k-steps behind that are on their way into LDS.  One block barrier per k-step: it publishes the stage whose
+// loads every wave has just waited for and frees the stage that every wave has just finished reading.
+// Against two k-steps read and waited for before the first MFMA of either (256 features x 128 rows, traced,
+// 7B shape): gate/up of 512 rows 206 -> 158 us (TN 3 -> 6: one round of 232 blocks instead of two of 460),
+// QKV 107 -> 97, O + down 128 -> 117; of 3584 rows 1127 -> 1049, 705 -> 612, 814 -> 780.  What bounds it now is
+// the power limit more than any unit: at 3584 rows the clock is 1.95 GHz with the matrix cores busy two
+// thirds of the time (registers only, random operands: 2.0 PFLOP/s; the library's largest product: 1.53; here 1.23).
+// Tried: one barrier per two k-steps (no change at TN = 6, 5 % slower at TN = 2, whose loads have less time to land),
+// 32x32x16 MFMAs (registers only, random operands: 10 % slower).
+//
 // RESIDUAL GEMMs (few output features) are split S ways along K so that the
 // grid fills the chip; the S partial tiles go to `part` and are added to the
 // residual stream, in split order, by the norm kernel that follows.  S is
 // fixed by the matrix, never by the number of rows: a row's sums are formed
 // in the same order whatever else is in the batch.
-// grid: ceil(n_tiles / 16) * S * ceil(G / 8) blocks; rows run fastest, so
+// grid: ceil(n_tiles / (4 TN)) * S * ceil(G / 8) blocks; rows run fastest, so
 // consecutive blocks share a weight range.
 template <int OFF>
 __device__ __forceinline__ u32x4_t lds_read16(uint32_t addr)
@@ -253,14 +261,43 @@ __device__ __forceinline__ u32x4_t lds_read16(uint32_t addr)
     return v;
 }
 
-// TN: weight fragments per wave (4: the 256-feature tile above; 3: 192 features).  The launcher picks the
-// one whose grid fills the chip's compute units better (QKV of 512 rows: 192 blocks of 256 features, or 256
-// blocks of 192); an output element's sums do not depend on it.
-template <int EPI, int TN = kPfTN>
+// 16 bytes per lane from byte `offset` of the buffer to dst + 16 lane, without passing through registers
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t buffer, uint4 *dst, int offset)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer, (__attribute__((address_space(3))) void *)dst, 16, offset, 0, 0, 0);
+}
+
+// waits until at most N of this wave's loads are outstanding, then for the block
+template <int N>
+__device__ __forceinline__ void wait_loads_and_meet()
+{
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+// fragments per stage, loads per wave and stage, and stages of the ring
+__host__ __device__ constexpr int pg_units(int TN) { return 4 * TN + 16; }
+__host__ __device__ constexpr int pg_loads(int TN) { return (pg_units(TN) + 7) / 8; }
+constexpr int kPgStages = 4;
+__host__ __device__ constexpr size_t pg_lds_bytes(int TN) { return (size_t)kPgStages * pg_loads(TN) * 8 * 1024; }
+
+// calls f with 0, 1, ... as compile-time constants
+template <int... I, typename F>
+__device__ __forceinline__ void index_each(std::integer_sequence<int, I...>, F f)
+{
+    f(std::integral_constant<int, I>{}...);
+}
+
+// one wave's fragments of a k-step
+template <int TN>
+struct PgFrags {
+    u32x4_t w[TN], xh[kPfTM], xl[kPfTM];
+};
+
+template <int EPI, int TN>
 __global__ __launch_bounds__(kPgThreads) void prefill_gemm_kernel(PrefillArgs a)
 {
-    static_assert(TN == 3 || TN == 4, "a wave holds 3 or 4 weight fragments");
-    extern __shared__ uint4 ring[];   // [kPgStages][kPgUnits][64]
+    constexpr int kUnits = pg_units(TN), kLoads = pg_loads(TN), kStageUnits = kLoads * 8;
+    extern __shared__ uint4 ring[];   // [kPgStages][kStageUnits][64]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wf = wave & 3, wr = wave >> 2;
     const int n_br = (a.G + 7) / 8;
@@ -280,34 +317,37 @@ __global__ __launch_bounds__(kPgThreads) void prefill_gemm_kernel(PrefillArgs a)
     const int nks = a.nks;
     const int ks0 = (int)((long long)sp * nks / a.S), n_it = (int)((long long)(sp + 1) * nks / a.S) - ks0;
 
-    // this wave's share of a stage: units 4 wave .. 4 wave + 3 (waves 0..3 weights, 4..7 activations); with
-    // TN = 3 a weight wave's fourth unit is an empty descriptor (zeros, nothing fetched): every wave still
-    // issues four loads per stage, which is what the waits below count
-    __amdgpu_buffer_rsrc_t rs[4];
-    int uoff[4];
-    const int ustride = wave < 4 ? 1024 : 2048;
+    // this wave's share of a stage: units kLoads * wave .. + kLoads - 1 (units 0 .. 4 TN - 1 weights, then row
+    // groups x (hi, lo)); a unit past the end is an empty descriptor: every wave issues the same number of
+    // loads per stage, which is what the waits below count
+    __amdgpu_buffer_rsrc_t rs[kLoads];
+    int uoff[kLoads], ustride[kLoads];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        if (wave < 4) {
-            const int tile = F0 + TN * wave + j;
-            const bool have = j < TN && tile < a.n_tiles;
-            rs[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.Wp + (size_t)(have ? tile : 0) * nks * 64), 0,
-                                                      have ? nks * 1024 : 0, 0x00020000);
+    for (int j = 0; j < kLoads; ++j) {
+        const int u = kLoads * wave + j;
+        if (u < 4 * TN) {
+            const int tile = F0 + u;
+            const bool have = tile < a.n_tiles;
+            rs[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.Wp + ((size_t)(have ? tile : 0) * nks + ks0) * 64), 0,
+                                                      have ? n_it * 1024 : 0, 0x00020000);
             uoff[j] = 0;
+            ustride[j] = 1024;
         } else {
-            const int n_g = a.G - G0 < 8 ? a.G - G0 : 8;
-            const int u = 4 * (wave - 4) + j;   // (row group, hi | lo)
-            rs[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.Xq + (size_t)G0 * nks * 128), 0, n_g * nks * 2048,
-                                                      0x00020000);
-            uoff[j] = ((u >> 1) * nks * 2 + (u & 1)) * 1024;
+            // the descriptor ends with this row group's last k-step of the split
+            const int v = u - 4 * TN, g = G0 + (v >> 1);   // (row group, hi | lo)
+            const bool have = u < kUnits && g < a.G;
+            rs[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.Xq + ((size_t)(have ? g : 0) * nks + ks0) * 128), 0,
+                                                      have ? n_it * 2048 : 0, 0x00020000);
+            uoff[j] = (v & 1) * 1024;
+            ustride[j] = 2048;
         }
     }
-    auto request = [&](int it) {
-        uint4 *dst = ring + ((size_t)(it & (kPgStages - 1)) * kPgUnits + 4 * wave) * 64;
+    // stage `slot` of the ring <- k-step `it` (past the end: zeros, nothing fetched)
+    auto request = [&](int it, int slot) __attribute__((always_inline)) {
+        uint4 *dst = ring + ((size_t)slot * kStageUnits + kLoads * wave) * 64;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs[j], (__attribute__((address_space(3))) void *)(dst + j * 64), 16,
-                                                     uoff[j] + (ks0 + it) * ustride + lane * 16, 0, 0, 0);
+        for (int j = 0; j < kLoads; ++j)
+            load_to_lds(rs[j], dst + j * 64, uoff[j] + it * ustride[j] + lane * 16);
     };
 
     f32x4 acc[TN][kPfTM];
@@ -315,69 +355,72 @@ __global__ __launch_bounds__(kPgThreads) void prefill_gemm_kernel(PrefillArgs a)
     for (int t = 0; t < TN; ++t)
 #pragma unroll
         for (int g = 0; g < kPfTM; ++g) acc[t][g] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)ring;
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)ring + (uint32_t)lane * 16;
 
     // The fragment reads are written as assembly: reads the compiler can see would make it wait for
-    // every outstanding load into LDS first (it cannot tell the ring's stages apart), and the ring
-    // exists to keep three stages in flight.
-    auto read_stage = [&](u32x4_t (&w)[4], u32x4_t (&xh)[kPfTM], u32x4_t (&xl)[kPfTM], int it) {
-        const uint32_t sbase = lds_base + (uint32_t)(it & (kPgStages - 1)) * (kPgUnits * 1024) + (uint32_t)lane * 16;
-        const uint32_t aw = sbase + (uint32_t)(4 * wf) * 1024, ax = sbase + (uint32_t)(16 + 8 * wr) * 1024;
-        w[0] = lds_read16<0>(aw); w[1] = lds_read16<1024>(aw); w[2] = lds_read16<2048>(aw);
-        if (TN == 4) w[3] = lds_read16<3072>(aw);
-        else w[3] = w[2];
-        xh[0] = lds_read16<0>(ax); xh[1] = lds_read16<2048>(ax); xh[2] = lds_read16<4096>(ax); xh[3] = lds_read16<6144>(ax);
-        xl[0] = lds_read16<1024>(ax); xl[1] = lds_read16<3072>(ax); xl[2] = lds_read16<5120>(ax); xl[3] = lds_read16<7168>(ax);
+    // every outstanding load into LDS first (it cannot tell the ring's stages apart).
+    using Frags = PgFrags<TN>;
+    // read i of a stage: weight fragments, then the row groups' hi terms, then their lo terms
+    auto read_one = [&](auto index, Frags &f, uint32_t aw, uint32_t ax) __attribute__((always_inline)) {
+        constexpr int i = decltype(index)::value;
+        if constexpr (i < TN) f.w[i] = lds_read16<1024 * i>(aw);
+        else if constexpr (i < TN + 4) f.xh[i - TN] = lds_read16<2048 * (i - TN)>(ax);
+        else f.xl[i - TN - 4] = lds_read16<2048 * (i - TN - 4) + 1024>(ax);
     };
-    auto wait_reads = [&](u32x4_t (&w)[4], u32x4_t (&xh)[kPfTM], u32x4_t (&xl)[kPfTM]) {
+    auto wait_reads = [&](Frags &f) __attribute__((always_inline)) {
+        // (the second statement carries the remaining registers through the same wait)
         asm volatile("s_waitcnt lgkmcnt(0)"
-                     : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(xh[0]), "+v"(xh[1]), "+v"(xh[2]), "+v"(xh[3]),
-                       "+v"(xl[0]), "+v"(xl[1]), "+v"(xl[2]), "+v"(xl[3]));
+                     : "+v"(f.xh[0]), "+v"(f.xh[1]), "+v"(f.xh[2]), "+v"(f.xh[3]), "+v"(f.xl[0]), "+v"(f.xl[1]), "+v"(f.xl[2]), "+v"(f.xl[3]));
+#pragma unroll
+        for (int t = 0; t < TN; ++t) asm volatile("" : "+v"(f.w[t]));
     };
-    auto mma = [&](const u32x4_t (&w)[4], const u32x4_t (&xh)[kPfTM], const u32x4_t (&xl)[kPfTM]) {
-#pragma unroll
-        for (int t = 0; t < TN; ++t)
-#pragma unroll
-            for (int g = 0; g < kPfTM; ++g)
-                acc[t][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[t]), __builtin_bit_cast(bf16x8, xh[g]),
-                                                                    acc[t][g], 0, 0, 0);
-#pragma unroll
-        for (int t = 0; t < TN; ++t)
-#pragma unroll
-            for (int g = 0; g < kPfTM; ++g)
-                acc[t][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[t]), __builtin_bit_cast(bf16x8, xl[g]),
-                                                                    acc[t][g], 0, 0, 0);
+    // MFMA j of a k-step: every (weight, row group) pair's hi term, then every pair's lo term
+    auto mma_one = [&](const Frags &f, int j) __attribute__((always_inline)) {
+        const int t = (j % (4 * TN)) / 4, g = j % 4;
+        acc[t][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.w[t]),
+                                                            __builtin_bit_cast(bf16x8, j < 4 * TN ? f.xh[g] : f.xl[g]), acc[t][g], 0, 0, 0);
     };
-    // Two k-steps per block barrier.  The barrier of round j is reached by a wave once its own loads of
-    // stages 2j and 2j + 1 have landed (at most the two younger stages still outstanding) and its reads of
-    // the previous round's stages have returned; it publishes this round's stages and frees the previous
-    // round's slots for stages 2j + 2 and 2j + 3.  All four slots are requested before the first round.
-    u32x4_t wA[4], hA[kPfTM], lA[kPfTM], wB[4], hB[kPfTM], lB[kPfTM];
+    // The reads of the next k-step's fragments from stage `slot`, one every few MFMAs of this one's, the last
+    // some MFMAs before the end: issued in one go they would fill the LDS queue and hold up every wave's MFMAs
+    // until they are through.
+    auto interleave = [&](const Frags &cur, Frags &next, int slot) __attribute__((always_inline)) {
+        constexpr int NR = TN + 8, NM = 8 * TN, SPAN = NM * 85 / 100;
+        const uint32_t sbase = lds_base + (uint32_t)slot * (kStageUnits * 1024);
+        const uint32_t aw = sbase + (uint32_t)(TN * wf) * 1024, ax = sbase + (uint32_t)(4 * TN + 8 * wr) * 1024;
+        auto part = [&](auto index) __attribute__((always_inline)) {
+            constexpr int i = decltype(index)::value;
+            read_one(index, next, aw, ax);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int s = 0; s < kPgStages; ++s)
-        if (s < n_it) request(s);
-    for (int it = 0; it < n_it; it += 2) {
-        // (the next round's stages are requested after this barrier, so only in round 0 is anything younger
-        // than this round's stages outstanding: stages 2 and 3 from the prologue)
-        if (it == 0 && n_it > 3) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-        else if (it == 0 && n_it == 3) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        asm volatile("s_barrier" ::: "memory");
-        if (it > 0) {
-            if (it + 2 < n_it) request(it + 2);
-            if (it + 3 < n_it) request(it + 3);
-        }
-        read_stage(wA, hA, lA, it);
-        if (it + 1 < n_it) read_stage(wB, hB, lB, it + 1);
-        wait_reads(wA, hA, lA);
-        mma(wA, hA, lA);
-        if (it + 1 < n_it) {
-            wait_reads(wB, hB, lB);
-            mma(wB, hB, lB);
-        }
+            for (int j = i * SPAN / NR; j < (i + 1 == NR ? NM : (i + 1) * SPAN / NR); ++j) mma_one(cur, j);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        index_each(std::make_integer_sequence<int, NR>{}, [&](auto... index) __attribute__((always_inline)) { (part(index), ...); });
+    };
+    // One k-step: `cur` holds its fragments.  This wave's loads of k-step it + 1 have landed when at most the
+    // kPgStages - 2 younger stages are outstanding; after the barrier every wave's have, and every wave has its
+    // fragments of k-step it in registers, so that slot is free for k-step it + kPgStages.
+    auto step = [&](const Frags &cur, Frags &next, int it) __attribute__((always_inline)) {
+        wait_loads_and_meet<(kPgStages - 2) * kLoads>();
+        request(it + kPgStages, it & (kPgStages - 1));
+        interleave(cur, next, (it + 1) & (kPgStages - 1));
+        wait_reads(next);
+    };
+#pragma unroll
+    for (int s = 0; s < kPgStages; ++s) request(s, s);
+    Frags fa, fb;
+    wait_loads_and_meet<(kPgStages - 1) * kLoads>();
+    index_each(std::make_integer_sequence<int, TN + 8>{}, [&](auto... index) __attribute__((always_inline)) {
+        (read_one(index, fa, lds_base + (uint32_t)(TN * wf) * 1024, lds_base + (uint32_t)(4 * TN + 8 * wr) * 1024), ...);
+    });
+    wait_reads(fa);
+    for (int it = 0; it < n_it; it += 2) {   // (an odd n_it ends with a k-step of zeros)
+        step(fa, fb, it);
+        step(fb, fa, it + 1);
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the last requests, of nothing)
 
-    const int slot = lane & 15, kg = lane >> 4;
+    const int slot16 = lane & 15, kg = lane >> 4;
     const int r0 = a.L & 15;
     const int f0 = F0 + TN * wf, g0 = G0 + 4 * wr;
 #pragma unroll
@@ -385,7 +428,7 @@ __global__ __launch_bounds__(kPgThreads) void prefill_gemm_kernel(PrefillArgs a)
         if (f0 + t >= a.n_tiles) break;   // wave-uniform
 #pragma unroll
         for (int g = 0; g < kPfTM; ++g) {
-            const int m = (g0 + g) * 16 + slot;
+            const int m = (g0 + g) * 16 + slot16;
             const bool valid = g0 + g < a.G && m >= r0 && m < r0 + a.P;
             prefill_epilogue<EPI>(a, f0 + t, m, kg, acc[t][g], valid, sp);
         }
