@@ -35,7 +35,7 @@ int kv_heads_of(const anpd_model_cfg &c) { return c.n_kv_heads > 0 ? c.n_kv_head
 int kv_dim_of(const anpd_model_cfg &c) { return kv_heads_of(c) * c.head_dim; }
 
 struct Layout {  // byte offsets into the model workspace
-    size_t rope_tab, tok, tree, batch, result, counter, x, h, y, qkv, att, gu, a, logits, part;
+    size_t rope_tab, tree, batch, result, counter, gen_ctr, x, qkv, att, a, logits, part;
     // fast path: packed operands, partial sums of squares, packed weights
     size_t xp_d, xp_att, xp_f, ssp_a, ssp_b, qp, head_ctr, layer_tab, amax, row_ctr, bar, wp_lm, total;
     size_t xp_layers, xp_stride;   // the one-kernel step's operands (bytes; stride between the layers' sets in bf16 elements: 0, one set)
@@ -85,18 +85,15 @@ Layout make_layout(const anpd_model_cfg *c)
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return at; };
     L.rope_tab = take((size_t)c->max_positions * (c->head_dim / 2) * sizeof(float2));
-    L.tok = take(ANPD_MAX_WINDOW * sizeof(int32_t));
     L.tree = take(3 * ANPD_MAX_WINDOW * sizeof(int32_t));                 // draft tree: parent, depth, visibility mask
     L.batch = take(ANPD_MAX_WINDOW * sizeof(int32_t) + ANPD_MAX_WINDOW * sizeof(SeqRef));   // batched step: sequence of every row, sequences
-    // accepted, next, predictions, accepted path of a tree, (accepted, next) of every sequence of a batch
-    L.result = take((2 + ANPD_MAX_WINDOW + ANPD_MAX_WINDOW + 1 + 2 * ANPD_MAX_WINDOW) * sizeof(int32_t));
-    L.counter = take(sizeof(uint32_t));
+    // accepted, next, predictions, accepted path of a tree
+    L.result = take((2 + ANPD_MAX_WINDOW + ANPD_MAX_WINDOW + 1) * sizeof(int32_t));
+    L.counter = take(32 * sizeof(uint32_t));   // (the word 16 on takes the length updates of a batch that go nowhere)
+    L.gen_ctr = take((size_t)c->n_heads * (ANPD_MAX_WINDOW / 16) * 64 * sizeof(uint32_t));
     L.x = take(MW * d * 4);
-    L.h = take(MW * d * 4);
-    L.y = take(MW * d * 4);
-    L.qkv = take(MW * (d + 2 * kvd) * 4);
+    L.qkv = take(MW * d * 4);
     L.att = take(MW * d * 4);
-    L.gu = take(MW * 2 * F * 4);
     L.a = take(MW * F * 4);
     L.logits = take(MW * V * 4);
     L.part = take((size_t)c->n_heads * L.max_splits * (wants_mfma(c) ? 32 : MW) * (c->head_dim + 2) * 4);
@@ -162,7 +159,7 @@ struct anpd_model {
     Layout lay;
     char *ws;
     bool mfma;
-    int n_cu;
+    int n_cu, device;
     bool mega;            // the one-kernel step is available
     bool mega_tree;       // ... and so is its draft-tree form
     bool mega_batch;      // ... and its several-sequences form
@@ -212,19 +209,13 @@ size_t page_bytes_of(const anpd_model_cfg &c)
 
 // ---- GEMM dispatch -----------------------------------------------------------
 
-// Up to three weight matrices side by side: n0 rows of W0, n1 of W1 (0 if absent), n2 of W2.
-int32_t launch_gemm_dot(const float *X, int M, int K, const void *W0, const void *W1, const void *W2, int n0, int n1,
-                        int n2, float *Y, int ldy, int dtype, hipStream_t st)
+// fp32 matrix cores on the caller's row-major weights; n_blocks: output features / 16, or pairs of 16.
+template <typename WT, int MODE>
+int32_t launch_gen(const GenArgs &a, int n_blocks, hipStream_t st)
 {
-    constexpr int R = 4;
-    int n_total = n0 + n1 + n2;
-    dim3 grid((unsigned)((n_total + 4 * R - 1) / (4 * R)));
-    if (dtype == ANPD_BF16)
-        hipLaunchKernelGGL((gemm_dot_kernel<bf16_t, R>), grid, dim3(256), 0, st, X, M, K, (const bf16_t *)W0,
-                           (const bf16_t *)W1, (const bf16_t *)W2, n0, n1, n_total, Y, ldy);
-    else
-        hipLaunchKernelGGL((gemm_dot_kernel<float, R>), grid, dim3(256), 0, st, X, M, K, (const float *)W0,
-                           (const float *)W1, (const float *)W2, n0, n1, n_total, Y, ldy);
+    // more than 16 rows: two row tiles per block, so that the weights are read once
+    if (a.M > 16) hipLaunchKernelGGL((gemm_gen_kernel<WT, MODE, 2>), dim3((unsigned)n_blocks, (unsigned)((a.M + 31) / 32)), dim3(512), 0, st, a);
+    else hipLaunchKernelGGL((gemm_gen_kernel<WT, MODE, 1>), dim3((unsigned)n_blocks), dim3(512), 0, st, a);
     HIP_TRY(hipGetLastError());
     return ANPD_OK;
 }
@@ -386,20 +377,22 @@ void collect_marks(anpd_model *m)
     m->prof_steps += 1;
 }
 
-// tree: the window is a draft tree whose parent / depth / mask arrays are in the workspace
+// The generic step: per layer QKV (+ norm, RoPE, cache write) -> attention (+ merge) -> O (+ residual) -> gate/up
+// (+ norm, SwiGLU) -> down (+ residual); then LM head (+ norm) -> argmax / accept.
+// tree: the window is a draft tree whose parent / depth / mask arrays are in the workspace.
+// cache_only: a piece of a prompt of which neither logits nor predictions are wanted.
 template <typename KT>
-int32_t run_step_generic(anpd_model *m, anpd_kv *kv, int M, int mode, hipStream_t st, bool tree = false)
+int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, int mode, float *logits, hipStream_t st,
+                         bool tree = false, bool cache_only = false)
 {
     const anpd_model_cfg &c = m->cfg;
     const Layout &L = m->lay;
     char *ws = m->ws;
     const int d = c.d_model, F = c.d_ffn, V = c.vocab, H = c.n_heads, dh = c.head_dim;
-    const int Hkv = kv_heads_of(c), kvd = kv_dim_of(c);
-    float *x = (float *)(ws + L.x), *h = (float *)(ws + L.h), *y = (float *)(ws + L.y);
-    float *qkv = (float *)(ws + L.qkv), *att = (float *)(ws + L.att), *gu = (float *)(ws + L.gu);
-    float *a = (float *)(ws + L.a), *logits = (float *)(ws + L.logits), *part = (float *)(ws + L.part);
-    const float2 *rope = (const float2 *)(ws + L.rope_tab);
-    const int32_t *tok = (const int32_t *)(ws + L.tok);
+    const int Hkv = kv_heads_of(c);
+    float *x = (float *)(ws + L.x), *q = (float *)(ws + L.qkv), *att = (float *)(ws + L.att);
+    float *act = (float *)(ws + L.a), *part = (float *)(ws + L.part);
+    uint32_t *attn_ctr = (uint32_t *)(ws + L.gen_ctr);
     int32_t *result = (int32_t *)(ws + L.result);
     uint32_t *counter = (uint32_t *)(ws + L.counter);
     KT *pool = (KT *)kv->pool;
@@ -409,51 +402,75 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, int M, int mode, hipStream_
     const uint32_t *t_mask = tree ? (const uint32_t *)(t_parent + 2 * ANPD_MAX_WINDOW) : nullptr;
     int32_t rc;
 
+    GenArgs base;
+    std::memset(&base, 0, sizeof(base));
+    base.M = M;
+    base.eps = c.rms_eps;
+    base.rope = (const float2 *)(ws + L.rope_tab);
+    base.pool = kv->pool;
+    base.page_table = kv->d_table;
+    base.len_ptr = kv->d_len;
+    base.depth = t_depth;
+    base.n_layers = c.n_layers;
+    base.n_heads = H;
+    base.n_kv_heads = Hkv;
+    base.head_dim = dh;
+    base.page_tokens = c.page_tokens;
+    auto gemm = [&](const float *X, int K, const void *W, const void *gain, float *Y, int ldy) {
+        GenArgs g = base;
+        g.X = X;
+        g.K = K;
+        g.W0 = W;
+        g.gain = gain;
+        g.Y = Y;
+        g.ldy = ldy;
+        return g;
+    };
+
     m->ev_used = 0;
     mark(m, -1, st);
     hipLaunchKernelGGL((embed_kernel<KT>), dim3(M), dim3(256), 0, st, (const KT *)m->embed, tok, x, d);
+    mark(m, ANPD_PROF_OTHER, st);
     for (int l = 0; l < c.n_layers; ++l) {
-        hipLaunchKernelGGL((addnorm_kernel<KT>), dim3(M), dim3(256), 0, st, x, l == 0 ? (const float *)nullptr : y,
-                           (const KT *)m->attn_norm[l], h, d, c.rms_eps);
-        mark(m, ANPD_PROF_OTHER, st);
-        if ((rc = launch_gemm_dot(h, M, d, m->wq[l], m->wk[l], m->wv[l], d, kvd, kvd, qkv, d + 2 * kvd, c.dtype, st)) != ANPD_OK) return rc;
-        mark(m, ANPD_PROF_GEMM_QKV, st);
-        hipLaunchKernelGGL((rope_kv_kernel<KT>), dim3(M), dim3(256), 0, st, qkv, rope, pool, kv->d_table, kv->d_len, l,
-                           c.n_layers, H, Hkv, dh, c.page_tokens, t_depth);
-        mark(m, ANPD_PROF_OTHER, st);
-        if (dh == 128) {
-            hipLaunchKernelGGL((attn_kernel<KT, 128>), dim3(H, n_splits), dim3(256), 0, st, qkv, d + 2 * kvd, pool, kv->d_table,
-                               kv->d_len, M, l, c.n_layers, H, Hkv, c.page_tokens, c.max_window, L.max_splits, scale, part, t_mask);
-            hipLaunchKernelGGL((attn_combine_kernel<128>), dim3(M, H), dim3(128), 0, st, part, kv->d_len, H,
-                               c.max_window, L.max_splits, att, (bf16_t *)nullptr, 8);
-        } else {
-            hipLaunchKernelGGL((attn_kernel<KT, 64>), dim3(H, n_splits), dim3(256), 0, st, qkv, d + 2 * kvd, pool, kv->d_table,
-                               kv->d_len, M, l, c.n_layers, H, Hkv, c.page_tokens, c.max_window, L.max_splits, scale, part, t_mask);
-            hipLaunchKernelGGL((attn_combine_kernel<64>), dim3(M, H), dim3(64), 0, st, part, kv->d_len, H, c.max_window,
-                               L.max_splits, att, (bf16_t *)nullptr, 8);
+        {
+            GenArgs g = gemm(x, d, m->wq[l], m->attn_norm[l], q, d);
+            g.W1 = m->wk[l];
+            g.W2 = m->wv[l];
+            g.layer = l;
+            if ((rc = launch_gen<KT, GEN_QKV>(g, (H + 2 * Hkv) * (dh / 32), st)) != ANPD_OK) return rc;
         }
+        mark(m, ANPD_PROF_GEMM_QKV, st);
+        const dim3 grid((unsigned)H, (unsigned)n_splits, (unsigned)((M + 15) / 16));
+        if (dh == 128)
+            hipLaunchKernelGGL((attn_kernel<KT, 128>), grid, dim3(256), 0, st, q, d, pool, kv->d_table, kv->d_len, M, l, c.n_layers, H, Hkv,
+                               c.page_tokens, c.max_window, L.max_splits, scale, part, attn_ctr, att, t_mask);
+        else
+            hipLaunchKernelGGL((attn_kernel<KT, 64>), grid, dim3(256), 0, st, q, d, pool, kv->d_table, kv->d_len, M, l, c.n_layers, H, Hkv,
+                               c.page_tokens, c.max_window, L.max_splits, scale, part, attn_ctr, att, t_mask);
         mark(m, ANPD_PROF_ATTN, st);
-        if ((rc = launch_gemm_dot(att, M, d, m->wo[l], nullptr, nullptr, d, 0, 0, y, d, c.dtype, st)) != ANPD_OK) return rc;
+        if ((rc = launch_gen<KT, GEN_RESIDUAL>(gemm(att, d, m->wo[l], nullptr, x, d), d / 16, st)) != ANPD_OK) return rc;
         mark(m, ANPD_PROF_GEMM_O, st);
-        hipLaunchKernelGGL((addnorm_kernel<KT>), dim3(M), dim3(256), 0, st, x, y, (const KT *)m->ffn_norm[l], h, d,
-                           c.rms_eps);
-        mark(m, ANPD_PROF_OTHER, st);
-        if ((rc = launch_gemm_dot(h, M, d, m->w_gate[l], m->w_up[l], nullptr, F, F, 0, gu, 2 * F, c.dtype, st)) != ANPD_OK) return rc;
+        {
+            GenArgs g = gemm(x, d, m->w_gate[l], m->ffn_norm[l], act, F);
+            g.W1 = m->w_up[l];
+            if ((rc = launch_gen<KT, GEN_GATE_UP>(g, F / 16, st)) != ANPD_OK) return rc;
+        }
         mark(m, ANPD_PROF_GEMM_GATE_UP, st);
-        hipLaunchKernelGGL(swiglu_kernel, dim3((F + 255) / 256, M), dim3(256), 0, st, gu, a, F);
-        mark(m, ANPD_PROF_OTHER, st);
-        if ((rc = launch_gemm_dot(a, M, F, m->w_down[l], nullptr, nullptr, d, 0, 0, y, d, c.dtype, st)) != ANPD_OK) return rc;
+        if ((rc = launch_gen<KT, GEN_RESIDUAL>(gemm(act, F, m->w_down[l], nullptr, x, d), d / 16, st)) != ANPD_OK) return rc;
         mark(m, ANPD_PROF_GEMM_DOWN, st);
     }
-    hipLaunchKernelGGL((addnorm_kernel<KT>), dim3(M), dim3(256), 0, st, x, y, (const KT *)m->final_norm, h, d,
-                       c.rms_eps);
-    mark(m, ANPD_PROF_OTHER, st);
-    if ((rc = launch_gemm_dot(h, M, d, m->lm_head, nullptr, nullptr, V, 0, 0, logits, V, c.dtype, st)) != ANPD_OK) return rc;
+    if (cache_only) {
+        hipLaunchKernelGGL(advance_length_kernel, dim3(1), dim3(64), 0, st, kv->d_len, M);
+        mark(m, ANPD_PROF_OTHER, st);
+        HIP_TRY(hipGetLastError());
+        return ANPD_OK;
+    }
+    if ((rc = launch_gen<KT, GEN_LOGITS>(gemm(x, d, m->lm_head, m->final_norm, logits, V), V / 16, st)) != ANPD_OK) return rc;
     mark(m, ANPD_PROF_GEMM_LM_HEAD, st);
-    hipLaunchKernelGGL(argmax_accept_kernel, dim3(M), dim3(1024), 0, st, logits, V, M, tok, mode, result, kv->d_len,
+    hipLaunchKernelGGL(argmax_accept_kernel, dim3(M), dim3(1024), 0, st, logits, V, M, tok, mode, result, m->pin_dev + 32, kv->d_len,
                        counter);
     if (tree) {
-        hipLaunchKernelGGL(accept_tree_kernel, dim3(1), dim3(64), 0, st, tok, t_parent, t_depth, M, result, kv->d_len, kv->len);
+        hipLaunchKernelGGL(accept_tree_kernel, dim3(1), dim3(64), 0, st, tok, t_parent, t_depth, M, result, m->pin_dev + 32, kv->d_len, kv->len);
         hipLaunchKernelGGL((kv_compact_kernel<KT>), dim3((unsigned)(c.n_layers * 2 * Hkv)), dim3(128), 0, st, pool, kv->d_table,
                            (const int32_t *)result, kv->len, c.n_layers, Hkv, dh, c.page_tokens);
     }
@@ -469,7 +486,7 @@ struct BatchLaunch {
     int n_seq, n_blocks /* (split, sequence) blocks per head */, grid_splits /* splits of the longest sequence */;
 };
 
-int32_t run_step_fast(anpd_model *m, anpd_kv *kv, int M, int mode, hipStream_t st, bool tree = false,
+int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, int mode, float *logits, hipStream_t st, bool tree = false,
                       const BatchLaunch *batch = nullptr)
 {
     const anpd_model_cfg &c = m->cfg;
@@ -478,13 +495,11 @@ int32_t run_step_fast(anpd_model *m, anpd_kv *kv, int M, int mode, hipStream_t s
     const int d = c.d_model, F = c.d_ffn, V = c.vocab, H = c.n_heads, dh = c.head_dim;
     const int Hkv = kv_heads_of(c), kvd = kv_dim_of(c);
     const int cls = window_class(M);
-    float *x = (float *)(ws + L.x);
-    float *logits = (float *)(ws + L.logits), *part = (float *)(ws + L.part);
+    float *x = (float *)(ws + L.x), *part = (float *)(ws + L.part);
     bf16_t *qp = (bf16_t *)(ws + L.qp);
     uint32_t *head_ctr = (uint32_t *)(ws + L.head_ctr);
     bf16_t *xp_d = (bf16_t *)(ws + L.xp_d), *xp_att = (bf16_t *)(ws + L.xp_att), *xp_f = (bf16_t *)(ws + L.xp_f);
     float *ssp_a = (float *)(ws + L.ssp_a), *ssp_b = (float *)(ws + L.ssp_b);
-    const int32_t *tok = (const int32_t *)(ws + L.tok);
     int32_t *result = (int32_t *)(ws + L.result);
     uint32_t *counter = (uint32_t *)(ws + L.counter);
     const float scale = 1.0f / sqrtf((float)dh);
@@ -618,10 +633,10 @@ int32_t run_step_fast(anpd_model *m, anpd_kv *kv, int M, int mode, hipStream_t s
     }
     mark(m, ANPD_PROF_GEMM_LM_HEAD, st);
     hipLaunchKernelGGL(argmax_accept_kernel, dim3(M), dim3(1024), 0, st, logits, V, M, tok, batch ? (int)ANPD_APPEND : mode, result,
-                       batch ? dummy_len : kv->d_len, counter);
-    if (batch) hipLaunchKernelGGL(accept_batch_kernel, dim3(1), dim3(64), 0, st, tok, b_seqs, batch->n_seq, mode, result);
+                       m->pin_dev + 32, batch ? dummy_len : kv->d_len, counter);
+    if (batch) hipLaunchKernelGGL(accept_batch_kernel, dim3(1), dim3(64), 0, st, tok, b_seqs, batch->n_seq, mode, (const int32_t *)result, m->pin_dev + 256);
     if (tree) {
-        hipLaunchKernelGGL(accept_tree_kernel, dim3(1), dim3(64), 0, st, tok, t_parent, t_depth, M, result, kv->d_len, kv->len);
+        hipLaunchKernelGGL(accept_tree_kernel, dim3(1), dim3(64), 0, st, tok, t_parent, t_depth, M, result, m->pin_dev + 32, kv->d_len, kv->len);
         hipLaunchKernelGGL(kvf_compact_kernel, dim3((unsigned)(c.n_layers * 2 * Hkv)), dim3(128), 0, st, (bf16_t *)kv->pool,
                            kv->d_table, (const int32_t *)result, kv->len, c.n_layers, Hkv, dh);
     }
@@ -640,7 +655,8 @@ struct MegaBatch {
     const int32_t *row_seq;
     const int32_t *len;
 };
-int32_t run_step_mega(anpd_model *m, anpd_kv *kv, const int32_t *window, int M, int mode, bool want_logits, hipStream_t st,
+// logits: where they go (null: nowhere).
+int32_t run_step_mega(anpd_model *m, anpd_kv *kv, const int32_t *window, int M, int mode, float *logits, hipStream_t st,
                       const int32_t *tree = nullptr, const MegaBatch *batch = nullptr)
 {
     const anpd_model_cfg &c = m->cfg;
@@ -665,7 +681,7 @@ int32_t run_step_mega(anpd_model *m, anpd_kv *kv, const int32_t *window, int M, 
     if (kv) { g.pool = (bf16_t *)kv->pool; g.page_table = kv->d_table; g.len_ptr = kv->d_len; }
     g.rope = (const float2 *)(ws + L.rope_tab);
     g.max_splits = L.max_splits;
-    g.logits = want_logits ? (float *)(ws + L.logits) : nullptr;
+    g.logits = logits;
     g.amax = (unsigned long long *)(ws + L.amax);
     for (int i = 0; i < 16; ++i) g.tok[i] = i < M ? window[i] : 0;
     g.result = (int32_t *)(ws + L.result);
@@ -772,7 +788,7 @@ int32_t launch_prefill_gemm(const PrefillArgs &a, int n_cu, hipStream_t st)
 
 // All P rows at once; per layer norm -> QKV(+RoPE, cache write) -> attention -> O(+residual) -> norm ->
 // gate/up(+SwiGLU) -> down(+residual); the last row then goes through the step's LM head and argmax.
-int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const PrefillLayout &PL, hipStream_t st)
+int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const PrefillLayout &PL, float *logits, hipStream_t st)
 {
     const anpd_model_cfg &c = m->cfg;
     const Layout &L = m->lay;
@@ -888,17 +904,37 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
         a.nks = nks_d;
         a.n_tiles = V / 16;
         a.ssp = (const float *)(ws + L.ssp_a);
-        a.Y = (float *)(ws + L.logits);
+        a.Y = logits;
         a.ldy = V;
         if ((rc = launch_fast<EPI_LOGITS>(a, m->n_cu, false, st)) != ANPD_OK) return rc;
     }
     mark(m, ANPD_PROF_GEMM_LM_HEAD, st);
-    hipLaunchKernelGGL(argmax_accept_kernel, dim3(1), dim3(1024), 0, st, (const float *)(ws + L.logits), V, 1,
-                       (const int32_t *)(ws + L.tok), (int)ANPD_APPEND, (int32_t *)(ws + L.result), kv->d_len,
-                       (uint32_t *)(ws + L.counter));
+    hipLaunchKernelGGL(argmax_accept_kernel, dim3(1), dim3(1024), 0, st, (const float *)logits, V, 1, StepTokens(),
+                       (int)ANPD_APPEND, (int32_t *)(ws + L.result), m->pin_dev + 32, kv->d_len, (uint32_t *)(ws + L.counter));
     mark(m, ANPD_PROF_OTHER, st);
     HIP_TRY(hipGetLastError());
     return ANPD_OK;
+}
+
+// Where a step's LM head writes: straight into the caller's buffer when that is memory of this device that takes
+// 16-byte stores, else into the workspace, from where it is copied (a buffer of another GPU, say).
+float *logits_target(const anpd_model *m, float *out_logits)
+{
+    float *own = (float *)(m->ws + m->lay.logits);
+    if (!out_logits || ((uintptr_t)out_logits & 15) != 0) return own;
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, out_logits) != hipSuccess) {
+        (void)hipGetLastError();
+        return own;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == m->device ? out_logits : own;
+}
+
+StepTokens step_tokens(const int32_t *window, int n)
+{
+    StepTokens t;
+    for (int i = 0; i < ANPD_MAX_WINDOW; ++i) t.t[i] = i < n ? window[i] : 0;
+    return t;
 }
 
 // After the stream has been synchronised: did a grid barrier of the one-kernel step give up?  Then the
@@ -957,6 +993,11 @@ int32_t anpd_model_create(const anpd_model_cfg *cfg, const anpd_weights *w, void
         m->n_cu = 256;
         if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0)
             m->n_cu = prop.multiProcessorCount;
+        // (where the workspace lies, which is where the step runs)
+        hipPointerAttribute_t at;
+        m->device = dev;
+        if (hipPointerGetAttributes(&at, workspace) == hipSuccess) m->device = at.device;
+        else (void)hipGetLastError();
     }
     m->embed = w->embed;
     m->final_norm = w->final_norm;
@@ -1282,25 +1323,18 @@ int32_t anpd_verify(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, int32
     hipStream_t st = (hipStream_t)stream;
     int32_t rc = ensure_pages(kv, kv->len + n_window, st);
     if (rc != ANPD_OK) return rc;
-    // The persistent kernel takes the window by value and writes its result and error flag into the
-    // pinned buffer itself; the other paths go through copies.
+    // The window goes to the kernels by value, and they write the result (and the persistent kernel its error
+    // flag) into the pinned buffer themselves.
     const bool one_kernel = m->mega && (n_window <= 8 || (n_window <= 16 && m->mega_rows16));
-    int32_t *res = m->pin + 32;
-    if (one_kernel) {
-        rc = run_step_mega(m, kv, window, n_window, mode, out_logits != nullptr, st);
-        if (rc != ANPD_OK) return rc;
-    } else {
-        std::memcpy(m->pin, window, sizeof(int32_t) * (size_t)n_window);
-        HIP_TRY(hipMemcpyAsync(m->ws + m->lay.tok, m->pin, sizeof(int32_t) * (size_t)n_window, hipMemcpyHostToDevice, st));
-        if (m->mfma) rc = run_step_fast(m, kv, n_window, mode, st);
-        else if (m->cfg.dtype == ANPD_BF16) rc = run_step_generic<bf16_t>(m, kv, n_window, mode, st);
-        else rc = run_step_generic<float>(m, kv, n_window, mode, st);
-        if (rc != ANPD_OK) return rc;
-        HIP_TRY(hipMemcpyAsync(res, m->ws + m->lay.result, sizeof(int32_t) * (size_t)(2 + n_window), hipMemcpyDeviceToHost, st));
-    }
-    if (out_logits)
-        HIP_TRY(hipMemcpyAsync(out_logits, m->ws + m->lay.logits, sizeof(float) * (size_t)n_window * m->cfg.vocab,
-                               hipMemcpyDeviceToDevice, st));
+    const int32_t *res = m->pin + 32;
+    float *logits = logits_target(m, out_logits);
+    if (one_kernel) rc = run_step_mega(m, kv, window, n_window, mode, out_logits ? logits : nullptr, st);
+    else if (m->mfma) rc = run_step_fast(m, kv, step_tokens(window, n_window), n_window, mode, logits, st);
+    else if (m->cfg.dtype == ANPD_BF16) rc = run_step_generic<bf16_t>(m, kv, step_tokens(window, n_window), n_window, mode, logits, st);
+    else rc = run_step_generic<float>(m, kv, step_tokens(window, n_window), n_window, mode, logits, st);
+    if (rc != ANPD_OK) return rc;
+    if (out_logits && out_logits != logits)
+        HIP_TRY(hipMemcpyAsync(out_logits, logits, sizeof(float) * (size_t)n_window * m->cfg.vocab, hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (one_kernel && barrier_gave_up(m, st)) return fail(ANPD_E_HIP, "anpd_verify: the persistent kernel timed out at a grid barrier");
     collect_marks(m);
@@ -1344,26 +1378,23 @@ int32_t anpd_verify_tree(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, 
         td[i] = td[parent[i]] + 1;
         tm[i] = tm[parent[i]] | (1u << i);
     }
-    int32_t *res = m->pin + 32;
-    // windows of up to 8 rows: the one-kernel step in its draft-tree form (tokens and tree by value, result
-    // written to pinned memory by the kernel); otherwise one launch per operation
+    const int32_t *res = m->pin + 32;
+    float *logits = logits_target(m, out_logits);
+    // windows of up to 8 rows: the one-kernel step in its draft-tree form (tree by value as well); otherwise one
+    // launch per operation, the tree uploaded
     const bool one_kernel = m->mega && m->mega_tree && n_window <= 8;
     if (one_kernel) {
-        rc = run_step_mega(m, kv, window, n_window, ANPD_APPEND, out_logits != nullptr, st, tp);
-        if (rc != ANPD_OK) return rc;
+        rc = run_step_mega(m, kv, window, n_window, ANPD_APPEND, out_logits ? logits : nullptr, st, tp);
     } else {
-        std::memcpy(m->pin, window, sizeof(int32_t) * (size_t)n_window);
-        HIP_TRY(hipMemcpyAsync(m->ws + m->lay.tok, m->pin, sizeof(int32_t) * (size_t)n_window, hipMemcpyHostToDevice, st));
+        const StepTokens tok = step_tokens(window, n_window);
         HIP_TRY(hipMemcpyAsync(m->ws + m->lay.tree, tp, sizeof(int32_t) * 3 * ANPD_MAX_WINDOW, hipMemcpyHostToDevice, st));
-        if (m->mfma) rc = run_step_fast(m, kv, n_window, ANPD_APPEND, st, true);
-        else if (m->cfg.dtype == ANPD_BF16) rc = run_step_generic<bf16_t>(m, kv, n_window, ANPD_APPEND, st, true);
-        else rc = run_step_generic<float>(m, kv, n_window, ANPD_APPEND, st, true);
-        if (rc != ANPD_OK) return rc;
-        HIP_TRY(hipMemcpyAsync(res, m->ws + m->lay.result, sizeof(int32_t) * (size_t)(2 + 2 * ANPD_MAX_WINDOW + 1), hipMemcpyDeviceToHost, st));
+        if (m->mfma) rc = run_step_fast(m, kv, tok, n_window, ANPD_APPEND, logits, st, true);
+        else if (m->cfg.dtype == ANPD_BF16) rc = run_step_generic<bf16_t>(m, kv, tok, n_window, ANPD_APPEND, logits, st, true);
+        else rc = run_step_generic<float>(m, kv, tok, n_window, ANPD_APPEND, logits, st, true);
     }
-    if (out_logits)
-        HIP_TRY(hipMemcpyAsync(out_logits, m->ws + m->lay.logits, sizeof(float) * (size_t)n_window * m->cfg.vocab,
-                               hipMemcpyDeviceToDevice, st));
+    if (rc != ANPD_OK) return rc;
+    if (out_logits && out_logits != logits)
+        HIP_TRY(hipMemcpyAsync(out_logits, logits, sizeof(float) * (size_t)n_window * m->cfg.vocab, hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (one_kernel && barrier_gave_up(m, st)) return fail(ANPD_E_HIP, "anpd_verify_tree: the persistent kernel timed out at a grid barrier");
     collect_marks(m);
@@ -1430,25 +1461,23 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
     // At most 8 rows in all (decoding batches, short windows): the persistent kernel takes the sequences by
     // value and writes the results into the pinned buffer itself; otherwise copies and the fused launches.
     const bool one_kernel = m->mega && m->mega_batch && total <= 8;
-    int32_t *res = m->pin + 256;
+    const int32_t *res = m->pin + 256;
+    float *logits = logits_target(m, out_logits);
     int32_t rc;
     if (one_kernel) {
         int32_t lens[8];
         for (int s = 0; s < n_seq; ++s) lens[s] = kvs[s]->len;
         MegaBatch mb = {n_seq, seqs, row_seq, lens};
-        rc = run_step_mega(m, nullptr, m->pin, total, mode, out_logits != nullptr, st, nullptr, &mb);
-        if (rc != ANPD_OK) return rc;
+        rc = run_step_mega(m, nullptr, m->pin, total, mode, out_logits ? logits : nullptr, st, nullptr, &mb);
     } else {
-        HIP_TRY(hipMemcpyAsync(m->ws + m->lay.tok, m->pin, sizeof(int32_t) * (size_t)total, hipMemcpyHostToDevice, st));
         HIP_TRY(hipMemcpyAsync(m->ws + m->lay.batch, row_seq, sizeof(int32_t) * (size_t)total, hipMemcpyHostToDevice, st));
         HIP_TRY(hipMemcpyAsync(m->ws + m->lay.batch + ANPD_MAX_WINDOW * sizeof(int32_t), seqs, sizeof(SeqRef) * (size_t)n_seq,
                                hipMemcpyHostToDevice, st));
-        rc = run_step_fast(m, nullptr, total, mode, st, false, &bl);
-        if (rc != ANPD_OK) return rc;
-        HIP_TRY(hipMemcpyAsync(res, m->ws + m->lay.result + 67 * sizeof(int32_t), sizeof(int32_t) * 2 * (size_t)n_seq, hipMemcpyDeviceToHost, st));
+        rc = run_step_fast(m, nullptr, step_tokens(m->pin, total), total, mode, logits, st, false, &bl);
     }
-    if (out_logits)
-        HIP_TRY(hipMemcpyAsync(out_logits, m->ws + m->lay.logits, sizeof(float) * (size_t)total * m->cfg.vocab, hipMemcpyDeviceToDevice, st));
+    if (rc != ANPD_OK) return rc;
+    if (out_logits && out_logits != logits)
+        HIP_TRY(hipMemcpyAsync(out_logits, logits, sizeof(float) * (size_t)total * m->cfg.vocab, hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (one_kernel && barrier_gave_up(m, st)) return fail(ANPD_E_HIP, "anpd_verify_batch: the persistent kernel timed out at a grid barrier");
     collect_marks(m);
@@ -1485,18 +1514,29 @@ int32_t anpd_prefill(anpd_model_t *m, anpd_kv_t *kv, const int32_t *tokens, int3
     const size_t V = (size_t)m->cfg.vocab;
 
     if (!m->mfma) {
-        // dot-product models: the prompt goes through the step in windows of max_window appended rows
-        int32_t acc = 0, last_n = 0;
+        // models on the caller's weights: the prompt goes through the step in windows of max_window appended rows, all
+        // enqueued before the first is waited for; logits and prediction of the last row only
+        int32_t rc = ensure_pages(kv, kv->len + n_tokens, st);
+        if (rc != ANPD_OK) return rc;
+        float *logits = (float *)(m->ws + m->lay.logits);
+        int last_n = 0;
         for (int i = 0; i < n_tokens; i += last_n) {
             last_n = n_tokens - i < m->cfg.max_window ? n_tokens - i : m->cfg.max_window;
-            int32_t rc = anpd_verify(m, kv, tokens + i, last_n, ANPD_APPEND, &acc, out_next, nullptr, nullptr, stream);
+            const bool more = i + last_n < n_tokens;
+            const StepTokens tok = step_tokens(tokens + i, last_n);
+            rc = m->cfg.dtype == ANPD_BF16 ? run_step_generic<bf16_t>(m, kv, tok, last_n, ANPD_APPEND, logits, st, false, more)
+                                           : run_step_generic<float>(m, kv, tok, last_n, ANPD_APPEND, logits, st, false, more);
             if (rc != ANPD_OK) return rc;
+            kv->len += last_n;
+            if (m->prof) {
+                HIP_TRY(hipStreamSynchronize(st));
+                collect_marks(m);
+            }
         }
-        if (out_logits) {
-            HIP_TRY(hipMemcpyAsync(out_logits, m->ws + m->lay.logits + (size_t)(last_n - 1) * V * sizeof(float), V * sizeof(float),
-                                   hipMemcpyDeviceToDevice, st));
-            HIP_TRY(hipStreamSynchronize(st));
-        }
+        if (out_logits)
+            HIP_TRY(hipMemcpyAsync(out_logits, logits + (size_t)(last_n - 1) * V, V * sizeof(float), hipMemcpyDeviceToDevice, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        *out_next = m->pin[33];
         return ANPD_OK;
     }
 
@@ -1509,12 +1549,12 @@ int32_t anpd_prefill(anpd_model_t *m, anpd_kv_t *kv, const int32_t *tokens, int3
     if (rc != ANPD_OK) return rc;
     char *pws = (char *)workspace;
     HIP_TRY(hipMemcpyAsync(pws + PL.tok, tokens, sizeof(int32_t) * (size_t)n_tokens, hipMemcpyHostToDevice, st));
-    rc = run_prefill_mfma(m, kv, n_tokens, pws, PL, st);
+    float *logits = logits_target(m, out_logits);
+    rc = run_prefill_mfma(m, kv, n_tokens, pws, PL, logits, st);
     if (rc != ANPD_OK) return rc;
-    int32_t *res = m->pin + 32;
-    HIP_TRY(hipMemcpyAsync(res, m->ws + m->lay.result, sizeof(int32_t) * 3, hipMemcpyDeviceToHost, st));
-    if (out_logits)
-        HIP_TRY(hipMemcpyAsync(out_logits, m->ws + m->lay.logits, V * sizeof(float), hipMemcpyDeviceToDevice, st));
+    const int32_t *res = m->pin + 32;
+    if (out_logits && out_logits != logits)
+        HIP_TRY(hipMemcpyAsync(out_logits, logits, V * sizeof(float), hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
     collect_marks(m);
     *out_next = res[1];
@@ -1551,7 +1591,17 @@ int32_t anpd_linear(const float *X, const void *W, float *Y, int32_t M, int32_t 
         return fail(ANPD_E_INVAL, "anpd_linear: need 1 <= M <= %d, K %% 8 == 0, N %% 16 == 0", ANPD_MAX_WINDOW);
     if (dtype != ANPD_F32 && dtype != ANPD_BF16) return fail(ANPD_E_INVAL, "anpd_linear: unknown dtype");
     hipStream_t st = (hipStream_t)stream;
-    if (path == ANPD_GEMM_DOT) return launch_gemm_dot(X, M, K, W, nullptr, nullptr, N, 0, 0, Y, N, dtype, st);
+    if (path == ANPD_GEMM_DOT) {
+        GenArgs g;
+        std::memset(&g, 0, sizeof(g));
+        g.X = X;
+        g.M = M;
+        g.K = K;
+        g.W0 = W;
+        g.Y = Y;
+        g.ldy = N;
+        return dtype == ANPD_BF16 ? launch_gen<bf16_t, GEN_PLAIN>(g, N / 16, st) : launch_gen<float, GEN_PLAIN>(g, N / 16, st);
+    }
     if (path != ANPD_GEMM_MFMA && path != ANPD_GEMM_MFMA_STREAM)
         return fail(ANPD_E_INVAL, "anpd_linear: unknown path %d", path);
     if (dtype != ANPD_BF16) return fail(ANPD_E_INVAL, "anpd_linear: the MFMA path needs bf16 weights");

@@ -716,10 +716,9 @@ __device__ __forceinline__ void embed_tile(const bf16_t *__restrict__ E, const i
     }
 }
 
-__global__ __launch_bounds__(64) void embed_fast_kernel(const bf16_t *__restrict__ E, const int32_t *__restrict__ tok,
-                                                         FastArgs a)
+__global__ __launch_bounds__(64) void embed_fast_kernel(const bf16_t *__restrict__ E, StepTokens tok, FastArgs a)
 {
-    embed_tile<false>(E, tok, a, blockIdx.x, threadIdx.x);
+    embed_tile<false>(E, tok.t, a, blockIdx.x, threadIdx.x);
 }
 
 // fp32 [M][K] -> packed split operand (stand-alone linear entry point)
@@ -1287,25 +1286,24 @@ __global__ __launch_bounds__(128) void kvf_compact_kernel(bf16_t *__restrict__ p
 
 // Acceptance for several sequences verified in one step, after argmax_accept_kernel has left the
 // per-row predictions in result[2..]: Algorithm 1's rule inside every sequence's own rows.  Sequence s
-// gets result[67 + 2 s] = accepted, result[68 + 2 s] = next, and its length advances by 1 + accepted.
-// One thread.
-__global__ void accept_batch_kernel(const int32_t *__restrict__ window, const SeqRef *__restrict__ seqs, int n_seq, int mode,
-                                    int32_t *__restrict__ result)
+// gets host_result[2 s] = accepted, host_result[2 s + 1] = next (pinned host memory), and its length advances by
+// 1 + accepted.  One thread per sequence (one thread for all of 32: 16 us).
+__global__ __launch_bounds__(64) void accept_batch_kernel(StepTokens window, const SeqRef *__restrict__ seqs, int n_seq, int mode,
+                                                           const int32_t *__restrict__ result, int32_t *__restrict__ host_result)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    const int s = threadIdx.x;
+    if (s >= n_seq) return;
     const int32_t *pred = result + 2;
-    for (int s = 0; s < n_seq; ++s) {
-        const int r0 = seqs[s].row0, n = seqs[s].n_rows;
-        int a = 0;
-        if (mode == 0) {
-            while (a < n - 1 && window[r0 + a + 1] == pred[r0 + a]) ++a;
-        } else {
-            a = n - 1;
-        }
-        result[67 + 2 * s] = a;
-        result[68 + 2 * s] = pred[r0 + a];
-        *seqs[s].len_ptr += 1 + a;
+    const int r0 = seqs[s].row0, n = seqs[s].n_rows;
+    int a = 0;
+    if (mode == 0) {
+        while (a < n - 1 && window.t[r0 + a + 1] == pred[r0 + a]) ++a;
+    } else {
+        a = n - 1;
     }
+    st_system(host_result + 2 * s, a);
+    st_system(host_result + 2 * s + 1, pred[r0 + a]);
+    *seqs[s].len_ptr += 1 + a;
 }
 
 // Copies n positions of one layer between fp32 [n][d] arrays and the fast-path cache layout.

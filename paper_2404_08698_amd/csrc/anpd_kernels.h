@@ -250,108 +250,13 @@ __host__ __device__ __forceinline__ size_t xp_offset(int cls, int m, int k, int 
     return ((((size_t)ks * nt + frag) * 64) + (size_t)kg * 16 + slot) * 8 + j;
 }
 
-// ------------------------------------------------------------------ embed
+// A step's tokens, passed to the kernels by value: nothing is uploaded before a step.
+constexpr int kMaxRows = 32;   // ANPD_MAX_WINDOW
+struct StepTokens {
+    int32_t t[kMaxRows];
+};
 
-// x[r][:] = E[token[r]][:]   grid: M blocks
-template <typename WT>
-__global__ __launch_bounds__(256) void embed_kernel(const WT *__restrict__ E, const int32_t *__restrict__ tok,
-                                                     float *__restrict__ x, int d)
-{
-    int r = blockIdx.x;
-    const WT *src = E + (size_t)tok[r] * d;
-    for (int i = threadIdx.x; i < d; i += blockDim.x) x[(size_t)r * d + i] = load_f32(src, (size_t)i);
-}
-
-// --------------------------------------------------- residual add + RMSNorm
-
-// x[r] += y[r] (if y), then h[r] = x[r] * g / sqrt(mean(x[r]^2) + eps).
-// grid: M blocks, one row each; the reduction order depends on d only.
-template <typename WT>
-__global__ __launch_bounds__(256) void addnorm_kernel(float *__restrict__ x, const float *__restrict__ y,
-                                                       const WT *__restrict__ g, float *__restrict__ h, int d,
-                                                       float eps)
-{
-    __shared__ float part[4];
-    int r = blockIdx.x;
-    float *xr = x + (size_t)r * d;
-    float ss = 0.f;
-    for (int i = threadIdx.x; i < d; i += 256) {
-        float v = xr[i];
-        if (y) {
-            v += y[(size_t)r * d + i];
-            xr[i] = v;
-        }
-        ss = fmaf(v, v, ss);
-    }
-    ss = wave_sum(ss);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
-    __syncthreads();
-    float tot = ((part[0] + part[1]) + part[2]) + part[3];
-    float rinv = 1.0f / sqrtf(tot / (float)d + eps);
-    for (int i = threadIdx.x; i < d; i += 256) {
-        float v = xr[i] * load_f32(g, (size_t)i) * rinv;
-        h[(size_t)r * d + i] = v;
-    }
-}
-
-// --------------------------------------------------------------- GEMM (dot)
-//
-// Wavefront dot-product form of Y[M][N] = X[M][K] * W[N][K]^T.  A wave owns R
-// output columns; its 64 lanes stride over K in 8-element pieces (one 16-byte
-// load of bf16 weights per lane per row), multiply against the fp32 rows of X
-// and finish with a butterfly sum over the lanes.  Exact fp32 products, fp32
-// accumulation.  The weight matrix may be given as up to three row segments
-// (Wq|Wk|Wv or Wgate|Wup) of n_seg0, n_seg1 and the remaining rows (multiples of
-// R), written side by side into Y.
-// grid: n_total / (4 * R) blocks of 4 waves.
-template <typename WT, int R>
-__global__ __launch_bounds__(256) void gemm_dot_kernel(const float *__restrict__ X, int M, int K,
-                                                        const WT *__restrict__ W0, const WT *__restrict__ W1,
-                                                        const WT *__restrict__ W2, int n_seg0, int n_seg1, int n_total,
-                                                        float *__restrict__ Y, int ldy)
-{
-    const int lane = threadIdx.x & 63;
-    const int n0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * R;
-    if (n0 >= n_total) return;
-    const int seg = n0 < n_seg0 ? 0 : (n0 < n_seg0 + n_seg1 ? 1 : 2);
-    const WT *W = (seg == 0 ? W0 : (seg == 1 ? W1 : W2)) + (size_t)(n0 - (seg == 0 ? 0 : (seg == 1 ? n_seg0 : n_seg0 + n_seg1))) * K;
-
-    for (int m0 = 0; m0 < M; m0 += 8) {
-        float acc[R][8];
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int mm = 0; mm < 8; ++mm) acc[r][mm] = 0.f;
-
-        for (int k = lane * 8; k < K; k += 64 * 8) {
-            float w[R][8];
-#pragma unroll
-            for (int r = 0; r < R; ++r) load8(W + (size_t)r * K + k, w[r]);
-#pragma unroll
-            for (int mm = 0; mm < 8; ++mm) {
-                if (m0 + mm < M) {
-                    float xv[8];
-                    load8(X + (size_t)(m0 + mm) * K + k, xv);
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) acc[r][mm] = fmaf(xv[i], w[r][i], acc[r][mm]);
-                }
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int mm = 0; mm < 8; ++mm) {
-                float v = wave_sum(acc[r][mm]);
-                if (lane == 0 && m0 + mm < M) Y[(size_t)(m0 + mm) * ldy + n0 + r] = v;
-            }
-    }
-}
-
-// ------------------------------------------------------- RoPE + KV write
-//
-// Page layout: [page][layer][k|v][head][token in page][head_dim].
+// Page layout of the generic path: [page][layer][k|v][head][token in page][head_dim].
 __device__ __forceinline__ size_t kv_offset(int page, int layer, int n_layers, int kv, int head, int n_heads,
                                             int tok_in_page, int page_tokens, int head_dim)
 {
@@ -359,219 +264,420 @@ __device__ __forceinline__ size_t kv_offset(int page, int layer, int n_layers, i
            (size_t)tok_in_page * head_dim;
 }
 
-// A row of the fused qkv buffer is [q: n_heads * head_dim | k: n_kv_heads * head_dim | v: the same].
-// Rotates q (in place, in the fused qkv buffer) and k by the row's absolute
-// position len + r, pair (i, i + head_dim/2) by angle pos * base^(-2i/head_dim)
-// (cos/sin from a table computed in double on the host), and writes k and v of
-// the row into the cache in the storage type.  grid: M blocks.
-template <typename KT>
-__global__ __launch_bounds__(256) void rope_kv_kernel(float *__restrict__ qkv, const float2 *__restrict__ rope_tab,
-                                                       KT *__restrict__ pool, const int32_t *__restrict__ page_table,
-                                                       const int32_t *__restrict__ len_ptr, int layer, int n_layers,
-                                                       int n_heads, int n_kv_heads, int head_dim, int page_tokens,
-                                                       const int32_t *__restrict__ depth /* draft tree: nullable */)
+// ------------------------------------------------------------------ embed
+
+// x[r][:] = E[token[r]][:]   grid: M blocks
+template <typename WT>
+__global__ __launch_bounds__(256) void embed_kernel(const WT *__restrict__ E, StepTokens tok, float *__restrict__ x, int d)
 {
-    const int r = blockIdx.x, d = n_heads * head_dim, dkv = n_kv_heads * head_dim, half = head_dim >> 1;
-    const int pos = *len_ptr + r;                              // the row's cache slot
-    const int rpos = depth ? *len_ptr + depth[r] : pos;        // the row's rotary position
-    const int page = page_table[pos / page_tokens], tip = pos % page_tokens;
-    float *q = qkv + (size_t)r * (d + 2 * dkv), *k = q + d, *v = k + dkv;
-    for (int idx = threadIdx.x; idx < n_heads * half; idx += 256) {
-        int hd = idx / half, i = idx - hd * half;
-        float2 cs = rope_tab[(size_t)rpos * half + i];
-        int e0 = hd * head_dim + i, e1 = e0 + half;
-        float qa = q[e0], qb = q[e1];
-        q[e0] = qa * cs.x - qb * cs.y;
-        q[e1] = qb * cs.x + qa * cs.y;
-        if (hd >= n_kv_heads) continue;
-        float ka = k[e0], kb = k[e1];
-        size_t ko = kv_offset(page, layer, n_layers, 0, hd, n_kv_heads, tip, page_tokens, head_dim);
-        size_t vo = kv_offset(page, layer, n_layers, 1, hd, n_kv_heads, tip, page_tokens, head_dim);
-        store_kv(pool, ko + i, ka * cs.x - kb * cs.y);
-        store_kv(pool, ko + i + half, kb * cs.x + ka * cs.y);
-        store_kv(pool, vo + i, v[e0]);
-        store_kv(pool, vo + i + half, v[e1]);
+    int r = blockIdx.x;
+    const WT *src = E + (size_t)tok.t[r] * d;
+    for (int i = threadIdx.x; i < d; i += blockDim.x) x[(size_t)r * d + i] = load_f32(src, (size_t)i);
+}
+
+// ------------------------------------------------ GEMM (fp32 matrix cores)
+//
+// Y[M][N] = X[M][K] * W[N][K]^T with exact fp32 products on v_mfma_f32_16x16x4_f32, weights (fp32 or bf16)
+// row-major as the caller gave them.  Block = 8 waves on 16 output features (two times 16 where the epilogue
+// pairs them) x 16 or 32 rows; wave w takes the 128-byte chunks w, w + 8, ... of a weight row (32 columns of fp32, 64
+// of bf16), lane (r, kg) holding 32 bytes of weight row r and the same columns of window row r, i.e. an MFMA
+// contracts one column of each of four lanes.  A wave's loads of two or three chunks are in flight together.  The partial tiles meet in LDS and are
+// added in pairs.  An element's sums do not depend on the other rows, on M or on the block's row count.
+//
+// At the shapes this path is made for (d 256, FFN 688) every kernel is a chain of latencies, so the step is cut
+// into as few launches as the grid-wide dependencies allow: RMSNorm is folded in (x * gain goes into the product,
+// the block sums x^2 of its rows beside it, 1 / rms scales the result), and so are rotary embedding and cache
+// write, residual add and SwiGLU.  One layer is five launches where one per operation took eleven, and a launch
+// takes 3-4 us instead of 11 (dot products with a butterfly over the lanes per output: 40 us at 32 rows, which
+// it took eight at a time).
+enum { GEN_PLAIN = 0, GEN_QKV = 1, GEN_RESIDUAL = 2, GEN_GATE_UP = 3, GEN_LOGITS = 4 };
+__host__ __device__ constexpr bool gen_norm(int mode) { return mode == GEN_QKV || mode == GEN_GATE_UP || mode == GEN_LOGITS; }
+__host__ __device__ constexpr bool gen_pairs(int mode) { return mode == GEN_QKV || mode == GEN_GATE_UP; }
+
+struct GenArgs {
+    const float *X;       // [M][K]
+    int M, K;
+    const void *W0, *W1, *W2;   // PLAIN, LOGITS, RESIDUAL: W0; GATE_UP: gate, up; QKV: wq, wk, wv
+    const void *gain;     // QKV, GATE_UP, LOGITS: the RMSNorm of X that is folded in
+    float eps;
+    float *Y;             // PLAIN, LOGITS: output; QKV: rotated q; RESIDUAL: updated in place; GATE_UP: silu(gate) * up
+    int ldy;
+    // QKV
+    const float2 *rope;
+    void *pool;
+    const int32_t *page_table, *len_ptr;
+    const int32_t *depth; // draft tree: a row's rotary position is length + depth (nullable)
+    int layer, n_layers, n_heads, n_kv_heads, head_dim, page_tokens;
+};
+
+// eight weights as they lie in memory
+template <typename WT>
+struct Raw8;
+template <>
+struct Raw8<float> {
+    float4 a, b;
+    __device__ __forceinline__ void clear() { a = b = make_float4(0.f, 0.f, 0.f, 0.f); }
+    __device__ __forceinline__ void load(const float *p) { a = *reinterpret_cast<const float4 *>(p); b = *reinterpret_cast<const float4 *>(p + 4); }
+    __device__ __forceinline__ float at(int j) const { const float4 &v = j < 4 ? a : b; return (j & 3) == 0 ? v.x : ((j & 3) == 1 ? v.y : ((j & 3) == 2 ? v.z : v.w)); }
+};
+template <>
+struct Raw8<bf16_t> {
+    uint4 a;
+    __device__ __forceinline__ void clear() { a = make_uint4(0, 0, 0, 0); }
+    __device__ __forceinline__ void load(const bf16_t *p) { a = *reinterpret_cast<const uint4 *>(p); }
+    __device__ __forceinline__ float at(int j) const
+    {
+        const uint32_t v = (j >> 1) == 0 ? a.x : ((j >> 1) == 1 ? a.y : ((j >> 1) == 2 ? a.z : a.w));
+        return __uint_as_float(j & 1 ? v & 0xffff0000u : v << 16);
+    }
+};
+
+// grid: (features / 16, or pairs of 16; ceil(M / (16 RT)))
+template <typename WT, int MODE, int RT>
+__global__ __launch_bounds__(512, sizeof(WT) == 2 && RT == 1 ? 4 : 2) void gemm_gen_kernel(GenArgs a)
+{
+    constexpr int NW = gen_pairs(MODE) ? 2 : 1, S = sizeof(WT) == 2 ? 2 : 1, WAVES = 8,
+                  U = S == 2 && (NW == 2 || RT == 2) ? 2 : 3;   // chunks in flight: what two blocks per compute unit have registers for
+    constexpr bool NORM = gen_norm(MODE);
+    __shared__ float red[WAVES][NW][RT][64][4];
+    __shared__ float ssq[WAVES][RT][16];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 15, kg = lane >> 4;
+    const int K = a.K, m0 = blockIdx.y * 16 * RT;
+
+    // the weight rows of this block's tiles
+    const WT *w[NW];
+    int sect = 0, head = 0, i0 = 0;   // QKV: q | k | v, its head, the pair's first dimension
+    if (MODE == GEN_QKV) {
+        const int half = a.head_dim / 2, per_head = half / 16;
+        head = blockIdx.x / per_head;
+        i0 = 16 * (blockIdx.x - head * per_head);
+        sect = head < a.n_heads ? 0 : (head < a.n_heads + a.n_kv_heads ? 1 : 2);
+        head -= sect == 0 ? 0 : (sect == 1 ? a.n_heads : a.n_heads + a.n_kv_heads);
+        const WT *W = (const WT *)(sect == 0 ? a.W0 : (sect == 1 ? a.W1 : a.W2)) + (size_t)(head * a.head_dim + i0 + r) * K;
+        w[0] = W;
+        w[NW - 1] = W + (size_t)half * K;
+    } else {
+        w[0] = (const WT *)a.W0 + (size_t)(blockIdx.x * 16 + r) * K;
+        if (NW == 2) w[NW - 1] = (const WT *)a.W1 + (size_t)(blockIdx.x * 16 + r) * K;
+    }
+    const WT *gain = (const WT *)a.gain;
+    // QKV: what the epilogue of the finishing waves needs besides the sums, requested first: position -> page, angles
+    int pos = 0, page = 0;
+    float2 cs[4];
+    if (MODE == GEN_QKV && wave < RT && m0 + 16 * wave + r < a.M) {
+        const int m = m0 + 16 * wave + r, len = *a.len_ptr;
+        pos = len + m;   // the row's cache slot
+        if (sect > 0) page = a.page_table[pos / a.page_tokens];
+        if (sect < 2) {
+            const float2 *c = a.rope + (size_t)(a.depth ? len + a.depth[m] : pos) * (a.head_dim / 2) + i0 + 4 * kg;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) cs[q] = c[q];
+        }
+    }
+
+    // several chains of sums side by side: shorter chains round less (the result is as close to the 64-bit one as
+    // the dot products' was) and do not wait for one another
+    constexpr int NA = NW == 2 ? 4 : 8;
+    f32x4 acc[NA][NW][RT];
+    float ss[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        ss[t] = 0.f;
+#pragma unroll
+        for (int n = 0; n < NW; ++n)
+#pragma unroll
+            for (int q = 0; q < NA; ++q) acc[q][n][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    for (int c0 = wave; c0 * 32 * S < K; c0 += WAVES * U) {
+        Raw8<WT> wv[U][S][NW];
+        Raw8<WT> gv[U][S];
+        float xv[U][S][RT][8];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                const int k = (c0 + u * WAVES) * 32 * S + 8 * (S * kg + s);
+#pragma unroll
+                for (int n = 0; n < NW; ++n) wv[u][s][n].clear();
+                gv[u][s].clear();
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+#pragma unroll
+                    for (int t = 0; t < RT; ++t) xv[u][s][t][i] = 0.f;
+                if (k < K) {
+#pragma unroll
+                    for (int n = 0; n < NW; ++n) wv[u][s][n].load(w[n] + k);
+#pragma unroll
+                    for (int t = 0; t < RT; ++t)
+                        if (m0 + 16 * t + r < a.M) load8(a.X + (size_t)(m0 + 16 * t + r) * K + k, xv[u][s][t]);
+                    if (NORM) gv[u][s].load(gain + k);
+                }
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+#pragma unroll
+                    for (int t = 0; t < RT; ++t) {
+                        float x = xv[u][s][t][j];
+                        if (NORM) {
+                            ss[t] = fmaf(x, x, ss[t]);
+                            x *= gv[u][s].at(j);
+                        }
+#pragma unroll
+                        for (int n = 0; n < NW; ++n)
+                            acc[j % NA][n][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[u][s][n].at(j), x, acc[j % NA][n][t], 0, 0, 0);
+                    }
+                }
+    }
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        ss[t] = rows_sum(ss[t]);
+        if (kg == 0) ssq[wave][t][r] = ss[t];
+#pragma unroll
+        for (int n = 0; n < NW; ++n) {
+            f32x4 s = (acc[0][n][t] + acc[1][n][t]) + (acc[2][n][t] + acc[3][n][t]);
+            if (NA == 8) s += (acc[NA - 4][n][t] + acc[NA - 3][n][t]) + (acc[NA - 2][n][t] + acc[NA - 1][n][t]);
+            *reinterpret_cast<f32x4 *>(red[wave][n][t][lane]) = s;
+        }
+    }
+    __syncthreads();
+    if (wave >= RT) return;
+    // wave t finishes row tile t: lane (m, kg) has features 4 kg .. 4 kg + 3 of row m0 + 16 t + m
+    const int t = wave, m = m0 + 16 * t + r;
+    f32x4 y[NW];
+#pragma unroll
+    for (int n = 0; n < NW; ++n) {
+        f32x4 p[WAVES];
+#pragma unroll
+        for (int v = 0; v < WAVES; ++v) p[v] = *reinterpret_cast<const f32x4 *>(red[v][n][t][lane]);
+        y[n] = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+    }
+    if (NORM) {
+        float q[WAVES];
+#pragma unroll
+        for (int v = 0; v < WAVES; ++v) q[v] = ssq[v][t][r];
+        const float tot = ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
+        const float rinv = 1.0f / sqrtf(tot / (float)K + a.eps);
+#pragma unroll
+        for (int n = 0; n < NW; ++n) y[n] = y[n] * rinv;
+    }
+    if (m >= a.M) return;
+    const int f = blockIdx.x * 16 + 4 * kg;   // (all but QKV)
+    if (MODE == GEN_PLAIN || MODE == GEN_LOGITS) {
+        // (the caller's buffer need not be aligned for wide stores)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a.Y[(size_t)m * a.ldy + f + i] = y[0][i];
+    } else if (MODE == GEN_RESIDUAL) {
+        f32x4 *x = reinterpret_cast<f32x4 *>(a.Y + (size_t)m * a.ldy + f);
+        *x = *x + y[0];
+    } else if (MODE == GEN_GATE_UP) {
+        f32x4 o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = y[0][i] / (1.0f + expf(-y[0][i])) * y[NW - 1][i];
+        *reinterpret_cast<f32x4 *>(a.Y + (size_t)m * a.ldy + f) = o;
+    } else {
+        const int half = a.head_dim / 2, i = i0 + 4 * kg;
+        f32x4 lo = y[0], hi = y[NW - 1];
+        if (sect < 2) {   // rotate the pairs (i, i + head_dim / 2) by the row's position
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                lo[q] = y[0][q] * cs[q].x - y[NW - 1][q] * cs[q].y;
+                hi[q] = y[NW - 1][q] * cs[q].x + y[0][q] * cs[q].y;
+            }
+        }
+        if (sect == 0) {
+            float *q = a.Y + (size_t)m * a.ldy + head * a.head_dim + i;
+            *reinterpret_cast<f32x4 *>(q) = lo;
+            *reinterpret_cast<f32x4 *>(q + half) = hi;
+        } else {
+            const size_t o = kv_offset(page, a.layer, a.n_layers, sect - 1, head, a.n_kv_heads, pos % a.page_tokens, a.page_tokens, a.head_dim) + i;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                store_kv((WT *)a.pool, o + q, lo[q]);
+                store_kv((WT *)a.pool, o + half + q, hi[q]);
+            }
+        }
     }
 }
 
 // ------------------------------------------------------------- attention
 //
 // Window-causal attention of the M query rows over the paged cache.  Keys are
-// cut into fixed splits of kAttnSplit absolute positions; block (head, split)
-// computes, for each row, the split's score maximum, sum of exponentials and
-// unnormalised weighted V sum; attn_combine_kernel merges the splits of a row
-// in increasing order.  Row r sees keys 0..len + r; keys it must not see get
+// cut into fixed splits of kAttnSplit absolute positions; block (head, split, 16-row group), one wave per 16
+// keys, computes for each row the split's score maximum, sum of exponentials and unnormalised weighted V sum on
+// the fp32 matrix cores; the last block of a (head, row group) merges the splits of its rows in increasing
+// order.  Row r sees keys 0..len + r; keys it must not see get
 // weight exactly 0, so a row's numbers do not depend on M.
-// Lane layout: a key's head_dim elements are spread over DH/8 lanes (16 bytes
-// of bf16 each), so a wave reads 64*8 consecutive elements of the page.
-// part: [head][split][max_window][DH + 2] = (o[DH], max, denominator).
-// grid: (n_heads, n_splits), 4 waves.
+// part: outputs [head][split][max_window][DH], then (maximum, denominator) [head][split][max_window][2].
+// counter: [head][row group], a 256-byte line each, zero between calls.
+// grid: (n_heads, n_splits, ceil(M / 16)), 4 waves.
 template <typename KT, int DH>
-__global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ qkv, int q_stride, const KT *__restrict__ pool,
+__global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ q, int q_stride, const KT *__restrict__ pool,
                                                     const int32_t *__restrict__ page_table,
                                                     const int32_t *__restrict__ len_ptr, int M, int layer, int n_layers,
                                                     int n_heads, int n_kv_heads, int page_tokens, int max_window,
                                                     int max_splits, float scale, float *__restrict__ part,
+                                                    uint32_t *__restrict__ counter, float *__restrict__ att,
                                                     const uint32_t *__restrict__ row_mask /* draft tree: nullable */)
 {
-    constexpr int LPK = DH / 8;        // lanes per key
-    constexpr int KPG = 64 / LPK;      // keys per wave group
-    constexpr int NG = kAttnSplit / KPG;
-    __shared__ float sc[8][kAttnSplit];
-    __shared__ float stat[8][2];
-    __shared__ float red[4][8][DH];
-
-    const int head = blockIdx.x, split = blockIdx.y;
+    constexpr int NC = DH / 16, WAVES = kAttnSplit / 16;
+    __shared__ float red[WAVES][NC][64][4];
+    __shared__ float wmax[WAVES][16], wden[WAVES][16];
+    __shared__ bool last;
+    const int head = blockIdx.x, split = blockIdx.y, m0 = 16 * blockIdx.z;
     const int kvh = head / (n_heads / n_kv_heads);   // the key / value head this query head reads
     const int L = *len_ptr;
-    const int s0 = split * kAttnSplit;
-    if (s0 >= L + M) return;  // no key of this split exists for any row
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int ksub = lane / LPK, dg = lane % LPK;
+    const int n_splits = (L + M + kAttnSplit - 1) / kAttnSplit;
+    if (split >= n_splits) return;  // no key of this split exists for any row
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 15, kg = lane >> 4;
+    const int key0 = split * kAttnSplit + 16 * wave, m = m0 + r;
 
-    for (int m0 = 0; m0 < M; m0 += 8) {
-        // ---- scores
-        float qv[8][8];
+    // every load of the wave goes out together: lane (r, kg) takes columns 16 c + 4 kg .. + 4 of key key0 + r and of
+    // query row m0 + r, and dimensions 16 c + r of the values of keys key0 + 4 kg .. + 4
+    float kf[NC][4], qf[NC][4], vf[NC][4];
 #pragma unroll
-        for (int mm = 0; mm < 8; ++mm) {
-            if (m0 + mm < M) {
-                load8(qkv + (size_t)(m0 + mm) * q_stride + head * DH + dg * 8, qv[mm]);
-            } else {
+    for (int c = 0; c < NC; ++c)
 #pragma unroll
-                for (int i = 0; i < 8; ++i) qv[mm][i] = 0.f;
+        for (int i = 0; i < 4; ++i) { kf[c][i] = 0.f; qf[c][i] = 0.f; vf[c][i] = 0.f; }
+    if (m < M) {
+        const float *qr = q + (size_t)m * q_stride + head * DH + 4 * kg;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(qr + 16 * c);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) qf[c][i] = v[i];
+        }
+    }
+    if (key0 + r < L + M) {
+        const int key = key0 + r;
+        const KT *kr = pool + kv_offset(page_table[key / page_tokens], layer, n_layers, 0, kvh, n_kv_heads, key % page_tokens, page_tokens, DH) + 4 * kg;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) kf[c][i] = load_f32(kr, (size_t)(16 * c + i));
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int key = key0 + 4 * kg + i;
+        if (key < L + M) {
+            const KT *vr = pool + kv_offset(page_table[key / page_tokens], layer, n_layers, 1, kvh, n_kv_heads, key % page_tokens, page_tokens, DH) + r;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) vf[c][i] = load_f32(vr, (size_t)(16 * c));
+        }
+    }
+    // ---- scores: lane (r, kg) has keys key0 + 4 kg + i of row m
+    // (eight chains, as in the GEMM)
+    f32x4 sq[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        sq[j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = j & 1; c < NC; c += 2) sq[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][j >> 1], qf[c][j >> 1], sq[j], 0, 0, 0);
+    }
+    const f32x4 s = ((sq[0] + sq[1]) + (sq[2] + sq[3])) + ((sq[4] + sq[5]) + (sq[6] + sq[7]));
+    const uint32_t vis = row_mask && m < M ? row_mask[m] : 0u;
+    float p[4], mx = kMasked;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int key = key0 + 4 * kg + i;
+        const bool sees = row_mask ? key < L || (key - L < 32 && ((vis >> (key - L)) & 1u)) : key <= L + m;
+        p[i] = m < M && sees ? s[i] * scale : kMasked;
+        mx = fmaxf(mx, p[i]);
+    }
+    mx = rows_max(mx);
+    if (kg == 0) wmax[wave][r] = mx;
+    __syncthreads();
+    float bm = wmax[0][r], den = 0.f;
+#pragma unroll
+    for (int v = 1; v < WAVES; ++v) bm = fmaxf(bm, wmax[v][r]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        p[i] = p[i] > 0.5f * kMasked ? expf(p[i] - bm) : 0.f;
+        den += p[i];
+    }
+    den = rows_sum(den);
+    if (kg == 0) wden[wave][r] = den;
+    // ---- weighted V: lane (r, kg) has dimensions 16 c + 4 kg .. + 4 of row m
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        f32x4 o[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c][i], p[i], (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        *reinterpret_cast<f32x4 *>(red[wave][c][lane]) = (o[0] + o[1]) + (o[2] + o[3]);
+    }
+    __syncthreads();
+    const size_t slot0 = ((size_t)head * max_splits) * max_window, stride = (size_t)max_window;   // rows of (head, split 0); rows per split
+    float *po = part, *ps = part + (size_t)n_heads * max_splits * max_window * DH;
+    for (int c = wave; c < NC; c += WAVES) {
+        f32x4 o = *reinterpret_cast<const f32x4 *>(red[0][c][lane]);
+#pragma unroll
+        for (int v = 1; v < WAVES; ++v) o += *reinterpret_cast<const f32x4 *>(red[v][c][lane]);
+        if (m < M) stc16<true>(po + (slot0 + split * stride + m) * DH + 16 * c + 4 * kg, o);
+    }
+    if (wave == 0 && kg == 0 && m < M) {
+        float d = wden[0][r];
+#pragma unroll
+        for (int v = 1; v < WAVES; ++v) d += wden[v][r];
+        stc8<true>(ps + (slot0 + split * stride + m) * 2, make_uint2(__float_as_uint(bm), __float_as_uint(d)));
+    }
+    // ---- the last block of this head and row group merges the splits
+    wait_stores();
+    __syncthreads();
+    uint32_t *ctr = counter + ((size_t)head * (kMaxRows / 16) + blockIdx.z) * 64;
+    if (threadIdx.x == 0)
+        last = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == (uint32_t)n_splits;
+    __syncthreads();
+    if (!last) return;
+    if (threadIdx.x == 0) st_agent(ctr, 0u);
+    constexpr int SB = 8, DQ = DH / 4;
+    for (int idx = threadIdx.x; idx < 16 * DQ; idx += 256) {
+        const int row = m0 + idx / DQ, e4 = idx % DQ;
+        if (row >= M) continue;
+        const int ns = (L + row) / kAttnSplit + 1;   // splits that hold keys this row may see
+        const uint4 *o4 = reinterpret_cast<const uint4 *>(po);
+        const uint2 *s2 = reinterpret_cast<const uint2 *>(ps);
+        float g = kMasked;
+        for (int s0 = 0; s0 < ns; s0 += SB) {
+            float mv[SB];
+#pragma unroll
+            for (int j = 0; j < SB; ++j) mv[j] = __uint_as_float(ld8_at<true>(s2 + slot0, (uint32_t)((s0 + j < ns ? s0 + j : s0) * stride + row)).x);
+#pragma unroll
+            for (int j = 0; j < SB; ++j) g = fmaxf(g, mv[j]);
+        }
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+        float dn = 0.f;
+        for (int s0 = 0; s0 < ns; s0 += SB) {
+            uint4 ov[SB];
+            uint2 st[SB];
+#pragma unroll
+            for (int j = 0; j < SB; ++j) {
+                const uint32_t at = (uint32_t)((s0 + j < ns ? s0 + j : s0) * stride + row);
+                ov[j] = ld16_at<true>(o4 + slot0 * DQ, at * DQ + e4);
+                st[j] = ld8_at<true>(s2 + slot0, at);
+            }
+#pragma unroll
+            for (int j = 0; j < SB; ++j) {
+                if (s0 + j >= ns) continue;
+                const float wgt = expf(__uint_as_float(st[j].x) - g);
+                dn = fmaf(wgt, __uint_as_float(st[j].y), dn);
+                o[0] = fmaf(wgt, __uint_as_float(ov[j].x), o[0]);
+                o[1] = fmaf(wgt, __uint_as_float(ov[j].y), o[1]);
+                o[2] = fmaf(wgt, __uint_as_float(ov[j].z), o[2]);
+                o[3] = fmaf(wgt, __uint_as_float(ov[j].w), o[3]);
             }
         }
-        for (int g = wave; g < NG; g += 4) {
-            const int jl = g * KPG + ksub, j = s0 + jl;
-            const bool exists = j < L + M;
-            float kv[8];
-            if (exists) {
-                int page = page_table[j / page_tokens];
-                load8(pool + kv_offset(page, layer, n_layers, 0, kvh, n_kv_heads, j % page_tokens, page_tokens, DH) + dg * 8, kv);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) kv[i] = 0.f;
-            }
-#pragma unroll
-            for (int mm = 0; mm < 8; ++mm) {
-                float p = 0.f;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) p = fmaf(qv[mm][i], kv[i], p);
-#pragma unroll
-                for (int off = LPK / 2; off >= 1; off >>= 1) p += __shfl_xor(p, off, kWave);
-                if (dg == 0) {
-                    bool sees = j <= L + m0 + mm;
-                    if (row_mask && m0 + mm < M) sees = j < L || (j - L < 32 && ((row_mask[m0 + mm] >> (j - L)) & 1u));
-                    sc[mm][jl] = (exists && m0 + mm < M && sees) ? p * scale : kMasked;
-                }
-            }
-        }
-        __syncthreads();
-        // ---- per-row maximum, exponentials, denominator (one key per lane)
-        for (int mm = wave; mm < 8; mm += 4) {
-            float s = sc[mm][lane];
-            float mx = wave_max(s);
-            float p = (s > 0.5f * kMasked) ? expf(s - mx) : 0.f;
-            sc[mm][lane] = p;
-            float den = wave_sum(p);
-            if (lane == 0) { stat[mm][0] = mx; stat[mm][1] = den; }
-        }
-        __syncthreads();
-        // ---- weighted V
-        float acc[8][8];
-#pragma unroll
-        for (int mm = 0; mm < 8; ++mm)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc[mm][i] = 0.f;
-        for (int g = wave; g < NG; g += 4) {
-            const int jl = g * KPG + ksub, j = s0 + jl;
-            if (j < L + M) {
-                float vv[8];
-                int page = page_table[j / page_tokens];
-                load8(pool + kv_offset(page, layer, n_layers, 1, kvh, n_kv_heads, j % page_tokens, page_tokens, DH) + dg * 8, vv);
-#pragma unroll
-                for (int mm = 0; mm < 8; ++mm) {
-                    float p = sc[mm][jl];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) acc[mm][i] = fmaf(p, vv[i], acc[mm][i]);
-                }
-            }
-        }
-        // sum the KPG key streams of the wave (lanes that differ in ksub), then the waves in order
-#pragma unroll
-        for (int mm = 0; mm < 8; ++mm)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                float v = acc[mm][i];
-#pragma unroll
-                for (int off = 32; off >= LPK; off >>= 1) v += __shfl_xor(v, off, kWave);
-                acc[mm][i] = v;
-            }
-        if (ksub == 0) {
-#pragma unroll
-            for (int mm = 0; mm < 8; ++mm)
-#pragma unroll
-                for (int i = 0; i < 8; ++i) red[wave][mm][dg * 8 + i] = acc[mm][i];
-        }
-        __syncthreads();
-        for (int idx = threadIdx.x; idx < 8 * DH; idx += 256) {
-            int mm = idx / DH, e = idx - mm * DH;
-            if (m0 + mm < M) {
-                float o = ((red[0][mm][e] + red[1][mm][e]) + red[2][mm][e]) + red[3][mm][e];
-                part[(((size_t)head * max_splits + split) * max_window + (m0 + mm)) * (DH + 2) + e] = o;
-            }
-        }
-        if (threadIdx.x < 8 && m0 + threadIdx.x < M) {
-            size_t base = (((size_t)head * max_splits + split) * max_window + (m0 + threadIdx.x)) * (DH + 2) + DH;
-            part[base] = stat[threadIdx.x][0];
-            part[base + 1] = stat[threadIdx.x][1];
-        }
-        __syncthreads();
+        o[0] /= dn; o[1] /= dn; o[2] /= dn; o[3] /= dn;
+        *reinterpret_cast<f32x4 *>(att + (size_t)row * n_heads * DH + head * DH + 4 * e4) = o;
     }
 }
 
-// Merge the splits of (row, head) in increasing split order.  Row r has keys in
-// splits 0..(len + r) / kAttnSplit.  Writes att as fp32 and optionally as the
-// split bf16 operand of the output projection.  grid: (M, n_heads), DH threads.
-template <int DH>
-__global__ __launch_bounds__(DH) void attn_combine_kernel(const float *__restrict__ part,
-                                                           const int32_t *__restrict__ len_ptr, int n_heads,
-                                                           int max_window, int max_splits, float *__restrict__ att,
-                                                           bf16_t *__restrict__ atts, int cls)
+// Appends n rows to the cache's length: a window of a prompt of which only the cache entries are wanted.
+__global__ void advance_length_kernel(int32_t *__restrict__ len_ptr, int n)
 {
-    const int r = blockIdx.x, head = blockIdx.y, e = threadIdx.x;
-    const int ns = (*len_ptr + r) / kAttnSplit + 1;
-    const float *p = part + (((size_t)head * max_splits) * max_window + r) * (DH + 2);
-    const size_t stride = (size_t)max_window * (DH + 2);
-    float gm = kMasked;
-    for (int s = 0; s < ns; ++s) gm = fmaxf(gm, p[s * stride + DH]);
-    float o = 0.f, den = 0.f;
-    for (int s = 0; s < ns; ++s) {
-        float w = expf(p[s * stride + DH] - gm);
-        o = fmaf(w, p[s * stride + e], o);
-        den = fmaf(w, p[s * stride + DH + 1], den);
-    }
-    float v = o / den;
-    const int d = n_heads * DH;
-    att[(size_t)r * d + head * DH + e] = v;
-    if (atts) {
-        bf16_t hi = f32_to_bf16(v);
-        atts[xp_offset(cls, r, head * DH + e, 0)] = hi;
-        atts[xp_offset(cls, r, head * DH + e, 1)] = f32_to_bf16(v - bf16_to_f32(hi));
-    }
-}
-
-// ------------------------------------------------------------------ SwiGLU
-
-// a[r][i] = silu(gu[r][i]) * gu[r][F + i]    grid: (ceil(F/256), M)
-__global__ __launch_bounds__(256) void swiglu_kernel(const float *__restrict__ gu, float *__restrict__ a,
-                                                      int F)
-{
-    int r = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= F) return;
-    float g = gu[(size_t)r * 2 * F + i], u = gu[(size_t)r * 2 * F + F + i];
-    float v = g / (1.0f + expf(-g)) * u;
-    a[(size_t)r * F + i] = v;
+    if (threadIdx.x == 0 && blockIdx.x == 0) *len_ptr += n;
 }
 
 // ------------------------------------------- argmax + acceptance + commit
@@ -580,11 +686,11 @@ __global__ __launch_bounds__(256) void swiglu_kernel(const float *__restrict__ g
 // block to finish applies Algorithm 1's accept rule: a = longest prefix with
 // window[i + 1] == pred[i]; next = pred[a]; the cache length advances by 1 + a
 // (rejected rows are simply left beyond the length and overwritten later).
-// result: [0] = a, [1] = next, [2..2+M) = pred.   grid: M blocks of 1024.
-__global__ __launch_bounds__(1024) void argmax_accept_kernel(const float *__restrict__ logits, int V, int M,
-                                                              const int32_t *__restrict__ window, int mode,
-                                                              int32_t *__restrict__ result, int32_t *__restrict__ len_ptr,
-                                                              uint32_t *__restrict__ counter)
+// result: [0] = a, [1] = next, [2..2+M) = pred; host_result: the same in pinned host memory, so that no copy
+// follows.   grid: M blocks of 1024.
+__global__ __launch_bounds__(1024) void argmax_accept_kernel(const float *__restrict__ logits, int V, int M, StepTokens window,
+                                                              int mode, int32_t *__restrict__ result, int32_t *__restrict__ host_result,
+                                                              int32_t *__restrict__ len_ptr, uint32_t *__restrict__ counter)
 {
     __shared__ float bv[16];
     __shared__ int bi[16];
@@ -611,18 +717,21 @@ __global__ __launch_bounds__(1024) void argmax_accept_kernel(const float *__rest
         st_agent(result + 2 + r, (int32_t)besti);
         wait_stores();
         last = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(M - 1);
+        st_system(host_result + 2 + r, (int32_t)besti);   // (after the counter: its way to the host is long)
     }
     __syncthreads();
     if (last && threadIdx.x == 0) {
         const int32_t *pred = result + 2;
         int a = 0;
         if (mode == 0) {
-            while (a < M - 1 && window[a + 1] == ld_agent(pred + a)) ++a;
+            while (a < M - 1 && window.t[a + 1] == ld_agent(pred + a)) ++a;
         } else {
             a = M - 1;
         }
         result[0] = a;
         result[1] = ld_agent(pred + a);
+        st_system(host_result, a);
+        st_system(host_result + 1, ld_agent(pred + a));
         *len_ptr += 1 + a;
         st_agent(counter, 0u);
     }
@@ -633,9 +742,9 @@ __global__ __launch_bounds__(1024) void argmax_accept_kernel(const float *__rest
 // is and window[r] equals the prediction made at the parent; the deepest accepted row wins (lowest
 // index among equally deep).  result[0] = its depth a, result[1] = the prediction at that row,
 // result[34 + j] = the window row at depth j of the accepted path; length += 1 + a.   One thread.
-__global__ void accept_tree_kernel(const int32_t *__restrict__ window, const int32_t *__restrict__ parent,
+__global__ void accept_tree_kernel(StepTokens window, const int32_t *__restrict__ parent,
                                    const int32_t *__restrict__ depth, int M, int32_t *__restrict__ result,
-                                   int32_t *__restrict__ len_ptr, int len_before)
+                                   int32_t *__restrict__ host_result, int32_t *__restrict__ len_ptr, int len_before)
 {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     const int32_t *pred = result + 2;
@@ -643,15 +752,20 @@ __global__ void accept_tree_kernel(const int32_t *__restrict__ window, const int
     int best = 0;
     for (int r = 1; r < M; ++r) {
         const int p = parent[r];
-        if (((acc >> p) & 1u) && window[r] == pred[p]) {
+        if (((acc >> p) & 1u) && window.t[r] == pred[p]) {
             acc |= 1u << r;
             if (depth[r] > depth[best]) best = r;
         }
     }
     const int a = depth[best];
-    for (int r = best, j = a; j >= 0; --j, r = parent[r]) result[34 + j] = r;
+    for (int r = best, j = a; j >= 0; --j, r = parent[r]) {
+        result[34 + j] = r;
+        st_system(host_result + 34 + j, r);
+    }
     result[0] = a;
     result[1] = pred[best];
+    st_system(host_result, a);
+    st_system(host_result + 1, pred[best]);
     *len_ptr = len_before + 1 + a;
 }
 

@@ -1,0 +1,75 @@
+"""The generic (row-major weights, exact fp32 products) kernels at the edges of their tiles."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import decoder as od
+from paper_2404_08698_amd import binding as B
+from paper_2404_08698_amd import synth
+import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+# one and two row tiles, the last row of a tile; K of one partial chunk, of one wave's share, one chunk into the
+# second turn of the waves' ring and beyond it; one and several feature tiles
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("m,n,k", [(1, 16, 8), (5, 48, 40), (16, 16, 256), (17, 32, 264), (32, 80, 776), (31, 16, 1600)])
+def test_linear(dtype, m, n, k):
+    g = torch.Generator().manual_seed(m * 1000 + k)
+    x = torch.randn(m, k, generator=g)
+    w = torch.randn(n, k, generator=g).to(dtype)
+    y = B.linear(x.cuda(), w.cuda(), B.GEMM_DOT).cpu().double()
+    ref = x.double() @ w.double().t()
+    # products exact, k sums of fp32 at worst: k * 2^-24 times the sum of magnitudes
+    bound = k * 2.0 ** -24 * (x.double().abs() @ w.double().abs().t())
+    assert torch.all((y - ref).abs() <= bound)
+    one = B.linear(x[m - 1:].contiguous().cuda(), w.cuda(), B.GEMM_DOT).cpu().double()
+    assert torch.equal(one[0], y[m - 1])    # a row's sums do not depend on the other rows
+
+
+@pytest.mark.parametrize("shape,page_tokens", [(synth.TINY, 8), (synth.TINY, 256), (synth.TINY_MQA, 16),
+                                               (dataclasses.replace(synth.MID_GQA, dtype="f32"), 32)])
+@pytest.mark.parametrize("cached", [0, 47, 64, 130])
+def test_windows_across_tile_and_split_edges(shape, page_tokens, cached):
+    w = synth.make_weights(shape, 5)
+    cap = 256
+    dec = od.Decoder(shape, w, cap)
+    model = B.Model(shape, H.to_cuda(w), max_window=32, max_positions=cap, page_tokens=page_tokens)
+    kv = B.KVCache(model, cap)
+    if cached:
+        H.seed_kv_both(shape, dec, kv, cached, 9)
+    pos = cached
+    for n in (17, 1, 16, 32):
+        win = synth.random_tokens(shape.vocab, n, pos + 1)
+        ref = dec.forward(win)
+        dec.set_length(pos + n)
+        # (an odd address: the logits go through the workspace; an even one takes them directly)
+        flat = torch.empty(n * shape.vocab + 1, dtype=torch.float32, device="cuda")
+        buf = flat[1:] if n == 17 else flat[:-1]
+        B.verify(model, kv, win, B.APPEND, out_logits=buf)
+        err = float(np.max(np.abs(buf.cpu().numpy().astype(np.float64).reshape(n, -1) - ref)))
+        assert err < H.TOL["f32"], (n, err)
+        pos += n
+
+
+def test_prompt_windows_leave_what_one_window_at_a_time_leaves():
+    shape = synth.TINY
+    w = H.to_cuda(synth.make_weights(shape, 5))
+    model = B.Model(shape, w, max_window=32, max_positions=256)
+    a, b = B.KVCache(model, 256), B.KVCache(model, 256)
+    prompt = synth.random_tokens(shape.vocab, 107, 3)
+    last = torch.empty(shape.vocab, dtype=torch.float32, device="cuda")
+    rows = torch.empty(11, shape.vocab, dtype=torch.float32, device="cuda")
+    t0 = B.prefill(model, a, prompt, out_logits=last)
+    for lo in (0, 32, 64):
+        B.verify(model, b, prompt[lo:lo + 32], B.APPEND)
+    _, t1 = B.verify(model, b, prompt[96:], B.APPEND, out_logits=rows)
+    assert t0 == t1 and a.length == b.length == 107 and torch.equal(last, rows[10])
+    for layer in range(shape.n_layers):
+        for x, y in zip(a.read(layer, 0, 107), b.read(layer, 0, 107)):
+            assert torch.equal(x, y)
+    win = synth.random_tokens(shape.vocab, 5, 77)     # the device's length followed
+    assert B.verify(model, a, win, want_predicts=True) == B.verify(model, b, win, want_predicts=True)
