@@ -37,7 +37,7 @@ int kv_dim_of(const anpd_model_cfg &c) { return kv_heads_of(c) * c.head_dim; }
 struct Layout {  // byte offsets into the model workspace
     size_t rope_tab, tree, batch, result, counter, gen_ctr, x, qkv, att, a, logits, part;
     // fast path: packed operands, partial sums of squares, packed weights
-    size_t xp_d, xp_att, xp_f, ssp_a, ssp_b, qp, head_ctr, layer_tab, amax, row_ctr, bar, wp_lm, total;
+    size_t xp_d, xp_att, xp_f, ssp_a, ssp_b, split_part, qp, head_ctr, layer_tab, amax, row_ctr, bar, wp_lm, total;
     size_t xp_layers, xp_stride;   // the one-kernel step's operands (bytes; stride between the layers' sets in bf16 elements: 0, one set)
     std::vector<size_t> wp_qkv, wp_o, wp_gu, wp_down;
     int max_splits;
@@ -97,7 +97,7 @@ Layout make_layout(const anpd_model_cfg *c)
     L.a = take(MW * F * 4);
     L.logits = take(MW * V * 4);
     L.part = take((size_t)c->n_heads * L.max_splits * (wants_mfma(c) ? 32 : MW) * (c->head_dim + 2) * 4);
-    L.xp_d = L.xp_att = L.xp_f = L.ssp_a = L.ssp_b = L.qp = L.head_ctr = L.wp_lm = 0;
+    L.xp_d = L.xp_att = L.xp_f = L.ssp_a = L.ssp_b = L.split_part = L.qp = L.head_ctr = L.wp_lm = 0;
     L.layer_tab = L.amax = L.row_ctr = L.bar = 0;
     L.xp_layers = L.xp_stride = 0;
     if (wants_mfma(c)) {
@@ -111,6 +111,7 @@ Layout make_layout(const anpd_model_cfg *c)
         L.xp_layers = take((3 * x_operand_elems((int)d) + x_operand_elems((int)F)) * sizeof(bf16_t));
         L.ssp_a = take((d / 16) * 32 * 4);
         L.ssp_b = take((d / 16) * 32 * 4);
+        if (c->max_window > 16) L.split_part = take((d / 16) * 8 * 4 * 1024);   // partial tiles of the split O / down projections
         L.qp = take((size_t)c->n_heads * 4 * (c->head_dim / 32) * 1024);
         L.head_ctr = take((size_t)c->n_heads * kCounterStride * sizeof(uint32_t));
         L.layer_tab = take((size_t)c->n_layers * sizeof(LayerW));
@@ -222,6 +223,24 @@ int32_t launch_gen(const GenArgs &a, int n_blocks, hipStream_t st)
 
 // ---- fast path: packed MFMA GEMMs ---------------------------------------------
 
+template <int T, int D, int EPI>
+int32_t launch_wide(const FastArgs &a, int blocks, hipStream_t st)
+{
+    const size_t smem = (size_t)(T < 4 ? T : 4) * kFastWaves * 4 * 256 * sizeof(float);
+    static bool attr_set = false;   // per instantiation
+    if (!attr_set) {
+        HIP_TRY(hipFuncSetAttribute((const void *)gemm_wide_kernel<T, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+        attr_set = true;
+    }
+    hipLaunchKernelGGL((gemm_wide_kernel<T, D, EPI>), dim3((unsigned)blocks), dim3(kFastThreads), smem, st, a);
+    return ANPD_OK;
+}
+
+// O and down projections.  17..32 rows with at most two tiles per compute unit: split by k-step class (see
+// gemm_split_kernel), 8 classes x n_cu / 8 groups of 8 to 16 tiles each.  Fewer tiles than one per compute unit
+// (small models) stay with one launch, which is all they are.
+int32_t launch_residual(FastArgs &a, int n_cu, float *part, hipStream_t st);
+
 template <int EPI>
 int32_t launch_fast(FastArgs &a, int n_cu, bool force_stream, hipStream_t st)
 {
@@ -281,9 +300,16 @@ int32_t launch_fast(FastArgs &a, int n_cu, bool force_stream, hipStream_t st)
                 attr_set2 = true;
             }
             hipLaunchKernelGGL((gemm_group_kernel<2, 4, EPI>), grid, block, smem, st, a);
+        } else if (a.n_tiles <= n_cu && kpw >= 8) {
+            // (17..32 rows, one tile per compute unit, K long enough to fill the ring: at K = 256 it costs 10 % of the
+            // tiny model's step)
+            if (int32_t rc = launch_wide<1, 8, EPI>(a, a.n_tiles, st); rc != ANPD_OK) return rc;
         } else if (per_block <= 2) {
             size_t smem = (size_t)2 * kFastWaves * 4 * 256 * sizeof(float);
             hipLaunchKernelGGL((gemm_group_kernel<4, 2, EPI>), grid, block, smem, st, a);
+        } else if (const int passes = (per_block + 7) / 8, per_pass = (per_block + passes - 1) / passes; per_pass > 4) {
+            // as few passes over the operand as the accumulators allow
+            if (int32_t rc = per_pass <= 6 ? launch_wide<6, 3, EPI>(a, blocks, st) : launch_wide<8, 2, EPI>(a, blocks, st); rc != ANPD_OK) return rc;
         } else {
             size_t smem = (size_t)4 * kFastWaves * 4 * 256 * sizeof(float);
             static bool attr_set = false;
@@ -294,6 +320,22 @@ int32_t launch_fast(FastArgs &a, int n_cu, bool force_stream, hipStream_t st)
             hipLaunchKernelGGL((gemm_group_kernel<4, 4, EPI>), grid, block, smem, st, a);
         }
     }
+    HIP_TRY(hipGetLastError());
+    return ANPD_OK;
+}
+
+int32_t launch_residual(FastArgs &a, int n_cu, float *part, hipStream_t st)
+{
+    const int groups = n_cu / 8, waves = groups > 0 ? (a.n_tiles + groups - 1) / groups : 0;
+    if (a.cls != 32 || waves < kFastWaves || waves > kSplitMaxWaves) return launch_fast<EPI_RESIDUAL>(a, n_cu, false, st);
+    static bool attr_set = false;
+    if (!attr_set) {
+        HIP_TRY(hipFuncSetAttribute((const void *)gemm_split_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSplitLds));
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(gemm_split_kernel, dim3((unsigned)((a.n_tiles + waves - 1) / waves * 8)), dim3((unsigned)(waves * 64)), kSplitLds, st, a, part);
+    hipLaunchKernelGGL((split_merge_kernel<EPI_RESIDUAL>), dim3((unsigned)a.n_tiles, (unsigned)((a.M + 15) / 16)), dim3(64), 0, st, a,
+                       (const float *)part);
     HIP_TRY(hipGetLastError());
     return ANPD_OK;
 }
@@ -499,7 +541,7 @@ int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, 
     bf16_t *qp = (bf16_t *)(ws + L.qp);
     uint32_t *head_ctr = (uint32_t *)(ws + L.head_ctr);
     bf16_t *xp_d = (bf16_t *)(ws + L.xp_d), *xp_att = (bf16_t *)(ws + L.xp_att), *xp_f = (bf16_t *)(ws + L.xp_f);
-    float *ssp_a = (float *)(ws + L.ssp_a), *ssp_b = (float *)(ws + L.ssp_b);
+    float *ssp_a = (float *)(ws + L.ssp_a), *ssp_b = (float *)(ws + L.ssp_b), *split_part = (float *)(ws + L.split_part);
     int32_t *result = (int32_t *)(ws + L.result);
     uint32_t *counter = (uint32_t *)(ws + L.counter);
     const float scale = 1.0f / sqrtf((float)dh);
@@ -593,7 +635,7 @@ int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, 
             a.gain = (const bf16_t *)m->ffn_norm[l];
             a.xp_next = xp_d;
             a.ssp_next = ssp_b;
-            if ((rc = launch_fast<EPI_RESIDUAL>(a, m->n_cu, false, st)) != ANPD_OK) return rc;
+            if ((rc = launch_residual(a, m->n_cu, split_part, st)) != ANPD_OK) return rc;
         }
         mark(m, ANPD_PROF_GEMM_O, st);
         {
@@ -616,7 +658,7 @@ int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, 
             a.gain = (const bf16_t *)(l + 1 < c.n_layers ? m->attn_norm[(size_t)l + 1] : m->final_norm);
             a.xp_next = xp_d;
             a.ssp_next = ssp_a;
-            if ((rc = launch_fast<EPI_RESIDUAL>(a, m->n_cu, false, st)) != ANPD_OK) return rc;
+            if ((rc = launch_residual(a, m->n_cu, split_part, st)) != ANPD_OK) return rc;
         }
         mark(m, ANPD_PROF_GEMM_DOWN, st);
     }

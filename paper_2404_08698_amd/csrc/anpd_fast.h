@@ -193,21 +193,47 @@ __device__ __forceinline__ void compute_rinv(const FastArgs &a, float *rinv /* L
     const int rows = a.cls == 8 ? 8 : 32;
     const int slots = kFastThreads / rows;            // 64 or 16 threads per row
     const int m = tid % rows, g0 = tid / rows;
-    for (int g = g0; g < NG; g += slots) {
-        float s = 0.f;
+    if (rows == 32) {
+        // four groups per thread, the loads of all four together
+        constexpr int P = NG / 16;
+        float s[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) s[p] = 0.f;
         if (m < a.M) {
-            for (int t0 = g; t0 < a.n_ss; t0 += B * NG) {
-                float v[B];
+            for (int t0 = g0; t0 < a.n_ss; t0 += B * NG) {
+                float v[P][B];
 #pragma unroll
-                for (int u = 0; u < B; ++u) {
-                    const int t = t0 + u * NG;
-                    v[u] = ldf_at<COH>(a.ssp, (uint32_t)((t < a.n_ss ? t : t0) * 32 + m));
-                }
+                for (int p = 0; p < P; ++p)
 #pragma unroll
-                for (int u = 0; u < B; ++u) s += (t0 + u * NG < a.n_ss) ? v[u] : 0.f;
+                    for (int u = 0; u < B; ++u) {
+                        const int t = t0 + p * 16 + u * NG;
+                        v[p][u] = ldf_at<COH>(a.ssp, (uint32_t)((t < a.n_ss ? t : t0) * 32 + m));
+                    }
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int u = 0; u < B; ++u) s[p] += (t0 + p * 16 + u * NG < a.n_ss) ? v[p][u] : 0.f;
             }
         }
-        scratch[g * 32 + m] = s;
+#pragma unroll
+        for (int p = 0; p < P; ++p) scratch[(g0 + p * 16) * 32 + m] = s[p];
+    } else {
+        for (int g = g0; g < NG; g += slots) {
+            float s = 0.f;
+            if (m < a.M) {
+                for (int t0 = g; t0 < a.n_ss; t0 += B * NG) {
+                    float v[B];
+#pragma unroll
+                    for (int u = 0; u < B; ++u) {
+                        const int t = t0 + u * NG;
+                        v[u] = ldf_at<COH>(a.ssp, (uint32_t)((t < a.n_ss ? t : t0) * 32 + m));
+                    }
+#pragma unroll
+                    for (int u = 0; u < B; ++u) s += (t0 + u * NG < a.n_ss) ? v[u] : 0.f;
+                }
+            }
+            scratch[g * 32 + m] = s;
+        }
     }
     block_sync_lds();
     if (tid < rows) {
@@ -461,6 +487,26 @@ __device__ __forceinline__ void reduce_and_finish(const FastArgs &a, int tile, c
     }
 }
 
+// The same for one pair of fragments (rows 16 pr .. + 16) of a tile: NT / 2 waves share a tile's epilogue.
+template <int NT, int EPI>
+__device__ __forceinline__ void reduce_and_finish_pair(const FastArgs &a, int tile, int pr, const float *red /* [8][NT][256] */,
+                                                       int lane, const float *rinv)
+{
+    f32x4 hi[kFastWaves], lo[kFastWaves];
+#pragma unroll
+    for (int w = 0; w < kFastWaves; ++w) {
+        hi[w] = *reinterpret_cast<const f32x4 *>(red + (((size_t)w * NT + 2 * pr) * 64 + lane) * 4);
+        lo[w] = *reinterpret_cast<const f32x4 *>(red + (((size_t)w * NT + 2 * pr + 1) * 64 + lane) * 4);
+    }
+#pragma unroll
+    for (int w = 1; w < kFastWaves; ++w) {
+        hi[0] += hi[w];
+        lo[0] += lo[w];
+    }
+    const int m = pr * 16 + (lane & 15);
+    epilogue<EPI, false>(a, tile, m, lane >> 4, hi[0] + lo[0], m < a.M, rinv);
+}
+
 // The same for an operand of NF fragments in the class-8 arrangement (packed_class): fragment f holds rows
 // 8 f .. 8 f + 7 as (hi | lo) slots, and its partial tiles are finished exactly like the one fragment of a
 // window of up to 8 rows.  red: [nw][NF][256].  pre: the staged operands of every fragment, if any.
@@ -679,9 +725,211 @@ __global__ __launch_bounds__(kFastThreads) void gemm_group_kernel(FastArgs a)
             for (int f = 0; f < NT; ++f)
                 *reinterpret_cast<f32x4 *>(red_dyn + ((((size_t)t * kFastWaves + wave) * NT + f) * 64 + lane) * 4) = acc[t][f];
         __syncthreads();
-        if (wave < ntl)
-            reduce_and_finish<NT, EPI>(a, t0 + wave, red_dyn + (size_t)wave * kFastWaves * NT * 256, kFastWaves, lane, rinv);
+        if constexpr (NT == 4) {   // two waves per tile
+            if (wave < 2 * ntl)
+                reduce_and_finish_pair<NT, EPI>(a, t0 + (wave >> 1), wave & 1, red_dyn + (size_t)(wave >> 1) * kFastWaves * NT * 256, lane, rinv);
+        } else {
+            if (wave < ntl)
+                reduce_and_finish<NT, EPI>(a, t0 + wave, red_dyn + (size_t)wave * kFastWaves * NT * 256, kFastWaves, lane, rinv);
+        }
     }
+}
+
+// ------------------------------------------- GEMM, four operand fragments, more tiles per pass
+//
+// Windows of 17..32 rows.  What these GEMMs pay for is bytes into the compute units: measured over the 7B and
+// 13B shapes a launch takes 4 us + weights / 6.4 TB/s + operand / 22 TB/s, the two one after the other (loads come
+// back in the order they were issued), and deeper register rings change nothing.  The operand is 512 KB per pass
+// and compute unit at K = 4096, so what helps is fewer passes: all of a block's tiles at once where the
+// accumulators fit (T = 6: 96 registers, 8: 128), paid for with a ring of D stages of one k-step.  7B gate/up,
+// 32 rows: two passes of <4, 4> 45.5 us, one of T = 6 37.9; LM head 53.7 -> 47.5 (T = 8); 13B gate/up 59.1 -> 50.6.
+// With one tile per compute unit (T = 1): 7B down 38.4 us as 128 blocks of two tiles, 34.0 as 256 of one.
+// Same k-step assignment (wave, wave + 8, ...) and summation order as the other forms: bit-identical results.
+template <int T, int D, int EPI>
+__global__ __launch_bounds__(kFastThreads) void gemm_wide_kernel(FastArgs a)
+{
+    constexpr int NT = 4, TR = T < 4 ? T : 4;   // tiles that meet in LDS at a time
+    extern __shared__ float red_dyn[];          // [TR][kFastWaves][NT][256]
+    __shared__ float rinv[32];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nks = a.nks;
+    // the norm's partial sums are requested before the first weights and reduced behind them (d_model up to 4096)
+    __shared__ float ss_scratch[epi_has_norm(EPI) ? 64 * 32 : 1];
+    const bool ss_early = epi_has_norm(EPI) && a.n_ss <= 256;
+    float ssv[4][4];
+    if (ss_early) rinv_issue<false, 4>(a, ssv, threadIdx.x);
+    else if (epi_has_norm(EPI)) compute_rinv(a, rinv, ss_scratch);
+    const int first = (int)(((long long)blockIdx.x * a.n_tiles) / gridDim.x);
+    const int last = (int)(((long long)(blockIdx.x + 1) * a.n_tiles) / gridDim.x);
+    const int n_mine = last - first;
+    const int n_pass = (n_mine + T - 1) / T;
+    const int per_pass = n_pass > 0 ? (n_mine + n_pass - 1) / n_pass : 0;
+    const int kpw = (nks + kFastWaves - 1) / kFastWaves;
+    __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.Xp), 0, nks * NT * 1024, 0x00020000);
+    for (int t0 = first; t0 < last; t0 += per_pass) {
+        const int ntl = last - t0 < per_pass ? last - t0 : per_pass;
+        __amdgpu_buffer_rsrc_t rw[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const bool have = t < ntl;   // absent tiles: an empty buffer, reads zeros and fetches nothing
+            rw[t] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.Wp + (size_t)(have ? t0 + t : 0) * nks * 64), 0,
+                                                      have ? nks * 1024 : 0, 0x00020000);
+        }
+        f32x4 acc[T][NT];
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int f = 0; f < NT; ++f) acc[t][f] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        u32x4_t w[D][T], x[D][NT];
+        // past the last k-step: outside every buffer, reads zeros (the whole offset is in the checked operand)
+        auto load = [&](int s, int i) __attribute__((always_inline)) {
+            const int ks = wave + kFastWaves * i;
+#pragma unroll
+            for (int f = 0; f < NT; ++f) x[s][f] = __builtin_amdgcn_raw_buffer_load_b128(rx, lane * 16 + (ks * NT + f) * 1024, 0, 0);
+#pragma unroll
+            for (int t = 0; t < T; ++t) w[s][t] = __builtin_amdgcn_raw_buffer_load_b128(rw[t], lane * 16 + ks * 1024, 0, kAuxStream);
+        };
+#pragma unroll
+        for (int s = 0; s < D; ++s) load(s, s);
+        if (ss_early && t0 == first) {
+            rinv_partial_to_lds<4>(ssv, ss_scratch, threadIdx.x);
+            block_sync_lds();
+            rinv_from_lds<4>(a, rinv, ss_scratch, threadIdx.x);   // (read behind the barriers below)
+        }
+        for (int i = 0; i < kpw; i += D) {
+#pragma unroll
+            for (int s = 0; s < D; ++s) {
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+#pragma unroll
+                    for (int f = 0; f < NT; ++f)
+                        acc[t][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[s][t]),
+                                                                            __builtin_bit_cast(bf16x8, x[s][f]), acc[t][f], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                load(s, i + s + D);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int tb = 0; tb < T; tb += TR) {
+            __syncthreads();   // the partial tiles before these have been consumed
+#pragma unroll
+            for (int t = tb; t < tb + TR && t < T; ++t)
+#pragma unroll
+                for (int f = 0; f < NT; ++f)
+                    *reinterpret_cast<f32x4 *>(red_dyn + ((((size_t)(t - tb) * kFastWaves + wave) * NT + f) * 64 + lane) * 4) = acc[t][f];
+            __syncthreads();
+            if ((wave >> 1) < TR && tb + (wave >> 1) < ntl)   // two waves per tile
+                reduce_and_finish_pair<NT, EPI>(a, t0 + tb + (wave >> 1), wave & 1, red_dyn + (size_t)(wave >> 1) * kFastWaves * NT * 256, lane, rinv);
+        }
+    }
+}
+
+// ------------------------------------------- GEMM split by k-step class (O and down projections of 17..32 rows)
+//
+// With one or two tiles per compute unit every compute unit would read the whole operand (1.4 MB for the 7B down
+// projection) for 0.35 MB of weights.  Here a block takes ONE of the eight k-step classes (k-steps c, c + 8, ...: the
+// share of one wave of the other forms) of a group of tiles, one tile per wave: the class's eighth of the operand
+// passes through LDS and serves every wave.  A wave's sums are the other forms' per-wave partial tiles,
+// so adding the eight classes in order (split_merge_kernel, which runs the epilogue) gives the same bits.
+// Costs a round trip of 8 partial tiles per tile through the caches and a second launch.  Measured with that launch,
+// 7B, 32 rows: down 38.4 -> 24.7 us, O 17.4 -> 13.9;
+// whole steps (gate/up and LM head in fewer passes included): 7B, 17 rows, 8 layers 1446 -> 1216 us, 13B, 17 rows, 4 layers 865 -> 760.
+// part: [tile][class][4][64][4] fp32.  grid: 8 x groups (class fastest, so that the blocks of a class, which share
+// its operand, are dealt to one XCD); blockDim = 64 x tiles per group, at most 16 waves.
+constexpr int kSplitDepth = 16;   // k-steps in flight per wave; k-steps of operand per LDS buffer
+constexpr int kSplitMaxWaves = 16;
+constexpr size_t kSplitLds = (size_t)(2 * kSplitDepth * 4 + 1) * 1024;   // two buffers, and a place for loads of nothing
+__device__ __forceinline__ void split_load_lds(__amdgpu_buffer_rsrc_t buffer, uint4 *dst, int offset)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer, (__attribute__((address_space(3))) void *)dst, 16, offset, 0, 0, 0);
+}
+__global__ __launch_bounds__(kSplitMaxWaves * 64) void gemm_split_kernel(FastArgs a, float *__restrict__ part)
+{
+    constexpr int NT = 4, D = kSplitDepth, XL = D * NT / kFastWaves;   // operand loads per wave and buffer, at least 8 waves
+    extern __shared__ uint4 xs[];   // [2][D][NT][64], [64]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
+    const int nks = a.nks, c = blockIdx.x & 7, tile = (int)(blockIdx.x >> 3) * n_waves + wave;
+    const bool have = tile < a.n_tiles;
+    const int kpc = (nks - c + 7) / 8;   // k-steps of this class
+    __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.Wp + (size_t)(have ? tile : 0) * nks * 64), 0,
+                                                                  have ? nks * 1024 : 0, 0x00020000);
+    __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.Xp), 0, nks * NT * 1024, 0x00020000);
+    u32x4_t w[D];
+    // past the last k-step: outside the buffer, reads zeros
+    auto load_w = [&](int s, int i) __attribute__((always_inline)) {
+        w[s] = __builtin_amdgcn_raw_buffer_load_b128(rw, lane * 16 + (c + 8 * i) * 1024, 0, kAuxStream);
+    };
+    // the operand of k-steps i0 .. i0 + D - 1 -> buffer b; every wave issues XL loads (with more than 8 waves some of
+    // nothing, to the spare place): the waits below count them
+    auto load_x = [&](int i0, int b) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < XL; ++j) {
+            const int u = wave + n_waves * j, k = u / NT, f = u % NT;
+            const bool real = u < D * NT;
+            split_load_lds(rx, xs + (real ? (size_t)(b * D * NT + u) * 64 : (size_t)2 * D * NT * 64),
+                           real ? lane * 16 + ((c + 8 * (i0 + k)) * NT + f) * 1024 : 0x7ffffff0);
+        }
+    };
+    load_x(0, 0);
+#pragma unroll
+    for (int s = 0; s < D; ++s) load_w(s, s);
+    load_x(D, 1);
+    f32x4 acc[NT];
+#pragma unroll
+    for (int f = 0; f < NT; ++f) acc[f] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)xs + lane * 16;
+    for (int i0 = 0, b = 0; i0 < kpc; i0 += D, b ^= 1) {
+        // younger than this buffer's loads: D of weights, XL of the other buffer
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kSplitDepth + kSplitDepth * 4 / kFastWaves) : "memory");
+        const uint32_t xb = base + (uint32_t)b * (D * NT * 1024);
+#pragma unroll
+        for (int s = 0; s < D; ++s) {
+            u32x4_t xv[NT];
+#pragma unroll
+            for (int f = 0; f < NT; ++f) asm volatile("ds_read_b128 %0, %1" : "=v"(xv[f]) : "v"(xb + (uint32_t)(s * NT + f) * 1024) : "memory");
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(xv[0]), "+v"(xv[1]), "+v"(xv[2]), "+v"(xv[3]));
+#pragma unroll
+            for (int f = 0; f < NT; ++f)
+                acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[s]), __builtin_bit_cast(bf16x8, xv[f]), acc[f], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            load_w(s, i0 + D + s);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        asm volatile("s_barrier" ::: "memory");   // every wave has read this buffer
+        load_x(i0 + 2 * D, b);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (!have) return;
+    // only rows of the window: fragments 2 p, 2 p + 1 hold the hi and lo sums of rows 16 p ..
+    f32x4 *p = reinterpret_cast<f32x4 *>(part) + ((size_t)tile * 8 + c) * NT * 64 + lane;
+#pragma unroll
+    for (int f = 0; f < NT; ++f)
+        if ((f >> 1) * 16 + (lane & 15) < a.M) p[f * 64] = acc[f];
+}
+
+// The eight classes of a tile, added in order, then the epilogue.  grid: (n_tiles, 2) waves; y: rows 16 y ..
+template <int EPI>
+__global__ __launch_bounds__(64) void split_merge_kernel(FastArgs a, const float *__restrict__ part)
+{
+    const int lane = threadIdx.x, tile = blockIdx.x, pr = blockIdx.y, m = 16 * pr + (lane & 15);
+    const bool valid = m < a.M;
+    const f32x4 *q = reinterpret_cast<const f32x4 *>(part) + ((size_t)tile * 32 + 2 * pr) * 64 + lane;
+    f32x4 h[8], l[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        h[c] = l[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if (valid) {
+            h[c] = q[(size_t)c * 256];
+            l[c] = q[(size_t)c * 256 + 64];
+        }
+    }
+#pragma unroll
+    for (int c = 1; c < 8; ++c) {
+        h[0] += h[c];
+        l[0] += l[c];
+    }
+    epilogue<EPI>(a, tile, m, lane >> 4, h[0] + l[0], valid, nullptr);
 }
 
 // ------------------------------------------------------------------ embed
