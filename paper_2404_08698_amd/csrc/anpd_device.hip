@@ -113,7 +113,7 @@ Layout make_layout(const anpd_model_cfg *c)
         L.ssp_b = take((d / 16) * 32 * 4);
         if (c->max_window > 16) L.split_part = take((d / 16) * 8 * 4 * 1024);   // partial tiles of the split O / down projections
         L.qp = take((size_t)c->n_heads * 4 * (c->head_dim / 32) * 1024);
-        L.head_ctr = take((size_t)c->n_heads * kCounterStride * sizeof(uint32_t));
+        L.head_ctr = take((size_t)c->n_heads * ANPD_MAX_WINDOW * kCounterStride * sizeof(uint32_t));   // [group of rows or sequence][head]
         L.layer_tab = take((size_t)c->n_layers * sizeof(LayerW));
         L.amax = take((V / 16) * 32 * sizeof(unsigned long long));
         L.row_ctr = take(sizeof(uint32_t));
@@ -525,7 +525,7 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int 
 // -> gate/up(+norm, SwiGLU) -> down(+residual); then LM head(+norm) -> argmax / accept.
 // A batched step: the sequences' descriptions are in the workspace (Layout::batch); `kv` is unused.
 struct BatchLaunch {
-    int n_seq, n_blocks /* (split, sequence) blocks per head */, grid_splits /* splits of the longest sequence */;
+    int n_seq, grid_splits /* splits of the longest sequence */;
 };
 
 int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, int mode, float *logits, hipStream_t st, bool tree = false,
@@ -607,7 +607,7 @@ int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, 
         if (batch) {
 #define ANPD_ATTN_B(DH_, MAXP_)                                                                                            \
     hipLaunchKernelGGL((attn_batch_kernel<DH_, MAXP_>), dim3(H, n_splits, batch->n_seq), dim3(kFastThreads), 0, st,      \
-                       (const uint4 *)qp, b_seqs, b_row_seq, batch->n_blocks, M, l, c.n_layers, H, Hkv, L.max_splits, scale, part, \
+                       (const uint4 *)qp, b_seqs, M, l, c.n_layers, H, Hkv, L.max_splits, scale, part, \
                        head_ctr, xp_att, cls)
             if (dh == 128) { if (one_page) ANPD_ATTN_B(128, 1); else ANPD_ATTN_B(128, kFastPages); }
             else if (one_page) ANPD_ATTN_B(64, 1);
@@ -615,7 +615,7 @@ int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, 
 #undef ANPD_ATTN_B
         } else {
 #define ANPD_ATTN(DH_, TREE_, MAXP_)                                                                                       \
-    hipLaunchKernelGGL((attn_fast_kernel<DH_, TREE_, MAXP_>), dim3(H, n_splits), dim3(kFastThreads), 0, st, (const uint4 *)qp,  \
+    hipLaunchKernelGGL((attn_fast_kernel<DH_, TREE_, MAXP_>), dim3(H, n_splits, (M + 7) / 8), dim3(kFastThreads), 0, st, (const uint4 *)qp,  \
                        (const bf16_t *)kv->pool, kv->d_table, kv->d_len, M, l, c.n_layers, H, Hkv, L.max_splits, scale, part,   \
                        head_ctr, xp_att, cls, t_mask)
 #define ANPD_ATTN_T(DH_, MAXP_) do { if (tree) ANPD_ATTN(DH_, true, MAXP_); else ANPD_ATTN(DH_, false, MAXP_); } while (0)
@@ -1483,7 +1483,7 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
     // joint window, sequence of every row, sequences
     int32_t *row_seq = m->pin + 384;
     SeqRef *seqs = (SeqRef *)(m->pin + 512);
-    BatchLaunch bl = {n_seq, 0, 0};
+    BatchLaunch bl = {n_seq, 0};
     int row = 0;
     for (int s = 0; s < n_seq; ++s) {
         anpd_kv *kv = kvs[s];
@@ -1493,7 +1493,6 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
         seqs[s].row0 = row;
         seqs[s].n_rows = n_windows[s];
         const int splits = n_splits_of(kv->len + n_windows[s]);
-        bl.n_blocks += splits;
         if (splits > bl.grid_splits) bl.grid_splits = splits;
         for (int i = 0; i < n_windows[s]; ++i, ++row) {
             m->pin[row] = windows[s][i];

@@ -1168,8 +1168,10 @@ __device__ __forceinline__ size_t part_s_index(int n_heads, int head, int split,
 // MODE 1 (tree): the window is a draft tree; row_mask[m] has bit r set if window row r is row m itself
 // or one of its ancestors, and row m sees the cached positions plus exactly those rows.
 // MODE 2 (batch): the window holds several sequences side by side; this task belongs to the sequence
-// whose cache is (pool, page_table, L) and works on its rows [batch->row0, + n_rows) only; the head's
-// splits of ALL sequences are merged by the last of batch->n_blocks blocks.
+// whose cache is (pool, page_table, L) and works on its rows [batch->row0, + n_rows) only.
+// In the persistent kernel (COH) the head's splits of all rows (of ALL sequences) are merged by the last of
+// batch->n_blocks blocks; a task of the separate kernels belongs to a group of rows (eight rows of a window, or a
+// sequence) given by `batch` in every mode, and the last block of the group merges its rows.
 enum { ATTN_CHAIN = 0, ATTN_TREE = 1, ATTN_BATCH = 2 };
 struct AttnBatch {
     int row0, n_rows, n_blocks;
@@ -1195,11 +1197,12 @@ __device__ __forceinline__ void attn_task(AttnShared<DH> &sh, AttnKV<DH> &kv, in
                                           int publish, const AttnStash *stash, bool stashed1, bool stashed2,
                                           uint4 *q_lds, bool q_in_lds, bool more_tasks)
 {
-    constexpr bool TREE = MODE == ATTN_TREE, BATCH = MODE == ATTN_BATCH;
+    constexpr bool TREE = MODE == ATTN_TREE, BATCH = MODE == ATTN_BATCH, ROWS = BATCH || !COH;
     const int tid = fresh_tid();
     constexpr int NKS = DH / 32, NDT = DH / 16;
     const int lane = tid & 63, wave = tid >> 6, slot = lane & 15, kg = lane >> 4;
-    const int row0 = BATCH ? batch->row0 : 0, row_end = BATCH ? batch->row0 + batch->n_rows : M;   // this task's rows
+    const int row0 = ROWS ? batch->row0 : 0, row_end = ROWS ? batch->row0 + batch->n_rows : M;   // this task's rows
+    const int n_new = BATCH ? row_end - row0 : row_end;   // window rows whose keys these rows may see
     const int rg0 = row0 >> 3;
     const int kv_head = head / (n_heads / n_kv_heads);
     ANPD_STAMP(0);
@@ -1211,7 +1214,7 @@ __device__ __forceinline__ void attn_task(AttnShared<DH> &sh, AttnKV<DH> &kv, in
     AttnKV<DH> kvb;
     kvb.loaded = false;
     auto request = [&](AttnKV<DH> &dst, int j) __attribute__((always_inline)) {
-        attn_load_kv<DH, COH>(dst, kv_head, split, L, row_end - row0, pool, page_table, layer, n_layers, n_kv_heads, false, j);
+        attn_load_kv<DH, COH>(dst, kv_head, split, L, n_new, pool, page_table, layer, n_layers, n_kv_heads, false, j);
     };
     if (!kv.loaded) request(kv, 0);
     // The separate kernels (COH = false) go through a split's pages with ONE set of page registers, each page
@@ -1242,7 +1245,7 @@ __device__ __forceinline__ void attn_task(AttnShared<DH> &sh, AttnKV<DH> &kv, in
             if (kOneSet ? n_pages > 1 : n_pages > 2) request(kv, 0);   // (otherwise every page is still in its registers)
         }
         const int m = rg * 8 + (slot & 7);
-        const bool row_ok = slot < 8 && m < M && (!BATCH || (m >= row0 && m < row_end));
+        const bool row_ok = slot < 8 && m < M && (!ROWS || (m >= row0 && m < row_end));
         uint32_t vis = 0;
         if (TREE) vis = row_mask[m < M ? m : 0];
         // running maximum and denominator of this wave's pages for row m; the output accumulates in the
@@ -1254,7 +1257,7 @@ __device__ __forceinline__ void attn_task(AttnShared<DH> &sh, AttnKV<DH> &kv, in
         // one page: scores, exponentials against the new running maximum, P, O += V^T P
         auto page = [&](const AttnKV<DH> &cur, int j) __attribute__((always_inline)) {
             const int key0 = split_begin(split) + (wave + kFastWaves * j) * 16;
-            if (key0 >= L + (row_end - row0)) return;   // (whole wave) nothing of this page exists yet
+            if (key0 >= L + n_new) return;   // (whole wave) nothing of this page exists yet
             // ---- scores S[key][row]
             f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1399,7 +1402,7 @@ __device__ __forceinline__ void attn_task(AttnShared<DH> &sh, AttnKV<DH> &kv, in
     wait_stores();
     block_sync_lds();
     ANPD_STAMP(3);
-    const int n_blocks = BATCH ? batch->n_blocks : n_splits_of(L + M);
+    const int n_blocks = ROWS ? batch->n_blocks : n_splits_of(L + M);
     if (tid == 0)
         sh.last = __hip_atomic_fetch_add(&head_counter[head * kCounterStride], (uint32_t)publish, __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT) + (uint32_t)publish == (uint32_t)n_blocks;
@@ -1414,10 +1417,12 @@ __device__ __forceinline__ void attn_task(AttnShared<DH> &sh, AttnKV<DH> &kv, in
     constexpr int SB = 8, DQ = DH / 4;
     const uint4 *po = reinterpret_cast<const uint4 *>(part + part_o_index(head, 0, max_splits, 0, DH));
     const uint2 *ps = reinterpret_cast<const uint2 *>(part + part_s_index(n_heads, head, 0, max_splits, 0, DH));
-    for (int idx = tid; idx < M * DQ; idx += kFastThreads) {
-        const int row = idx / DQ, e4 = idx - row * DQ;
-        int ns = split_of(L + row) + 1;
-        if (BATCH) {   // the row's own sequence decides how many splits it has
+    // (the separate kernels merge a task's own rows, the persistent kernel the rows of all sequences together)
+    const int first_row = COH ? 0 : row0, n_merge = COH ? M : row_end - row0;
+    for (int idx = tid; idx < n_merge * DQ; idx += kFastThreads) {
+        const int row = first_row + idx / DQ, e4 = idx % DQ;
+        int ns = split_of(BATCH ? L + row - row0 : L + row) + 1;
+        if (BATCH && COH) {   // the row's own sequence decides how many splits it has
             const SeqRef sq = batch->seqs[batch->row_seq[row]];
             ns = split_of(*sq.len_ptr + (row - sq.row0)) + 1;
         }
@@ -1465,7 +1470,9 @@ __device__ __forceinline__ void attn_task(AttnShared<DH> &sh, AttnKV<DH> &kv, in
     ANPD_STAMP(6);
 }
 
-// grid: (n_heads, n_splits_of(len + M)), kFastWaves waves.
+// Block (head, split, group of eight rows): one block for all rows of a wide window went through its pages once
+// per eight rows, one wait after the other (17 rows at 2048 positions: ATTN17_FIGURES).
+// head_counter: [group][head].   grid: (n_heads, n_splits_of(len + M), ceil(M / 8)), kFastWaves waves.
 template <int DH, bool TREE = false, int MAXP = kFastPages>
 __global__ __launch_bounds__(kFastThreads) void attn_fast_kernel(const uint4 *__restrict__ qp, const bf16_t *__restrict__ pool,
                                                           const int32_t *__restrict__ page_table,
@@ -1476,22 +1483,24 @@ __global__ __launch_bounds__(kFastThreads) void attn_fast_kernel(const uint4 *__
                                                           const uint32_t *__restrict__ row_mask)
 {
     __shared__ AttnShared<DH> sh;
-    const int L = *len_ptr;
-    if (split_begin(blockIdx.y) >= L + M) return;
+    const int L = *len_ptr, row0 = 8 * (int)blockIdx.z, row_end = row0 + 8 < M ? row0 + 8 : M;
+    if (split_begin(blockIdx.y) >= L + row_end) return;
     AttnKV<DH> kv;
     kv.loaded = false;
+    AttnBatch bt = {row0, row_end - row0, n_splits_of(L + row_end), nullptr, nullptr};
     attn_task<DH, false, NoPrefetch, TREE ? ATTN_TREE : ATTN_CHAIN, NoPrefetch, MAXP>(sh, kv, blockIdx.x, blockIdx.y, L, qp, pool, page_table, M, layer,
                                                                     n_layers, n_heads, n_kv_heads, max_splits, scale, part,
-                                                                    head_counter, xp_att, cls, NoPrefetch(), row_mask, nullptr,
-                                                                    NoPrefetch(), 1, nullptr, false, false, nullptr, false, false);
+                                                                    head_counter + (size_t)blockIdx.z * n_heads * kCounterStride, xp_att, cls,
+                                                                    NoPrefetch(), row_mask, &bt, NoPrefetch(), 1, nullptr, false, false,
+                                                                    nullptr, false, false);
 }
 
 // Several sequences' windows in one step: block (head, split, sequence) works on that sequence's rows
-// against that sequence's cache.   grid: (n_heads, largest number of splits of any sequence, n_seq).
+// against that sequence's cache; the last block of a (head, sequence) merges them.
+// head_counter: [sequence][head].   grid: (n_heads, largest number of splits of any sequence, n_seq).
 template <int DH, int MAXP = kFastPages>
 __global__ __launch_bounds__(kFastThreads) void attn_batch_kernel(const uint4 *__restrict__ qp, const SeqRef *__restrict__ seqs,
-                                                           const int32_t *__restrict__ row_seq, int n_blocks, int M, int layer,
-                                                           int n_layers, int n_heads, int n_kv_heads, int max_splits,
+                                                           int M, int layer, int n_layers, int n_heads, int n_kv_heads, int max_splits,
                                                            float scale, float *__restrict__ part,
                                                            uint32_t *__restrict__ head_counter, bf16_t *__restrict__ xp_att,
                                                            int cls)
@@ -1502,9 +1511,10 @@ __global__ __launch_bounds__(kFastThreads) void attn_batch_kernel(const uint4 *_
     if (split_begin(blockIdx.y) >= L + sq.n_rows) return;
     AttnKV<DH> kv;
     kv.loaded = false;
-    AttnBatch bt = {sq.row0, sq.n_rows, n_blocks, seqs, row_seq};
+    AttnBatch bt = {sq.row0, sq.n_rows, n_splits_of(L + sq.n_rows), nullptr, nullptr};
     attn_task<DH, false, NoPrefetch, ATTN_BATCH, NoPrefetch, MAXP>(sh, kv, blockIdx.x, blockIdx.y, L, qp, sq.pool, sq.page_table, M, layer, n_layers,
-                                                 n_heads, n_kv_heads, max_splits, scale, part, head_counter, xp_att, cls,
+                                                 n_heads, n_kv_heads, max_splits, scale, part,
+                                                 head_counter + (size_t)blockIdx.z * n_heads * kCounterStride, xp_att, cls,
                                                  NoPrefetch(), nullptr, &bt, NoPrefetch(), 1, nullptr, false, false, nullptr, false, false);
 }
 
