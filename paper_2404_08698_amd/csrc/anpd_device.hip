@@ -526,6 +526,7 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int 
 // A batched step: the sequences' descriptions are in the workspace (Layout::batch); `kv` is unused.
 struct BatchLaunch {
     int n_seq, grid_splits /* splits of the longest sequence */;
+    bool decode;   // one row per sequence and sequences enough: one block per (head, sequence)
 };
 
 int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, int mode, float *logits, hipStream_t st, bool tree = false,
@@ -609,7 +610,14 @@ int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, 
     hipLaunchKernelGGL((attn_batch_kernel<DH_, MAXP_>), dim3(H, n_splits, batch->n_seq), dim3(kFastThreads), 0, st,      \
                        (const uint4 *)qp, b_seqs, M, l, c.n_layers, H, Hkv, L.max_splits, scale, part, \
                        head_ctr, xp_att, cls)
-            if (dh == 128) { if (one_page) ANPD_ATTN_B(128, 1); else ANPD_ATTN_B(128, kFastPages); }
+            if (batch->decode) {
+                if (dh == 128)
+                    hipLaunchKernelGGL((attn_decode_kernel<128>), dim3(H, batch->n_seq), dim3(kFastThreads), 0, st, (const uint4 *)qp, b_seqs, l,
+                                       c.n_layers, H, Hkv, scale, xp_att, cls);
+                else
+                    hipLaunchKernelGGL((attn_decode_kernel<64>), dim3(H, batch->n_seq), dim3(kFastThreads), 0, st, (const uint4 *)qp, b_seqs, l,
+                                       c.n_layers, H, Hkv, scale, xp_att, cls);
+            } else if (dh == 128) { if (one_page) ANPD_ATTN_B(128, 1); else ANPD_ATTN_B(128, kFastPages); }
             else if (one_page) ANPD_ATTN_B(64, 1);
             else ANPD_ATTN_B(64, kFastPages);
 #undef ANPD_ATTN_B
@@ -1483,7 +1491,7 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
     // joint window, sequence of every row, sequences
     int32_t *row_seq = m->pin + 384;
     SeqRef *seqs = (SeqRef *)(m->pin + 512);
-    BatchLaunch bl = {n_seq, 0};
+    BatchLaunch bl = {n_seq, 0, false};
     int row = 0;
     for (int s = 0; s < n_seq; ++s) {
         anpd_kv *kv = kvs[s];
@@ -1499,6 +1507,12 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
             row_seq[row] = s;
         }
     }
+    // One row per sequence: one block per (head, sequence) once those fill the chip (two fit a compute unit), with a
+    // margin where the sequences are long and a half-empty last round costs more (7B shape, 4 layers, us per step, cut
+    // into splits -> not cut: 500 positions, 10 / 16 / 18 / 32 sequences 597 -> 608, 675 -> 659, 760 -> 750, 1722 -> 1612 (8
+    // layers); 2500 positions, 10 / 16 / 18 / 24 / 32 sequences 854 -> 958, 1103 -> 1126, 1236 -> 1267, 1491 -> 1476, 1778 -> 1744)
+    bl.decode = total == n_seq && bl.grid_splits <= kDecodeSplits &&
+                (long long)n_seq * m->cfg.n_heads >= (bl.grid_splits <= kSmallSplits ? 2 : 3) * m->n_cu;
     // At most 8 rows in all (decoding batches, short windows): the persistent kernel takes the sequences by
     // value and writes the results into the pinned buffer itself; otherwise copies and the fused launches.
     const bool one_kernel = m->mega && m->mega_batch && total <= 8;

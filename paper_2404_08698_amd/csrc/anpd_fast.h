@@ -1471,7 +1471,7 @@ __device__ __forceinline__ void attn_task(AttnShared<DH> &sh, AttnKV<DH> &kv, in
 }
 
 // Block (head, split, group of eight rows): one block for all rows of a wide window went through its pages once
-// per eight rows, one wait after the other (17 rows at 2048 positions: ATTN17_FIGURES).
+// per eight rows, one wait after the other (17 rows at 2048 positions: 31.7 us per layer, now 23.8).
 // head_counter: [group][head].   grid: (n_heads, n_splits_of(len + M), ceil(M / 8)), kFastWaves waves.
 template <int DH, bool TREE = false, int MAXP = kFastPages>
 __global__ __launch_bounds__(kFastThreads) void attn_fast_kernel(const uint4 *__restrict__ qp, const bf16_t *__restrict__ pool,
@@ -1516,6 +1516,170 @@ __global__ __launch_bounds__(kFastThreads) void attn_batch_kernel(const uint4 *_
                                                  n_heads, n_kv_heads, max_splits, scale, part,
                                                  head_counter + (size_t)blockIdx.z * n_heads * kCounterStride, xp_att, cls,
                                                  NoPrefetch(), nullptr, &bt, NoPrefetch(), 1, nullptr, false, false, nullptr, false, false);
+}
+
+// Plain decoding of many sequences (one row each): one block per (head, sequence), its wave w going through the
+// pages w, w + 8, ... of every split one after the other without meeting the other waves: the next page's K is
+// requested when this page's scores are done, its V when this page's output is.  The waves' (maximum, denominator,
+// output) of every split stay in LDS; behind ONE block barrier the splits are formed and merged in the order of
+// attn_task, so the bits are its bits.  What bounds attn_batch_kernel here is that a block holds its 64 KB of pages
+// for one round trip only and then meets, reduces, stores and counts for as long (32 sequences of 512 positions,
+// 32 heads, 282 MB: 73 us there, 65 here; 4.3 TB/s).
+// A sequence may have up to kDecodeSplits splits (4096 positions).   grid: (n_heads, n_seq).
+constexpr int kDecodeSplits = 16;
+template <int DH>
+__global__ __launch_bounds__(kFastThreads) void attn_decode_kernel(const uint4 *__restrict__ qp, const SeqRef *__restrict__ seqs, int layer,
+                                                            int n_layers, int n_heads, int n_kv_heads, float scale,
+                                                            bf16_t *__restrict__ xp_att, int cls)
+{
+    constexpr int NKS = DH / 32, NDT = DH / 16;
+    __shared__ float part_o[kDecodeSplits][kFastWaves][DH];
+    __shared__ float part_m[kDecodeSplits][kFastWaves], part_d[kDecodeSplits][kFastWaves];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), slot = lane & 15, kg = lane >> 4;
+    const SeqRef sq = seqs[blockIdx.y];
+    const int L = *sq.len_ptr, head = blockIdx.x, kvh = head / (n_heads / n_kv_heads), m = sq.row0, my_slot = m & 7;
+    const int ns = n_splits_of(L + 1);
+    // the wave's i-th page: one per split up to kSmallSplits, then kFastPages per split
+    auto split_at = [](int i) { return i < kSmallSplits ? i : kSmallSplits + (i - kSmallSplits) / kFastPages; };
+    auto key_at = [&](int i) {
+        const int s = split_at(i), j = i < kSmallSplits ? 0 : (i - kSmallSplits) % kFastPages;
+        return split_begin(s) + (wave + kFastWaves * j) * 16;
+    };
+    const bool mine = key_at(lane) <= L;   // (keys 0 .. L exist; a wave's pages come in increasing order)
+    const int ids = mine ? sq.page_table[key_at(lane) >> 4] : 0;
+    const int n_pages = __builtin_popcountll(__builtin_amdgcn_ballot_w64(mine));
+    if (n_pages > 0) {
+        uint4 qf[NKS], kf[NKS];
+        uint2 vf[NDT];
+        auto load_k = [&](int i) __attribute__((always_inline)) {
+            const uint4 *kp = reinterpret_cast<const uint4 *>(sq.pool + kvf_base(__builtin_amdgcn_readlane(ids, i), layer, n_layers, 0, kvh, n_kv_heads, DH));
+#pragma unroll
+            for (int q = 0; q < NKS; ++q) kf[q] = kp[q * 64 + lane];
+        };
+        auto load_v = [&](int i) __attribute__((always_inline)) {
+            const uint2 *vp = reinterpret_cast<const uint2 *>(sq.pool + kvf_base(__builtin_amdgcn_readlane(ids, i), layer, n_layers, 1, kvh, n_kv_heads, DH));
+#pragma unroll
+            for (int q = 0; q < NDT; ++q) vf[q] = vp[q * 64 + lane];
+        };
+        attn_load_q<DH, false>(qf, qp, head, m >> 3);
+        load_k(0);
+        load_v(0);
+        const float scale2 = scale * 1.44269504088896f;
+        const bool row_ok = slot == my_slot;
+        float m_run = kMasked, d_run = 0.f;
+        f32x4 o_acc[NDT];
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) o_acc[dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < n_pages; ++i) {
+            const int key0 = key_at(i), next = i + 1 < n_pages ? i + 1 : i;   // (the last page is requested again rather than none: L2)
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[ks]), __builtin_bit_cast(bf16x8, qf[ks]), acc, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            load_k(next);
+            __builtin_amdgcn_sched_barrier(0);
+            // (as in attn_task)
+            float sc[4], mx = kMasked;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float v = (acc[q] + row_down8(acc[q])) * scale2;
+                sc[q] = row_ok && key0 + 4 * kg + q <= L ? v : kMasked;
+                mx = fmaxf(mx, sc[q]);
+            }
+            mx = rows_max(mx);
+            const float m_new = fmaxf(m_run, mx);
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+            float p[4], den = 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                p[q] = sc[q] > 0.5f * kMasked ? __builtin_amdgcn_exp2f(sc[q] - m_new) : 0.f;
+                den += p[q];
+            }
+            d_run = fmaf(d_run, alpha, den);
+            m_run = m_new;
+            if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
+                const float up = row_up8(alpha);
+                const float af = slot < 8 ? alpha : up;
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt) o_acc[dt] = o_acc[dt] * af;
+            }
+            bf16x4s pb;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float up = row_up8(p[q]);
+                const float pv = slot < 8 ? p[q] : up;
+                const bf16_t hi = f32_to_bf16(pv);
+                const bf16_t o = slot < 8 ? hi : f32_to_bf16(pv - bf16_to_f32(hi));
+                pb[q] = (short)o;
+            }
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt)
+                o_acc[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4s, vf[dt]), pb, o_acc[dt], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            load_v(next);
+            __builtin_amdgcn_sched_barrier(0);
+            const int s = split_at(i);
+            if (i + 1 == n_pages || split_at(i + 1) != s) {   // the wave's share of this split is done
+                d_run = rows_sum(d_run);
+                if (slot == my_slot && kg == 0) { part_m[s][wave] = m_run; part_d[s][wave] = d_run; }
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt) {
+                    f32x4 o;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) o[q] = o_acc[dt][q] + row_down8(o_acc[dt][q]);
+                    if (slot == my_slot) *reinterpret_cast<f32x4 *>(&part_o[s][wave][16 * dt + 4 * kg]) = o;
+                    o_acc[dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                }
+                m_run = kMasked;
+                d_run = 0.f;
+            }
+        }
+    }
+    __syncthreads();
+    // four adjacent output elements per thread: the splits' sums in wave order, merged in increasing order
+    constexpr int HW = kFastWaves / 2;
+    const int e4 = threadIdx.x;
+    if (e4 >= DH / 4) return;
+    auto split_max = [&](int s, int nw) {   // nw: waves that have keys of this split
+        float bm = part_m[s][0];
+        for (int w = 1; w < nw; ++w) bm = fmaxf(bm, part_m[s][w]);
+        return bm;
+    };
+    auto waves_of = [&](int s) { const int n = (L - split_begin(s)) / 16 + 1; return n < kFastWaves ? n : kFastWaves; };
+    float g = kMasked;
+    for (int s = 0; s < ns; ++s) g = fmaxf(g, split_max(s, waves_of(s)));
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    float den = 0.f;
+    for (int s = 0; s < ns; ++s) {
+        const int nw = waves_of(s);
+        const float bm = split_max(s, nw);
+        f32x4 ot[kFastWaves];
+        float dsum = 0.f;
+#pragma unroll
+        for (int w = 0; w < kFastWaves; ++w) {
+            ot[w] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            if (w < nw) {
+                const float wf = __builtin_amdgcn_exp2f(part_m[s][w] - bm);
+                // (made opaque: attn_task's products pass through LDS and are never fused with the sums that follow)
+                float d = part_d[s][w] * wf;
+                asm volatile("" : "+v"(d));
+                dsum = w == 0 ? d : dsum + d;
+                ot[w] = *reinterpret_cast<const f32x4 *>(&part_o[s][w][4 * e4]) * wf;
+                asm volatile("" : "+v"(ot[w]));
+            }
+        }
+        f32x4 tot = ot[0] + ot[HW];
+#pragma unroll
+        for (int w = 1; w < HW; ++w) tot += ot[w] + ot[w + HW];
+        const float wgt = __builtin_amdgcn_exp2f(bm - g);
+        den = fmaf(wgt, dsum, den);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = fmaf(wgt, tot[q], o[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[q] /= den;
+    xp_store4<false>(xp_att, cls, m, head * DH + 4 * e4, o);
 }
 
 // After a draft tree has been verified: the accepted path's rows path[1..a] sit in cache slots

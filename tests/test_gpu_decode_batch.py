@@ -1,0 +1,53 @@
+"""Plain decoding of many sequences in one step: bit for bit the sequences verified alone, at the ends of pages, of splits
+and of the eight one-page splits, and where the rule for the many-sequences attention kernel does not hold."""
+import pytest
+import torch
+
+from paper_2404_08698_amd import binding as B
+from paper_2404_08698_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+MHA = synth.ModelShape(2, 2048, 32, 64, 512, 1024, "bf16")
+GQA = synth.ModelShape(2, 4096, 32, 128, 512, 1024, "bf16", n_kv_heads=4)
+
+
+def _run(shape, lengths, max_positions):
+    w = synth.make_weights(shape, 3, device="cuda")
+    model = B.Model(shape, w, max_window=32, max_positions=max_positions)
+    n = len(lengths)
+    joint, alone = [], []
+    for i, length in enumerate(lengths):
+        pair = []
+        for _ in range(2):
+            kv = B.KVCache(model, length + 8)
+            kv.set_page_order([(j * 7 + i) % kv.num_pages for j in range(kv.num_pages)] if kv.num_pages % 7 else list(range(kv.num_pages)))
+            for layer in range(shape.n_layers):
+                if length:
+                    k, v = synth.kv_fill(shape, 100 + i, layer, length, device="cuda")
+                    kv.write(layer, 0, k.float().contiguous(), v.float().contiguous())
+            kv.truncate(length)
+            pair.append(kv)
+        joint.append(pair[0])
+        alone.append(pair[1])
+    for step in range(2):
+        wins = [[synth.random_tokens(shape.vocab, 1, 31 * step + i)[0]] for i in range(n)]
+        logits = torch.empty(n, shape.vocab, dtype=torch.float32, device="cuda")
+        got = B.verify_batch(model, joint, wins, out_logits=logits)
+        for i in range(n):
+            row = torch.empty(1, shape.vocab, dtype=torch.float32, device="cuda")
+            assert B.verify(model, alone[i], wins[i], out_logits=row) == got[i], (step, i)
+            assert torch.equal(row[0], logits[i]), (step, i, lengths[i])
+
+
+def test_short_sequences():
+    _run(MHA, [0, 1, 15, 16, 17, 112, 127, 128, 129, 255, 300, 511, 512, 640, 700, 895, 896, 1000, 1022, 33], 1100)
+
+
+def test_long_sequences():
+    _run(GQA, [1023, 1024, 1025, 1151, 1152, 1153, 1407, 1408, 1409, 2000, 5, 4094, 3000, 200, 900, 1300, 77], 4200)
+
+
+def test_sequences_past_the_kernels_splits_and_too_few_of_them():
+    _run(GQA, [4100, 20, 30, 40, 50, 60, 70, 80, 90, 100, 110, 120, 130, 140, 150, 160], 4200)
+    _run(MHA, [100, 200, 300, 400, 500, 600, 700, 800, 900], 1100)
