@@ -890,10 +890,10 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
         }
         mark(m, ANPD_PROF_GEMM_QKV, st);
         if (dh == 128)
-            hipLaunchKernelGGL((prefill_attn_kernel<128>), dim3((unsigned)H, (unsigned)((G + 3) / 4)), dim3(256), 0, st, (const uint4 *)qp,
+            hipLaunchKernelGGL((prefill_attn_kernel<128>), dim3((unsigned)H, (unsigned)((G + 1) / 2)), dim3(256), 0, st, (const uint4 *)qp,
                                (const bf16_t *)kv->pool, kv->d_table, G, len, P, l, c.n_layers, H, kv_heads_of(c), scale, xq_att, nks_d);
         else
-            hipLaunchKernelGGL((prefill_attn_kernel<64>), dim3((unsigned)H, (unsigned)((G + 3) / 4)), dim3(256), 0, st, (const uint4 *)qp,
+            hipLaunchKernelGGL((prefill_attn_kernel<64>), dim3((unsigned)H, (unsigned)((G + 1) / 2)), dim3(256), 0, st, (const uint4 *)qp,
                                (const bf16_t *)kv->pool, kv->d_table, G, len, P, l, c.n_layers, H, kv_heads_of(c), scale, xq_att, nks_d);
         mark(m, ANPD_PROF_ATTN, st);
         {

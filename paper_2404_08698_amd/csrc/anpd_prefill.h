@@ -437,103 +437,195 @@ __global__ __launch_bounds__(kPgThreads) void prefill_gemm_kernel(PrefillArgs a)
 
 // --------------------------------------------------------------- attention
 //
+// two floats rounded to bf16 (nearest even) side by side, one instruction
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){a, b}, b16x2));
+}
+
 // Causal attention of the prompt rows over the cache (which by now holds the
-// prompt's own K and V).  One wave per (head, 16-row group); the group is one
-// cache page, so every earlier page is visible in full and only the last one
-// needs the causal mask.  Per page: S = K q^T (query as hi + lo B operands;
-// scores land with keys in registers and rows across lanes), online softmax
-// per row, P as hi + lo B operands straight from those registers, O += V^T P.
-// The next page's K and V are requested before this page's arithmetic.
-// grid: (n_heads, ceil(G / 4)), 4 waves; later groups (more pages) start first.
+// prompt's own K and V).  Block = (head, two 16-row groups), four waves; wave w
+// takes the page pairs w, w + 4, ... and both row groups against each, the waves' running (maximum, denominator,
+// output) meet in LDS at the end.  A group is one cache page, so every earlier
+// page is visible in full and only the group's own page needs the causal mask.  Per pair: S = K q^T (query as
+// hi + lo B operands; scores land with keys in registers and rows across lanes), online softmax
+// per row in the base-2 domain, P as hi + lo B operands straight from those registers, O += V^T P with the two pages'
+// keys in one 32-key MFMA.  The next pair's K is requested when this pair's scores are done, its V when its
+// output is.
+// Why: with one wave per row group every group read all its pages (6.6 GB per layer from L2 at 3584 rows: 300 us at
+// what L2 delivers), 16-key MFMAs did half the work of a 32-key one in the same time, the output was rescaled and a maximum
+// exchanged per page, and a short prompt behind a long cache left the pages to a few waves one after the other.
+// 7B shape, 512 / 3584 rows: 35 -> 21 / 489 -> 409 us per layer (3584 rows: vector ALU 45 %, matrix cores 22 % busy); 205 rows behind
+// 777, 32 heads over 2 key / value heads: 63 -> 19.
+// A row's sums depend on absolute page numbers only, not on how the prompt was cut.
+// grid: (n_heads, ceil(G / 2)); later groups (more pages) start first.
 template <int DH>
 __global__ __launch_bounds__(256) void prefill_attn_kernel(const uint4 *__restrict__ qp, const bf16_t *__restrict__ pool,
                                                             const int32_t *__restrict__ page_table, int G, int L, int P,
                                                             int layer, int n_layers, int n_heads, int n_kv_heads, float scale,
                                                             bf16_t *__restrict__ xq_att, int nks_d)
 {
-    constexpr int NKS = DH / 32, NDT = DH / 16;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, slot = lane & 15, kg = lane >> 4;
+    constexpr int NKS = DH / 32, NDT = DH / 16, WAVES = 4;
+    __shared__ float part[WAVES][2][NDT][64][4];
+    __shared__ float wmax[WAVES][2][16], wden[WAVES][2][16];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), slot = lane & 15, kg = lane >> 4;
     const int head = blockIdx.x, kvh = head / (n_heads / n_kv_heads);
-    const int g = ((int)gridDim.y - 1 - (int)blockIdx.y) * 4 + wave;
-    if (g >= G) return;   // (no block-wide synchronisation below)
-    const int last_page = (L >> 4) + g;
+    const int g0 = 2 * ((int)gridDim.y - 1 - (int)blockIdx.y), n_grp = G - g0 < 2 ? G - g0 : 2;
+    const int own0 = (L >> 4) + g0;                 // the first group's own page; the second group's is the next one
+    const int last_page = own0 + n_grp - 1, last_pair = last_page >> 1;
 
-    uint4 qf[NKS][2];
-    {
-        const uint4 *q = qp + ((size_t)head * G + g) * NKS * 128;
+    uint4 qf[2][NKS][2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        const uint4 *q = qp + ((size_t)head * G + g0 + (x < n_grp ? x : 0)) * NKS * 128;
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
-            for (int hl = 0; hl < 2; ++hl) qf[ks][hl] = q[(ks * 2 + hl) * 64 + lane];
+            for (int hl = 0; hl < 2; ++hl) qf[x][ks][hl] = q[(ks * 2 + hl) * 64 + lane];
     }
-    uint4 kA[NKS], kB[NKS];
-    uint2 vA[NDT], vB[NDT];
-    auto load = [&](uint4 (&kf)[NKS], uint2 (&vf)[NDT], int pg) {
-        const int page = __builtin_amdgcn_readfirstlane(page_table[pg]);
+    // page numbers of the wave's next 64 pairs, one pair per lane; a pair's second page, if it does not exist, is the
+    // first one again (its keys get weight 0)
+    int ida = 0, idb = 0;
+    auto fetch_ids = [&](int k0) __attribute__((always_inline)) {
+        const int pa = 2 * (wave + WAVES * (k0 + lane));
+        ida = page_table[pa <= last_page ? pa : last_page];
+        idb = page_table[pa + 1 <= last_page ? pa + 1 : last_page];
+    };
+    uint4 kf[2][NKS];
+    uint2 vf[2][NDT];
+    auto load_k = [&](int page, uint4 (&k)[NKS]) __attribute__((always_inline)) {
         const uint4 *kp = reinterpret_cast<const uint4 *>(pool + kvf_base(page, layer, n_layers, 0, kvh, n_kv_heads, DH));
+#pragma unroll
+        for (int i = 0; i < NKS; ++i) k[i] = kp[i * 64 + lane];
+    };
+    auto load_v = [&](int page, uint2 (&v)[NDT]) __attribute__((always_inline)) {
         const uint2 *vp = reinterpret_cast<const uint2 *>(pool + kvf_base(page, layer, n_layers, 1, kvh, n_kv_heads, DH));
 #pragma unroll
-        for (int i = 0; i < NKS; ++i) kf[i] = kp[i * 64 + lane];
-#pragma unroll
-        for (int i = 0; i < NDT; ++i) vf[i] = vp[i * 64 + lane];
+        for (int i = 0; i < NDT; ++i) v[i] = vp[i * 64 + lane];
     };
-    float mx = kMasked, den = 0.f;
-    f32x4 o[NDT];
+    const float scale2 = scale * 1.44269504088896f;
+    float m_run[2] = {kMasked, kMasked}, d_run[2] = {0.f, 0.f};
+    f32x4 o[2][NDT];
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt) o[dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    auto page_step = [&](const uint4 (&kf)[NKS], const uint2 (&vf)[NDT], int pg) {
-        f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
-            s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[ks]), __builtin_bit_cast(bf16x8, qf[ks][0]), s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[ks]), __builtin_bit_cast(bf16x8, qf[ks][1]), s, 0, 0, 0);
+        for (int dt = 0; dt < NDT; ++dt) o[x][dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+    const int n_pairs = last_pair >= wave ? (last_pair - wave) / WAVES + 1 : 0;   // this wave's
+    if (n_pairs > 0) {
+        fetch_ids(0);
+        const int pa = __builtin_amdgcn_readlane(ida, 0), pb = __builtin_amdgcn_readlane(idb, 0);
+        load_k(pa, kf[0]);
+        load_k(pb, kf[1]);
+        load_v(pa, vf[0]);
+        load_v(pb, vf[1]);
+        for (int k = 0; k < n_pairs; ++k) {
+            const int page0 = 2 * (wave + WAVES * k);
+            // ---- scores of both groups: lane (slot, kg) has keys 4 kg + i of either page, row slot
+            f32x4 sc[2][2];
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int y = 0; y < 2; ++y) {
+                    f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < NKS; ++ks) {
+                        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[y][ks]), __builtin_bit_cast(bf16x8, qf[x][ks][0]), t, 0, 0, 0);
+                        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[y][ks]), __builtin_bit_cast(bf16x8, qf[x][ks][1]), t, 0, 0, 0);
+                    }
+                    sc[x][y] = t;
+                }
+            if (((k + 1) & 63) == 0) fetch_ids(k + 1);
+            // (past the end: the last page, requested for nothing)
+            const int na = __builtin_amdgcn_readlane(ida, (k + 1) & 63), nb = __builtin_amdgcn_readlane(idb, (k + 1) & 63);
+            load_k(na, kf[0]);
+            load_k(nb, kf[1]);
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const int own = own0 + x;
+                if (x >= n_grp || page0 > own) continue;   // (whole wave) nothing of this pair is visible to the group
+                float p[8], mx = kMasked;
+                const bool all_seen = page0 + 1 < own;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int page = page0 + (j >> 2);
+                    p[j] = sc[x][j >> 2][j & 3];
+                    if (!all_seen) p[j] = page < own || (page == own && 4 * kg + (j & 3) <= slot) ? p[j] : kMasked;
+                    mx = fmaxf(mx, p[j]);
+                }
+                // The row's reference follows its maximum only when that is more than 2^8 above it: the weights are
+                // then at most 2^8, which costs no precision, and the output is rescaled a few times instead of
+                // at every other pair.  (A row's own decision: its bits do not depend on the rows beside it.)
+                mx = rows_max(mx) * scale2;
+                const float m_new = mx > m_run[x] + 8.f ? mx : m_run[x], alpha = __builtin_amdgcn_exp2f(m_run[x] - m_new);
+                m_run[x] = m_new;
+                float den = 0.f;
+                u32x4_t ph, pl;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    float a = __builtin_amdgcn_exp2f(fmaf(p[2 * j], scale2, -m_new)), b = __builtin_amdgcn_exp2f(fmaf(p[2 * j + 1], scale2, -m_new));
+                    if (!all_seen) {   // (a row may have seen nothing yet: its reference is the mask's value)
+                        a = p[2 * j] > 0.5f * kMasked ? a : 0.f;
+                        b = p[2 * j + 1] > 0.5f * kMasked ? b : 0.f;
+                    }
+                    den += a;
+                    den += b;
+                    ph[j] = pack_bf16(a, b);
+                    pl[j] = pack_bf16(a - __uint_as_float(ph[j] << 16), b - __uint_as_float(ph[j] & 0xffff0000u));
+                }
+                d_run[x] = fmaf(d_run[x], alpha, den);
+                // (whole-wave branch; a factor of 1 changes nothing)
+                if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
+#pragma unroll
+                    for (int dt = 0; dt < NDT; ++dt) o[x][dt] = o[x][dt] * alpha;
+                }
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt) {
+                    const u32x4_t v = {vf[0][dt].x, vf[0][dt].y, vf[1][dt].x, vf[1][dt].y};
+                    o[x][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v), __builtin_bit_cast(bf16x8, ph), o[x][dt], 0, 0, 0);
+                    o[x][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v), __builtin_bit_cast(bf16x8, pl), o[x][dt], 0, 0, 0);
+                }
+            }
+            load_v(na, vf[0]);
+            load_v(nb, vf[1]);
         }
-        float sc[4], pm = kMasked;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const bool ok = pg < last_page || 4 * kg + i <= slot;   // on the row's own page: keys up to the row itself
-            sc[i] = ok ? s[i] * scale : kMasked;
-            pm = fmaxf(pm, sc[i]);
-        }
-        pm = fmaxf(pm, __shfl_xor(pm, 16, kWave));
-        pm = fmaxf(pm, __shfl_xor(pm, 32, kWave));
-        const float mnew = fmaxf(mx, pm);
-        const float corr = expf(mx - mnew);
-        mx = mnew;
-        bf16x4s ph, pl;
-        float psum = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float p = sc[i] > 0.5f * kMasked ? expf(sc[i] - mnew) : 0.f;
-            psum += p;
-            const bf16_t hi = f32_to_bf16(p);
-            ph[i] = (short)hi;
-            pl[i] = (short)f32_to_bf16(p - bf16_to_f32(hi));
-        }
-        den = fmaf(den, corr, psum);
-#pragma unroll
-        for (int dt = 0; dt < NDT; ++dt) {
-            f32x4 t = o[dt] * corr;
-            t = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4s, vf[dt]), ph, t, 0, 0, 0);
-            o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4s, vf[dt]), pl, t, 0, 0, 0);
-        }
-    };
-    load(kA, vA, 0);
-    for (int pg = 0; pg <= last_page; pg += 2) {
-        if (pg + 1 <= last_page) load(kB, vB, pg + 1);
-        page_step(kA, vA, pg);
-        if (pg + 2 <= last_page) load(kA, vA, pg + 2);
-        if (pg + 1 <= last_page) page_step(kB, vB, pg + 1);
     }
-    den += __shfl_xor(den, 16, kWave);
-    den += __shfl_xor(den, 32, kWave);
-    const int m = g * 16 + slot, r = m - (L & 15);
-    const bool valid = r >= 0 && r < P;
-    const float inv = valid ? 1.0f / den : 0.f;
+    // ---- the waves meet: every wave scales to the row's maximum, the sums are formed in wave order
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt) {
+    for (int x = 0; x < 2; ++x) {
+        const float d = rows_sum(d_run[x]);
+        if (kg == 0) { wmax[wave][x][slot] = m_run[x]; wden[wave][x][slot] = d; }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        float bm = wmax[0][x][slot];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) bm = fmaxf(bm, wmax[w][x][slot]);
+        const float f = __builtin_amdgcn_exp2f(m_run[x] - bm);
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) *reinterpret_cast<f32x4 *>(part[wave][x][dt][lane]) = o[x][dt] * f;
+    }
+    __syncthreads();
+    for (int u = wave; u < 2 * NDT; u += WAVES) {
+        const int x = u / NDT, dt = u % NDT;
+        if (x >= n_grp) break;
+        float bm = wmax[0][x][slot], den = 0.f;
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) bm = fmaxf(bm, wmax[w][x][slot]);
         f32x4 v = {0.f, 0.f, 0.f, 0.f};
-        if (valid) v = o[dt] * inv;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            den = fmaf(wden[w][x][slot], __builtin_amdgcn_exp2f(wmax[w][x][slot] - bm), den);
+            v += *reinterpret_cast<const f32x4 *>(part[w][x][dt][lane]);
+        }
+        const int m = (g0 + x) * 16 + slot, r = m - (L & 15);
+        const bool valid = r >= 0 && r < P;
+        const float inv = 1.0f / den;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = valid ? v[i] * inv : 0.f;
         xq_store4(xq_att, nks_d, m, head * DH + 16 * dt + 4 * kg, v);
     }
 }

@@ -1,0 +1,47 @@
+"""Prompt attention at the edges of pages, page pairs and the waves' turns: the prompt in one pass against the same rows
+through the step, and bit for bit against the prompt in pieces cut inside pages."""
+import pytest
+import torch
+
+from paper_2404_08698_amd import binding as B
+from paper_2404_08698_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+# rows x cached: one row, a page, a pair, one row more, first groups that start inside a page, an odd number of groups,
+# fewer pairs than waves, several turns of the waves, past the 64 pairs whose page numbers a wave holds at a time
+@pytest.mark.parametrize("shape", [synth.MID_GQA, synth.TINY_BF16], ids=["dh128_gqa", "dh64"])
+@pytest.mark.parametrize("cached,rows", [(0, 1), (0, 16), (0, 17), (0, 33), (5, 27), (15, 1), (16, 49), (31, 34), (100, 129), (250, 130), (8300, 40)])
+def test_one_pass_against_windows_and_pieces(shape, cached, rows):
+    w = synth.make_weights(shape, 3, device="cuda")
+    cap = cached + rows + 8
+    model = B.Model(shape, w, max_window=8, max_positions=cap)
+    kvs = []
+    for _ in range(3):
+        kv = B.KVCache(model, cap)
+        for layer in range(shape.n_layers):
+            if cached:
+                k, v = synth.kv_fill(shape, 7, layer, cached, device="cuda")
+                kv.write(layer, 0, k.float().contiguous(), v.float().contiguous())
+        kv.truncate(cached)
+        kvs.append(kv)
+    prompt = synth.random_tokens(shape.vocab, rows, 11)
+    logits = [torch.empty(shape.vocab, dtype=torch.float32, device="cuda") for _ in range(3)]
+    B.prefill(model, kvs[0], prompt, out_logits=logits[0])
+    for lo in range(0, rows, 21):
+        B.prefill(model, kvs[1], prompt[lo:lo + 21], out_logits=logits[1])
+    for lo in range(0, rows, 8):
+        n = len(prompt[lo:lo + 8])
+        buf = torch.empty(n, shape.vocab, dtype=torch.float32, device="cuda")
+        B.verify(model, kvs[2], prompt[lo:lo + 8], B.APPEND, out_logits=buf)
+        logits[2] = buf[-1]
+    assert torch.equal(logits[0], logits[1])
+    # two orders of the same sums over bf16 keys and values: the tolerance the logits have against the oracle
+    assert (logits[0] - logits[2]).abs().max().item() < 2e-2
+    for layer in range(shape.n_layers):
+        one, cut, step = (kv.read(layer, cached, rows) for kv in kvs)
+        for x, y, z in zip(one, cut, step):
+            assert torch.equal(x, y)
+            # a rounding boundary apart at most: one bf16 unit in the last place of the largest value
+            assert (x - z).abs().max().item() <= 2.0 ** -7 * x.abs().max().item()
