@@ -875,8 +875,16 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
     mark(m, -1, st);
     // columns F .. 32 * nks_f of the down projection's operand meet zero weights: they must not hold NaN patterns
     if (F % 32 != 0) HIP_TRY(hipMemsetAsync(xq_f, 0, (size_t)G * nks_f * 2048, st));
-    hipLaunchKernelGGL((prefill_norm_kernel<true>), dim3((unsigned)(G * 16)), dim3(256), 0, st, (const bf16_t *)m->embed, tok, x,
-                       (const float *)nullptr, 0, (const bf16_t *)m->attn_norm[0], xq, nks_d, d, len, P, inv_d, c.rms_eps);
+    auto norm = [&](const bf16_t *gain, bool embed) {
+#define ANPD_NORM(EMBED_, NV_)                                                                                              \
+    hipLaunchKernelGGL((prefill_norm_kernel<EMBED_, NV_>), dim3((unsigned)((G + 7) / 8 * 128)), dim3(256), 0, st, (const bf16_t *)m->embed, tok, x, \
+                       (const float *)part, gain, xq, nks_d, d, G, len, P, inv_d, c.rms_eps)
+        if (d <= 4096) { if (embed) ANPD_NORM(true, 4); else ANPD_NORM(false, 4); }
+        else if (embed) ANPD_NORM(true, 8);
+        else ANPD_NORM(false, 8);
+#undef ANPD_NORM
+    };
+    norm((const bf16_t *)m->attn_norm[0], true);
     mark(m, ANPD_PROF_OTHER, st);
     for (int l = 0; l < c.n_layers; ++l) {
         {
@@ -906,8 +914,7 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
             if ((rc = launch_prefill_gemm<EPI_RESIDUAL>(a, m->n_cu, st)) != ANPD_OK) return rc;
         }
         mark(m, ANPD_PROF_GEMM_O, st);
-        hipLaunchKernelGGL((prefill_norm_kernel<false>), dim3((unsigned)(G * 16)), dim3(256), 0, st, (const bf16_t *)nullptr, tok, x,
-                           (const float *)part, kPgSplit, (const bf16_t *)m->ffn_norm[l], xq, nks_d, d, len, P, inv_d, c.rms_eps);
+        norm((const bf16_t *)m->ffn_norm[l], false);
         mark(m, ANPD_PROF_OTHER, st);
         {
             PrefillArgs a = base;
@@ -931,8 +938,7 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
         }
         mark(m, ANPD_PROF_GEMM_DOWN, st);
         if (l + 1 < c.n_layers) {
-            hipLaunchKernelGGL((prefill_norm_kernel<false>), dim3((unsigned)(G * 16)), dim3(256), 0, st, (const bf16_t *)nullptr, tok,
-                               x, (const float *)part, kPgSplit, (const bf16_t *)m->attn_norm[(size_t)l + 1], xq, nks_d, d, len, P, inv_d, c.rms_eps);
+            norm((const bf16_t *)m->attn_norm[(size_t)l + 1], false);
             mark(m, ANPD_PROF_OTHER, st);
         }
     }
