@@ -46,7 +46,7 @@ enum {
 
 enum { ANPD_F32 = 0, ANPD_BF16 = 1 };               /* storage type of weights and of cached K/V */
 enum { ANPD_VERIFY = 0, ANPD_APPEND = 1 };          /* anpd_verify modes */
-/* GEMM forms.  DOT: wavefront dot products on the caller's row-major weights (any dtype).
+/* GEMM forms.  DOT: exact fp32 products (fp32 matrix cores) on the caller's row-major weights (any dtype).
  * MFMA: matrix cores on bf16 weights repacked into fragment order.  MFMA_STREAM (anpd_linear
  * only) forces the MFMA form that streams the activation operand instead of holding it in
  * registers; both MFMA forms give bit-identical results.  With MFMA, a window runs as ONE
@@ -274,7 +274,7 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
  *   out_logits (nullable, DEVICE, vocab floats): the last row's logits.
  *   workspace: DEVICE, 256-byte aligned, >= anpd_prefill_workspace_bytes(m, n_tokens) bytes,
  *   used only during the call (about 175 KB per token at the 7B shape).  Models on the
- *   dot-product path (f32 weights) process the prompt in windows of max_window rows and need no
+ *   generic path (ANPD_GEMM_DOT, f32 weights) process the prompt in windows of max_window rows and need no
  *   workspace: the size is 0 and workspace may be NULL.
  * Blocks until the result is on the host.
  * Errors: ANPD_E_RANGE (bad token), ANPD_E_CAPACITY (length + n_tokens > max_tokens, or the

@@ -228,7 +228,7 @@ int32_t launch_wide(const FastArgs &a, int blocks, hipStream_t st)
 {
     const size_t smem = (size_t)(T < 4 ? T : 4) * kFastWaves * 4 * 256 * sizeof(float);
     static bool attr_set = false;   // per instantiation
-    if (!attr_set) {
+    if (smem > 65536 && !attr_set) {
         HIP_TRY(hipFuncSetAttribute((const void *)gemm_wide_kernel<T, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
         attr_set = true;
     }
