@@ -240,7 +240,7 @@ int32_t anpd_verify_tree(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, 
 
 /* Several sequences in one step: their windows go through every weight matrix together, so the
  * weights are streamed once for all of them (the step is bound by that stream: measured at the 7B
- * shape, up to 8 rows cost a one-row step, 9 to 16 rows 1.3 and 17 to 32 rows 1.9 times that).  The
+ * shape, up to 8 rows cost a one-row step, 9 to 16 rows 1.3 and 17 to 32 rows 1.5 times that).  The
  * paper verifies one sequence at a time (Algorithm 1); this is the same step for n_seq independent
  * runs of it.
  *   kvs (host array of n_seq handles): one cache per sequence, all of model m, all different.

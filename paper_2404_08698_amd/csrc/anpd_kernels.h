@@ -219,13 +219,6 @@ __device__ __forceinline__ float wave_sum(float v)
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
     return v;
 }
-__device__ __forceinline__ float wave_max(float v)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
-    return v;
-}
-
 // Window class: how many 16-row MFMA slots a window of M rows occupies (8 = half a tile).
 __host__ __device__ __forceinline__ int window_class(int M) { return M <= 8 ? 8 : (M <= 16 ? 16 : 32); }
 
