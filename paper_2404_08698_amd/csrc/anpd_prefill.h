@@ -549,8 +549,9 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(const uint4 *__restri
             const int na = __builtin_amdgcn_readlane(ida, (k + 1) & 63), nb = __builtin_amdgcn_readlane(idb, (k + 1) & 63);
             load_k(na, kf[0]);
             load_k(nb, kf[1]);
+            // (the second group first: a page that it must not see, the first must not see either)
 #pragma unroll
-            for (int x = 0; x < 2; ++x) {
+            for (int x = 1; x >= 0; --x) {
                 const int own = own0 + x;
                 if (x >= n_grp || page0 > own) continue;   // (whole wave) nothing of this pair is visible to the group
                 float p[8], mx = kMasked;
@@ -587,6 +588,11 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(const uint4 *__restri
                 if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
 #pragma unroll
                     for (int dt = 0; dt < NDT; ++dt) o[x][dt] = o[x][dt] * alpha;
+                }
+                // a page behind the group's own takes no part at all: 0 times an infinity in its V would be NaN
+                if (page0 + 1 > own) {
+#pragma unroll
+                    for (int dt = 0; dt < NDT; ++dt) vf[1][dt] = make_uint2(0, 0);
                 }
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt) {

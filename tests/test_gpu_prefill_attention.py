@@ -45,3 +45,20 @@ def test_one_pass_against_windows_and_pieces(shape, cached, rows):
             assert torch.equal(x, y)
             # a rounding boundary apart at most: one bf16 unit in the last place of the largest value
             assert (x - z).abs().max().item() <= 2.0 ** -7 * x.abs().max().item()
+
+
+# the first row of a page pair's second page, one inside it, the last row of a first page, the first of a pair
+@pytest.mark.parametrize("shape", [synth.MID_GQA, synth.TINY_BF16], ids=["dh128_gqa", "dh64"])
+@pytest.mark.parametrize("at", [16, 20, 47, 48, 64, 90])
+def test_a_row_that_is_not_finite_leaves_the_pages_before_it_alone(shape, at):
+    w = synth.make_weights(shape, 3, device="cuda")
+    w["embed"][7] = float("nan")
+    model = B.Model(shape, w, max_window=8, max_positions=128)
+    prompt = [t if t != 7 else 8 for t in synth.random_tokens(shape.vocab, 100, 11)]
+    page0 = at // 16 * 16
+    whole, before = B.KVCache(model, 128), B.KVCache(model, 128)
+    B.prefill(model, whole, prompt[:at] + [7] + prompt[at + 1:])
+    B.prefill(model, before, prompt[:page0])
+    for layer in range(shape.n_layers):
+        for x, y in zip(whole.read(layer, 0, page0), before.read(layer, 0, page0)):
+            assert torch.equal(x, y), layer   # (NaN equals nothing)
