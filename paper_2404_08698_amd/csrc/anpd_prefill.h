@@ -571,18 +571,24 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(const uint4 *__restri
                 m_run[x] = m_new;
                 float den = 0.f;
                 u32x4_t ph, pl;
+                auto weights = [&](bool select) __attribute__((always_inline)) {
+                    den = 0.f;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    float a = __builtin_amdgcn_exp2f(fmaf(p[2 * j], scale2, -m_new)), b = __builtin_amdgcn_exp2f(fmaf(p[2 * j + 1], scale2, -m_new));
-                    if (!all_seen) {   // (a row may have seen nothing yet: its reference is the mask's value)
-                        a = p[2 * j] > 0.5f * kMasked ? a : 0.f;
-                        b = p[2 * j + 1] > 0.5f * kMasked ? b : 0.f;
+                    for (int j = 0; j < 4; ++j) {
+                        float a = __builtin_amdgcn_exp2f(fmaf(p[2 * j], scale2, -m_new)), b = __builtin_amdgcn_exp2f(fmaf(p[2 * j + 1], scale2, -m_new));
+                        if (select) {   // (a row may have seen nothing yet: its reference is the mask's value)
+                            a = p[2 * j] > 0.5f * kMasked ? a : 0.f;
+                            b = p[2 * j + 1] > 0.5f * kMasked ? b : 0.f;
+                        }
+                        den += a;
+                        den += b;
+                        ph[j] = pack_bf16(a, b);
+                        pl[j] = pack_bf16(a - __uint_as_float(ph[j] << 16), b - __uint_as_float(ph[j] & 0xffff0000u));
                     }
-                    den += a;
-                    den += b;
-                    ph[j] = pack_bf16(a, b);
-                    pl[j] = pack_bf16(a - __uint_as_float(ph[j] << 16), b - __uint_as_float(ph[j] & 0xffff0000u));
-                }
+                };
+                weights(!all_seen);
+                // a key whose score is NaN has weight 0, as in a step (looked for behind the sums: one comparison)
+                if (__builtin_amdgcn_ballot_w64(den != den) != 0) weights(true);
                 d_run[x] = fmaf(d_run[x], alpha, den);
                 // (whole-wave branch; a factor of 1 changes nothing)
                 if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {

@@ -62,3 +62,26 @@ def test_a_row_that_is_not_finite_leaves_the_pages_before_it_alone(shape, at):
     for layer in range(shape.n_layers):
         for x, y in zip(whole.read(layer, 0, page0), before.read(layer, 0, page0)):
             assert torch.equal(x, y), layer   # (NaN equals nothing)
+
+
+# a cached key with a NaN: on a page seen in full by every row, on the last cached one, on the rows' own page
+@pytest.mark.parametrize("shape", [synth.MID_GQA, synth.TINY_BF16], ids=["dh128_gqa", "dh64"])
+@pytest.mark.parametrize("at,cached,rows", [(3, 64, 40), (63, 64, 40), (150, 200, 33), (40, 50, 3)])
+def test_a_key_with_a_nan_has_weight_zero_as_in_a_step(shape, at, cached, rows):
+    w = synth.make_weights(shape, 3, device="cuda")
+    model = B.Model(shape, w, max_window=8, max_positions=256)
+    prompt = synth.random_tokens(shape.vocab, rows, 11)
+    one, step = B.KVCache(model, 256), B.KVCache(model, 256)
+    for kv in (one, step):
+        for layer in range(shape.n_layers):
+            k, v = (t.float().contiguous() for t in synth.kv_fill(shape, 7, layer, cached, device="cuda"))
+            k[at] = float("nan")
+            kv.write(layer, 0, k, v)
+        kv.truncate(cached)
+    got = torch.empty(shape.vocab, dtype=torch.float32, device="cuda")
+    B.prefill(model, one, prompt, out_logits=got)
+    for lo in range(0, rows, 8):
+        ref = torch.empty(len(prompt[lo:lo + 8]), shape.vocab, dtype=torch.float32, device="cuda")
+        B.verify(model, step, prompt[lo:lo + 8], B.APPEND, out_logits=ref)
+    assert torch.isfinite(ref[-1]).all()
+    assert (got - ref[-1]).abs().max().item() < 2e-2   # (as in the comparison with windows above)
