@@ -871,9 +871,15 @@ __global__ __launch_bounds__(kSplitMaxWaves * 64) void gemm_split_kernel(FastArg
                            real ? lane * 16 + ((c + 8 * (i0 + k)) * NT + f) * 1024 : 0x7ffffff0);
         }
     };
+    // (buffer 0, weights, buffer 1: the order that the wait in the loop counts on, held against the compiler, to which
+    // the three have nothing to do with one another)
     load_x(0, 0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int s = 0; s < D; ++s) load_w(s, s);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
     load_x(D, 1);
     f32x4 acc[NT];
 #pragma unroll
@@ -885,10 +891,13 @@ __global__ __launch_bounds__(kSplitMaxWaves * 64) void gemm_split_kernel(FastArg
         const uint32_t xb = base + (uint32_t)b * (D * NT * 1024);
 #pragma unroll
         for (int s = 0; s < D; ++s) {
+            // (read and waited for in one statement: no instruction of the compiler's can come between)
             u32x4_t xv[NT];
-#pragma unroll
-            for (int f = 0; f < NT; ++f) asm volatile("ds_read_b128 %0, %1" : "=v"(xv[f]) : "v"(xb + (uint32_t)(s * NT + f) * 1024) : "memory");
-            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(xv[0]), "+v"(xv[1]), "+v"(xv[2]), "+v"(xv[3]));
+            asm volatile("ds_read_b128 %0, %4 offset:%5\n\tds_read_b128 %1, %4 offset:%6\n\tds_read_b128 %2, %4 offset:%7\n\t"
+                         "ds_read_b128 %3, %4 offset:%8\n\ts_waitcnt lgkmcnt(0)"
+                         : "=&v"(xv[0]), "=&v"(xv[1]), "=&v"(xv[2]), "=&v"(xv[3])
+                         : "v"(xb), "n"((s * NT) * 1024), "n"((s * NT + 1) * 1024), "n"((s * NT + 2) * 1024), "n"((s * NT + 3) * 1024)
+                         : "memory");
 #pragma unroll
             for (int f = 0; f < NT; ++f)
                 acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[s]), __builtin_bit_cast(bf16x8, xv[f]), acc[f], 0, 0, 0);

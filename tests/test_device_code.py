@@ -1,0 +1,111 @@
+"""The built gfx950 code of the kernels that read LDS through assembly statements.  The compiler does not know that such
+a read's registers are still being written, so its own code must leave them alone until the wait behind them: checked
+here on what it made of the sources (no GPU needed).  For the kernel whose wait counts rely on the order of its first
+loads, the order as well."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_2404_08698_amd import binding as B
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+pytestmark = pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no llvm-objdump")
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """{mangled name: [(address, instruction, operands)]} of the library's device code."""
+    B.lib()
+    blob = open(B.LIB_PATH, "rb").read()
+    at = blob.index(b"__CLANG_OFFLOAD_BUNDLE__")
+    count, pos = struct.unpack_from("<Q", blob, at + 24)[0], at + 32
+    for _ in range(count):
+        offset, size, length = struct.unpack_from("<QQQ", blob, pos)
+        triple = blob[pos + 24:pos + 24 + length]
+        pos += 24 + length
+        if b"gfx950" in triple:
+            code = blob[at + offset:at + offset + size]
+    path = tmp_path_factory.mktemp("code") / "device.co"
+    path.write_bytes(code)
+    text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(path)], capture_output=True, text=True, check=True).stdout
+    out, cur = {}, None
+    for line in text.splitlines():
+        head = re.match(r"^[0-9a-f]+ <(\S+)>:$", line)
+        if head:
+            cur = out.setdefault(head.group(1), [])
+            continue
+        m = re.match(r"^\t(\S+)\s*(.*?)\s*// ([0-9A-F]+):", line)
+        if m and cur is not None:
+            cur.append((int(m.group(3), 16), m.group(1), m.group(2)))
+    return out
+
+
+def _registers(operands):
+    """Vector registers named in an operand text."""
+    found = set()
+    for bank, lo, hi in re.findall(r"\b([va])\[(\d+):(\d+)\]", operands):
+        found |= {(bank, r) for r in range(int(lo), int(hi) + 1)}
+    return found | {(bank, int(r)) for bank, r in re.findall(r"\b([va])(\d+)\b", operands)}
+
+
+def _faults(code):
+    """Instructions that touch a register an LDS read is still writing, over every path through the kernel."""
+    index = {address: i for i, (address, _, _) in enumerate(code)}
+    seen, todo, bad = set(), [(0, ())], []
+    while todo:
+        i, flight = todo.pop()      # flight: registers written by each outstanding LDS / scalar memory operation, oldest first
+        while i < len(code) and (i, flight) not in seen:
+            seen.add((i, flight))
+            address, name, operands = code[i]
+            waits = re.search(r"lgkmcnt\((\d+)\)", operands) if name == "s_waitcnt" else None
+            if waits:
+                keep = int(waits.group(1))
+                flight = flight[len(flight) - keep:] if keep else ()
+            elif name.startswith(("ds_", "s_load", "s_buffer_load")):
+                busy = frozenset().union(*flight)
+                dst = operands.split(",")[0] if name.startswith(("ds_read", "ds_bpermute", "ds_swizzle")) else ""
+                if _registers(operands) & busy:
+                    bad.append((hex(address), name, operands))
+                flight += (frozenset(_registers(dst)),)
+            elif flight and _registers(operands) & frozenset().union(*flight):
+                bad.append((hex(address), name, operands))
+            if name == "s_endpgm":
+                break
+            if name.startswith(("s_cbranch", "s_branch")):
+                jump = operands.split()[0]
+                target = address + 4 + 4 * (int(jump) - (0x10000 if int(jump) >= 0x8000 else 0))
+                todo.append((index[target], flight))
+                if name == "s_branch":
+                    break
+            i += 1
+    return bad
+
+
+@pytest.mark.parametrize("name,count", [("prefill_gemm_kernel", 15), ("gemm_split_kernel", 1)])
+def test_registers_of_reads_in_flight_are_left_alone(kernels, name, count):
+    mine = {k: v for k, v in kernels.items() if name in k}
+    assert len(mine) == count
+    for k, code in mine.items():
+        assert sum(n == "ds_read_b128" for _, n, _ in code) >= 4, k
+        assert not _faults(code), k
+        assert not [c for c in code if c[1].startswith("scratch_")], k    # no register was parked in memory
+
+
+def test_the_checker_sees_a_register_that_is_used_too_early():
+    read, wait, end = (0, "ds_read_b128", "v[4:7], v1"), (8, "s_waitcnt", "lgkmcnt(0)"), (16, "s_endpgm", "")
+    assert not _faults([read, wait, (12, "v_mov_b32_e32", "v9, v5"), end])
+    assert _faults([read, (8, "v_mov_b32_e32", "v9, v5"), (12, "s_waitcnt", "lgkmcnt(0)"), end])
+    assert _faults([read, (8, "v_mov_b32_e32", "v7, 0"), (12, "s_waitcnt", "lgkmcnt(0)"), end])
+    assert _faults([read, (8, "ds_read_b128", "v[8:11], v1"), (12, "s_waitcnt", "lgkmcnt(1)"), (14, "v_mov_b32_e32", "v0, v8"), end])
+
+
+def test_split_gemm_requests_its_operand_around_the_first_weights(kernels):
+    """Its waits leave 16 weight loads and the other buffer's 8 operand loads outstanding: the first buffer's operand
+    loads have to be the oldest, the second's the youngest."""
+    code = next(v for k, v in kernels.items() if "gemm_split_kernel" in k)
+    barrier = next(i for i, c in enumerate(code) if c[1] == "s_barrier")
+    loads = ["x" if c[2].endswith("lds") else "w" for c in code[:barrier] if c[1].startswith("buffer_load")]
+    assert "".join(loads) == "x" * 8 + "w" * 16 + "x" * 8
