@@ -972,18 +972,22 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
     return ANPD_OK;
 }
 
-// Where a step's LM head writes: straight into the caller's buffer when that is memory of this device that takes
-// 16-byte stores, else into the workspace, from where it is copied (a buffer of another GPU, say).
-float *logits_target(const anpd_model *m, float *out_logits)
+// Where a step's LM head writes its n logits: straight into the caller's buffer when that is memory of this device that
+// takes 16-byte stores and holds them all, else into the workspace, from where they are copied (a buffer of another
+// GPU, say; one that is too short makes the copy fail, where stores would go past its end).
+float *logits_target(const anpd_model *m, float *out_logits, size_t n)
 {
     float *own = (float *)(m->ws + m->lay.logits);
     if (!out_logits || ((uintptr_t)out_logits & 15) != 0) return own;
     hipPointerAttribute_t at;
-    if (hipPointerGetAttributes(&at, out_logits) != hipSuccess) {
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&at, out_logits) != hipSuccess || hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)out_logits) != hipSuccess) {
         (void)hipGetLastError();
         return own;
     }
-    return at.type == hipMemoryTypeDevice && at.device == m->device ? out_logits : own;
+    const bool fits = (char *)out_logits + n * sizeof(float) <= (char *)base + size;
+    return at.type == hipMemoryTypeDevice && at.device == m->device && fits ? out_logits : own;
 }
 
 StepTokens step_tokens(const int32_t *window, int n)
@@ -1383,7 +1387,7 @@ int32_t anpd_verify(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, int32
     // flag) into the pinned buffer themselves.
     const bool one_kernel = m->mega && (n_window <= 8 || (n_window <= 16 && m->mega_rows16));
     const int32_t *res = m->pin + 32;
-    float *logits = logits_target(m, out_logits);
+    float *logits = logits_target(m, out_logits, (size_t)n_window * m->cfg.vocab);
     if (one_kernel) rc = run_step_mega(m, kv, window, n_window, mode, out_logits ? logits : nullptr, st);
     else if (m->mfma) rc = run_step_fast(m, kv, step_tokens(window, n_window), n_window, mode, logits, st);
     else if (m->cfg.dtype == ANPD_BF16) rc = run_step_generic<bf16_t>(m, kv, step_tokens(window, n_window), n_window, mode, logits, st);
@@ -1435,7 +1439,7 @@ int32_t anpd_verify_tree(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, 
         tm[i] = tm[parent[i]] | (1u << i);
     }
     const int32_t *res = m->pin + 32;
-    float *logits = logits_target(m, out_logits);
+    float *logits = logits_target(m, out_logits, (size_t)n_window * m->cfg.vocab);
     // windows of up to 8 rows: the one-kernel step in its draft-tree form (tree by value as well); otherwise one
     // launch per operation, the tree uploaded
     const bool one_kernel = m->mega && m->mega_tree && n_window <= 8;
@@ -1523,7 +1527,7 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
     // value and writes the results into the pinned buffer itself; otherwise copies and the fused launches.
     const bool one_kernel = m->mega && m->mega_batch && total <= 8;
     const int32_t *res = m->pin + 256;
-    float *logits = logits_target(m, out_logits);
+    float *logits = logits_target(m, out_logits, (size_t)total * m->cfg.vocab);
     int32_t rc;
     if (one_kernel) {
         int32_t lens[8];
@@ -1610,7 +1614,7 @@ int32_t anpd_prefill(anpd_model_t *m, anpd_kv_t *kv, const int32_t *tokens, int3
     if (rc != ANPD_OK) return rc;
     char *pws = (char *)workspace;
     HIP_TRY(hipMemcpyAsync(pws + PL.tok, tokens, sizeof(int32_t) * (size_t)n_tokens, hipMemcpyHostToDevice, st));
-    float *logits = logits_target(m, out_logits);
+    float *logits = logits_target(m, out_logits, V);
     rc = run_prefill_mfma(m, kv, n_tokens, pws, PL, logits, st);
     if (rc != ANPD_OK) return rc;
     const int32_t *res = m->pin + 32;

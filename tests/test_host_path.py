@@ -1,0 +1,120 @@
+"""The library's host code on a stand-in for the HIP runtime (hip_stub.cpp: kernels are written down, not run): which
+calls it makes, with what, and what it leaves behind when one of them fails.  Each test is a process of its own."""
+import ctypes as C
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CHILD = os.environ.get("ANPD_HIP_STUB")     # set in the test's own process: the built stand-in
+
+
+@pytest.fixture(scope="session")
+def stub(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-w",
+                    os.path.join(HERE, "hip_stub.cpp"), "-o", out], check=True)
+    return out
+
+
+def in_child(stub, name, *args):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), name, *map(str, args)], capture_output=True, text=True, timeout=120,
+                       env=dict(os.environ, ANPD_HIP_STUB=stub, PYTHONPATH=os.path.dirname(HERE)))
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+# ------------------------------------------------------------------------------------------- in the child
+
+class Host:
+    """The library on the stand-in, with a one-layer model and caches in host memory."""
+
+    def __init__(self, d=256, heads=4, dh=64, ffn=256, vocab=512, dtype="bf16", kv_heads=0, path=0, max_window=32, max_positions=256, layers=1):
+        sys.modules["torch"] = None           # (it would bring a HIP runtime of its own)
+        self.stub = C.CDLL(CHILD, mode=C.RTLD_GLOBAL)
+        self.stub.stub_name.restype = C.c_char_p
+        self.stub.stub_arg0.restype = C.c_void_p
+        self.stub.stub_arg0.argtypes = [C.c_int]
+        self.stub.stub_memory.argtypes = [C.c_void_p, C.c_size_t, C.c_int]
+        from paper_2404_08698_amd import binding as B
+        self.B, self.L, self.keep = B, B.lib(), []
+        cfg = B.ModelCfg(layers, d, heads, dh, ffn, vocab, 1e-5, 10000.0, B.BF16 if dtype == "bf16" else B.F32, 16, max_window,
+                         max_positions, path, kv_heads)
+        w = B.Weights()
+        dummy = self.memory(4096)
+        for name in ("embed", "final_norm", "lm_head"):
+            setattr(w, name, dummy)
+        for name in B._PER_LAYER:
+            arr = (C.c_void_p * layers)(*[dummy] * layers)
+            self.keep.append(arr)
+            setattr(w, name, C.cast(arr, C.POINTER(C.c_void_p)))
+        n = self.L.anpd_model_workspace_bytes(C.byref(cfg))
+        self.ws, self.ws_bytes, self.model, self.vocab = self.memory(n), n, C.c_void_p(), vocab
+        self.ok(self.L.anpd_model_create(C.byref(cfg), C.byref(w), self.ws, n, None, C.byref(self.model)))
+
+    def memory(self, n, device=0, offset=0):
+        """Address of n bytes of "device" memory, 256-byte aligned plus offset; exactly those are known as such."""
+        buf = C.create_string_buffer(n + 512 + offset)
+        self.keep.append(buf)
+        at = (C.addressof(buf) + 255) // 256 * 256
+        self.stub.stub_memory(at, n + offset, device)
+        return at + offset
+
+    def ok(self, rc):
+        assert rc >= 0, (rc, self.L.anpd_last_error())
+
+    def cache(self, max_tokens, length=0):
+        n = self.L.anpd_kv_pool_bytes(self.model, max_tokens)
+        kv, pool = C.c_void_p(), self.memory(n)
+        self.ok(self.L.anpd_kv_create(self.model, pool, n, max_tokens, C.byref(kv)))
+        self.ok(self.L.anpd_kv_truncate(kv, length, None))
+        return kv
+
+    def names(self):
+        return [self.stub.stub_name(i).decode() for i in range(self.stub.stub_launches())]
+
+    def logits_of_argmax(self):
+        """Where the last argmax kernel reads the logits, that is, where the LM head wrote them."""
+        at = [i for i, n in enumerate(self.names()) if "argmax_accept" in n][-1]
+        return self.stub.stub_arg0(at)
+
+    def verify(self, kv, n, out):
+        acc, nxt = C.c_int32(), C.c_int32()
+        return self.L.anpd_verify(self.model, kv, (C.c_int32 * n)(*range(n)), n, self.B.APPEND, C.byref(acc), C.byref(nxt), None, out, None)
+
+    def prefill(self, kv, n, out=None):
+        nxt = C.c_int32()
+        nb = self.L.anpd_prefill_workspace_bytes(self.model, n)
+        return self.L.anpd_prefill(self.model, kv, (C.c_int32 * n)(*[i % self.vocab for i in range(n)]), n, C.byref(nxt), out,
+                                   self.memory(nb) if nb else None, nb, None)
+
+
+def child_logits(dtype, path):
+    h = Host(dtype=dtype, path=int(path))
+    kv = h.cache(256)
+    own = lambda p: h.ws <= p < h.ws + h.ws_bytes
+    for call, rows, size in ((lambda out: h.verify(kv, 20, out), 20, 20 * 512 * 4), (lambda out: h.prefill(kv, 33, out), 1, 512 * 4)):
+        h.ok(h.L.anpd_kv_truncate(kv, 0, None))
+        direct = h.memory(size)
+        h.ok(call(direct))
+        if int(path) == h.B.GEMM_MFMA_LAUNCHES or rows > 1:   # (a prompt on the generic path copies its last row)
+            assert h.logits_of_argmax() == direct
+        for other in (h.memory(size, offset=4), h.memory(size, device=1)):    # not for wide stores; another GPU's
+            h.ok(h.L.anpd_kv_truncate(kv, 0, None))
+            h.ok(call(other))
+            assert own(h.logits_of_argmax())
+        # memory that ends before the logits do: nothing may be written past its end, the copy says so
+        h.ok(h.L.anpd_kv_truncate(kv, 0, None))
+        assert call(h.memory(size - 4)) == h.B.E_HIP
+        assert own(h.logits_of_argmax())
+        h.stub.hipGetLastError()    # (the copy's error, which stays until it is read)
+
+
+@pytest.mark.parametrize("dtype,path", [("bf16", 4), ("bf16", 1), ("f32", 0)])
+def test_logits_go_straight_to_a_buffer_that_holds_them_only(stub, dtype, path):
+    in_child(stub, "child_logits", dtype, path)
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[1]](*sys.argv[2:])
