@@ -1581,26 +1581,40 @@ int32_t anpd_prefill(anpd_model_t *m, anpd_kv_t *kv, const int32_t *tokens, int3
     if (!m->mfma) {
         // models on the caller's weights: the prompt goes through the step in windows of max_window appended rows, all
         // enqueued before the first is waited for; logits and prediction of the last row only
-        int32_t rc = ensure_pages(kv, kv->len + n_tokens, st);
-        if (rc != ANPD_OK) return rc;
-        float *logits = (float *)(m->ws + m->lay.logits);
-        int last_n = 0;
-        for (int i = 0; i < n_tokens; i += last_n) {
-            last_n = n_tokens - i < m->cfg.max_window ? n_tokens - i : m->cfg.max_window;
-            const bool more = i + last_n < n_tokens;
-            const StepTokens tok = step_tokens(tokens + i, last_n);
-            rc = m->cfg.dtype == ANPD_BF16 ? run_step_generic<bf16_t>(m, kv, tok, last_n, ANPD_APPEND, logits, st, false, more)
-                                           : run_step_generic<float>(m, kv, tok, last_n, ANPD_APPEND, logits, st, false, more);
+        const int32_t len0 = kv->len;
+        auto windows = [&]() -> int32_t {
+            int32_t rc = ensure_pages(kv, len0 + n_tokens, st);
             if (rc != ANPD_OK) return rc;
-            kv->len += last_n;
-            if (m->prof) {
-                HIP_TRY(hipStreamSynchronize(st));
-                collect_marks(m);
+            float *logits = (float *)(m->ws + m->lay.logits);
+            int last_n = 0;
+            for (int i = 0; i < n_tokens; i += last_n) {
+                last_n = n_tokens - i < m->cfg.max_window ? n_tokens - i : m->cfg.max_window;
+                const bool more = i + last_n < n_tokens;
+                const StepTokens tok = step_tokens(tokens + i, last_n);
+                rc = m->cfg.dtype == ANPD_BF16 ? run_step_generic<bf16_t>(m, kv, tok, last_n, ANPD_APPEND, logits, st, false, more)
+                                               : run_step_generic<float>(m, kv, tok, last_n, ANPD_APPEND, logits, st, false, more);
+                if (rc != ANPD_OK) return rc;
+                kv->len += last_n;
+                if (m->prof) {
+                    HIP_TRY(hipStreamSynchronize(st));
+                    collect_marks(m);
+                }
             }
+            if (out_logits)
+                HIP_TRY(hipMemcpyAsync(out_logits, logits + (size_t)(last_n - 1) * V, V * sizeof(float), hipMemcpyDeviceToDevice, st));
+            HIP_TRY(hipStreamSynchronize(st));
+            return ANPD_OK;
+        };
+        if (const int32_t rc = windows(); rc != ANPD_OK) {
+            // some windows may have run, some not: the cache is what it was, on the host and on the device
+            (void)hipStreamSynchronize(st);
+            kv->len = len0;
+            kv->pin[0] = len0;
+            (void)hipMemcpyAsync(kv->d_len, kv->pin, sizeof(int32_t), hipMemcpyHostToDevice, st);
+            (void)hipStreamSynchronize(st);
+            release_pages(kv, len0);
+            return rc;
         }
-        if (out_logits)
-            HIP_TRY(hipMemcpyAsync(out_logits, logits + (size_t)(last_n - 1) * V, V * sizeof(float), hipMemcpyDeviceToDevice, st));
-        HIP_TRY(hipStreamSynchronize(st));
         *out_next = m->pin[33];
         return ANPD_OK;
     }

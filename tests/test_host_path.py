@@ -38,7 +38,7 @@ class Host:
         self.stub.stub_arg0.argtypes = [C.c_int]
         self.stub.stub_memory.argtypes = [C.c_void_p, C.c_size_t, C.c_int]
         from paper_2404_08698_amd import binding as B
-        self.B, self.L, self.keep = B, B.lib(), []
+        self.B, self.L, self.keep, self.length_at = B, B.lib(), [], {}
         cfg = B.ModelCfg(layers, d, heads, dh, ffn, vocab, 1e-5, 10000.0, B.BF16 if dtype == "bf16" else B.F32, 16, max_window,
                          max_positions, path, kv_heads)
         w = B.Weights()
@@ -69,6 +69,9 @@ class Host:
         kv, pool = C.c_void_p(), self.memory(n)
         self.ok(self.L.anpd_kv_create(self.model, pool, n, max_tokens, C.byref(kv)))
         self.ok(self.L.anpd_kv_truncate(kv, length, None))
+        # the length lies behind the pages, which end at a multiple of 256 bytes; so does the page table behind it
+        pages = self.L.anpd_kv_num_pages(kv)
+        self.length_at[kv.value] = pool + n - ((pages + 1) * 4 + 255) // 256 * 256
         return kv
 
     def names(self):
@@ -114,6 +117,37 @@ def child_logits(dtype, path):
 @pytest.mark.parametrize("dtype,path", [("bf16", 4), ("bf16", 1), ("f32", 0)])
 def test_logits_go_straight_to_a_buffer_that_holds_them_only(stub, dtype, path):
     in_child(stub, "child_logits", dtype, path)
+
+
+def child_failing_prompt(dtype, path):
+    """Every launch of a prompt of three windows fails once; the copy of its logits fails, too."""
+    h = Host(dtype=dtype, path=int(path), max_window=16)
+    kv = h.cache(256, 20)
+    d_len = C.c_int32.from_address(h.length_at[kv.value])
+
+    def unchanged():
+        h.stub.hipGetLastError()
+        assert h.L.anpd_kv_length(kv) == 20 and d_len.value == 20
+    h.stub.stub_forget()
+    h.ok(h.prefill(kv, 40))
+    launches = h.stub.stub_launches()
+    assert sum("embed_kernel" in n for n in h.names()) == 3 and h.L.anpd_kv_length(kv) == 60
+    for nth in range(1, launches + 1):
+        h.ok(h.L.anpd_kv_truncate(kv, 20, None))
+        d_len.value = 36        # as the first window leaves it (the stand-in runs no kernel)
+        h.stub.stub_fail_launch(nth)
+        assert h.prefill(kv, 40) == h.B.E_HIP
+        unchanged()
+    d_len.value = 60
+    assert h.prefill(kv, 40, h.memory(512 * 4 - 4)) == h.B.E_HIP
+    unchanged()
+    h.ok(h.prefill(kv, 40))
+    assert h.L.anpd_kv_length(kv) == 60
+
+
+@pytest.mark.parametrize("dtype,path", [("f32", 0), ("bf16", 1)])
+def test_a_prompt_in_windows_that_fails_half_way_leaves_the_cache_as_it_was(stub, dtype, path):
+    in_child(stub, "child_failing_prompt", dtype, path)
 
 
 if __name__ == "__main__":
