@@ -1503,6 +1503,7 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
     SeqRef *seqs = (SeqRef *)(m->pin + 512);
     BatchLaunch bl = {n_seq, 0, false};
     int row = 0;
+    long long pages = 0, longest = 0;   // that one wave of attn_decode_kernel goes through: of all sequences, of the longest
     for (int s = 0; s < n_seq; ++s) {
         anpd_kv *kv = kvs[s];
         seqs[s].pool = (bf16_t *)kv->pool;
@@ -1512,6 +1513,9 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
         seqs[s].n_rows = n_windows[s];
         const int splits = n_splits_of(kv->len + n_windows[s]);
         if (splits > bl.grid_splits) bl.grid_splits = splits;
+        const long long walk = kv->len / (16 * kFastWaves) + 1;
+        pages += walk;
+        if (walk > longest) longest = walk;
         for (int i = 0; i < n_windows[s]; ++i, ++row) {
             m->pin[row] = windows[s][i];
             row_seq[row] = s;
@@ -1519,10 +1523,19 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
     }
     // One row per sequence: one block per (head, sequence) once those fill the chip (two fit a compute unit), with a
     // margin where the sequences are long and a half-empty last round costs more (7B shape, 4 layers, us per step, cut
-    // into splits -> not cut: 500 positions, 10 / 16 / 18 / 32 sequences 597 -> 608, 675 -> 659, 760 -> 750, 1722 -> 1612 (8
-    // layers); 2500 positions, 10 / 16 / 18 / 24 / 32 sequences 854 -> 958, 1103 -> 1126, 1236 -> 1267, 1491 -> 1476, 1778 -> 1744)
-    bl.decode = total == n_seq && bl.grid_splits <= kDecodeSplits &&
-                (long long)n_seq * m->cfg.n_heads >= (bl.grid_splits <= kSmallSplits ? 2 : 3) * m->n_cu;
+    // into splits -> not cut: 500 positions, 10 / 16 / 18 / 32 sequences 597 -> 608, 675 -> 659, 760 -> 750, 917 -> 843;
+    // 2500 positions, 10 / 16 / 18 / 24 / 32 sequences 854 -> 958, 1103 -> 1126, 1236 -> 1267, 1491 -> 1476, 1778 -> 1744;
+    // 13B shape, 13 sequences, a second round of 8 blocks: 500 positions 874 -> 871, 1000 positions 991 -> 1003)
+    // - unless one long sequence would be walked alone, by eight waves a page after the other, while the chip has nothing
+    // else to do: the pages per slot (two a compute unit) have to be at least 2/3 of the longest walk, half of it where
+    // query heads share keys and values, whose pages then come from L2.  Beside 100-position sequences, 7B shape: 31 +
+    // one of 4000 834 -> 956, 23 + one 779 -> 928, 28 + 4 of 4000 969 -> 1006, 9 + 9 of 1000 788 -> 821 (below the
+    // line); 24 + 8 of 1000 858 -> 842, 24 of 300 + 8 of 3000 1164 -> 1135, 100 to 4000 in equal steps, 24 / 32
+    // sequences 1333 -> 1357, 1575 -> 1565 (above it); ChatGLM3 shape: 31 + one of 4000 868 -> 993, 28 + 4 of 1000 847 -> 849
+    // (below), 24 + 8 of 3000 1010 -> 965, 100 to 4000 1337 -> 1203 (above).
+    const bool filled = (long long)n_seq * m->cfg.n_heads >= (bl.grid_splits <= kSmallSplits ? 2 : 3) * m->n_cu;
+    const bool even = 3 * pages * m->cfg.n_heads >= (kv_heads_of(m->cfg) < m->cfg.n_heads ? 3 : 4) * longest * m->n_cu;
+    bl.decode = total == n_seq && bl.grid_splits <= kDecodeSplits && filled && even;
     // At most 8 rows in all (decoding batches, short windows): the persistent kernel takes the sequences by
     // value and writes the results into the pinned buffer itself; otherwise copies and the fused launches.
     const bool one_kernel = m->mega && m->mega_batch && total <= 8;

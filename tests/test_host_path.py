@@ -150,5 +150,32 @@ def test_a_prompt_in_windows_that_fails_half_way_leaves_the_cache_as_it_was(stub
     in_child(stub, "child_failing_prompt", dtype, path)
 
 
+def child_route(lengths, heads, kv_heads, dh, expected):
+    lengths, heads, dh = [int(x) for x in lengths.split(",")], int(heads), int(dh)
+    h = Host(d=heads * dh, heads=heads, dh=dh, kv_heads=int(kv_heads), max_positions=4200)
+    n = len(lengths)
+    kvs = [h.cache(x + 8, x) for x in lengths]
+    one = C.POINTER(C.c_int32)
+    rows = [(C.c_int32 * 1)(i) for i in range(n)]
+    h.stub.stub_forget()
+    h.ok(h.L.anpd_verify_batch(h.model, (C.c_void_p * n)(*kvs), n, (one * n)(*[C.cast(r, one) for r in rows]), (C.c_int32 * n)(*[1] * n),
+                               h.B.VERIFY, (C.c_int32 * n)(), (C.c_int32 * n)(), None, None))
+    taken = {k for k in ("attn_decode", "attn_batch", "verify_mega") if any(k in name for name in h.names())}
+    assert taken == {expected}, taken
+
+
+# heads, key / value heads, cached tokens: enough blocks, too few, one long sequence among short ones, in between
+@pytest.mark.parametrize("heads,kv_heads,lengths,route", [
+    (32, 32, [500] * 16, "attn_decode"), (32, 32, [500] * 15, "attn_batch"), (40, 40, [500] * 13, "attn_decode"),
+    (32, 32, [1023] * 32, "attn_decode"), (32, 4, [2500] * 24, "attn_decode"), (32, 4, [2500] * 23, "attn_batch"),
+    (32, 4, [4095] * 24, "attn_decode"), (32, 4, [4095] * 23 + [4096], "attn_batch"), (32, 32, [500] * 8, "verify_mega"),
+    (32, 32, [100] * 31 + [4000], "attn_batch"), (32, 32, [100] * 31 + [1000], "attn_batch"), (32, 4, [100] * 31 + [4000], "attn_batch"),
+    (32, 32, [100] * 9 + [1000] * 9, "attn_batch"), (32, 32, [100] * 24 + [1000] * 8, "attn_decode"),
+    (32, 4, [100] * 24 + [3000] * 8, "attn_decode"), (32, 32, [307 + 13 * i for i in range(32)], "attn_decode"),
+])
+def test_attention_kernel_of_a_batch_of_one_row_windows(stub, heads, kv_heads, lengths, route):
+    in_child(stub, "child_route", ",".join(map(str, lengths)), heads, kv_heads, 64, route)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](*sys.argv[2:])
