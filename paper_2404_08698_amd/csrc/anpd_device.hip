@@ -221,6 +221,27 @@ int32_t launch_gen(const GenArgs &a, int n_blocks, hipStream_t st)
     return ANPD_OK;
 }
 
+// anpd_linear on row-major weights.  bf16, a few rows and blocks enough: many blocks side by side beat many loads per
+// wave, whose last round of blocks is nearly empty; up to two rows (48 KB: LDS for two or three blocks) are kept in LDS.
+// us, otherwise -> as chosen: 22016 x 4096, 1 / 2 / 3 / 4 rows 52.0 -> 42.4, 51.7 -> 44.2, 52.9 -> 48.8, 55.2 -> 52.8 (8
+// rows 61.2 -> 62.6: not chosen); 27648 x 5120 75.4 -> 58.3, 77.9 -> 64.2, 80.8 -> 75.9, 83.3 -> 80.7; 8192 x 4096, two blocks per
+// compute unit, 1 row 18.9 -> 18.2 (4096 x 4096, one block: 11.7 either way); 16384 x 1024 13.2 -> 9.3.
+int32_t launch_linear_gen(const GenArgs &a, int N, int dtype, hipStream_t st)
+{
+    if (dtype != ANPD_BF16) return launch_gen<float, GEN_PLAIN>(a, N / 16, st);
+    int dev = 0, n_cu = 256;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) (void)hipGetLastError();
+    const dim3 grid((unsigned)(N / 16)), block(512);
+    if (a.M <= 2 && a.M * a.K <= 12288 && N / 16 >= 2 * n_cu)
+        hipLaunchKernelGGL((gemm_gen_kernel<bf16_t, GEN_PLAIN, 1, FEW_ROWS_LDS>), grid, block, (size_t)a.M * a.K * sizeof(float), st, a);
+    else if (a.M <= 4 && N / 16 >= 3 * n_cu)
+        hipLaunchKernelGGL((gemm_gen_kernel<bf16_t, GEN_PLAIN, 1, FEW_ROWS>), grid, block, 0, st, a);
+    else
+        return launch_gen<bf16_t, GEN_PLAIN>(a, N / 16, st);
+    HIP_TRY(hipGetLastError());
+    return ANPD_OK;
+}
+
 // ---- fast path: packed MFMA GEMMs ---------------------------------------------
 
 template <int T, int D, int EPI>
@@ -1692,7 +1713,7 @@ int32_t anpd_linear(const float *X, const void *W, float *Y, int32_t M, int32_t 
         g.W0 = W;
         g.Y = Y;
         g.ldy = N;
-        return dtype == ANPD_BF16 ? launch_gen<bf16_t, GEN_PLAIN>(g, N / 16, st) : launch_gen<float, GEN_PLAIN>(g, N / 16, st);
+        return launch_linear_gen(g, N, dtype, st);
     }
     if (path != ANPD_GEMM_MFMA && path != ANPD_GEMM_MFMA_STREAM)
         return fail(ANPD_E_INVAL, "anpd_linear: unknown path %d", path);

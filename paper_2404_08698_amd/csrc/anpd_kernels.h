@@ -325,12 +325,18 @@ struct Raw8<bf16_t> {
     }
 };
 
+// FEW: forms for a few rows of bf16 weights and blocks for several rounds of the chip, one chunk in flight per wave and
+// four blocks per compute unit instead of three chunks and two.  FEW_ROWS_LDS keeps the window's rows in LDS: read from
+// memory they are two thirds of a wave's loads, and return behind the weights.  See launch_linear_gen.  An element's sums are the same.
 // grid: (features / 16, or pairs of 16; ceil(M / (16 RT)))
-template <typename WT, int MODE, int RT>
-__global__ __launch_bounds__(512, sizeof(WT) == 2 && RT == 1 ? 4 : 2) void gemm_gen_kernel(GenArgs a)
+enum { FEW_NO = 0, FEW_ROWS = 1, FEW_ROWS_LDS = 2 };
+template <typename WT, int MODE, int RT, int FEW = FEW_NO>
+__global__ __launch_bounds__(512, FEW ? 8 : (sizeof(WT) == 2 && RT == 1 ? 4 : 2)) void gemm_gen_kernel(GenArgs a)
 {
     constexpr int NW = gen_pairs(MODE) ? 2 : 1, S = sizeof(WT) == 2 ? 2 : 1, WAVES = 8,
-                  U = S == 2 && (NW == 2 || RT == 2) ? 2 : 3;   // chunks in flight: what two blocks per compute unit have registers for
+                  U = FEW ? 1 : (S == 2 && (NW == 2 || RT == 2) ? 2 : 3);   // chunks in flight: what the blocks of a compute unit have registers for
+    static_assert(FEW != FEW_ROWS_LDS || (RT == 1 && U == 1), "one row tile, one chunk at a time");
+    extern __shared__ float x_lds[];   // FEW_ROWS_LDS: [M][K]
     constexpr bool NORM = gen_norm(MODE);
     __shared__ float red[WAVES][NW][RT][64][4];
     __shared__ float ssq[WAVES][RT][16];
@@ -381,6 +387,10 @@ __global__ __launch_bounds__(512, sizeof(WT) == 2 && RT == 1 ? 4 : 2) void gemm_
 #pragma unroll
             for (int q = 0; q < NA; ++q) acc[q][n][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
+    if (FEW == FEW_ROWS_LDS) {
+        for (int i = 4 * (int)threadIdx.x; i < a.M * K; i += 4 * 512) *reinterpret_cast<float4 *>(x_lds + i) = *reinterpret_cast<const float4 *>(a.X + i);
+        __syncthreads();
+    }
     for (int c0 = wave; c0 * 32 * S < K; c0 += WAVES * U) {
         Raw8<WT> wv[U][S][NW];
         Raw8<WT> gv[U][S];
@@ -402,7 +412,7 @@ __global__ __launch_bounds__(512, sizeof(WT) == 2 && RT == 1 ? 4 : 2) void gemm_
                     for (int n = 0; n < NW; ++n) wv[u][s][n].load(w[n] + k);
 #pragma unroll
                     for (int t = 0; t < RT; ++t)
-                        if (m0 + 16 * t + r < a.M) load8(a.X + (size_t)(m0 + 16 * t + r) * K + k, xv[u][s][t]);
+                        if (m0 + 16 * t + r < a.M) load8((FEW == FEW_ROWS_LDS ? x_lds : a.X) + (size_t)(m0 + 16 * t + r) * K + k, xv[u][s][t]);
                     if (NORM) gv[u][s].load(gain + k);
                 }
             }

@@ -73,3 +73,15 @@ def test_prompt_windows_leave_what_one_window_at_a_time_leaves():
             assert torch.equal(x, y)
     win = synth.random_tokens(shape.vocab, 5, 77)     # the device's length followed
     assert B.verify(model, a, win, want_predicts=True) == B.verify(model, b, win, want_predicts=True)
+
+
+# bf16, a few rows, two and three blocks per compute unit (of 256): K of a partial chunk and of several turns of the
+# waves, the longest rows that are kept in LDS (12288 floats) and one piece more
+@pytest.mark.parametrize("n,k", [(8192, 8), (8192, 776), (8192, 4096), (12288, 264), (12288, 4104), (12288, 6144), (12288, 6152), (8192, 12288)])
+def test_linear_of_a_few_rows_has_the_bits_of_sixteen(n, k):
+    g = torch.Generator(device="cuda").manual_seed(n + k)
+    x = torch.randn(16, k, generator=g, device="cuda")
+    w = torch.randn(n, k, generator=g, device="cuda").to(torch.bfloat16)
+    y = B.linear(x, w, B.GEMM_DOT)
+    for m in (1, 2, 3, 4, 5):
+        assert torch.equal(y[:m], B.linear(x[:m].contiguous(), w, B.GEMM_DOT)), m
