@@ -221,25 +221,35 @@ int32_t launch_gen(const GenArgs &a, int n_blocks, hipStream_t st)
     return ANPD_OK;
 }
 
-// anpd_linear on row-major weights.  bf16, a few rows and blocks enough: many blocks side by side beat many loads per
-// wave, whose last round of blocks is nearly empty; up to two rows (48 KB: LDS for two or three blocks) are kept in LDS.
-// us, otherwise -> as chosen: 22016 x 4096, 1 / 2 / 3 / 4 rows 52.0 -> 42.4, 51.7 -> 44.2, 52.9 -> 48.8, 55.2 -> 52.8 (8
-// rows 61.2 -> 62.6: not chosen); 27648 x 5120 75.4 -> 58.3, 77.9 -> 64.2, 80.8 -> 75.9, 83.3 -> 80.7; 8192 x 4096, two blocks per
-// compute unit, 1 row 18.9 -> 18.2 (4096 x 4096, one block: 11.7 either way); 16384 x 1024 13.2 -> 9.3.
-int32_t launch_linear_gen(const GenArgs &a, int N, int dtype, hipStream_t st)
+// The same for what pays with a few rows: anpd_linear, LM head, O and down.  bf16, a few rows and blocks enough: many blocks
+// side by side beat many loads per wave, whose last round of blocks is nearly empty; up to two rows (48 KB: LDS for two
+// or three blocks) are kept in LDS.  us, otherwise -> as chosen: 22016 x 4096, 1 / 2 / 3 / 4 rows 52.0 -> 42.4, 51.7 -> 44.2,
+// 52.9 -> 48.8, 55.2 -> 52.8 (8 rows 61.2 -> 62.6: not chosen); 27648 x 5120 75.4 -> 58.3, 77.9 -> 64.2, 80.8 -> 75.9, 83.3 -> 80.7;
+// 8192 x 4096, two blocks per compute unit, 1 row 18.9 -> 18.2 (4096 x 4096, one block: 11.7 either way); 16384 x 1024
+// 13.2 -> 9.3; LM head of the 7B, 13B and ChatGLM3 shapes, 1 row 75 -> 66, 92 -> 80, 141 -> 121, 4 rows 80 -> 76, 101 -> 99, 152 -> 143
+// (the gate / up pairs lose by it: 7B, 1 row, 53 -> 62).  O and down: rows in LDS where more than one block per compute
+// unit reads them: 13B, 1 row, O 27.0 -> 25.4, down 54.9 -> 50.3 (7B, one block per compute unit, O 15.8 -> 16.8: not chosen).
+template <typename WT, int MODE>
+int32_t launch_gen_few(const GenArgs &a, int n_blocks, int n_cu, hipStream_t st)
 {
-    if (dtype != ANPD_BF16) return launch_gen<float, GEN_PLAIN>(a, N / 16, st);
-    int dev = 0, n_cu = 256;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) (void)hipGetLastError();
-    const dim3 grid((unsigned)(N / 16)), block(512);
-    if (a.M <= 2 && a.M * a.K <= 12288 && N / 16 >= 2 * n_cu)
-        hipLaunchKernelGGL((gemm_gen_kernel<bf16_t, GEN_PLAIN, 1, FEW_ROWS_LDS>), grid, block, (size_t)a.M * a.K * sizeof(float), st, a);
-    else if (a.M <= 4 && N / 16 >= 3 * n_cu)
-        hipLaunchKernelGGL((gemm_gen_kernel<bf16_t, GEN_PLAIN, 1, FEW_ROWS>), grid, block, 0, st, a);
-    else
-        return launch_gen<bf16_t, GEN_PLAIN>(a, N / 16, st);
-    HIP_TRY(hipGetLastError());
-    return ANPD_OK;
+    if constexpr (sizeof(WT) == 2) {
+        constexpr bool res = MODE == GEN_RESIDUAL;
+        const dim3 grid((unsigned)n_blocks), block(512);
+        // (55 KB and the 8.5 KB in which the sums meet: within the 64 KB that need no attribute)
+        if (a.M <= 2 && a.M * a.K <= (res ? 14080 : 12288) && (res ? n_blocks > n_cu : n_blocks >= 2 * n_cu)) {
+            hipLaunchKernelGGL((gemm_gen_kernel<WT, MODE, 1, FEW_ROWS_LDS>), grid, block, (size_t)a.M * a.K * sizeof(float), st, a);
+            HIP_TRY(hipGetLastError());
+            return ANPD_OK;
+        }
+        if constexpr (!res) {
+            if (a.M <= 4 && n_blocks >= 3 * n_cu) {
+                hipLaunchKernelGGL((gemm_gen_kernel<WT, MODE, 1, FEW_ROWS>), grid, block, 0, st, a);
+                HIP_TRY(hipGetLastError());
+                return ANPD_OK;
+            }
+        }
+    }
+    return launch_gen<WT, MODE>(a, n_blocks, st);
 }
 
 // ---- fast path: packed MFMA GEMMs ---------------------------------------------
@@ -511,7 +521,7 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int 
             hipLaunchKernelGGL((attn_kernel<KT, 64>), grid, dim3(256), 0, st, q, d, pool, kv->d_table, kv->d_len, M, l, c.n_layers, H, Hkv,
                                c.page_tokens, c.max_window, L.max_splits, scale, part, attn_ctr, att, t_mask);
         mark(m, ANPD_PROF_ATTN, st);
-        if ((rc = launch_gen<KT, GEN_RESIDUAL>(gemm(att, d, m->wo[l], nullptr, x, d), d / 16, st)) != ANPD_OK) return rc;
+        if ((rc = launch_gen_few<KT, GEN_RESIDUAL>(gemm(att, d, m->wo[l], nullptr, x, d), d / 16, m->n_cu, st)) != ANPD_OK) return rc;
         mark(m, ANPD_PROF_GEMM_O, st);
         {
             GenArgs g = gemm(x, d, m->w_gate[l], m->ffn_norm[l], act, F);
@@ -519,7 +529,7 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int 
             if ((rc = launch_gen<KT, GEN_GATE_UP>(g, F / 16, st)) != ANPD_OK) return rc;
         }
         mark(m, ANPD_PROF_GEMM_GATE_UP, st);
-        if ((rc = launch_gen<KT, GEN_RESIDUAL>(gemm(act, F, m->w_down[l], nullptr, x, d), d / 16, st)) != ANPD_OK) return rc;
+        if ((rc = launch_gen_few<KT, GEN_RESIDUAL>(gemm(act, F, m->w_down[l], nullptr, x, d), d / 16, m->n_cu, st)) != ANPD_OK) return rc;
         mark(m, ANPD_PROF_GEMM_DOWN, st);
     }
     if (cache_only) {
@@ -528,7 +538,7 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int 
         HIP_TRY(hipGetLastError());
         return ANPD_OK;
     }
-    if ((rc = launch_gen<KT, GEN_LOGITS>(gemm(x, d, m->lm_head, m->final_norm, logits, V), V / 16, st)) != ANPD_OK) return rc;
+    if ((rc = launch_gen_few<KT, GEN_LOGITS>(gemm(x, d, m->lm_head, m->final_norm, logits, V), V / 16, m->n_cu, st)) != ANPD_OK) return rc;
     mark(m, ANPD_PROF_GEMM_LM_HEAD, st);
     hipLaunchKernelGGL(argmax_accept_kernel, dim3(M), dim3(1024), 0, st, logits, V, M, tok, mode, result, m->pin_dev + 32, kv->d_len,
                        counter);
@@ -1713,7 +1723,9 @@ int32_t anpd_linear(const float *X, const void *W, float *Y, int32_t M, int32_t 
         g.W0 = W;
         g.Y = Y;
         g.ldy = N;
-        return launch_linear_gen(g, N, dtype, st);
+        int dev = 0, n_cu = 256;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) (void)hipGetLastError();
+        return dtype == ANPD_BF16 ? launch_gen_few<bf16_t, GEN_PLAIN>(g, N / 16, n_cu, st) : launch_gen<float, GEN_PLAIN>(g, N / 16, st);
     }
     if (path != ANPD_GEMM_MFMA && path != ANPD_GEMM_MFMA_STREAM)
         return fail(ANPD_E_INVAL, "anpd_linear: unknown path %d", path);

@@ -326,16 +326,20 @@ struct Raw8<bf16_t> {
 };
 
 // FEW: forms for a few rows of bf16 weights and blocks for several rounds of the chip, one chunk in flight per wave and
-// four blocks per compute unit instead of three chunks and two.  FEW_ROWS_LDS keeps the window's rows in LDS: read from
-// memory they are two thirds of a wave's loads, and return behind the weights.  See launch_linear_gen.  An element's sums are the same.
+// three or four blocks per compute unit instead of several chunks and two.  FEW_ROWS_LDS keeps the window's rows in LDS: read
+// from memory they are two thirds of a wave's loads, and return behind the weights.  See launch_gen_few.  (O and down, of
+// one or two blocks per compute unit, take the rows in LDS only and keep their chunks.)
+// Chunks in flight otherwise: what the blocks of a compute unit have registers for.  (One more in the bf16 LM head and
+// QKV spills 21 and 32 registers: LM head of the 7B, 13B and ChatGLM3 shapes, 1 row, 129 -> 75, 162 -> 92, 247 -> 141 us;
+// two layers' QKV 82 -> 74, 103 -> 92, 50 -> 48.)   An element's sums are the same in all forms.
 // grid: (features / 16, or pairs of 16; ceil(M / (16 RT)))
 enum { FEW_NO = 0, FEW_ROWS = 1, FEW_ROWS_LDS = 2 };
 template <typename WT, int MODE, int RT, int FEW = FEW_NO>
-__global__ __launch_bounds__(512, FEW ? 8 : (sizeof(WT) == 2 && RT == 1 ? 4 : 2)) void gemm_gen_kernel(GenArgs a)
+__global__ __launch_bounds__(512, FEW && MODE != GEN_RESIDUAL ? (gen_norm(MODE) ? 6 : 8) : (sizeof(WT) == 2 && RT == 1 ? 4 : 2)) void gemm_gen_kernel(GenArgs a)
 {
     constexpr int NW = gen_pairs(MODE) ? 2 : 1, S = sizeof(WT) == 2 ? 2 : 1, WAVES = 8,
-                  U = FEW ? 1 : (S == 2 && (NW == 2 || RT == 2) ? 2 : 3);   // chunks in flight: what the blocks of a compute unit have registers for
-    static_assert(FEW != FEW_ROWS_LDS || (RT == 1 && U == 1), "one row tile, one chunk at a time");
+                  U = (FEW && MODE != GEN_RESIDUAL) || (S == 2 && RT == 1 && MODE == GEN_QKV) ? 1 : (S == 2 && (NW == 2 || RT == 2 || MODE == GEN_LOGITS) ? 2 : 3);
+    static_assert(FEW == FEW_NO || RT == 1, "one row tile");
     extern __shared__ float x_lds[];   // FEW_ROWS_LDS: [M][K]
     constexpr bool NORM = gen_norm(MODE);
     __shared__ float red[WAVES][NW][RT][64][4];

@@ -85,3 +85,21 @@ def test_linear_of_a_few_rows_has_the_bits_of_sixteen(n, k):
     y = B.linear(x, w, B.GEMM_DOT)
     for m in (1, 2, 3, 4, 5):
         assert torch.equal(y[:m], B.linear(x[:m].contiguous(), w, B.GEMM_DOT)), m
+
+
+# bf16 weights: LM heads of two and three blocks per compute unit (of 256); O and down of just over one, K of down up to
+# what one row and not two may take in LDS, and beyond it
+@pytest.mark.parametrize("shape", [dataclasses.replace(synth.MID_GQA, vocab=8192), dataclasses.replace(synth.MID_GQA, vocab=12288),
+                                   synth.ModelShape(1, 4224, 33, 128, 7056, 512, "bf16", n_kv_heads=3),
+                                   synth.ModelShape(1, 4224, 33, 128, 14080, 512, "bf16", n_kv_heads=3),
+                                   synth.ModelShape(1, 4224, 33, 128, 14096, 512, "bf16", n_kv_heads=3)], ids=lambda s: "%dx%dx%d" % (s.d_model, s.d_ffn, s.vocab))
+def test_windows_of_a_few_rows_have_the_bits_of_sixteen(shape):
+    model = B.Model(shape, synth.make_weights(shape, 5, device="cuda"), max_window=16, max_positions=128, gemm_path=B.GEMM_DOT)
+    kv = B.KVCache(model, 128)
+    win = synth.random_tokens(shape.vocab, 16, 3)
+    rows = {}
+    for n in (16, 5, 4, 3, 2, 1):
+        kv.truncate(0)
+        rows[n] = torch.empty(n, shape.vocab, dtype=torch.float32, device="cuda")
+        B.verify(model, kv, win[:n], B.APPEND, out_logits=rows[n])
+        assert torch.equal(rows[n], rows[16][:n]), n
