@@ -10,6 +10,15 @@ pytestmark = pytest.mark.gpu
 
 MHA = synth.ModelShape(2, 2048, 32, 64, 512, 1024, "bf16")
 GQA = synth.ModelShape(2, 4096, 32, 128, 512, 1024, "bf16", n_kv_heads=4)
+MHA128 = synth.ModelShape(1, 4096, 32, 128, 512, 1024, "bf16")
+
+# cached tokens of batches that the rule gives to the many-sequences kernel on 256 compute units, in both steps of _run
+# (test_host_path.py holds the rule to that): within the eight one-page splits, and beyond, where a wave goes through
+# three pages per split, up to the last of the sixteen splits
+SHORT = [0, 1, 15, 16, 17, 112, 127, 128, 129, 255, 300, 511, 512, 640, 700, 895, 896, 1000, 1022, 33, 897, 903, 1007, 1021]
+LONG = [1023, 1024, 1025, 1151, 1152, 1153, 1279, 1280, 1281, 1407, 1408, 1409, 5, 1791, 1792, 2000, 2175, 2176, 2560, 3000, 3327, 3328,
+        3711, 3712, 4093, 4094, 77]
+DECODE = [(MHA, SHORT), (MHA128, SHORT), (GQA, SHORT), (MHA, LONG), (GQA, LONG)]
 
 
 def _run(shape, lengths, max_positions):
@@ -40,14 +49,13 @@ def _run(shape, lengths, max_positions):
             assert torch.equal(row[0], logits[i]), (step, i, lengths[i])
 
 
-def test_short_sequences():
-    _run(MHA, [0, 1, 15, 16, 17, 112, 127, 128, 129, 255, 300, 511, 512, 640, 700, 895, 896, 1000, 1022, 33], 1100)
+@pytest.mark.parametrize("shape,lengths", DECODE, ids=["dh64-short", "dh128-short", "dh128_gqa-short", "dh64-long", "dh128_gqa-long"])
+def test_sequences_of_one_row(shape, lengths):
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256    # (or the rule may choose the other kernel)
+    _run(shape, lengths, 4200)
 
 
-def test_long_sequences():
-    _run(GQA, [1023, 1024, 1025, 1151, 1152, 1153, 1407, 1408, 1409, 2000, 5, 4094, 3000, 200, 900, 1300, 77], 4200)
-
-
-def test_sequences_past_the_kernels_splits_and_too_few_of_them():
+def test_sequences_past_the_kernels_splits_too_few_and_uneven_ones():
     _run(GQA, [4100, 20, 30, 40, 50, 60, 70, 80, 90, 100, 110, 120, 130, 140, 150, 160], 4200)
     _run(MHA, [100, 200, 300, 400, 500, 600, 700, 800, 900], 1100)
+    _run(GQA, [100] * 31 + [4000], 4200)    # (one long sequence outweighs the others)

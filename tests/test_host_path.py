@@ -177,5 +177,12 @@ def test_attention_kernel_of_a_batch_of_one_row_windows(stub, heads, kv_heads, l
     in_child(stub, "child_route", ",".join(map(str, lengths)), heads, kv_heads, 64, route)
 
 
+def test_the_batches_meant_for_the_many_sequences_kernel_take_it(stub):
+    import test_gpu_decode_batch as G
+    for shape, lengths in G.DECODE:
+        for step in (0, 1):
+            in_child(stub, "child_route", ",".join(str(x + step) for x in lengths), shape.n_heads, shape.kv_heads, shape.head_dim, "attn_decode")
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](*sys.argv[2:])
