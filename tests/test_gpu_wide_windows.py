@@ -8,14 +8,18 @@ from paper_2404_08698_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-# on 256 compute units: d 4096 / 5120 split O and down (8 and 10 waves per block; K of one, two and three buffers, an odd
-# number of k-steps in a class), gate / up of 5, 6, 7 and 11 tiles per block (passes of 6, 8 and 2 x 6 tiles), LM heads of
-# one tile per compute unit and of 9 (two passes)
+# on 256 compute units: d 4096 to 8192 split O and down (8, 9, 10, 12 and 16 waves per block, the last block of d 4224 with
+# three tiles for its nine waves; K of one, two and three buffers, an odd number of k-steps in a class); gate / up of one
+# tile per compute unit (ffn 1360 / 2048) and of 5, 6, 7 and 11 tiles per block (one pass of T = 6, 6 and 8, two of 6), LM heads of
+# one tile per compute unit or fewer, of 2, 9 and 16 per block (two passes of 5 and of 8)
 SHAPES = {
     "d4096": synth.ModelShape(1, 4096, 32, 128, 11008, 4096, "bf16"),
     "d4096_narrow": synth.ModelShape(1, 4096, 32, 128, 1360, 36864, "bf16", n_kv_heads=2),
+    "d4224": synth.ModelShape(1, 4224, 33, 128, 10000, 65024, "bf16", n_kv_heads=3),
     "d5120": synth.ModelShape(1, 5120, 40, 128, 13824, 8192, "bf16"),
     "d4096_wide": synth.ModelShape(1, 4096, 64, 64, 21776, 2048, "bf16"),
+    "d6144": synth.ModelShape(1, 6144, 48, 128, 2048, 1024, "bf16", n_kv_heads=4),
+    "d8192": synth.ModelShape(1, 8192, 64, 128, 2048, 1024, "bf16", n_kv_heads=4),
 }
 
 
@@ -42,7 +46,7 @@ def test_rows_of_a_wide_window(name):
     assert torch.equal(rows[32][16:], last)
 
 
-@pytest.mark.parametrize("n,k", [(4096, 11008), (16, 2048), (4096, 264), (5120, 5120), (22016, 4096), (27648, 5120), (36864, 2056)])
+@pytest.mark.parametrize("n,k", [(4096, 11008), (16, 2048), (4096, 264), (5120, 5120), (22016, 4096), (27648, 5120), (36864, 2056), (53248, 1024), (65024, 520)])
 def test_linear_of_17_to_32_rows(n, k):
     g = torch.Generator(device="cuda").manual_seed(n + k)
     x = torch.randn(32, k, generator=g, device="cuda")
