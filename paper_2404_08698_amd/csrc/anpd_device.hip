@@ -267,11 +267,6 @@ int32_t launch_wide(const FastArgs &a, int blocks, hipStream_t st)
     return ANPD_OK;
 }
 
-// O and down projections.  17..32 rows with at most two tiles per compute unit: split by k-step class (see
-// gemm_split_kernel), 8 classes x n_cu / 8 groups of 8 to 16 tiles each.  Fewer tiles than one per compute unit
-// (small models) stay with one launch, which is all they are.
-int32_t launch_residual(FastArgs &a, int n_cu, float *part, hipStream_t st);
-
 template <int EPI>
 int32_t launch_fast(FastArgs &a, int n_cu, bool force_stream, hipStream_t st)
 {
@@ -355,6 +350,9 @@ int32_t launch_fast(FastArgs &a, int n_cu, bool force_stream, hipStream_t st)
     return ANPD_OK;
 }
 
+// O and down projections.  17..32 rows with at most two tiles per compute unit: split by k-step class (see
+// gemm_split_kernel), 8 classes x n_cu / 8 groups of 8 to 16 tiles each.  Fewer tiles than one per compute unit
+// (small models) stay with one launch, which is all they are.
 int32_t launch_residual(FastArgs &a, int n_cu, float *part, hipStream_t st)
 {
     const int groups = n_cu / 8, waves = groups > 0 ? (a.n_tiles + groups - 1) / groups : 0;
@@ -365,7 +363,7 @@ int32_t launch_residual(FastArgs &a, int n_cu, float *part, hipStream_t st)
         attr_set = true;
     }
     hipLaunchKernelGGL(gemm_split_kernel, dim3((unsigned)((a.n_tiles + waves - 1) / waves * 8)), dim3((unsigned)(waves * 64)), kSplitLds, st, a, part);
-    hipLaunchKernelGGL((split_merge_kernel<EPI_RESIDUAL>), dim3((unsigned)a.n_tiles, (unsigned)((a.M + 15) / 16)), dim3(64), 0, st, a,
+    hipLaunchKernelGGL(split_merge_kernel, dim3((unsigned)a.n_tiles, (unsigned)((a.M + 15) / 16)), dim3(64), 0, st, a,
                        (const float *)part);
     HIP_TRY(hipGetLastError());
     return ANPD_OK;

@@ -840,7 +840,8 @@ __global__ __launch_bounds__(kFastThreads) void gemm_wide_kernel(FastArgs a)
 constexpr int kSplitDepth = 16;   // k-steps in flight per wave; k-steps of operand per LDS buffer
 constexpr int kSplitMaxWaves = 16;
 constexpr size_t kSplitLds = (size_t)(2 * kSplitDepth * 4 + 1) * 1024;   // two buffers, and a place for loads of nothing
-__device__ __forceinline__ void split_load_lds(__amdgpu_buffer_rsrc_t buffer, uint4 *dst, int offset)
+// 16 bytes per lane from byte `offset` of the buffer to dst + 16 lane, without passing through registers
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t buffer, uint4 *dst, int offset)
 {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer, (__attribute__((address_space(3))) void *)dst, 16, offset, 0, 0, 0);
 }
@@ -867,7 +868,7 @@ __global__ __launch_bounds__(kSplitMaxWaves * 64) void gemm_split_kernel(FastArg
         for (int j = 0; j < XL; ++j) {
             const int u = wave + n_waves * j, k = u / NT, f = u % NT;
             const bool real = u < D * NT;
-            split_load_lds(rx, xs + (real ? (size_t)(b * D * NT + u) * 64 : (size_t)2 * D * NT * 64),
+            load_to_lds(rx, xs + (real ? (size_t)(b * D * NT + u) * 64 : (size_t)2 * D * NT * 64),
                            real ? lane * 16 + ((c + 8 * (i0 + k)) * NT + f) * 1024 : 0x7ffffff0);
         }
     };
@@ -918,7 +919,6 @@ __global__ __launch_bounds__(kSplitMaxWaves * 64) void gemm_split_kernel(FastArg
 }
 
 // The eight classes of a tile, added in order, then the epilogue.  grid: (n_tiles, 2) waves; y: rows 16 y ..
-template <int EPI>
 __global__ __launch_bounds__(64) void split_merge_kernel(FastArgs a, const float *__restrict__ part)
 {
     const int lane = threadIdx.x, tile = blockIdx.x, pr = blockIdx.y, m = 16 * pr + (lane & 15);
@@ -938,7 +938,7 @@ __global__ __launch_bounds__(64) void split_merge_kernel(FastArgs a, const float
         h[0] += h[c];
         l[0] += l[c];
     }
-    epilogue<EPI>(a, tile, m, lane >> 4, h[0] + l[0], valid, nullptr);
+    epilogue<EPI_RESIDUAL>(a, tile, m, lane >> 4, h[0] + l[0], valid, nullptr);
 }
 
 // ------------------------------------------------------------------ embed

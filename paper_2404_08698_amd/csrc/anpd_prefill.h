@@ -268,12 +268,6 @@ __device__ __forceinline__ u32x4_t lds_read16(uint32_t addr)
     return v;
 }
 
-// 16 bytes per lane from byte `offset` of the buffer to dst + 16 lane, without passing through registers
-__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t buffer, uint4 *dst, int offset)
-{
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer, (__attribute__((address_space(3))) void *)dst, 16, offset, 0, 0, 0);
-}
-
 // waits until at most N of this wave's loads are outstanding, then for the block
 template <int N>
 __device__ __forceinline__ void wait_loads_and_meet()
