@@ -135,7 +135,7 @@ typedef struct {
     int32_t page_tokens;    /* tokens per KV page (16) */
     int32_t max_window;     /* largest n_window, 1..ANPD_MAX_WINDOW */
     int32_t max_positions;  /* largest KV capacity any anpd_kv_t of this model may have */
-    int32_t gemm_path;      /* ANPD_GEMM_*: AUTO = MFMA for bf16, dot products for f32 */
+    int32_t gemm_path;      /* ANPD_GEMM_*: AUTO = MFMA for bf16, DOT for f32 */
     int32_t n_kv_heads;     /* key / value heads shared by groups of n_heads / n_kv_heads query heads
                                (grouped-query attention, e.g. the ChatGLM model of the paper's Table 1:
                                query head h reads key / value head h / (n_heads / n_kv_heads));
@@ -239,8 +239,9 @@ int32_t anpd_verify_tree(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, 
                          int32_t *out_predicts, float *out_logits, void *stream);
 
 /* Several sequences in one step: their windows go through every weight matrix together, so the
- * weights are streamed once for all of them (the step is bound by that stream: measured at the 7B
- * shape, up to 8 rows cost a one-row step, 9 to 16 rows 1.3 and 17 to 32 rows 1.5 times that).  The
+ * weights are streamed once for all of them.  Measured at the 7B shape from 512 cached positions on, in
+ * one-row steps: one window of up to 8 rows 1.04, of 9 to 16 rows 1.3, of 17 to 32 rows 1.5 to 1.6; sequences of one
+ * row each, whose caches are all read, 8: 1.4, 16: 1.8, 32: 2.4; 8 sequences of 4 rows 1.8.  The
  * paper verifies one sequence at a time (Algorithm 1); this is the same step for n_seq independent
  * runs of it.
  *   kvs (host array of n_seq handles): one cache per sequence, all of model m, all different.

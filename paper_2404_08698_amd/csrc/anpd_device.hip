@@ -1,10 +1,12 @@
 // Device half of the C ABI: model / cache objects and the verification step.
 //
 // One step (paper, Section 3.1 "Parallel Decoding" step 2; Algorithm 1) is a
-// fixed sequence of kernel launches on the caller's stream.  Everything that
-// varies from step to step (cache length, page table, window tokens) is read
-// from device memory, and the only host <-> device traffic of a step is the
-// window upload and the (accepted, next, predictions) read-back.
+// fixed sequence of kernel launches on the caller's stream.  The window's
+// tokens go to the kernels by value; cache length and page table, and the
+// description of a draft tree or of a batch, are read from device memory (the
+// tree and the batch are uploaded unless the step is one kernel, which takes
+// them by value as well).  The kernels write (accepted, next, predictions)
+// into pinned host memory, and the logits where the caller wants them.
 #include <hip/hip_runtime.h>
 
 #include <cmath>

@@ -740,9 +740,11 @@ __global__ __launch_bounds__(kFastThreads) void gemm_group_kernel(FastArgs a)
 // Windows of 17..32 rows.  What these GEMMs pay for is bytes into the compute units: measured over the 7B and
 // 13B shapes a launch takes 4 us + weights / 6.4 TB/s + operand / 22 TB/s, the two one after the other (loads come
 // back in the order they were issued), and deeper register rings change nothing.  The operand is 512 KB per pass
-// and compute unit at K = 4096, so what helps is fewer passes: all of a block's tiles at once where the
-// accumulators fit (T = 6: 96 registers, 8: 128), paid for with a ring of D stages of one k-step.  7B gate/up,
-// 32 rows: two passes of <4, 4> 45.5 us, one of T = 6 37.9; LM head 53.7 -> 47.5 (T = 8); 13B gate/up 59.1 -> 50.6.
+// and compute unit at K = 4096, so what helps is fewer passes: all of a block's tiles at once (T = 6: 96 registers of
+// accumulators, 8: 128), paid for with a ring of D stages of one k-step.  With the epilogues of QKV, O and gate/up the
+// registers do not quite suffice: 2 to 8 of 256 are parked in scratch memory around the loop (12 to 36 bytes per lane; none in the LM
+// head and the plain product).  7B gate/up, 32 rows: two passes of <4, 4> 45.5 us, one of T = 6 37.9; LM head 53.7 -> 47.5 (T = 8);
+// 13B gate/up 59.1 -> 50.6.
 // With one tile per compute unit (T = 1): 7B down 38.4 us as 128 blocks of two tiles, 34.0 as 256 of one.
 // Same k-step assignment (wave, wave + 8, ...) and summation order as the other forms: bit-identical results.
 template <int T, int D, int EPI>

@@ -458,9 +458,14 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b)
 // Why: with one wave per row group every group read all its pages (6.6 GB per layer from L2 at 3584 rows: 300 us at
 // what L2 delivers), 16-key MFMAs did half the work of a 32-key one in the same time, the output was rescaled and a maximum
 // exchanged per page, and a short prompt behind a long cache left the pages to a few waves one after the other.
-// 7B shape, 512 / 3584 rows: 35 -> 21 / 489 -> 409 us per layer (3584 rows: vector ALU 45 %, matrix cores 22 % busy); 205 rows behind
-// 777, 32 heads over 2 key / value heads: 63 -> 19.
-// A row's sums depend on absolute page numbers only, not on how the prompt was cut.
+// 7B shape, 512 / 3584 rows: 35 -> 21 / 489 -> 409 us per layer; 205 rows behind 777, 32 heads over 2 key / value heads: 63 -> 19.
+// What bounds it at 3584 rows is that nothing covers a wave's exponentials: at head dim 128 a lane holds 231 registers and 80
+// accumulators, so a SIMD has one wave (vector ALU 45 %, matrix cores 22 % busy).
+// A row's sums depend on absolute page numbers only, not on how the prompt was cut.  (They are not, bit for bit, those of
+// one wave going page by page with a maximum that always moves: one layer's output is 8e-6 apart, 2^-17 being what the
+// weights' two bf16 terms keep, and equally far from the 64-bit result.)
+// What is not finite: a key whose score is NaN has weight 0; V of keys on a row's own page that the row must not see is
+// multiplied by 0, as in a step, V of later pages is not.
 // grid: (n_heads, ceil(G / 2)); later groups (more pages) start first.
 template <int DH>
 __global__ __launch_bounds__(256) void prefill_attn_kernel(const uint4 *__restrict__ qp, const bf16_t *__restrict__ pool,
