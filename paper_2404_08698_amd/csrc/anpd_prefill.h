@@ -459,14 +459,15 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b)
 // what L2 delivers), 16-key MFMAs did half the work of a 32-key one in the same time, the output was rescaled and a maximum
 // exchanged per page, and a short prompt behind a long cache left the pages to a few waves one after the other.
 // 7B shape, 512 / 3584 rows: 35 -> 21 / 489 -> 409 us per layer; 205 rows behind 777, 32 heads over 2 key / value heads: 63 -> 19.
-// What bounds it at 3584 rows is that nothing covers a wave's exponentials: at head dim 128 a lane holds 231 registers and 80
+// What bounds it at 3584 rows is that nothing covers a wave's exponentials: at head dim 128 a lane holds 238 registers and 80
 // accumulators, so a SIMD has one wave (vector ALU 45 %, matrix cores 22 % busy).
 // A row's sums depend on absolute page numbers only, not on how the prompt was cut.  (They are not, bit for bit, those of
 // one wave going page by page with a maximum that always moves: one layer's output is 8e-6 apart, 2^-17 being what the
 // weights' two bf16 terms keep, and equally far from the 64-bit result.)
-// What is not finite: a key whose score is NaN has weight 0; V of keys on a row's own page that the row must not see is
+// Scores of any size are right (see kHugeScore).  What is not finite: a key whose score is NaN has weight 0; V of keys on a row's own page that the row must not see is
 // multiplied by 0, as in a step, V of later pages is not.
 // grid: (n_heads, ceil(G / 2)); later groups (more pages) start first.
+constexpr float kHugeScore = 0x1p29f;   // rounding a base-2 score of this size may move it by 2^5; below it by 2^4, weights stay under 2^(8 + 16)
 template <int DH>
 __global__ __launch_bounds__(256) void prefill_attn_kernel(const uint4 *__restrict__ qp, const bf16_t *__restrict__ pool,
                                                             const int32_t *__restrict__ page_table, int G, int L, int P,
@@ -570,24 +571,32 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(const uint4 *__restri
                 m_run[x] = m_new;
                 float den = 0.f;
                 u32x4_t ph, pl;
-                auto weights = [&](bool select) __attribute__((always_inline)) {
+                auto weights = [&](bool select, bool huge) __attribute__((always_inline)) {
                     den = 0.f;
+                    auto weight = [&](float score) __attribute__((always_inline)) {
+                        float t = fmaf(score, scale2, -m_new);
+                        if (huge) {   // (opaque: the difference must not be fused with the product)
+                            float scaled = score * scale2;
+                            asm volatile("" : "+v"(scaled));
+                            t = fabsf(m_new) >= kHugeScore ? scaled - m_new : t;
+                        }
+                        const float w = __builtin_amdgcn_exp2f(t);
+                        return select && !(score > 0.5f * kMasked) ? 0.f : w;   // (a key that the row must not see)
+                    };
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        float a = __builtin_amdgcn_exp2f(fmaf(p[2 * j], scale2, -m_new)), b = __builtin_amdgcn_exp2f(fmaf(p[2 * j + 1], scale2, -m_new));
-                        if (select) {   // (a row may have seen nothing yet: its reference is the mask's value)
-                            a = p[2 * j] > 0.5f * kMasked ? a : 0.f;
-                            b = p[2 * j + 1] > 0.5f * kMasked ? b : 0.f;
-                        }
+                        const float a = weight(p[2 * j]), b = weight(p[2 * j + 1]);
                         den += a;
                         den += b;
                         ph[j] = pack_bf16(a, b);
                         pl[j] = pack_bf16(a - __uint_as_float(ph[j] << 16), b - __uint_as_float(ph[j] & 0xffff0000u));
                     }
                 };
-                weights(!all_seen);
-                // a key whose score is NaN has weight 0, as in a step (looked for behind the sums: one comparison)
-                if (__builtin_amdgcn_ballot_w64(den != den) != 0) weights(true);
+                weights(!all_seen, false);
+                // Looked for behind the sums, in two comparisons: a key whose score is NaN has weight 0, as in a step; and
+                // where the reference is huge, the fused product is not the product that it was rounded from: the
+                // difference, up to 2^-24 of it, would be the largest key's exponent.
+                if (__builtin_amdgcn_ballot_w64(den != den || fabsf(m_new) >= kHugeScore) != 0) weights(true, true);
                 d_run[x] = fmaf(d_run[x], alpha, den);
                 // (whole-wave branch; a factor of 1 changes nothing)
                 if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {

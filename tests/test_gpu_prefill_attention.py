@@ -64,10 +64,12 @@ def test_a_row_that_is_not_finite_leaves_the_pages_before_it_alone(shape, at):
             assert torch.equal(x, y), layer   # (NaN equals nothing)
 
 
-# a cached key with a NaN: on a page seen in full by every row, on the last cached one, on the rows' own page
+# a cached key with a NaN, or with values whose scores are far beyond what a rounded sum resolves: on a page seen in full by
+# every row, on the last cached one, on the rows' own page
 @pytest.mark.parametrize("shape", [synth.MID_GQA, synth.TINY_BF16], ids=["dh128_gqa", "dh64"])
 @pytest.mark.parametrize("at,cached,rows", [(3, 64, 40), (63, 64, 40), (150, 200, 33), (40, 50, 3)])
-def test_a_key_with_a_nan_has_weight_zero_as_in_a_step(shape, at, cached, rows):
+@pytest.mark.parametrize("value", [float("nan"), 1e6, 1e10, 1e20, 1e30])
+def test_a_key_with_a_nan_has_weight_zero_and_a_huge_one_its_weight_as_in_a_step(shape, at, cached, rows, value):
     w = synth.make_weights(shape, 3, device="cuda")
     model = B.Model(shape, w, max_window=8, max_positions=256)
     prompt = synth.random_tokens(shape.vocab, rows, 11)
@@ -75,7 +77,7 @@ def test_a_key_with_a_nan_has_weight_zero_as_in_a_step(shape, at, cached, rows):
     for kv in (one, step):
         for layer in range(shape.n_layers):
             k, v = (t.float().contiguous() for t in synth.kv_fill(shape, 7, layer, cached, device="cuda"))
-            k[at] = float("nan")
+            k[at, ::3] = value
             kv.write(layer, 0, k, v)
         kv.truncate(cached)
     got = torch.empty(shape.vocab, dtype=torch.float32, device="cuda")
