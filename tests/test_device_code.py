@@ -94,7 +94,7 @@ def test_registers_of_reads_in_flight_are_left_alone(kernels, name, count):
         assert not [c for c in code if c[1].startswith("scratch_")], k    # no register was parked in memory
 
 
-def test_the_checker_sees_a_register_that_is_used_too_early():
+def test_a_register_that_is_used_too_early_is_seen():
     read, wait, end = (0, "ds_read_b128", "v[4:7], v1"), (8, "s_waitcnt", "lgkmcnt(0)"), (16, "s_endpgm", "")
     assert not _faults([read, wait, (12, "v_mov_b32_e32", "v9, v5"), end])
     assert _faults([read, (8, "v_mov_b32_e32", "v9, v5"), (12, "s_waitcnt", "lgkmcnt(0)"), end])
