@@ -828,42 +828,119 @@ int32_t run_step_mega(anpd_model *m, anpd_kv *kv, const int32_t *window, int M, 
 
 // ---- prompt processing on the matrix cores ------------------------------------
 
-template <int EPI, int TN>
-int32_t launch_prefill_gemm_tn(const PrefillArgs &a, hipStream_t st)
+// One of the prompt GEMMs: sets the kernel's LDS size once (attr_set: per kernel), then launches it.
+template <typename K, typename... Args>
+int32_t launch_prefill_kernel(K kernel, bool &attr_set, long long blocks, int threads, size_t lds, hipStream_t st, const Args &...args)
 {
-    static bool attr_set = false;   // per instantiation
     if (!attr_set) {
-        HIP_TRY(hipFuncSetAttribute((const void *)prefill_gemm_kernel<EPI, TN>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pg_lds_bytes(TN)));
+        HIP_TRY(hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         attr_set = true;
     }
-    const int blocks = (a.n_tiles + 4 * TN - 1) / (4 * TN) * a.S * ((a.G + 7) / 8);
-    hipLaunchKernelGGL((prefill_gemm_kernel<EPI, TN>), dim3((unsigned)blocks), dim3(kPgThreads), pg_lds_bytes(TN), st, a);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3((unsigned)threads), lds, st, args...);
     HIP_TRY(hipGetLastError());
     return ANPD_OK;
 }
+// (blocks: of the template's width; see launch_prefill_gemm)
+template <int EPI, int TN>
+int32_t launch_prefill_wide(const PrefillArgs &a, long long blocks, hipStream_t st)
+{
+    static bool attr_set = false;
+    return launch_prefill_kernel(prefill_gemm_kernel<EPI, TN>, attr_set, blocks, kPgThreads, pg_lds_bytes(TN, 4), st, a);
+}
+template <int EPI, int TN>
+int32_t launch_prefill_narrow(const PrefillArgs &a, long long blocks, hipStream_t st)
+{
+    static bool attr_set = false;
+    return launch_prefill_kernel(prefill_narrow_kernel<EPI, TN>, attr_set, blocks, 256, pg_lds_bytes(TN, 2), st, a);
+}
+template <int EPI, int TB>
+int32_t launch_prefill_mixed(const PrefillArgs &a, int n_a, int tiles_a, long long blocks, hipStream_t st)
+{
+    static bool attr_set = false;
+    return launch_prefill_kernel(prefill_mixed_kernel<EPI, 6, TB>, attr_set, blocks, kPgThreads, pg_lds_bytes(6, 4), st, a, n_a, tiles_a);
+}
+template <int EPI, int TG>
+int32_t launch_prefill_few(const PrefillArgs &a, int waves, long long blocks, hipStream_t st)
+{
+    static bool attr_set = false;
+    return launch_prefill_kernel(prefill_few_kernel<EPI, TG>, attr_set, blocks, (waves + kFewLoaders) * 64, few_lds_bytes(TG), st, a);
+}
 
-// Blocks of 64 TN features: the TN whose grid takes the least time, counted in rounds of the chip's compute
-// units times the measured time of one round (us at K = 4096; the same within 3 % at one round of 512 rows and
-// at 4 to 19 rounds of 3584 rows).  Wider blocks read less per MFMA, narrower ones leave fewer compute units idle
-// in the last round: 512 rows of the 7B shape take TN 6 for gate/up (158 us; TN 2 / 3 / 4: 191 / 180 / 204), 3 for
-// QKV (97; 2 / 4 / 6: 128 / 108 / 144) and 4 for O and down; 205 rows of the ChatGLM3 shape take 2 for all but gate/up.
-constexpr double kPgRound[7] = {0, 0, 66, 90, 106, 126, 150};
+// Measured time of a block of 64 TN features x 128 rows with the chip full of them, us at K = 4096.
+constexpr double kPgBlock[7] = {0, 0, 64, 80, 96, 115, 141};
+
+// When the last of n_a blocks of time ta each and, behind them, n_b of time tb each ends, handed out to n_cu compute
+// units as these become free.
+double blocks_end(long long n_a, double ta, long long n_b, double tb, int n_cu)
+{
+    const long long later = n_a % n_cu, sooner = n_cu - later;   // compute units that end the first kind in the last round, and before it
+    const double t0 = (double)(n_a / n_cu) * ta, t1 = t0 + ta;
+    double end = later ? t1 : t0;
+    for (long long k0 = 0, k1 = 0; n_b > 0;) {   // the next group of compute units that is free takes one each
+        if (t0 + (double)k0 * tb <= t1 + (double)k1 * tb || later == 0) {
+            n_b -= sooner;
+            end = std::fmax(end, t0 + (double)++k0 * tb);
+        } else {
+            n_b -= later;
+            end = std::fmax(end, t1 + (double)++k1 * tb);
+        }
+    }
+    return end;
+}
+
+// How the product is cut into blocks; an element's sums are the same in every form (each ends with the figures of the
+// 7B shape, us).
 template <int EPI>
 int32_t launch_prefill_gemm(const PrefillArgs &a, int n_cu, hipStream_t st)
 {
-    int best = 0;
+    auto cols = [&](int tiles) { return (long long)((a.n_tiles + tiles - 1) / tiles) * a.S; };
+    // A few row groups: a tile per wave and as many waves per block as one round of blocks takes, if there is one:
+    // 64 TN features x 128 rows -> this, QKV of 16 / 32 / 64 / 128 rows 45 -> 17, 45 -> 19, 46 -> 20, 46 -> 27; gate/up
+    // of 16 / 32 / 64 rows 48 -> 27, 48 -> 28, 49 -> 31; down 33 -> 16, 33 -> 17, 34 -> 19.  (In two rounds it loses what
+    // it gains: gate/up of 128 rows 50 -> 50, down 35 -> 32 against 28 for the narrow form.)
+    const int tg = a.G == 1 ? 1 : 2, n_br2 = (a.G + tg - 1) / tg;
+    for (int waves = 3; waves <= kFewWaves; ++waves) {
+        const long long blocks = cols(waves) * n_br2;
+        if (blocks <= n_cu) return tg == 1 ? launch_prefill_few<EPI, 1>(a, waves, blocks, st) : launch_prefill_few<EPI, 2>(a, waves, blocks, st);
+    }
+    // Up to 128 rows: half as wide, of four waves, where that is at most one block per compute unit: gate/up 50 -> 47,
+    // down 35 -> 28 (they read half as much again per MFMA, which more rows would feel: two per compute unit, gate/up
+    // of 512 rows 136 -> 153).
+    if (a.G <= 8 && cols(4) <= n_cu) return launch_prefill_narrow<EPI, 2>(a, cols(4), st);
+    if (a.G <= 8 && cols(6) <= n_cu) return launch_prefill_narrow<EPI, 3>(a, cols(6), st);
+    // Blocks of 64 TN features: wider ones read less per MFMA, narrower ones leave fewer compute units idle in the
+    // last round (512 rows: 6 for gate/up, 3 for QKV, 4 for O and down).  Where the widest take some rounds and a
+    // piece of one, the piece in narrower blocks: gate/up of 768 / 1800 / 3584 rows 218 -> 205, 518 -> 481, 964 -> 921,
+    // QKV of 3584 538 -> 511, down of 1800 278 -> 259.
+    const int n_br = (a.G + 7) / 8;
+    int best = 0, best_b = 0, best_cols = 0;
     double least = 0;
     for (int tn = 6; tn >= 2; --tn) {
-        const long long blocks = (long long)((a.n_tiles + 4 * tn - 1) / (4 * tn)) * a.S * ((a.G + 7) / 8);
-        const double t = kPgRound[tn] * (double)((blocks + n_cu - 1) / n_cu);
+        const double t = blocks_end(cols(4 * tn) * n_br, kPgBlock[tn], 0, 0, n_cu);
         if (best == 0 || t < least) { least = t; best = tn; }
     }
+    const long long rounds = cols(24) * n_br / n_cu;
+    for (long long r = rounds; r >= 1 && r >= rounds - 1; --r) {
+        const int wide = (int)(r * n_cu / ((long long)n_br * a.S));   // columns of the widest blocks
+        if (wide < 1 || wide * 24 >= a.n_tiles) continue;
+        for (int tb = 4; tb >= 3; --tb) {
+            const long long n_b = (long long)((a.n_tiles - wide * 24 + 4 * tb - 1) / (4 * tb)) * a.S * n_br;
+            const double t = blocks_end((long long)wide * a.S * n_br, kPgBlock[6], n_b, kPgBlock[tb], n_cu);
+            if (t < 0.98 * least) { least = t; best_b = tb; best_cols = wide; }
+        }
+    }
+    if (best_b) {
+        const int n_a = best_cols * a.S * n_br, tiles_a = best_cols * 24;
+        const long long blocks = n_a + (long long)((a.n_tiles - tiles_a + 4 * best_b - 1) / (4 * best_b)) * a.S * n_br;
+        return best_b == 4 ? launch_prefill_mixed<EPI, 4>(a, n_a, tiles_a, blocks, st) : launch_prefill_mixed<EPI, 3>(a, n_a, tiles_a, blocks, st);
+    }
+    const long long blocks = cols(4 * best) * n_br;
     switch (best) {
-    case 2: return launch_prefill_gemm_tn<EPI, 2>(a, st);
-    case 3: return launch_prefill_gemm_tn<EPI, 3>(a, st);
-    case 4: return launch_prefill_gemm_tn<EPI, 4>(a, st);
-    case 5: return launch_prefill_gemm_tn<EPI, 5>(a, st);
-    default: return launch_prefill_gemm_tn<EPI, 6>(a, st);
+    case 2: return launch_prefill_wide<EPI, 2>(a, blocks, st);
+    case 3: return launch_prefill_wide<EPI, 3>(a, blocks, st);
+    case 4: return launch_prefill_wide<EPI, 4>(a, blocks, st);
+    case 5: return launch_prefill_wide<EPI, 5>(a, blocks, st);
+    default: return launch_prefill_wide<EPI, 6>(a, blocks, st);
     }
 }
 

@@ -30,7 +30,7 @@
 
 namespace anpd {
 
-constexpr int kPgThreads = 512;       // GEMM block: 8 waves, 4 (features) x 2 (rows)
+constexpr int kPgThreads = 512;       // GEMM block: 8 waves, 4 (features) x 2 (rows); half of it in the narrow form
 constexpr int kPfTM = 4;              // row groups per wave
 constexpr int kPgSplit = 4;           // K splits of the residual GEMMs
 
@@ -60,19 +60,26 @@ __host__ __device__ __forceinline__ size_t xq_offset(int nks, int m, int k, int 
     return ((((size_t)(m >> 4) * nks + (k >> 5)) * 2 + lo) * 64 + (size_t)((k >> 3) & 3) * 16 + (m & 15)) * 8 + (k & 7);
 }
 
+// two floats rounded to bf16 (nearest even) side by side, one instruction
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){a, b}, b16x2));
+}
+
+// the rests of a and b behind their bf16 halves `hi`, rounded to bf16
+__device__ __forceinline__ uint32_t pack_lo(float a, float b, uint32_t hi)
+{
+    return pack_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
+}
+
 // four consecutive columns k .. k + 3 (k % 4 == 0) of row m, as hi and lo terms
 __device__ __forceinline__ void xq_store4(bf16_t *xq, int nks, int m, int k, f32x4 v)
 {
-    bf16_t hi[4], lo[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        hi[i] = f32_to_bf16(v[i]);
-        lo[i] = f32_to_bf16(v[i] - bf16_to_f32(hi[i]));
-    }
-    *reinterpret_cast<uint2 *>(xq + xq_offset(nks, m, k, 0)) =
-        make_uint2((uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16));
-    *reinterpret_cast<uint2 *>(xq + xq_offset(nks, m, k, 1)) =
-        make_uint2((uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16));
+    const uint2 hi = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+    *reinterpret_cast<uint2 *>(xq + xq_offset(nks, m, k, 0)) = hi;
+    *reinterpret_cast<uint2 *>(xq + xq_offset(nks, m, k, 1)) = make_uint2(pack_lo(v[0], v[1], hi.x), pack_lo(v[2], v[3], hi.y));
 }
 
 __device__ __forceinline__ f32x4 widen4(uint2 b)
@@ -166,63 +173,118 @@ __host__ __device__ __forceinline__ size_t qpf_offset(int head, int G, int head_
 }
 
 // y: this lane's four outputs (features 4 kg .. 4 kg + 3 of weight tile `tile`) for row m.
-// Every lane of the wave must call this: the fused forms exchange values with lane ^ 32.
+// Every lane of the wave must call this: the fused forms exchange values with lane ^ 32.  (QKV: prefill_finish_qkv.)
 template <int EPI>
 __device__ __forceinline__ void prefill_epilogue(const PrefillArgs &a, int tile, int m, int kg, f32x4 y, bool valid, int sp)
 {
     if (EPI == EPI_RESIDUAL) {
         if (valid) *reinterpret_cast<f32x4 *>(a.part + ((size_t)sp * a.G * 16 + m) * a.d + tile * 16 + 4 * kg) = y;
     } else if (EPI == EPI_GATE_UP) {
-        f32x4 up;
+        // gate rows are in the lower half of the wave, the matching up rows in the upper half: two swaps give either half
+        // both rows of two of the four features (each lane all four, with half of the lanes' work thrown away, and
+        // the rows exchanged through LDS: see the kernel's comment)
+        float act[2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) up[i] = __shfl_xor(y[i], 32, kWave);
-        if (valid && kg < 2) {
-            f32x4 act;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) act[i] = y[i] / (1.0f + expf(-y[i])) * up[i];
-            xq_store4(a.out, a.out_nks, m, tile * 8 + 4 * kg, act);
+        for (int i = 0; i < 2; ++i) {
+            auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(y[i]), __float_as_uint(y[i + 2]), false, false);
+            const float g = __uint_as_float(p[0]), up = __uint_as_float(p[1]);
+            act[i] = g / (1.0f + expf(-g)) * up;
         }
-    } else if (EPI == EPI_QKV) {
-        const int Tq = a.n_heads * a.head_dim / 16, Tkv = a.n_kv_heads * a.head_dim / 16;
-        const int which = tile < Tq ? 0 : (tile < Tq + Tkv ? 1 : 2), t = tile - (which == 0 ? 0 : (which == 1 ? Tq : Tq + Tkv));
-        const int pos = (a.L & ~15) + m;
-        f32x4 other;
+        if (valid) {
+            const int k = tile * 8 + 4 * (kg & 1) + 2 * (kg >> 1);
+            const uint32_t hi = pack_bf16(act[0], act[1]);
+            *reinterpret_cast<uint32_t *>(a.out + xq_offset(a.out_nks, m, k, 0)) = hi;
+            *reinterpret_cast<uint32_t *>(a.out + xq_offset(a.out_nks, m, k, 1)) = pack_lo(act[0], act[1], hi);
+        }
+    }
+}
+
+// QKV: rotary embedding, query operand, cache write, for the row groups g0 .. g0 + TG - 1 of one weight tile.  What
+// depends on the tile or on the group alone is worked out once for all of them, and every angle is requested before
+// the first is used (one row group after the other, each with its own divisions, addresses and waits: 4400
+// instructions per wave behind the loop at TN = 3, 1800 now).
+// Tried: values exchanged between four lanes for stores of 8 bytes instead of four of 2 (no change).
+// page: byte offsets of the groups' pages in the pool.
+template <int TG>
+__device__ __forceinline__ void prefill_finish_qkv(const PrefillArgs &a, int tile, int g0, const f32x4 (&y)[TG], const bool (&valid)[TG],
+                                                   const size_t (&page)[TG])
+{
+    const int lane = threadIdx.x & 63, slot = lane & 15, kg = lane >> 4;
+    const int tph = a.head_dim / 16, half = a.head_dim / 2, Tq = a.n_heads * tph, Tkv = a.n_kv_heads * tph;
+    if (tile >= Tq + Tkv) {
+        const int t = tile - Tq - Tkv, h = t / tph, j = t - h * tph;
+        // (head block of the page, dimensions 16 j .. of it)
+        char *dst = (char *)(a.pool + kvf_base(0, a.layer, a.n_layers, 1, h, a.n_kv_heads, a.head_dim) + vf_elem(slot, 16 * j + 4 * kg));
 #pragma unroll
-        for (int i = 0; i < 4; ++i) other[i] = __shfl_xor(y[i], 32, kWave);
-        if (!valid) return;
-        const int page = a.page_table[pos >> 4], tk = pos & 15;
-        if (which < 2) {
-            const int tph = a.head_dim / 16, half = a.head_dim / 2;
-            const int h = t / tph, j = t - h * tph;
-            const int i0 = 8 * j + 4 * (kg & 1);
-            f32x4 o;
+        for (int g = 0; g < TG; ++g) {
+            if (!valid[g]) continue;
+            bf16_t *d = (bf16_t *)(dst + page[g]);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float2 cs = a.rope[(size_t)pos * half + i0 + i];
-                o[i] = kg < 2 ? y[i] * cs.x - other[i] * cs.y : y[i] * cs.x + other[i] * cs.y;
-            }
-            const int dim = i0 + (kg < 2 ? 0 : half);
-            if (which == 0) {
-                bf16_t hi[4], lo[4];
+            for (int i = 0; i < 4; ++i) d[4 * i] = (bf16_t)pack_bf16(y[g][i], 0.f);
+        }
+        return;
+    }
+    const bool is_q = tile < Tq;
+    const int t = is_q ? tile : tile - Tq, h = t / tph, j = t - h * tph;
+    const int i0 = 8 * j + 4 * (kg & 1), dim = i0 + (kg < 2 ? 0 : half);
+    f32x4 cs[TG][2];   // (cos, sin) of pairs 0, 1 and 2, 3
+    const float2 *rope = a.rope + (size_t)((a.L & ~15) + g0 * 16 + slot) * half + i0;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    hi[i] = f32_to_bf16(o[i]);
-                    lo[i] = f32_to_bf16(o[i] - bf16_to_f32(hi[i]));
-                }
-                *reinterpret_cast<uint2 *>(a.qp + qpf_offset(h, a.G, a.head_dim, m, dim, 0)) =
-                    make_uint2((uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16));
-                *reinterpret_cast<uint2 *>(a.qp + qpf_offset(h, a.G, a.head_dim, m, dim, 1)) =
-                    make_uint2((uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16));
-            } else {
-                bf16_t *dst = a.pool + kvf_base(page, a.layer, a.n_layers, 0, h, a.n_kv_heads, a.head_dim) + kf_elem(tk, dim);
-                *reinterpret_cast<uint2 *>(dst) = make_uint2((uint32_t)f32_to_bf16(o[0]) | ((uint32_t)f32_to_bf16(o[1]) << 16),
-                                                             (uint32_t)f32_to_bf16(o[2]) | ((uint32_t)f32_to_bf16(o[3]) << 16));
-            }
+    for (int g = 0; g < TG; ++g) {
+        cs[g][0] = cs[g][1] = (f32x4){1.f, 0.f, 1.f, 0.f};
+        if (valid[g]) {
+            const f32x4 *c = reinterpret_cast<const f32x4 *>(rope + (size_t)g * 16 * half);
+            cs[g][0] = c[0];
+            cs[g][1] = c[1];
+        }
+    }
+    char *k_dst = (char *)(a.pool + kvf_base(0, a.layer, a.n_layers, 0, h, a.n_kv_heads, a.head_dim) + kf_elem(slot, dim));
+    bf16_t *q_dst = a.qp + qpf_offset(h, a.G, a.head_dim, g0 * 16 + slot, dim, 0);
+    const int q_group = (a.head_dim >> 5) * 1024;   // elements between row groups; 512: from hi to lo
+#pragma unroll
+    for (int g = 0; g < TG; ++g) {
+        f32x4 o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            // the same output of lane ^ 32
+            auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(y[g][i]), __float_as_uint(y[g][i]), false, false);
+            const float other = __uint_as_float(kg < 2 ? p[1] : p[0]), c = cs[g][i >> 1][2 * (i & 1)], cross = other * cs[g][i >> 1][2 * (i & 1) + 1];
+            o[i] = kg < 2 ? fmaf(y[g][i], c, -cross) : fmaf(y[g][i], c, cross);
+        }
+        if (!valid[g]) continue;
+        const uint2 hi = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
+        if (is_q) {
+            *reinterpret_cast<uint2 *>(q_dst + g * q_group) = hi;
+            *reinterpret_cast<uint2 *>(q_dst + g * q_group + 512) = make_uint2(pack_lo(o[0], o[1], hi.x), pack_lo(o[2], o[3], hi.y));
         } else {
-            const int n = t * 16 + 4 * kg, h = n / a.head_dim, dim = n - h * a.head_dim;
-            bf16_t *dst = a.pool + kvf_base(page, a.layer, a.n_layers, 1, h, a.n_kv_heads, a.head_dim);
+            *reinterpret_cast<uint2 *>(k_dst + page[g]) = hi;
+        }
+    }
+}
+
+// The epilogues of one wave: tiles f0 .. f0 + TN - 1 (below tile_end), row groups g0 .. g0 + TG - 1 (below G).
+template <int EPI, int TN, int TG>
+__device__ __forceinline__ void prefill_finish(const PrefillArgs &a, int f0, int tile_end, int g0, const f32x4 (&acc)[TN][TG], int sp)
+{
+    const int lane = threadIdx.x & 63, kg = lane >> 4, r0 = a.L & 15;
+    bool valid[TG];
+    size_t page[TG];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) dst[vf_elem(tk, dim + i)] = f32_to_bf16(y[i]);
+    for (int g = 0; g < TG; ++g) {
+        const int m = (g0 + g) * 16 + (lane & 15);
+        valid[g] = g0 + g < a.G && m >= r0 && m < r0 + a.P;
+        page[g] = 0;
+        if (EPI == EPI_QKV && g0 + g < a.G)
+            page[g] = kvf_base(a.page_table[(a.L >> 4) + g0 + g], 0, a.n_layers, 0, 0, a.n_kv_heads, a.head_dim) * sizeof(bf16_t);
+    }
+#pragma unroll
+    for (int t = 0; t < TN; ++t) {
+        if (f0 + t >= tile_end) break;   // wave-uniform
+        if (EPI == EPI_QKV) {
+            prefill_finish_qkv<TG>(a, f0 + t, g0, acc[t], valid, page);
+        } else {
+#pragma unroll
+            for (int g = 0; g < TG; ++g) prefill_epilogue<EPI>(a, f0 + t, (g0 + g) * 16 + (lane & 15), kg, acc[t][g], valid[g], sp);
         }
     }
 }
@@ -230,7 +292,7 @@ __device__ __forceinline__ void prefill_epilogue(const PrefillArgs &a, int tile,
 // -------------------------------------------------------------------- GEMM
 //
 // Y^T[features][rows] = W X^T with hi and lo terms of X accumulated into the
-// same tile.  Block = 4 x 2 waves, 64 TN features x 128 rows, each wave
+// same tile.  Block = 4 x 2 waves (WF = 4), 64 TN features x 128 rows, each wave
 // TN weight fragments x 4 row groups.  Per k-step the block needs 4 TN weight
 // fragments and 16 activation fragments of 1 KiB; each wave requests its share
 // of them straight into LDS (buffer loads with the LDS bit: lane i's 16 bytes
@@ -240,18 +302,21 @@ __device__ __forceinline__ void prefill_epilogue(const PrefillArgs &a, int tile,
 // the L2 -> CU path once per block instead of once per wave that uses it.
 //
 // Three things take about the same time here - the matrix cores (8 TN MFMAs per wave and k-step), the LDS
-// reads (TN + 8 fragments per wave) and the L2 -> CU traffic (4 TN + 16 fragments per block; 85 GB/s per
-// compute unit at most) - so they have to run side by side: a wave holds the fragments of k-step i in one
-// set of registers while it reads those of k-step i + 1 into the other, one every few MFMAs, and the three
-// k-steps behind that are on their way into LDS.  One block barrier per k-step: it publishes the stage whose
-// loads every wave has just waited for and frees the stage that every wave has just finished reading.
-// Against two k-steps read and waited for before the first MFMA of either (256 features x 128 rows, traced,
-// 7B shape): gate/up of 512 rows 206 -> 158 us (TN 3 -> 6: one round of 232 blocks instead of two of 460),
-// QKV 107 -> 97, O + down 128 -> 117; of 3584 rows 1127 -> 1049, 705 -> 612, 814 -> 780.  What bounds it now is
-// the power limit more than any unit: at 3584 rows the clock is 1.95 GHz with the matrix cores busy two
-// thirds of the time (registers only, random operands: 2.0 PFLOP/s; the library's largest product: 1.53; here 1.23).
+// reads (TN + 8 fragments per wave) and the L2 -> CU traffic (4 TN + 16 fragments per block) - so they have to
+// run side by side: a wave holds the fragments of k-step i in one set of registers while it reads those of k-step
+// i + 1 into the other, one every few MFMAs, and the three k-steps behind that are on their way into LDS.  The
+// requests for the fourth go out between the MFMAs as well: all at once behind the barrier they held up every wave
+// until the queue had taken them (gate/up of 512 rows 141.5 -> 139.4 us, of 128 rows 87 -> 83).  One block barrier
+// per k-step: it publishes the stage whose loads every wave has just waited for and frees the stage that every
+// wave has just finished reading.
+// What is left (gate/up of 512 rows, one round of 232 blocks, 135.5 us): 0.93 us per k-step, of which the MFMAs
+// alone would take 0.66 at the clock that the power limit leaves them (0.79 without the loads into LDS, 0.83
+// without the reads; 0.79 with a third of the chip at work, and no faster without the reads: what they cost is
+// power), and 16 us around the loop.  Of those the SwiGLU of the epilogue took 4 more while every lane computed four
+// products and half the lanes threw them away (139.4 -> 135.5; gate/up of 3584 rows 983 -> 965).
 // Tried: one barrier per two k-steps (no change at TN = 6, 5 % slower at TN = 2, whose loads have less time to land),
-// 32x32x16 MFMAs (registers only, random operands: 10 % slower).
+// 32x32x16 MFMAs (registers only, random operands: 10 % slower), blocks of four waves, two per compute unit, whose
+// barriers fall at different times (half as much again to read per MFMA: gate/up of 3584 rows 1124 against 1002).
 //
 // RESIDUAL GEMMs (few output features) are split S ways along K so that the
 // grid fills the chip; the S partial tiles go to `part` and are added to the
@@ -275,11 +340,12 @@ __device__ __forceinline__ void wait_loads_and_meet()
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-// fragments per stage, loads per wave and stage, and stages of the ring
-__host__ __device__ constexpr int pg_units(int TN) { return 4 * TN + 16; }
-__host__ __device__ constexpr int pg_loads(int TN) { return (pg_units(TN) + 7) / 8; }
-constexpr int kPgStages = 4;
-__host__ __device__ constexpr size_t pg_lds_bytes(int TN) { return (size_t)kPgStages * pg_loads(TN) * 8 * 1024; }
+// WF: waves side by side along the features (2 along the rows).  Fragments per stage, loads per wave and stage, stages
+// of the ring, bytes of LDS (a stage's fragments; one place for the loads of nothing that make every wave's number even)
+__host__ __device__ constexpr int pg_units(int TN, int WF) { return WF * TN + 16; }
+__host__ __device__ constexpr int pg_loads(int TN, int WF) { return (pg_units(TN, WF) + 2 * WF - 1) / (2 * WF); }
+__host__ __device__ constexpr int pg_stages(int WF) { return WF == 4 ? 4 : 3; }
+__host__ __device__ constexpr size_t pg_lds_bytes(int TN, int WF) { return ((size_t)pg_stages(WF) * pg_units(TN, WF) + (pg_units(TN, WF) % (2 * WF) != 0)) * 1024; }
 
 // calls f with 0, 1, ... as compile-time constants
 template <int... I, typename F>
@@ -294,27 +360,28 @@ struct PgFrags {
     u32x4_t w[TN], xh[kPfTM], xl[kPfTM];
 };
 
-template <int EPI, int TN>
-__global__ __launch_bounds__(kPgThreads) void prefill_gemm_kernel(PrefillArgs a)
+// Block `block` of n_blocks that take the tiles [tile0, tile_end).
+template <int EPI, int TN, int WF>
+__device__ __forceinline__ void prefill_gemm_block(const PrefillArgs &a, int block, int n_blocks, int tile0, int tile_end)
 {
-    constexpr int kUnits = pg_units(TN), kLoads = pg_loads(TN), kStageUnits = kLoads * 8;
-    extern __shared__ uint4 ring[];   // [kPgStages][kStageUnits][64]
+    constexpr int kUnits = pg_units(TN, WF), kLoads = pg_loads(TN, WF), kStages = pg_stages(WF);
+    extern __shared__ uint4 ring[];   // [kStages][kUnits][64], [64]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wf = wave & 3, wr = wave >> 2;
+    const int wf = wave % WF, wr = wave / WF;
     const int n_br = (a.G + 7) / 8;
     // Blocks are dealt to the 8 XCDs in turn, and each XCD has its own L2.  Give XCD x a contiguous
     // range of the (weights, rows) order, so that the blocks sharing a weight range, and the row
     // blocks they all stream in step, meet in one L2 instead of being fetched into several.
     int id;
     {
-        const int n = (int)gridDim.x, per = (n + 7) / 8, rem = n % 8;
-        const int xcd = (int)blockIdx.x % 8, j = (int)blockIdx.x / 8;
+        const int n = n_blocks, per = (n + 7) / 8, rem = n % 8;
+        const int xcd = block % 8, j = block / 8;
         id = (rem == 0 || xcd < rem ? xcd * per : rem * per + (xcd - rem) * (per - 1)) + j;
     }
     const int br = id % n_br;
     id /= n_br;
     const int sp = id % a.S, bt = id / a.S;
-    const int F0 = bt * 4 * TN, G0 = br * 8;
+    const int F0 = tile0 + bt * WF * TN, G0 = br * 8;
     const int nks = a.nks;
     const int ks0 = (int)((long long)sp * nks / a.S), n_it = (int)((long long)(sp + 1) * nks / a.S) - ks0;
 
@@ -326,16 +393,16 @@ __global__ __launch_bounds__(kPgThreads) void prefill_gemm_kernel(PrefillArgs a)
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) {
         const int u = kLoads * wave + j;
-        if (u < 4 * TN) {
+        if (u < WF * TN) {
             const int tile = F0 + u;
-            const bool have = tile < a.n_tiles;
+            const bool have = tile < tile_end;
             rs[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.Wp + ((size_t)(have ? tile : 0) * nks + ks0) * 64), 0,
                                                       have ? n_it * 1024 : 0, 0x00020000);
             uoff[j] = 0;
             ustride[j] = 1024;
         } else {
             // the descriptor ends with this row group's last k-step of the split
-            const int v = u - 4 * TN, g = G0 + (v >> 1);   // (row group, hi | lo)
+            const int v = u - WF * TN, g = G0 + (v >> 1);   // (row group, hi | lo)
             const bool have = u < kUnits && g < a.G;
             rs[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.Xq + ((size_t)(have ? g : 0) * nks + ks0) * 128), 0,
                                                       have ? n_it * 2048 : 0, 0x00020000);
@@ -344,11 +411,13 @@ __global__ __launch_bounds__(kPgThreads) void prefill_gemm_kernel(PrefillArgs a)
         }
     }
     // stage `slot` of the ring <- k-step `it` (past the end: zeros, nothing fetched)
+    auto request_one = [&](int j, int it, int slot) __attribute__((always_inline)) {
+        const int u = kLoads * wave + j;
+        load_to_lds(rs[j], ring + (size_t)(u < kUnits ? slot * kUnits + u : kStages * kUnits) * 64, uoff[j] + it * ustride[j] + lane * 16);
+    };
     auto request = [&](int it, int slot) __attribute__((always_inline)) {
-        uint4 *dst = ring + ((size_t)slot * kStageUnits + kLoads * wave) * 64;
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j)
-            load_to_lds(rs[j], dst + j * 64, uoff[j] + it * ustride[j] + lane * 16);
+        for (int j = 0; j < kLoads; ++j) request_one(j, it, slot);
     };
 
     f32x4 acc[TN][kPfTM];
@@ -384,13 +453,16 @@ __global__ __launch_bounds__(kPgThreads) void prefill_gemm_kernel(PrefillArgs a)
     // The reads of the next k-step's fragments from stage `slot`, one every few MFMAs of this one's, the last
     // some MFMAs before the end: issued in one go they would fill the LDS queue and hold up every wave's MFMAs
     // until they are through.
-    auto interleave = [&](const Frags &cur, Frags &next, int slot) __attribute__((always_inline)) {
+    auto interleave = [&](const Frags &cur, Frags &next, int slot, int ahead, int free_slot) __attribute__((always_inline)) {
         constexpr int NR = TN + 8, NM = 8 * TN, SPAN = NM * 85 / 100;
-        const uint32_t sbase = lds_base + (uint32_t)slot * (kStageUnits * 1024);
-        const uint32_t aw = sbase + (uint32_t)(TN * wf) * 1024, ax = sbase + (uint32_t)(4 * TN + 8 * wr) * 1024;
+        const uint32_t sbase = lds_base + (uint32_t)slot * (kUnits * 1024);
+        const uint32_t aw = sbase + (uint32_t)(TN * wf) * 1024, ax = sbase + (uint32_t)(WF * TN + 8 * wr) * 1024;
         auto part = [&](auto index) __attribute__((always_inline)) {
             constexpr int i = decltype(index)::value;
             read_one(index, next, aw, ax);
+#pragma unroll
+            for (int j = 0; j < kLoads; ++j)
+                if (j * NR / kLoads == i) request_one(j, ahead, free_slot);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = i * SPAN / NR; j < (i + 1 == NR ? NM : (i + 1) * SPAN / NR); ++j) mma_one(cur, j);
@@ -399,20 +471,22 @@ __global__ __launch_bounds__(kPgThreads) void prefill_gemm_kernel(PrefillArgs a)
         index_each(std::make_integer_sequence<int, NR>{}, [&](auto... index) __attribute__((always_inline)) { (part(index), ...); });
     };
     // One k-step: `cur` holds its fragments.  This wave's loads of k-step it + 1 have landed when at most the
-    // kPgStages - 2 younger stages are outstanding; after the barrier every wave's have, and every wave has its
-    // fragments of k-step it in registers, so that slot is free for k-step it + kPgStages.
+    // kStages - 2 younger stages are outstanding; after the barrier every wave's have, and every wave has its
+    // fragments of k-step it in registers, so that slot is free for k-step it + kStages.
+    int slot = 0;   // of k-step it
     auto step = [&](const Frags &cur, Frags &next, int it) __attribute__((always_inline)) {
-        wait_loads_and_meet<(kPgStages - 2) * kLoads>();
-        request(it + kPgStages, it & (kPgStages - 1));
-        interleave(cur, next, (it + 1) & (kPgStages - 1));
+        wait_loads_and_meet<(kStages - 2) * kLoads>();
+        const int free_slot = slot;
+        slot = slot + 1 == kStages ? 0 : slot + 1;
+        interleave(cur, next, slot, it + kStages, free_slot);
         wait_reads(next);
     };
 #pragma unroll
-    for (int s = 0; s < kPgStages; ++s) request(s, s);
+    for (int s = 0; s < kStages; ++s) request(s, s);
     Frags fa, fb;
-    wait_loads_and_meet<(kPgStages - 1) * kLoads>();
+    wait_loads_and_meet<(kStages - 1) * kLoads>();
     index_each(std::make_integer_sequence<int, TN + 8>{}, [&](auto... index) __attribute__((always_inline)) {
-        (read_one(index, fa, lds_base + (uint32_t)(TN * wf) * 1024, lds_base + (uint32_t)(4 * TN + 8 * wr) * 1024), ...);
+        (read_one(index, fa, lds_base + (uint32_t)(TN * wf) * 1024, lds_base + (uint32_t)(WF * TN + 8 * wr) * 1024), ...);
     });
     wait_reads(fa);
     for (int it = 0; it < n_it; it += 2) {   // (an odd n_it ends with a k-step of zeros)
@@ -421,31 +495,143 @@ __global__ __launch_bounds__(kPgThreads) void prefill_gemm_kernel(PrefillArgs a)
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the last requests, of nothing)
 
-    const int slot16 = lane & 15, kg = lane >> 4;
-    const int r0 = a.L & 15;
     const int f0 = F0 + TN * wf, g0 = G0 + 4 * wr;
+    prefill_finish<EPI, TN, kPfTM>(a, f0, tile_end, g0, acc, sp);
+}
+
+template <int EPI, int TN>
+__global__ __launch_bounds__(kPgThreads) void prefill_gemm_kernel(PrefillArgs a)
+{
+    prefill_gemm_block<EPI, TN, 4>(a, blockIdx.x, gridDim.x, 0, a.n_tiles);
+}
+// half as wide, four waves
+template <int EPI, int TN>
+__global__ __launch_bounds__(256, 2) void prefill_narrow_kernel(PrefillArgs a)
+{
+    prefill_gemm_block<EPI, TN, 2>(a, blockIdx.x, gridDim.x, 0, a.n_tiles);
+}
+// the tiles [0, tiles_a) in blocks of TA, n_a of them, the rest in blocks of TB
+template <int EPI, int TA, int TB>
+__global__ __launch_bounds__(kPgThreads) void prefill_mixed_kernel(PrefillArgs a, int n_a, int tiles_a)
+{
+    if ((int)blockIdx.x < n_a) prefill_gemm_block<EPI, TA, 4>(a, blockIdx.x, n_a, 0, tiles_a);
+    else prefill_gemm_block<EPI, TB, 4>(a, (int)blockIdx.x - n_a, (int)gridDim.x - n_a, tiles_a, a.n_tiles);
+}
+
+// ------------------------------------------------- GEMM, few rows
+//
+// Prompts (pieces) of a few row groups: the weights' bytes are what counts, and the form above, made for tiles of 128
+// rows, keeps 24 to 72 KB of them in flight per compute unit, on a third of the chip.  Here a wave streams the one tile
+// that it owns through a ring of 16 k-steps of registers against TG row groups, whose fragments two waves of their own
+// bring through LDS, eight k-steps at a time, for all waves of the block: they wait for their own loads only, and the
+// others' weights stay in flight (loads of a wave come back in the order they were requested).  The waves meet once
+// per eight k-steps.  An element's sums are those of the form above: one chain over the k-steps, hi term, lo term.
+// Bound by the weights and, from about 64 rows, by what the operand and the weights (read once per TG groups) take from
+// L2: 7B shape, 32 / 64 rows, QKV 19.2 / 19.9 us (5.2 / 5.1 TB/s of weights; the form above 45), gate/up 28.4 / 30.9
+// (48), down 17.0 / 19.0 (33).  The order of a k-step's requests is in the source: left to itself the compiler put
+// the weight loads of eight k-steps together at their end, behind reads waited for one by one (QKV 21.3 / 24.0).
+// Tried: four row groups per block (no faster at any size), one wave or four bringing the operand (the same).
+constexpr int kFewChunk = 8, kFewBufs = 3;   // k-steps per buffer of the operand, buffers
+__host__ __device__ constexpr int few_units(int TG) { return kFewChunk * 2 * TG; }   // fragments per buffer
+__host__ __device__ constexpr size_t few_lds_bytes(int TG) { return (size_t)kFewBufs * few_units(TG) * 1024; }
+constexpr int kFewDepth = 16;   // weight fragments in flight per wave
+constexpr int kFewLoaders = 2;  // waves that bring the operand
+constexpr int kFewWaves = 14;   // most waves with a tile
+// blockDim: 64 x (tiles per block + kFewLoaders).  grid: ceil(n_tiles / tiles per block) * S * ceil(G / TG), rows fastest.
+template <int EPI, int TG>
+__global__ __launch_bounds__((kFewWaves + kFewLoaders) * 64) void prefill_few_kernel(PrefillArgs a)
+{
+    constexpr int D = kFewDepth, DX = kFewChunk, NB = kFewBufs, UNITS = few_units(TG);
+    extern __shared__ uint4 xs[];   // [NB][DX][TG][hi | lo][64]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = (int)(blockDim.x >> 6) - kFewLoaders;
+    const int n_br = (a.G + TG - 1) / TG;
+    int id;
+    {
+        const int n = (int)gridDim.x, per = (n + 7) / 8, rem = n % 8;
+        const int xcd = (int)blockIdx.x % 8, j = (int)blockIdx.x / 8;
+        id = (rem == 0 || xcd < rem ? xcd * per : rem * per + (xcd - rem) * (per - 1)) + j;
+    }
+    const int br = id % n_br;
+    id /= n_br;
+    const int sp = id % a.S, bt = id / a.S;
+    const int G0 = br * TG, nks = a.nks;
+    const int ks0 = (int)((long long)sp * nks / a.S), n_it = (int)((long long)(sp + 1) * nks / a.S) - ks0;
+    const int n_chunks = (n_it + DX - 1) / DX;
+    if (wave >= n_waves) {
+        // a wave that brings the operand, DX / kFewLoaders k-steps of every chunk: chunk c + NB - 1 is requested when chunk c is ready
+        const int k0 = (wave - n_waves) * (DX / kFewLoaders);
+        auto load_x = [&](int c) __attribute__((always_inline)) {
+            uint4 *dst = xs + (size_t)(c % NB) * UNITS * 64;
 #pragma unroll
-    for (int t = 0; t < TN; ++t) {
-        if (f0 + t >= a.n_tiles) break;   // wave-uniform
+            for (int g = 0; g < TG; ++g) {
+                const bool have = G0 + g < a.G;
+                __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.Xq + ((size_t)(have ? G0 + g : 0) * nks + ks0) * 128), 0,
+                                                                             have ? n_it * 2048 : 0, 0x00020000);
 #pragma unroll
-        for (int g = 0; g < kPfTM; ++g) {
-            const int m = (g0 + g) * 16 + slot16;
-            const bool valid = g0 + g < a.G && m >= r0 && m < r0 + a.P;
-            prefill_epilogue<EPI>(a, f0 + t, m, kg, acc[t][g], valid, sp);
+                for (int k = 0; k < DX / kFewLoaders; ++k)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        load_to_lds(r, dst + ((size_t)((k0 + k) * TG + g) * 2 + h) * 64, ((c * DX + k0 + k) * 2 + h) * 1024 + lane * 16);
+            }
+        };
+        for (int c = 0; c < NB - 1; ++c) load_x(c);
+        for (int c = 0; c < n_chunks; ++c) {
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NB - 2) * UNITS / kFewLoaders) : "memory");
+            load_x(c + NB - 1);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        return;
+    }
+    const int tile = bt * n_waves + wave;
+    const bool have = tile < a.n_tiles;
+    __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.Wp + ((size_t)(have ? tile : 0) * nks + ks0) * 64), 0,
+                                                                  have ? n_it * 1024 : 0, 0x00020000);
+    u32x4_t w[D];
+    auto load_w = [&](int s, int i) __attribute__((always_inline)) { w[s] = __builtin_amdgcn_raw_buffer_load_b128(rw, lane * 16 + i * 1024, 0, 0); };
+#pragma unroll
+    for (int s = 0; s < D; ++s) load_w(s, s);
+    f32x4 acc[TG];
+#pragma unroll
+    for (int g = 0; g < TG; ++g) acc[g] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    u32x4_t xf[2][TG][2];
+    int buf = 0;
+    for (int c0 = 0; c0 < n_chunks; c0 += D / DX) {
+#pragma unroll
+        for (int h = 0; h < D / DX; ++h) {
+            const int c = c0 + h;
+            if (c >= n_chunks) break;   // (the same for the whole block)
+            block_sync_lds();
+            const u32x4_t *x = reinterpret_cast<const u32x4_t *>(xs) + (size_t)buf * UNITS * 64 + lane;
+            buf = buf + 1 == NB ? 0 : buf + 1;
+            auto read_x = [&](int k) __attribute__((always_inline)) {
+#pragma unroll
+                for (int g = 0; g < TG; ++g) {
+                    xf[k & 1][g][0] = x[((k * TG + g) * 2) * 64];
+                    xf[k & 1][g][1] = x[((k * TG + g) * 2 + 1) * 64];
+                }
+            };
+            read_x(0);
+#pragma unroll
+            for (int k = 0; k < DX; ++k) {
+                const int s = h * DX + k;
+                if (k + 1 < DX) read_x(k + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int hl = 0; hl < 2; ++hl)
+#pragma unroll
+                    for (int g = 0; g < TG; ++g)
+                        acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[s]), __builtin_bit_cast(bf16x8, xf[k & 1][g][hl]), acc[g], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                load_w(s, c * DX + k + D);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     }
+    prefill_finish<EPI, 1, TG>(a, tile, a.n_tiles, G0, reinterpret_cast<f32x4 (&)[1][TG]>(acc), sp);
 }
 
 // --------------------------------------------------------------- attention
 //
-// two floats rounded to bf16 (nearest even) side by side, one instruction
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
-{
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    typedef __bf16 b16x2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){a, b}, b16x2));
-}
-
 // Causal attention of the prompt rows over the cache (which by now holds the
 // prompt's own K and V).  Block = (head, two 16-row groups), four waves; wave w
 // takes the page pairs w, w + 4, ... and both row groups against each, the waves' running (maximum, denominator,
