@@ -275,8 +275,8 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
  *   out_logits (nullable, DEVICE, vocab floats): the last row's logits.
  *   workspace: DEVICE, 256-byte aligned, >= anpd_prefill_workspace_bytes(m, n_tokens) bytes,
  *   used only during the call (about 175 KB per token at the 7B shape).  Models on the
- *   generic path (ANPD_GEMM_DOT, f32 weights) process the prompt in windows of max_window rows and need no
- *   workspace: the size is 0 and workspace may be NULL.
+ *   generic path (ANPD_GEMM_DOT, f32 weights) process the prompt in pieces of up to 256 rows and need no
+ *   workspace beyond the model's: the size is 0 and workspace may be NULL.
  * Blocks until the result is on the host.
  * Errors: ANPD_E_RANGE (bad token), ANPD_E_CAPACITY (length + n_tokens > max_tokens, or the
  * workspace is too small), ANPD_E_INVAL, ANPD_E_HIP.  Nothing is launched on the first three. */
@@ -339,7 +339,7 @@ int32_t anpd_linear(const float *X, const void *W, float *Y, int32_t M, int32_t 
  * anpd_linear on path ANPD_GEMM_MFMA (bf16 weights packed by anpd_pack_weights), but the split form of X
  * is kept in a device array that is part of the library (2 MiB, held by every GPU the library runs on
  * until the process ends) instead of a workspace argument.  The call allocates and frees nothing and
- * calls no allocating routine; the array is cleared by a kernel, not by a memset.
+ * calls no allocating routine; every word of the array that it reads, its own kernel has written before.
  *   X, Y, W: DEVICE, as in anpd_linear.  1 <= M <= ANPD_MAX_WINDOW, N % 16 == 0, K % 8 == 0,
  *   K <= ANPD_LINEAR_STATIC_MAX_K (ANPD_E_CAPACITY beyond that, nothing is launched).
  * Asynchronous on stream.  All calls on one GPU share that GPU's array: calls that overlap on one GPU

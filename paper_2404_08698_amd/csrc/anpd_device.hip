@@ -43,7 +43,12 @@ struct Layout {  // byte offsets into the model workspace
     size_t xp_layers, xp_stride;   // the one-kernel step's operands (bytes; stride between the layers' sets in bf16 elements: 0, one set)
     std::vector<size_t> wp_qkv, wp_o, wp_gu, wp_down;
     int max_splits;
+    int gen_rows, gen_part_rows;   // generic path: most rows that go through a layer together, and of those through attention
 };
+
+// Models on the caller's weights take a prompt in pieces of up to this many rows (a step's kernels, more of their blocks).
+constexpr int kGenPieceRows = 256;
+constexpr size_t kGenPartBytes = (size_t)16 << 20;   // attention's partial results of a piece, where that is more than a window's
 
 bool wants_mfma(const anpd_model_cfg *c)
 {
@@ -91,14 +96,26 @@ Layout make_layout(const anpd_model_cfg *c)
     L.batch = take(ANPD_MAX_WINDOW * sizeof(int32_t) + ANPD_MAX_WINDOW * sizeof(SeqRef));   // batched step: sequence of every row, sequences
     // accepted, next, predictions, accepted path of a tree
     L.result = take((2 + ANPD_MAX_WINDOW + ANPD_MAX_WINDOW + 1) * sizeof(int32_t));
-    L.counter = take(32 * sizeof(uint32_t));   // (the word 16 on takes the length updates of a batch that go nowhere)
-    L.gen_ctr = take((size_t)c->n_heads * (ANPD_MAX_WINDOW / 16) * 64 * sizeof(uint32_t));
-    L.x = take(MW * d * 4);
-    L.qkv = take(MW * d * 4);
-    L.att = take(MW * d * 4);
-    L.a = take(MW * F * 4);
+    L.counter = take(sizeof(uint32_t));
+    // (the matrix-core path has a workspace of the caller's for prompts)
+    L.gen_rows = L.gen_part_rows = (int)MW;
+    const size_t part_row = (size_t)c->n_heads * L.max_splits * (c->head_dim + 2) * 4;
+    if (!wants_mfma(c)) {
+        const int longest = c->max_positions < kGenPieceRows ? c->max_positions : kGenPieceRows;
+        if (longest > L.gen_rows) L.gen_rows = longest;
+        const int rows = (int)(kGenPartBytes / part_row / 16 * 16);
+        if (rows > L.gen_part_rows) L.gen_part_rows = rows < L.gen_rows ? rows : L.gen_rows;
+        // (more than one launch of attention: each begins with a row group)
+        if (L.gen_part_rows < L.gen_rows && L.gen_part_rows % 16 != 0) L.gen_rows = L.gen_part_rows;
+    }
+    const size_t GR = (size_t)L.gen_rows;
+    L.gen_ctr = take((size_t)c->n_heads * ((L.gen_part_rows + 15) / 16) * 64 * sizeof(uint32_t));
+    L.x = take(GR * d * 4);
+    L.qkv = take(GR * d * 4);
+    L.att = take(GR * d * 4);
+    L.a = take(GR * F * 4);
     L.logits = take(MW * V * 4);
-    L.part = take((size_t)c->n_heads * L.max_splits * (wants_mfma(c) ? 32 : MW) * (c->head_dim + 2) * 4);
+    L.part = take(part_row * (wants_mfma(c) ? 32 : L.gen_part_rows));
     L.xp_d = L.xp_att = L.xp_f = L.ssp_a = L.ssp_b = L.split_part = L.qp = L.head_ctr = L.wp_lm = 0;
     L.layer_tab = L.amax = L.row_ctr = L.bar = 0;
     L.xp_layers = L.xp_stride = 0;
@@ -371,6 +388,13 @@ int32_t launch_residual(FastArgs &a, int n_cu, float *part, hipStream_t st)
     return ANPD_OK;
 }
 
+// the operand of anpd_linear (window class cls)
+void launch_split(const float *X, bf16_t *xp, int M, int K, int cls, hipStream_t st)
+{
+    const int nks = (K + 31) / 32;
+    hipLaunchKernelGGL(split_packed_kernel, dim3((unsigned)((4 * nks + 255) / 256), (unsigned)cls), dim3(256), 0, st, X, xp, M, K, nks, cls);
+}
+
 int32_t launch_pack(const void *s0, const void *s1, const void *s2, void *dst, int mode, int n_tiles, int K, int d,
                     int head_dim, int kvd, hipStream_t st)
 {
@@ -450,13 +474,43 @@ void collect_marks(anpd_model *m)
     m->prof_steps += 1;
 }
 
-// The generic step: per layer QKV (+ norm, RoPE, cache write) -> attention (+ merge) -> O (+ residual) -> gate/up
+StepTokens step_tokens(const int32_t *window, int n)
+{
+    StepTokens t;
+    for (int i = 0; i < ANPD_MAX_WINDOW; ++i) t.t[i] = i < n ? window[i] : 0;
+    return t;
+}
+
+// What the last kernel of a step writes, and where.
+AcceptArgs accept_args(anpd_model *m, int32_t *len_ptr)
+{
+    AcceptArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.result = (int32_t *)(m->ws + m->lay.result);
+    a.host_result = m->pin_dev + 32;
+    a.host_batch = m->pin_dev + 256;
+    a.len_ptr = len_ptr;
+    a.counter = (uint32_t *)(m->ws + m->lay.counter);
+    return a;
+}
+void launch_accept(int kind, const float *logits, int V, int M, const StepTokens &tok, int mode, const AcceptArgs &a, hipStream_t st)
+{
+#define ANPD_ACCEPT(K_) hipLaunchKernelGGL((argmax_accept_kernel<K_>), dim3((unsigned)M), dim3(1024), 0, st, logits, V, M, tok, mode, a)
+    if (kind == ACCEPT_TREE) ANPD_ACCEPT(ACCEPT_TREE);
+    else if (kind == ACCEPT_BATCH) ANPD_ACCEPT(ACCEPT_BATCH);
+    else ANPD_ACCEPT(ACCEPT_CHAIN);
+#undef ANPD_ACCEPT
+}
+
+// The generic forward: per layer QKV (+ norm, RoPE, cache write) -> attention (+ merge) -> O (+ residual) -> gate/up
 // (+ norm, SwiGLU) -> down (+ residual); then LM head (+ norm) -> argmax / accept.
 // tree: the window is a draft tree whose parent / depth / mask arrays are in the workspace.
-// cache_only: a piece of a prompt of which neither logits nor predictions are wanted.
+// piece: the rows are M tokens of a prompt (up to Layout::gen_rows), of which only the cache entries are wanted
+// (PIECE_CACHE) or, besides them, logits and prediction of the last row (PIECE_LAST).
+enum Piece { PIECE_NONE, PIECE_CACHE, PIECE_LAST };
 template <typename KT>
-int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, int mode, float *logits, hipStream_t st,
-                         bool tree = false, bool cache_only = false)
+int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int M, int mode, float *logits, hipStream_t st,
+                         bool tree = false, Piece piece = PIECE_NONE)
 {
     const anpd_model_cfg &c = m->cfg;
     const Layout &L = m->lay;
@@ -467,10 +521,8 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int 
     float *act = (float *)(ws + L.a), *part = (float *)(ws + L.part);
     uint32_t *attn_ctr = (uint32_t *)(ws + L.gen_ctr);
     int32_t *result = (int32_t *)(ws + L.result);
-    uint32_t *counter = (uint32_t *)(ws + L.counter);
     KT *pool = (KT *)kv->pool;
     const float scale = 1.0f / sqrtf((float)dh);
-    const int n_splits = (kv->len + M + kAttnSplit - 1) / kAttnSplit;
     const int32_t *t_parent = (const int32_t *)(ws + L.tree), *t_depth = tree ? t_parent + ANPD_MAX_WINDOW : nullptr;
     const uint32_t *t_mask = tree ? (const uint32_t *)(t_parent + 2 * ANPD_MAX_WINDOW) : nullptr;
     int32_t rc;
@@ -502,7 +554,11 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int 
 
     m->ev_used = 0;
     mark(m, -1, st);
-    hipLaunchKernelGGL((embed_kernel<KT>), dim3(M), dim3(256), 0, st, (const KT *)m->embed, tok, x, d);
+    // (the tokens by value, a window of them per launch)
+    for (int i = 0; i < M; i += c.max_window) {
+        const int n = M - i < c.max_window ? M - i : c.max_window;
+        hipLaunchKernelGGL((embed_kernel<KT>), dim3(n), dim3(256), 0, st, (const KT *)m->embed, step_tokens(tokens + i, n), x + (size_t)i * d, d);
+    }
     mark(m, ANPD_PROF_OTHER, st);
     for (int l = 0; l < c.n_layers; ++l) {
         {
@@ -513,13 +569,16 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int 
             if ((rc = launch_gen<KT, GEN_QKV>(g, (H + 2 * Hkv) * (dh / 32), st)) != ANPD_OK) return rc;
         }
         mark(m, ANPD_PROF_GEMM_QKV, st);
-        const dim3 grid((unsigned)H, (unsigned)n_splits, (unsigned)((M + 15) / 16));
-        if (dh == 128)
-            hipLaunchKernelGGL((attn_kernel<KT, 128>), grid, dim3(256), 0, st, q, d, pool, kv->d_table, kv->d_len, M, l, c.n_layers, H, Hkv,
-                               c.page_tokens, c.max_window, L.max_splits, scale, part, attn_ctr, att, t_mask);
-        else
-            hipLaunchKernelGGL((attn_kernel<KT, 64>), grid, dim3(256), 0, st, q, d, pool, kv->d_table, kv->d_len, M, l, c.n_layers, H, Hkv,
-                               c.page_tokens, c.max_window, L.max_splits, scale, part, attn_ctr, att, t_mask);
+        for (int row0 = 0; row0 < M; row0 += L.gen_part_rows) {
+            const int end = M - row0 < L.gen_part_rows ? M : row0 + L.gen_part_rows;
+            const dim3 grid((unsigned)H, (unsigned)((kv->len + end + kAttnSplit - 1) / kAttnSplit), (unsigned)((end - row0 + 15) / 16));
+#define ANPD_ATTN_G(DH_)                                                                                                          \
+    hipLaunchKernelGGL((attn_kernel<KT, DH_>), grid, dim3(256), 0, st, q, d, pool, kv->d_table, kv->d_len, end, l, c.n_layers, H, Hkv, \
+                       c.page_tokens, row0, L.gen_part_rows, L.max_splits, scale, part, attn_ctr, att, t_mask)
+            if (dh == 128) ANPD_ATTN_G(128);
+            else ANPD_ATTN_G(64);
+#undef ANPD_ATTN_G
+        }
         mark(m, ANPD_PROF_ATTN, st);
         if ((rc = launch_gen_few<KT, GEN_RESIDUAL>(gemm(att, d, m->wo[l], nullptr, x, d), d / 16, m->n_cu, st)) != ANPD_OK) return rc;
         mark(m, ANPD_PROF_GEMM_O, st);
@@ -532,21 +591,24 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int 
         if ((rc = launch_gen_few<KT, GEN_RESIDUAL>(gemm(act, F, m->w_down[l], nullptr, x, d), d / 16, m->n_cu, st)) != ANPD_OK) return rc;
         mark(m, ANPD_PROF_GEMM_DOWN, st);
     }
-    if (cache_only) {
+    if (piece == PIECE_CACHE) {
         hipLaunchKernelGGL(advance_length_kernel, dim3(1), dim3(64), 0, st, kv->d_len, M);
         mark(m, ANPD_PROF_OTHER, st);
         HIP_TRY(hipGetLastError());
         return ANPD_OK;
     }
-    if ((rc = launch_gen_few<KT, GEN_LOGITS>(gemm(x, d, m->lm_head, m->final_norm, logits, V), V / 16, m->n_cu, st)) != ANPD_OK) return rc;
+    const int before = piece == PIECE_LAST ? M - 1 : 0;   // rows in front of the first whose logits are wanted
+    base.M = M - before;
+    if ((rc = launch_gen_few<KT, GEN_LOGITS>(gemm(x + (size_t)before * d, d, m->lm_head, m->final_norm, logits, V), V / 16, m->n_cu, st)) != ANPD_OK) return rc;
     mark(m, ANPD_PROF_GEMM_LM_HEAD, st);
-    hipLaunchKernelGGL(argmax_accept_kernel, dim3(M), dim3(1024), 0, st, logits, V, M, tok, mode, result, m->pin_dev + 32, kv->d_len,
-                       counter);
-    if (tree) {
-        hipLaunchKernelGGL(accept_tree_kernel, dim3(1), dim3(64), 0, st, tok, t_parent, t_depth, M, result, m->pin_dev + 32, kv->d_len, kv->len);
+    AcceptArgs ac = accept_args(m, kv->d_len);
+    ac.before = before;
+    ac.parent = t_parent;
+    ac.depth = t_depth;
+    launch_accept(tree ? ACCEPT_TREE : ACCEPT_CHAIN, logits, V, M - before, step_tokens(tokens + before, M - before), mode, ac, st);
+    if (tree)
         hipLaunchKernelGGL((kv_compact_kernel<KT>), dim3((unsigned)(c.n_layers * 2 * Hkv)), dim3(128), 0, st, pool, kv->d_table,
                            (const int32_t *)result, kv->len, c.n_layers, Hkv, dh, c.page_tokens);
-    }
     mark(m, ANPD_PROF_OTHER, st);
     HIP_TRY(hipGetLastError());
     return ANPD_OK;
@@ -575,14 +637,12 @@ int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, 
     bf16_t *xp_d = (bf16_t *)(ws + L.xp_d), *xp_att = (bf16_t *)(ws + L.xp_att), *xp_f = (bf16_t *)(ws + L.xp_f);
     float *ssp_a = (float *)(ws + L.ssp_a), *ssp_b = (float *)(ws + L.ssp_b), *split_part = (float *)(ws + L.split_part);
     int32_t *result = (int32_t *)(ws + L.result);
-    uint32_t *counter = (uint32_t *)(ws + L.counter);
     const float scale = 1.0f / sqrtf((float)dh);
     const int n_splits = batch ? batch->grid_splits : n_splits_of(kv->len + M);
     const bool one_page = n_splits <= kSmallSplits;
     const int nks_d = (d + 31) / 32, nks_f = (F + 31) / 32;
     const int32_t *b_row_seq = (const int32_t *)(ws + L.batch);
     const SeqRef *b_seqs = (const SeqRef *)(ws + L.batch + ANPD_MAX_WINDOW * sizeof(int32_t));
-    int32_t *dummy_len = (int32_t *)(ws + L.counter) + 16;   // the per-row argmax kernel's length update goes nowhere in a batch
     const int32_t *t_parent = (const int32_t *)(ws + L.tree), *t_depth = t_parent + ANPD_MAX_WINDOW;
     const uint32_t *t_mask = (const uint32_t *)(t_parent + 2 * ANPD_MAX_WINDOW);
     int32_t rc;
@@ -713,14 +773,15 @@ int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, 
         if ((rc = launch_fast<EPI_LOGITS>(a, m->n_cu, false, st)) != ANPD_OK) return rc;
     }
     mark(m, ANPD_PROF_GEMM_LM_HEAD, st);
-    hipLaunchKernelGGL(argmax_accept_kernel, dim3(M), dim3(1024), 0, st, logits, V, M, tok, batch ? (int)ANPD_APPEND : mode, result,
-                       m->pin_dev + 32, batch ? dummy_len : kv->d_len, counter);
-    if (batch) hipLaunchKernelGGL(accept_batch_kernel, dim3(1), dim3(64), 0, st, tok, b_seqs, batch->n_seq, mode, (const int32_t *)result, m->pin_dev + 256);
-    if (tree) {
-        hipLaunchKernelGGL(accept_tree_kernel, dim3(1), dim3(64), 0, st, tok, t_parent, t_depth, M, result, m->pin_dev + 32, kv->d_len, kv->len);
+    AcceptArgs ac = accept_args(m, batch ? nullptr : kv->d_len);
+    ac.parent = t_parent;
+    ac.depth = t_depth;
+    ac.seqs = b_seqs;
+    ac.n_seq = batch ? batch->n_seq : 0;
+    launch_accept(batch ? ACCEPT_BATCH : (tree ? ACCEPT_TREE : ACCEPT_CHAIN), logits, V, M, tok, mode, ac, st);
+    if (tree)
         hipLaunchKernelGGL(kvf_compact_kernel, dim3((unsigned)(c.n_layers * 2 * Hkv)), dim3(128), 0, st, (bf16_t *)kv->pool,
                            kv->d_table, (const int32_t *)result, kv->len, c.n_layers, Hkv, dh);
-    }
     mark(m, ANPD_PROF_OTHER, st);
     HIP_TRY(hipGetLastError());
     return ANPD_OK;
@@ -1073,8 +1134,7 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
         if ((rc = launch_fast<EPI_LOGITS>(a, m->n_cu, false, st)) != ANPD_OK) return rc;
     }
     mark(m, ANPD_PROF_GEMM_LM_HEAD, st);
-    hipLaunchKernelGGL(argmax_accept_kernel, dim3(1), dim3(1024), 0, st, (const float *)logits, V, 1, StepTokens(),
-                       (int)ANPD_APPEND, (int32_t *)(ws + L.result), m->pin_dev + 32, kv->d_len, (uint32_t *)(ws + L.counter));
+    launch_accept(ACCEPT_CHAIN, logits, V, 1, StepTokens(), (int)ANPD_APPEND, accept_args(m, kv->d_len), st);
     mark(m, ANPD_PROF_OTHER, st);
     HIP_TRY(hipGetLastError());
     return ANPD_OK;
@@ -1096,13 +1156,6 @@ float *logits_target(const anpd_model *m, float *out_logits, size_t n)
     }
     const bool fits = (char *)out_logits + n * sizeof(float) <= (char *)base + size;
     return at.type == hipMemoryTypeDevice && at.device == m->device && fits ? out_logits : own;
-}
-
-StepTokens step_tokens(const int32_t *window, int n)
-{
-    StepTokens t;
-    for (int i = 0; i < ANPD_MAX_WINDOW; ++i) t.t[i] = i < n ? window[i] : 0;
-    return t;
 }
 
 // After the stream has been synchronised: did a grid barrier of the one-kernel step give up?  Then the
@@ -1498,8 +1551,8 @@ int32_t anpd_verify(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, int32
     float *logits = logits_target(m, out_logits, (size_t)n_window * m->cfg.vocab);
     if (one_kernel) rc = run_step_mega(m, kv, window, n_window, mode, out_logits ? logits : nullptr, st);
     else if (m->mfma) rc = run_step_fast(m, kv, step_tokens(window, n_window), n_window, mode, logits, st);
-    else if (m->cfg.dtype == ANPD_BF16) rc = run_step_generic<bf16_t>(m, kv, step_tokens(window, n_window), n_window, mode, logits, st);
-    else rc = run_step_generic<float>(m, kv, step_tokens(window, n_window), n_window, mode, logits, st);
+    else if (m->cfg.dtype == ANPD_BF16) rc = run_step_generic<bf16_t>(m, kv, window, n_window, mode, logits, st);
+    else rc = run_step_generic<float>(m, kv, window, n_window, mode, logits, st);
     if (rc != ANPD_OK) return rc;
     if (out_logits && out_logits != logits)
         HIP_TRY(hipMemcpyAsync(out_logits, logits, sizeof(float) * (size_t)n_window * m->cfg.vocab, hipMemcpyDeviceToDevice, st));
@@ -1554,11 +1607,12 @@ int32_t anpd_verify_tree(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, 
     if (one_kernel) {
         rc = run_step_mega(m, kv, window, n_window, ANPD_APPEND, out_logits ? logits : nullptr, st, tp);
     } else {
-        const StepTokens tok = step_tokens(window, n_window);
-        HIP_TRY(hipMemcpyAsync(m->ws + m->lay.tree, tp, sizeof(int32_t) * 3 * ANPD_MAX_WINDOW, hipMemcpyHostToDevice, st));
-        if (m->mfma) rc = run_step_fast(m, kv, tok, n_window, ANPD_APPEND, logits, st, true);
-        else if (m->cfg.dtype == ANPD_BF16) rc = run_step_generic<bf16_t>(m, kv, tok, n_window, ANPD_APPEND, logits, st, true);
-        else rc = run_step_generic<float>(m, kv, tok, n_window, ANPD_APPEND, logits, st, true);
+        UploadWords up;
+        std::memcpy(up.w, tp, sizeof(int32_t) * 3 * ANPD_MAX_WINDOW);
+        hipLaunchKernelGGL(upload_kernel, dim3(1), dim3(kUploadWords), 0, st, (uint32_t *)(m->ws + m->lay.tree), up, 3 * ANPD_MAX_WINDOW);
+        if (m->mfma) rc = run_step_fast(m, kv, step_tokens(window, n_window), n_window, ANPD_APPEND, logits, st, true);
+        else if (m->cfg.dtype == ANPD_BF16) rc = run_step_generic<bf16_t>(m, kv, window, n_window, ANPD_APPEND, logits, st, true);
+        else rc = run_step_generic<float>(m, kv, window, n_window, ANPD_APPEND, logits, st, true);
     }
     if (rc != ANPD_OK) return rc;
     if (out_logits && out_logits != logits)
@@ -1656,9 +1710,12 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
         MegaBatch mb = {n_seq, seqs, row_seq, lens};
         rc = run_step_mega(m, nullptr, m->pin, total, mode, out_logits ? logits : nullptr, st, nullptr, &mb);
     } else {
-        HIP_TRY(hipMemcpyAsync(m->ws + m->lay.batch, row_seq, sizeof(int32_t) * (size_t)total, hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMemcpyAsync(m->ws + m->lay.batch + ANPD_MAX_WINDOW * sizeof(int32_t), seqs, sizeof(SeqRef) * (size_t)n_seq,
-                               hipMemcpyHostToDevice, st));
+        // sequence of every row, then the sequences (Layout::batch)
+        static_assert(sizeof(SeqRef) % 4 == 0 && sizeof(UploadWords) == ANPD_MAX_WINDOW * (sizeof(int32_t) + sizeof(SeqRef)), "a batch's description");
+        UploadWords up;
+        std::memcpy(up.w, row_seq, ANPD_MAX_WINDOW * sizeof(int32_t));
+        std::memcpy(up.w + ANPD_MAX_WINDOW, seqs, ANPD_MAX_WINDOW * sizeof(SeqRef));
+        hipLaunchKernelGGL(upload_kernel, dim3(1), dim3(kUploadWords), 0, st, (uint32_t *)(m->ws + m->lay.batch), up, kUploadWords);
         rc = run_step_fast(m, nullptr, step_tokens(m->pin, total), total, mode, logits, st, false, &bl);
     }
     if (rc != ANPD_OK) return rc;
@@ -1700,34 +1757,31 @@ int32_t anpd_prefill(anpd_model_t *m, anpd_kv_t *kv, const int32_t *tokens, int3
     const size_t V = (size_t)m->cfg.vocab;
 
     if (!m->mfma) {
-        // models on the caller's weights: the prompt goes through the step in windows of max_window appended rows, all
-        // enqueued before the first is waited for; logits and prediction of the last row only
+        // models on the caller's weights: the prompt goes through the step's kernels in pieces of up to kGenPieceRows
+        // appended rows, all enqueued before the first is waited for; logits and prediction of the last row only
         const int32_t len0 = kv->len;
-        auto windows = [&]() -> int32_t {
+        auto pieces = [&]() -> int32_t {
             int32_t rc = ensure_pages(kv, len0 + n_tokens, st);
             if (rc != ANPD_OK) return rc;
-            float *logits = (float *)(m->ws + m->lay.logits);
-            int last_n = 0;
-            for (int i = 0; i < n_tokens; i += last_n) {
-                last_n = n_tokens - i < m->cfg.max_window ? n_tokens - i : m->cfg.max_window;
-                const bool more = i + last_n < n_tokens;
-                const StepTokens tok = step_tokens(tokens + i, last_n);
-                rc = m->cfg.dtype == ANPD_BF16 ? run_step_generic<bf16_t>(m, kv, tok, last_n, ANPD_APPEND, logits, st, false, more)
-                                               : run_step_generic<float>(m, kv, tok, last_n, ANPD_APPEND, logits, st, false, more);
+            float *logits = logits_target(m, out_logits, V);
+            for (int i = 0, n; i < n_tokens; i += n) {
+                n = n_tokens - i < m->lay.gen_rows ? n_tokens - i : m->lay.gen_rows;
+                const Piece piece = i + n < n_tokens ? PIECE_CACHE : PIECE_LAST;
+                rc = m->cfg.dtype == ANPD_BF16 ? run_step_generic<bf16_t>(m, kv, tokens + i, n, ANPD_APPEND, logits, st, false, piece)
+                                               : run_step_generic<float>(m, kv, tokens + i, n, ANPD_APPEND, logits, st, false, piece);
                 if (rc != ANPD_OK) return rc;
-                kv->len += last_n;
+                kv->len += n;
                 if (m->prof) {
                     HIP_TRY(hipStreamSynchronize(st));
                     collect_marks(m);
                 }
             }
-            if (out_logits)
-                HIP_TRY(hipMemcpyAsync(out_logits, logits + (size_t)(last_n - 1) * V, V * sizeof(float), hipMemcpyDeviceToDevice, st));
+            if (out_logits && out_logits != logits) HIP_TRY(hipMemcpyAsync(out_logits, logits, V * sizeof(float), hipMemcpyDeviceToDevice, st));
             HIP_TRY(hipStreamSynchronize(st));
             return ANPD_OK;
         };
-        if (const int32_t rc = windows(); rc != ANPD_OK) {
-            // some windows may have run, some not: the cache is what it was, on the host and on the device
+        if (const int32_t rc = pieces(); rc != ANPD_OK) {
+            // some pieces may have run, some not: the cache is what it was, on the host and on the device
             (void)hipStreamSynchronize(st);
             kv->len = len0;
             kv->pin[0] = len0;
@@ -1814,8 +1868,7 @@ int32_t anpd_linear(const float *X, const void *W, float *Y, int32_t M, int32_t 
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0)
         n_cu = prop.multiProcessorCount;
     const int cls = window_class(M);
-    HIP_TRY(hipMemsetAsync(workspace, 0, anpd_linear_workspace_bytes(M, K), st));
-    hipLaunchKernelGGL(split_packed_kernel, dim3((K / 4 + 255) / 256, M), dim3(256), 0, st, X, (bf16_t *)workspace, M, K, cls);
+    launch_split(X, (bf16_t *)workspace, M, K, cls, st);
     FastArgs a;
     std::memset(&a, 0, sizeof(a));
     a.Wp = (const uint4 *)W;
@@ -1851,13 +1904,6 @@ StaticScratch g_static_scratch[kMaxDevices];   // zero-initialised: ptr == nullp
 
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
-// Clears `n16` 16-byte words (a kernel rather than a memset node, so that a caller may capture the call).
-__global__ __launch_bounds__(256) void fill_zero_kernel(uint4 *p, size_t n16)
-{
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n16) p[i] = make_uint4(0, 0, 0, 0);
-}
-
 extern "C" int32_t anpd_linear_static(const float *X, const void *W, float *Y, int32_t M, int32_t N, int32_t K, void *stream)
 {
     if (!X || !W || !Y) return fail(ANPD_E_INVAL, "anpd_linear_static: NULL argument");
@@ -1883,10 +1929,7 @@ extern "C" int32_t anpd_linear_static(const float *X, const void *W, float *Y, i
     }
     hipStream_t st = (hipStream_t)stream;
     const int cls = window_class(M);
-    // the array keeps the previous call's operand: rows and k-steps this call does not write must read as zeros
-    const size_t n16 = need / 16;
-    hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, st, (uint4 *)sc.ptr, n16);
-    hipLaunchKernelGGL(split_packed_kernel, dim3((K / 4 + 255) / 256, M), dim3(256), 0, st, X, (bf16_t *)sc.ptr, M, K, cls);
+    launch_split(X, (bf16_t *)sc.ptr, M, K, cls, st);
     FastArgs a;
     std::memset(&a, 0, sizeof(a));
     a.Wp = (const uint4 *)W;

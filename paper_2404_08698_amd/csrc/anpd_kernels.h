@@ -249,6 +249,17 @@ struct StepTokens {
     int32_t t[kMaxRows];
 };
 
+// Puts what a step needs in device memory - a draft tree, the sequences of a batch - there from the kernel's arguments.
+// (Copies from pinned memory, two for a batch, are launches of their own, and longer ones.)   grid: 1 block
+constexpr int kUploadWords = 32 + 32 * 8;
+struct UploadWords {
+    uint32_t w[kUploadWords];
+};
+__global__ __launch_bounds__(kUploadWords) void upload_kernel(uint32_t *__restrict__ dst, UploadWords words, int n)
+{
+    if ((int)threadIdx.x < n) dst[threadIdx.x] = words.w[threadIdx.x];
+}
+
 // Page layout of the generic path: [page][layer][k|v][head][token in page][head_dim].
 __device__ __forceinline__ size_t kv_offset(int page, int layer, int n_layers, int kv, int head, int n_heads,
                                             int tok_in_page, int page_tokens, int head_dim)
@@ -259,7 +270,7 @@ __device__ __forceinline__ size_t kv_offset(int page, int layer, int n_layers, i
 
 // ------------------------------------------------------------------ embed
 
-// x[r][:] = E[token[r]][:]   grid: M blocks
+// x[r][:] = E[token[r]][:]   grid: rows (at most kMaxRows)
 template <typename WT>
 __global__ __launch_bounds__(256) void embed_kernel(const WT *__restrict__ E, StepTokens tok, float *__restrict__ x, int d)
 {
@@ -518,14 +529,15 @@ __global__ __launch_bounds__(512, FEW && MODE != GEN_RESIDUAL ? (gen_norm(MODE) 
 // the fp32 matrix cores; the last block of a (head, row group) merges the splits of its rows in increasing
 // order.  Row r sees keys 0..len + r; keys it must not see get
 // weight exactly 0, so a row's numbers do not depend on M.
-// part: outputs [head][split][max_window][DH], then (maximum, denominator) [head][split][max_window][2].
-// counter: [head][row group], a 256-byte line each, zero between calls.
-// grid: (n_heads, n_splits, ceil(M / 16)), 4 waves.
+// A long window is gone through in launches of at most part_rows rows, of which this one takes those from row0 on.
+// part: outputs [head][split][part_rows][DH], then (maximum, denominator) [head][split][part_rows][2].
+// counter: [row group][head], a 256-byte line each, zero between calls.
+// grid: (n_heads, n_splits, row groups), 4 waves.
 template <typename KT, int DH>
 __global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ q, int q_stride, const KT *__restrict__ pool,
                                                     const int32_t *__restrict__ page_table,
                                                     const int32_t *__restrict__ len_ptr, int M, int layer, int n_layers,
-                                                    int n_heads, int n_kv_heads, int page_tokens, int max_window,
+                                                    int n_heads, int n_kv_heads, int page_tokens, int row0, int part_rows,
                                                     int max_splits, float scale, float *__restrict__ part,
                                                     uint32_t *__restrict__ counter, float *__restrict__ att,
                                                     const uint32_t *__restrict__ row_mask /* draft tree: nullable */)
@@ -534,11 +546,11 @@ __global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ q, 
     __shared__ float red[WAVES][NC][64][4];
     __shared__ float wmax[WAVES][16], wden[WAVES][16];
     __shared__ bool last;
-    const int head = blockIdx.x, split = blockIdx.y, m0 = 16 * blockIdx.z;
+    const int head = blockIdx.x, split = blockIdx.y, m0 = row0 + 16 * blockIdx.z;
     const int kvh = head / (n_heads / n_kv_heads);   // the key / value head this query head reads
     const int L = *len_ptr;
-    const int n_splits = (L + M + kAttnSplit - 1) / kAttnSplit;
-    if (split >= n_splits) return;  // no key of this split exists for any row
+    const int n_splits = (L + (m0 + 16 < M ? m0 + 16 : M) + kAttnSplit - 1) / kAttnSplit;
+    if (split >= n_splits) return;  // no row of the group sees a key of this split
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 15, kg = lane >> 4;
     const int key0 = split * kAttnSplit + 16 * wave, m = m0 + r;
 
@@ -616,24 +628,24 @@ __global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ q, 
         *reinterpret_cast<f32x4 *>(red[wave][c][lane]) = (o[0] + o[1]) + (o[2] + o[3]);
     }
     __syncthreads();
-    const size_t slot0 = ((size_t)head * max_splits) * max_window, stride = (size_t)max_window;   // rows of (head, split 0); rows per split
-    float *po = part, *ps = part + (size_t)n_heads * max_splits * max_window * DH;
+    const size_t slot0 = ((size_t)head * max_splits) * part_rows, stride = (size_t)part_rows;   // rows of (head, split 0); rows per split
+    float *po = part, *ps = part + (size_t)n_heads * max_splits * part_rows * DH;
     for (int c = wave; c < NC; c += WAVES) {
         f32x4 o = *reinterpret_cast<const f32x4 *>(red[0][c][lane]);
 #pragma unroll
         for (int v = 1; v < WAVES; ++v) o += *reinterpret_cast<const f32x4 *>(red[v][c][lane]);
-        if (m < M) stc16<true>(po + (slot0 + split * stride + m) * DH + 16 * c + 4 * kg, o);
+        if (m < M) stc16<true>(po + (slot0 + split * stride + (m - row0)) * DH + 16 * c + 4 * kg, o);
     }
     if (wave == 0 && kg == 0 && m < M) {
         float d = wden[0][r];
 #pragma unroll
         for (int v = 1; v < WAVES; ++v) d += wden[v][r];
-        stc8<true>(ps + (slot0 + split * stride + m) * 2, make_uint2(__float_as_uint(bm), __float_as_uint(d)));
+        stc8<true>(ps + (slot0 + split * stride + (m - row0)) * 2, make_uint2(__float_as_uint(bm), __float_as_uint(d)));
     }
     // ---- the last block of this head and row group merges the splits
     wait_stores();
     __syncthreads();
-    uint32_t *ctr = counter + ((size_t)head * (kMaxRows / 16) + blockIdx.z) * 64;
+    uint32_t *ctr = counter + ((size_t)blockIdx.z * n_heads + head) * 64;
     if (threadIdx.x == 0)
         last = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == (uint32_t)n_splits;
     __syncthreads();
@@ -650,7 +662,7 @@ __global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ q, 
         for (int s0 = 0; s0 < ns; s0 += SB) {
             float mv[SB];
 #pragma unroll
-            for (int j = 0; j < SB; ++j) mv[j] = __uint_as_float(ld8_at<true>(s2 + slot0, (uint32_t)((s0 + j < ns ? s0 + j : s0) * stride + row)).x);
+            for (int j = 0; j < SB; ++j) mv[j] = __uint_as_float(ld8_at<true>(s2 + slot0, (uint32_t)((s0 + j < ns ? s0 + j : s0) * stride + (row - row0))).x);
 #pragma unroll
             for (int j = 0; j < SB; ++j) g = fmaxf(g, mv[j]);
         }
@@ -661,7 +673,7 @@ __global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ q, 
             uint2 st[SB];
 #pragma unroll
             for (int j = 0; j < SB; ++j) {
-                const uint32_t at = (uint32_t)((s0 + j < ns ? s0 + j : s0) * stride + row);
+                const uint32_t at = (uint32_t)((s0 + j < ns ? s0 + j : s0) * stride + (row - row0));
                 ov[j] = ld16_at<true>(o4 + slot0 * DQ, at * DQ + e4);
                 st[j] = ld8_at<true>(s2 + slot0, at);
             }
@@ -689,26 +701,60 @@ __global__ void advance_length_kernel(int32_t *__restrict__ len_ptr, int n)
 
 // ------------------------------------------- argmax + acceptance + commit
 //
-// Block r finds argmax(logits[r]) (lowest index among equal maxima).  The last
-// block to finish applies Algorithm 1's accept rule: a = longest prefix with
-// window[i + 1] == pred[i]; next = pred[a]; the cache length advances by 1 + a
-// (rejected rows are simply left beyond the length and overwritten later).
-// result: [0] = a, [1] = next, [2..2+M) = pred; host_result: the same in pinned host memory, so that no copy
-// follows.   grid: M blocks of 1024.
+// Block r finds argmax(logits[r]) (lowest index among equal maxima); the last block to finish decides what is accepted,
+// advances the cache length and writes the result.  KIND:
+//   chain: Algorithm 1's rule: a = longest prefix with window[i + 1] == pred[i], next = pred[a], length += before + 1 + a
+//     (rejected rows are simply left beyond the length and overwritten later; before: rows of the same prompt piece
+//     in front of the first).  mode 1 accepts every row.
+//   tree: row r > 0 is accepted iff its parent is and window[r] equals the prediction made at the parent; the deepest
+//     accepted row wins (lowest index among equally deep); result[34 + j] = the row at depth j of the accepted path.
+//   batch: the chain's rule inside every sequence's own rows, each sequence's length advanced.
+// result: [0] = a, [1] = next, [2..2+M) = pred; host_result, host_batch (accepted, next of every sequence): in pinned host
+// memory, so that no copy follows.
+// One row is one block's loads: 16 bytes per thread and eight of them in flight (one value per thread and load took 14.6 us
+// for 17 rows at a vocabulary of 32000 and 24.3 for one at 65024; 7.7 and 8.7 now), and the last block's rules are one
+// lane per row or sequence (a launch of its own for a batch or a tree took 9 and 4.5 us more).   grid: M blocks of 1024.
+enum { ACCEPT_CHAIN = 0, ACCEPT_TREE = 1, ACCEPT_BATCH = 2 };
+// One sequence of a batched step: its cache and the window rows it owns (consecutive rows of the joint window).
+struct SeqRef {
+    bf16_t *pool;
+    const int32_t *page_table;
+    int32_t *len_ptr;
+    int32_t row0, n_rows;
+};
+struct AcceptArgs {
+    int32_t *result, *host_result, *len_ptr;
+    uint32_t *counter;
+    int before;                       // chain
+    const int32_t *parent, *depth;    // tree
+    const SeqRef *seqs;               // batch
+    int n_seq;
+    int32_t *host_batch;
+};
+template <int KIND>
 __global__ __launch_bounds__(1024) void argmax_accept_kernel(const float *__restrict__ logits, int V, int M, StepTokens window,
-                                                              int mode, int32_t *__restrict__ result, int32_t *__restrict__ host_result,
-                                                              int32_t *__restrict__ len_ptr, uint32_t *__restrict__ counter)
+                                                              int mode, AcceptArgs a)
 {
     __shared__ float bv[16];
     __shared__ int bi[16];
     __shared__ bool last;
     const int r = blockIdx.x;
-    const float *row = logits + (size_t)r * V;
+    const f32x4 *row = reinterpret_cast<const f32x4 *>(logits + (size_t)r * V);   // (V is a multiple of 16, logits are 16-byte aligned)
     float best = -INFINITY;
     int besti = 0x7fffffff;
-    for (int i = threadIdx.x; i < V; i += 1024) {
-        float v = row[i];
-        if (v > best || besti == 0x7fffffff) { best = v; besti = i; }
+    constexpr int U = 8;
+    for (int i0 = threadIdx.x; i0 < V / 4; i0 += 1024 * U) {
+        f32x4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + 1024 * u < V / 4) v[u] = row[i0 + 1024 * u];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (i0 + 1024 * u >= V / 4) break;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (v[u][j] > best || besti == 0x7fffffff) { best = v[u][j]; besti = 4 * (i0 + 1024 * u) + j; }
+        }
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
@@ -721,59 +767,66 @@ __global__ __launch_bounds__(1024) void argmax_accept_kernel(const float *__rest
     if (threadIdx.x == 0) {
         for (int w = 1; w < 16; ++w)
             if (bv[w] > best || (bv[w] == best && bi[w] < besti)) { best = bv[w]; besti = bi[w]; }
-        st_agent(result + 2 + r, (int32_t)besti);
+        st_agent(a.result + 2 + r, (int32_t)besti);
         wait_stores();
-        last = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(M - 1);
-        st_system(host_result + 2 + r, (int32_t)besti);   // (after the counter: its way to the host is long)
+        last = __hip_atomic_fetch_add(a.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(M - 1);
+        st_system(a.host_result + 2 + r, (int32_t)besti);   // (after the counter: its way to the host is long)
     }
     __syncthreads();
-    if (last && threadIdx.x == 0) {
-        const int32_t *pred = result + 2;
-        int a = 0;
-        if (mode == 0) {
-            while (a < M - 1 && window.t[a + 1] == ld_agent(pred + a)) ++a;
-        } else {
-            a = M - 1;
+    if (!last || threadIdx.x >= 64) return;
+    const int lane = threadIdx.x;
+    const int32_t pred = ld_agent(a.result + 2 + (lane < M ? lane : 0));
+    if (KIND == ACCEPT_CHAIN || KIND == ACCEPT_BATCH) {
+        // bit m: the token of row m + 1 is not the prediction made at row m
+        const unsigned long long wrong = __builtin_amdgcn_ballot_w64(lane + 1 < M && window.t[lane + 1 < M ? lane + 1 : 0] != pred);
+        constexpr bool seq = KIND == ACCEPT_BATCH;
+        const bool mine = lane < (seq ? a.n_seq : 1);
+        const int r0 = seq && mine ? a.seqs[lane].row0 : 0, n = seq ? (mine ? a.seqs[lane].n_rows : 1) : M;
+        const unsigned long long end = 1ull << (n - 1);   // the last row's prediction has no token to match
+        const int acc = mode == 0 ? __builtin_ctzll((wrong >> r0) | end) : n - 1;
+        const int32_t next = __shfl(pred, r0 + acc, kWave);
+        if (mine && seq) {
+            st_system(a.host_batch + 2 * lane, (int32_t)acc);
+            st_system(a.host_batch + 2 * lane + 1, next);
+            *a.seqs[lane].len_ptr += 1 + acc;
+        } else if (mine) {
+            a.result[0] = acc;
+            a.result[1] = next;
+            st_system(a.host_result, (int32_t)acc);
+            st_system(a.host_result + 1, next);
+            *a.len_ptr += a.before + 1 + acc;
         }
-        result[0] = a;
-        result[1] = ld_agent(pred + a);
-        st_system(host_result, a);
-        st_system(host_result + 1, ld_agent(pred + a));
-        *len_ptr += 1 + a;
-        st_agent(counter, 0u);
-    }
-}
-
-// Acceptance over a draft tree, after argmax_accept_kernel has left the per-row predictions in
-// result[2..] (run in APPEND mode on a copy of the length).  Row r > 0 is accepted iff its parent
-// is and window[r] equals the prediction made at the parent; the deepest accepted row wins (lowest
-// index among equally deep).  result[0] = its depth a, result[1] = the prediction at that row,
-// result[34 + j] = the window row at depth j of the accepted path; length += 1 + a.   One thread.
-__global__ void accept_tree_kernel(StepTokens window, const int32_t *__restrict__ parent,
-                                   const int32_t *__restrict__ depth, int M, int32_t *__restrict__ result,
-                                   int32_t *__restrict__ host_result, int32_t *__restrict__ len_ptr, int len_before)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const int32_t *pred = result + 2;
-    uint32_t acc = 1u;
-    int best = 0;
-    for (int r = 1; r < M; ++r) {
-        const int p = parent[r];
-        if (((acc >> p) & 1u) && window.t[r] == pred[p]) {
-            acc |= 1u << r;
-            if (depth[r] > depth[best]) best = r;
+    } else {
+        const int p = lane > 0 && lane < M ? a.parent[lane] : 0, depth = lane < M ? a.depth[lane] : 0;
+        // whether this row's token is the prediction made at its parent
+        const int32_t at_parent = __shfl(pred, p, kWave);
+        const unsigned long long right = __builtin_amdgcn_ballot_w64(lane > 0 && lane < M && window.t[lane < M ? lane : 0] == at_parent);
+        unsigned long long ok = 1ull;
+        int best_row = 0, best_depth = 0;
+        for (int q = 1; q < M; ++q) {
+            const int parent = __builtin_amdgcn_readlane(p, q), d = __builtin_amdgcn_readlane(depth, q);
+            if (((ok >> parent) & 1ull) && ((right >> q) & 1ull)) {
+                ok |= 1ull << q;
+                if (d > best_depth) { best_row = q; best_depth = d; }
+            }
+        }
+        const int32_t next = __builtin_amdgcn_readlane(pred, best_row);
+        for (int q = best_row, j = best_depth; j >= 0; --j) {
+            if (lane == 0) {
+                a.result[34 + j] = q;
+                st_system(a.host_result + 34 + j, (int32_t)q);
+            }
+            q = __builtin_amdgcn_readlane(p, q);
+        }
+        if (lane == 0) {
+            a.result[0] = best_depth;
+            a.result[1] = next;
+            st_system(a.host_result, (int32_t)best_depth);
+            st_system(a.host_result + 1, next);
+            *a.len_ptr += 1 + best_depth;
         }
     }
-    const int a = depth[best];
-    for (int r = best, j = a; j >= 0; --j, r = parent[r]) {
-        result[34 + j] = r;
-        st_system(host_result + 34 + j, r);
-    }
-    result[0] = a;
-    result[1] = pred[best];
-    st_system(host_result, a);
-    st_system(host_result + 1, pred[best]);
-    *len_ptr = len_before + 1 + a;
+    if (lane == 0) st_agent(a.counter, 0u);
 }
 
 // Generic-layout counterpart of kvf_compact_kernel.   grid: n_layers * 2 * n_heads blocks.

@@ -1,0 +1,36 @@
+"""Prompts of models on the caller's weights: pieces of many rows leave, bit for bit, what windows of a few rows through the
+step leave (a row's sums depend on nothing but the row)."""
+import pytest
+import torch
+
+from paper_2404_08698_amd import binding as B
+from paper_2404_08698_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+# one launch of attention per piece; max_positions of 20000, whose partial results of 256 rows would be more than 16 MiB: launches of
+# 48 rows; a window that is no multiple of a row group; 2 and 4 heads per key / value head; prompts of one piece, of two
+@pytest.mark.parametrize("shape,path,max_window,max_positions,before,rows", [
+    (synth.TINY, B.GEMM_AUTO, 32, 400, 0, 128), (synth.TINY, B.GEMM_AUTO, 5, 400, 37, 300), (synth.TINY, B.GEMM_AUTO, 32, 20000, 11, 270),
+    (synth.TINY_MQA, B.GEMM_AUTO, 7, 20000, 63, 65), (synth.MID_BF16, B.GEMM_DOT, 32, 600, 130, 257), (synth.MID_GQA, B.GEMM_DOT, 12, 600, 0, 17),
+])
+def test_pieces_give_the_bits_of_windows(shape, path, max_window, max_positions, before, rows):
+    w = synth.make_weights(shape, 4, device="cuda")
+    model = B.Model(shape, w, max_window=max_window, max_positions=max_positions, gemm_path=path)
+    capacity = before + rows
+    tokens = synth.random_tokens(shape.vocab, capacity, 9)
+    whole, parts = B.KVCache(model, capacity), B.KVCache(model, capacity)
+    a = torch.empty(shape.vocab, dtype=torch.float32, device="cuda")
+    t0 = t1 = None
+    if before:
+        B.prefill(model, whole, tokens[:before])
+    t0 = B.prefill(model, whole, tokens[before:], out_logits=a)
+    for lo in range(0, capacity, max_window):
+        window = tokens[lo:lo + max_window]
+        b = torch.empty(len(window), shape.vocab, dtype=torch.float32, device="cuda")
+        _, t1 = B.verify(model, parts, window, B.APPEND, out_logits=b)[:2]
+    assert whole.length == parts.length == capacity and t0 == t1 and torch.equal(a, b[-1])
+    for layer in range(shape.n_layers):
+        for x, y in zip(whole.read(layer, 0, capacity), parts.read(layer, 0, capacity)):
+            assert torch.equal(x, y)
