@@ -273,17 +273,29 @@ int32_t launch_gen_few(const GenArgs &a, int n_blocks, int n_cu, hipStream_t st)
 
 // ---- fast path: packed MFMA GEMMs ---------------------------------------------
 
+// A kernel of the fast path whose LDS may be more than the 64 KB that need no attribute (attr_set: per kernel)
+template <typename K>
+int32_t launch_lds(K kernel, bool &attr_set, int blocks, int threads, size_t lds, const FastArgs &a, hipStream_t st)
+{
+    if (lds > 65536 && !attr_set) {
+        HIP_TRY(hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3((unsigned)threads), lds, st, a);
+    HIP_TRY(hipGetLastError());
+    return ANPD_OK;
+}
 template <int T, int D, int EPI>
 int32_t launch_wide(const FastArgs &a, int blocks, hipStream_t st)
 {
-    const size_t smem = (size_t)(T < 4 ? T : 4) * kFastWaves * 4 * 256 * sizeof(float);
-    static bool attr_set = false;   // per instantiation
-    if (smem > 65536 && !attr_set) {
-        HIP_TRY(hipFuncSetAttribute((const void *)gemm_wide_kernel<T, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-        attr_set = true;
-    }
-    hipLaunchKernelGGL((gemm_wide_kernel<T, D, EPI>), dim3((unsigned)blocks), dim3(kFastThreads), smem, st, a);
-    return ANPD_OK;
+    static bool attr_set = false;
+    return launch_lds(gemm_wide_kernel<T, D, EPI>, attr_set, blocks, kFastThreads, (size_t)4 * kFastWaves * 4 * 256 * sizeof(float), a, st);
+}
+template <int NT, int EPI>
+int32_t launch_tile(const FastArgs &a, int waves, hipStream_t st)
+{
+    static bool attr_set = false;
+    return launch_lds(gemm_tile_kernel<NT, EPI>, attr_set, (a.n_tiles + waves - 1) / waves, (waves + 1) * 64, tile_lds_bytes(NT), a, st);
 }
 
 template <int EPI>
@@ -298,72 +310,24 @@ int32_t launch_fast(FastArgs &a, int n_cu, bool force_stream, hipStream_t st)
         else if (kpw <= 16) hipLaunchKernelGGL((gemm_xs_kernel<16, EPI>), grid, block, 0, st, a);
         else hipLaunchKernelGGL((gemm_xs_kernel<20, EPI>), grid, block, 0, st, a);
     } else if (a.cls == 8 || (a.cls == 16 && a.n_tiles <= n_cu)) {
-        // one block per tile; several blocks share a compute unit.  Also the faster form for 9..16 rows when
-        // there is only one tile per compute unit (grouping would leave half of them idle).
+        // one block per tile; several blocks share a compute unit.  Also the faster form for 9..16 rows when there is only
+        // one tile per compute unit (4096 x 11008, 12 rows: 27.4 us, a tile per wave 31.2).
         dim3 grid((unsigned)a.n_tiles), block(kFastWaves * 64);
         const int nt = a.cls / 8;
         size_t smem = (size_t)kFastWaves * nt * 256 * sizeof(float);
         if (nt == 1) hipLaunchKernelGGL((gemm_stream_kernel<1, EPI>), grid, block, smem, st, a);
         else hipLaunchKernelGGL((gemm_stream_kernel<2, EPI>), grid, block, smem, st, a);
     } else {
-        // windows of 9..32 rows: every block takes a contiguous range of at least two tiles, so that an
-        // activation fragment is loaded once for several weight tiles
-        const int nt = a.cls / 8;
-        int blocks = a.n_tiles / 2 < n_cu ? a.n_tiles / 2 : n_cu;
-        // (two fragments, between one and two tiles per compute unit: every compute unit gets a block of one or
-        // two tiles rather than half of them a block of two: 13B shape, 9 rows: -0.8 % per step)
-        if (nt == 2 && a.n_tiles < 2 * n_cu) blocks = a.n_tiles < n_cu ? a.n_tiles : n_cu;
-        if (blocks < 1) blocks = 1;
-        dim3 grid((unsigned)blocks), block(kFastWaves * 64);
-        const int per_block = (a.n_tiles + blocks - 1) / blocks;
-        if (nt == 2 && per_block <= 2) {
-            size_t smem = (size_t)2 * kFastWaves * 2 * 256 * sizeof(float);
-            hipLaunchKernelGGL((gemm_group_kernel<2, 2, EPI>), grid, block, smem, st, a);
-        } else if (nt == 2 && per_block > 4) {
-            // six, seven or eight tiles per pass: the smallest form that takes the block's tiles in one pass
-            // (the eight-tile form sits at the register limit)
-#define ANPD_GROUP2(TG_)                                                                                                          \
-    do {                                                                                                                          \
-        size_t smem = (size_t)TG_ * kFastWaves * 2 * 256 * sizeof(float);                                                         \
-        static bool attr_set_g = false;                                                                                           \
-        if (!attr_set_g) {                                                                                                        \
-            HIP_TRY(hipFuncSetAttribute((const void *)gemm_group_kernel<2, TG_, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, \
-                                        (int)smem));                                                                              \
-            attr_set_g = true;                                                                                                    \
-        }                                                                                                                         \
-        hipLaunchKernelGGL((gemm_group_kernel<2, TG_, EPI>), grid, block, smem, st, a);                                           \
-    } while (0)
-            if (per_block <= 6) ANPD_GROUP2(6);
-            else if (per_block == 7) ANPD_GROUP2(7);
-            else ANPD_GROUP2(8);
-#undef ANPD_GROUP2
-        } else if (nt == 2) {
-            size_t smem = (size_t)4 * kFastWaves * 2 * 256 * sizeof(float);
-            static bool attr_set2 = false;
-            if (!attr_set2) {
-                HIP_TRY(hipFuncSetAttribute((const void *)gemm_group_kernel<2, 4, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-                attr_set2 = true;
-            }
-            hipLaunchKernelGGL((gemm_group_kernel<2, 4, EPI>), grid, block, smem, st, a);
-        } else if (a.n_tiles <= n_cu && kpw >= 8) {
-            // (17..32 rows, one tile per compute unit, K long enough to fill the ring: at K = 256 it costs 10 % of the
-            // tiny model's step)
-            if (int32_t rc = launch_wide<1, 8, EPI>(a, a.n_tiles, st); rc != ANPD_OK) return rc;
-        } else if (per_block <= 2) {
-            size_t smem = (size_t)2 * kFastWaves * 4 * 256 * sizeof(float);
-            hipLaunchKernelGGL((gemm_group_kernel<4, 2, EPI>), grid, block, smem, st, a);
-        } else if (const int passes = (per_block + 7) / 8, per_pass = (per_block + passes - 1) / passes; per_pass > 4) {
-            // as few passes over the operand as the accumulators allow
-            if (int32_t rc = per_pass <= 6 ? launch_wide<6, 3, EPI>(a, blocks, st) : launch_wide<8, 2, EPI>(a, blocks, st); rc != ANPD_OK) return rc;
-        } else {
-            size_t smem = (size_t)4 * kFastWaves * 4 * 256 * sizeof(float);
+        // windows of 9..32 rows: a tile per wave where one round of blocks takes them all; else (LM heads) blocks of a
+        // contiguous range of tiles, in as few passes over the operand as the accumulators allow
+        const int per_block = (a.n_tiles + n_cu - 1) / n_cu;
+        if (per_block <= kTileWaves) return a.cls == 32 ? launch_tile<4, EPI>(a, per_block, st) : launch_tile<2, EPI>(a, per_block, st);
+        if (a.cls == 16) {
             static bool attr_set = false;
-            if (!attr_set) {
-                HIP_TRY(hipFuncSetAttribute((const void *)gemm_group_kernel<4, 4, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-                attr_set = true;
-            }
-            hipLaunchKernelGGL((gemm_group_kernel<4, 4, EPI>), grid, block, smem, st, a);
+            return launch_lds(gemm_group_kernel<2, 8, EPI>, attr_set, n_cu, kFastThreads, (size_t)8 * kFastWaves * 2 * 256 * sizeof(float), a, st);
         }
+        const int passes = (per_block + 7) / 8, per_pass = (per_block + passes - 1) / passes;
+        return per_pass <= 6 ? launch_wide<6, 3, EPI>(a, n_cu, st) : launch_wide<8, 2, EPI>(a, n_cu, st);
     }
     HIP_TRY(hipGetLastError());
     return ANPD_OK;
@@ -920,11 +884,11 @@ int32_t launch_prefill_mixed(const PrefillArgs &a, int n_a, int tiles_a, long lo
     static bool attr_set = false;
     return launch_prefill_kernel(prefill_mixed_kernel<EPI, 6, TB>, attr_set, blocks, kPgThreads, pg_lds_bytes(6, 4), st, a, n_a, tiles_a);
 }
-template <int EPI, int TG>
+template <int EPI, int TG, bool ONCE>
 int32_t launch_prefill_few(const PrefillArgs &a, int waves, long long blocks, hipStream_t st)
 {
     static bool attr_set = false;
-    return launch_prefill_kernel(prefill_few_kernel<EPI, TG>, attr_set, blocks, (waves + kFewLoaders) * 64, few_lds_bytes(TG), st, a);
+    return launch_prefill_kernel(prefill_few_kernel<EPI, TG, ONCE>, attr_set, blocks, (waves + kFewLoaders) * 64, few_lds_bytes(TG), st, a);
 }
 
 // Measured time of a block of 64 TN features x 128 rows with the chip full of them, us at K = 4096.
@@ -962,7 +926,9 @@ int32_t launch_prefill_gemm(const PrefillArgs &a, int n_cu, hipStream_t st)
     const int tg = a.G == 1 ? 1 : 2, n_br2 = (a.G + tg - 1) / tg;
     for (int waves = 3; waves <= kFewWaves; ++waves) {
         const long long blocks = cols(waves) * n_br2;
-        if (blocks <= n_cu) return tg == 1 ? launch_prefill_few<EPI, 1>(a, waves, blocks, st) : launch_prefill_few<EPI, 2>(a, waves, blocks, st);
+        if (blocks > n_cu) continue;
+        if (tg == 1) return launch_prefill_few<EPI, 1, true>(a, waves, blocks, st);
+        return n_br2 == 1 ? launch_prefill_few<EPI, 2, true>(a, waves, blocks, st) : launch_prefill_few<EPI, 2, false>(a, waves, blocks, st);
     }
     // Up to 128 rows: half as wide, of four waves, where that is at most one block per compute unit: gate/up 50 -> 47,
     // down 35 -> 28 (they read half as much again per MFMA, which more rows would feel: two per compute unit, gate/up

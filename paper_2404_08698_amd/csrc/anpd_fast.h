@@ -633,7 +633,7 @@ __global__ __launch_bounds__(kFastThreads) void gemm_stream_kernel(FastArgs a)
     if (wave == 0) reduce_and_finish<NT, EPI>(a, tile, red_dyn, kFastWaves, lane, rinv);
 }
 
-// ------------------------------------------- GEMM, grouped tiles (windows of 9..32 rows)
+// ------------------------------------------- GEMM, grouped tiles (windows of 9..16 rows, eight or more tiles per block)
 //
 // A window of more than 8 rows has NT = 2 or 4 activation fragments per
 // k-step, too many to keep in registers, and reading them again for every
@@ -717,32 +717,22 @@ __global__ __launch_bounds__(kFastThreads) void gemm_group_kernel(FastArgs a)
             for (int f = 0; f < NT; ++f)
                 *reinterpret_cast<f32x4 *>(red_dyn + ((((size_t)t * kFastWaves + wave) * NT + f) * 64 + lane) * 4) = acc[t][f];
         __syncthreads();
-        if constexpr (NT == 4) {   // two waves per tile
-            if (wave < 2 * ntl)
-                reduce_and_finish_pair<NT, EPI>(a, t0 + (wave >> 1), wave & 1, red_dyn + (size_t)(wave >> 1) * kFastWaves * NT * 256, lane, rinv);
-        } else {
-            if (wave < ntl)
-                reduce_and_finish<NT, EPI>(a, t0 + wave, red_dyn + (size_t)wave * kFastWaves * NT * 256, kFastWaves, lane, rinv);
-        }
+        if (wave < ntl) reduce_and_finish<NT, EPI>(a, t0 + wave, red_dyn + (size_t)wave * kFastWaves * NT * 256, kFastWaves, lane, rinv);
     }
 }
 
-// ------------------------------------------- GEMM, four operand fragments, more tiles per pass
+// ------------------------------------------- GEMM, four operand fragments, all of a block's tiles in a pass
 //
-// Windows of 17..32 rows.  What these GEMMs pay for is bytes into the compute units: measured over the 7B and
-// 13B shapes a launch takes 4 us + weights / 6.4 TB/s + operand / 22 TB/s, the two one after the other (loads come
-// back in the order they were issued), and deeper register rings change nothing.  The operand is 512 KB per pass
-// and compute unit at K = 4096, so what helps is fewer passes: all of a block's tiles at once (T = 6: 96 registers of
-// accumulators, 8: 128), paid for with a ring of D stages of one k-step.  With the epilogues of QKV, O and gate/up the
-// registers do not quite suffice: 2 to 8 of 256 are parked in scratch memory around the loop (12 to 36 bytes per lane; none in the LM
-// head and the plain product).  7B gate/up, 32 rows: two passes of <4, 4> 45.5 us, one of T = 6 37.9; LM head 53.7 -> 47.5 (T = 8);
-// 13B gate/up 59.1 -> 50.6.
-// With one tile per compute unit (T = 1): 7B down 38.4 us as 128 blocks of two tiles, 34.0 as 256 of one.
+// Windows of 17..32 rows with more tiles per block than the form below has waves for (the LM head).  The operand is 512 KB
+// per pass and compute unit at K = 4096, so what helps is fewer passes: all of a block's tiles at once (T = 6: 96
+// registers of accumulators, 8: 128), paid for with a ring of D stages of one k-step.  With the epilogues of QKV, O
+// and gate/up the registers do not quite suffice: 2 to 9 of 256 are parked in scratch memory around the loop (none in
+// the LM head and the plain product).  LM head of the 7B shape, 32 rows: two passes of four tiles 53.7 us, one of T = 8 47.5.
 // Same k-step assignment (wave, wave + 8, ...) and summation order as the other forms: bit-identical results.
 template <int T, int D, int EPI>
 __global__ __launch_bounds__(kFastThreads) void gemm_wide_kernel(FastArgs a)
 {
-    constexpr int NT = 4, TR = T < 4 ? T : 4;   // tiles that meet in LDS at a time
+    constexpr int NT = 4, TR = 4;               // tiles that meet in LDS at a time
     extern __shared__ float red_dyn[];          // [TR][kFastWaves][NT][256]
     __shared__ float rinv[32];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -819,6 +809,151 @@ __global__ __launch_bounds__(kFastThreads) void gemm_wide_kernel(FastArgs a)
     }
 }
 
+// 16 bytes per lane from byte `offset` of the buffer to dst + 16 lane, without passing through registers
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t buffer, uint4 *dst, int offset)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer, (__attribute__((address_space(3))) void *)dst, 16, offset, 0, 0, 0);
+}
+
+// ------------------------------------------- GEMM, a tile per wave (windows of 9..32 rows)
+//
+// In the forms above every wave reads its eighth of the operand for itself, and loads of a wave come back in the order
+// they were issued: the operand's (from L2) wait behind the weights' (from HBM) and take up the places of weights that
+// could be in flight.  Here a wave owns a tile and streams nothing but its weights, through a ring of D k-steps of
+// registers; the last wave of the block brings the operand through LDS, eight k-steps at a time, for all the others,
+// and sums the norm's partials meanwhile (in front of a block's first weights that was 4 us; in the same wave, but eight
+// round trips one after the other, the first operand came as late).  A lane keeps the sums of the eight k-step
+// classes (k-step mod 8) apart, which the other forms have in eight waves, and adds them in the same order at the
+// end: the same bits, and no exchange.  They are 32 NT registers; with them, the ring and the operand fragments of two k-steps
+// eight waves fit a compute unit at NT = 4, seven of them with a tile.
+// 7B, 17 rows, 8 layers (traced; before: grouped and wide form): QKV 26.2 -> 23.9 us, gate/up 42.3 -> 35.5 (5.1 TB/s);
+// 8192 x 4096 alone, 16 rows, 20.5 -> 17.3.  What is left: HBM at 5.3 TB/s where the same loads from the memory-side
+// cache run at 6.3, and start and end of a launch.
+// Tried: rings of 24 and 32 k-steps (no change), one class after the other, whose sums take a quarter of the registers (weights
+// in pieces of 1 KB: QKV 32, gate/up 43).
+// blockDim: 64 x (tiles per block + 1).  grid: ceil(n_tiles / tiles per block).
+constexpr int kTileChunk = kFastWaves;   // k-steps per buffer of the operand: one of every class
+constexpr int kTileBufs = 3;
+constexpr int kTileWaves = 7;   // most tiles per block
+// weight fragments in flight per wave: what the registers hold beside the sums
+__host__ __device__ constexpr int tile_depth(int NT) { return NT == 2 ? 32 : 16; }
+__host__ __device__ constexpr size_t tile_lds_bytes(int NT) { return (size_t)kTileBufs * kTileChunk * NT * 1024 + 64 * 32 * 4; }
+template <int NT, int EPI>
+__global__ __launch_bounds__((kTileWaves + 1) * 64) void gemm_tile_kernel(FastArgs a)
+{
+    constexpr int D = tile_depth(NT), DX = kTileChunk, NB = kTileBufs, UNITS = DX * NT;
+    extern __shared__ uint4 xs[];   // [NB][DX][NT][64], then the norm's group sums [64][32]
+    __shared__ float rinv[32];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = (int)(blockDim.x >> 6) - 1;
+    const int nks = a.nks, n_chunks = (nks + DX - 1) / DX;
+    if (wave == n_waves) {
+        __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.Xp), 0, nks * NT * 1024, 0x00020000);
+        int buf = 0;
+        auto load_x = [&](int c) __attribute__((always_inline)) {   // (past the last k-step: zeros)
+            uint4 *dst = xs + (size_t)buf * UNITS * 64;
+            buf = buf + 1 == NB ? 0 : buf + 1;
+#pragma unroll
+            for (int u = 0; u < UNITS; ++u) load_to_lds(rx, dst + u * 64, (c * UNITS + u) * 1024 + lane * 16);
+        };
+        for (int c = 0; c < NB - 1; ++c) load_x(c);
+        float *sums = reinterpret_cast<float *>(xs + (size_t)NB * UNITS * 64);
+        if (epi_has_norm(EPI)) {
+            // compute_rinv's sums: the partials of tiles g, g + 64, ... in increasing order for each group g; a lane has four
+            // rows of the groups lane / 8 + 8 j, and all of its loads are in flight together
+            const float *p = a.ssp + 4 * (lane & 7);
+            f32x4 s[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s[j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            for (int t0 = lane >> 3; t0 < a.n_ss; t0 += 4 * 64) {
+                f32x4 v[8][4];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int t = t0 + 8 * j + 64 * u;
+                        v[j][u] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                        if (t < a.n_ss) v[j][u] = *reinterpret_cast<const f32x4 *>(p + (size_t)t * 32);
+                    }
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) s[j] += v[j][u];
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) *reinterpret_cast<f32x4 *>(sums + ((lane >> 3) + 8 * j) * 32 + 4 * (lane & 7)) = s[j];
+        }
+        for (int c = 0; c < n_chunks; ++c) {
+            // (chunk c has landed when at most the younger ones' loads are outstanding)
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NB - 2) * UNITS) : "memory");
+            if (epi_has_norm(EPI) && c == 0 && lane < 32) {
+                float tot = 0.f;
+#pragma unroll 16
+                for (int g = 0; g < 64; ++g) tot += sums[g * 32 + lane];
+                rinv[lane] = 1.0f / sqrtf(fmaf(tot, a.inv_d, a.eps));
+            }
+            load_x(c + NB - 1);
+        }
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (the last requests, of nothing; rinv)
+        return;
+    }
+    const int tile = blockIdx.x * n_waves + wave;
+    const bool have = tile < a.n_tiles;
+    __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.Wp + (size_t)(have ? tile : 0) * nks * 64), 0,
+                                                                  have ? nks * 1024 : 0, 0x00020000);
+    u32x4_t w[D];
+    // past the last k-step: outside the buffer, reads zeros (the whole offset is in the checked operand)
+    auto load_w = [&](int s, int i) __attribute__((always_inline)) { w[s] = __builtin_amdgcn_raw_buffer_load_b128(rw, lane * 16 + i * 1024, 0, kAuxStream); };
+#pragma unroll
+    for (int s = 0; s < D; ++s) load_w(s, s);
+    f32x4 acc[DX][NT];
+#pragma unroll
+    for (int k = 0; k < DX; ++k)
+#pragma unroll
+        for (int f = 0; f < NT; ++f) acc[k][f] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    u32x4_t xf[2][NT];
+    int buf = 0;
+    for (int c0 = 0; c0 < n_chunks; c0 += D / DX) {
+#pragma unroll
+        for (int h = 0; h < D / DX; ++h) {
+            const int c = c0 + h;
+            if (c >= n_chunks) break;   // (the same for the whole block)
+            block_sync_lds();
+            const u32x4_t *x = reinterpret_cast<const u32x4_t *>(xs) + (size_t)buf * UNITS * 64 + lane;
+            buf = buf + 1 == NB ? 0 : buf + 1;
+            auto read_x = [&](int k) __attribute__((always_inline)) {
+#pragma unroll
+                for (int f = 0; f < NT; ++f) xf[k & 1][f] = x[(k * NT + f) * 64];
+            };
+            read_x(0);
+#pragma unroll
+            for (int k = 0; k < DX; ++k) {
+                const int s = h * DX + k;
+                if (k + 1 < DX) read_x(k + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int f = 0; f < NT; ++f)
+                    acc[k][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[s]), __builtin_bit_cast(bf16x8, xf[k & 1][f]), acc[k][f], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                load_w(s, c * DX + k + D);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    block_sync_lds();   // rinv
+    if (!have) return;
+#pragma unroll
+    for (int p = 0; p < NT / 2; ++p) {
+        f32x4 hi = acc[0][2 * p], lo = acc[0][2 * p + 1];
+#pragma unroll
+        for (int k = 1; k < DX; ++k) {
+            hi += acc[k][2 * p];
+            lo += acc[k][2 * p + 1];
+        }
+        const int m = 16 * p + (lane & 15);
+        epilogue<EPI>(a, tile, m, lane >> 4, hi + lo, m < a.M, rinv);
+    }
+}
+
 // ------------------------------------------- GEMM split by k-step class (O and down projections of 17..32 rows)
 //
 // With one or two tiles per compute unit every compute unit would read the whole operand (1.4 MB for the 7B down
@@ -834,11 +969,6 @@ __global__ __launch_bounds__(kFastThreads) void gemm_wide_kernel(FastArgs a)
 constexpr int kSplitDepth = 16;   // k-steps in flight per wave; k-steps of operand per LDS buffer
 constexpr int kSplitMaxWaves = 16;
 constexpr size_t kSplitLds = (size_t)(2 * kSplitDepth * 4 + 1) * 1024;   // two buffers, and a place for loads of nothing
-// 16 bytes per lane from byte `offset` of the buffer to dst + 16 lane, without passing through registers
-__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t buffer, uint4 *dst, int offset)
-{
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer, (__attribute__((address_space(3))) void *)dst, 16, offset, 0, 0, 0);
-}
 __global__ __launch_bounds__(kSplitMaxWaves * 64) void gemm_split_kernel(FastArgs a, float *__restrict__ part)
 {
     constexpr int NT = 4, D = kSplitDepth, XL = D * NT / kFastWaves;   // operand loads per wave and buffer, at least 8 waves
