@@ -647,8 +647,10 @@ __global__ __launch_bounds__((kFewWaves + kFewLoaders) * 64) void prefill_few_ke
 // what L2 delivers), 16-key MFMAs did half the work of a 32-key one in the same time, the output was rescaled and a maximum
 // exchanged per page, and a short prompt behind a long cache left the pages to a few waves one after the other.
 // 7B shape, 512 / 3584 rows: 35 -> 21 / 489 -> 409 us per layer; 205 rows behind 777, 32 heads over 2 key / value heads: 63 -> 19.
-// What bounds it at 3584 rows is that nothing covers a wave's exponentials: at head dim 128 a lane holds 238 registers and 80
-// accumulators, so a SIMD has one wave (vector ALU 45 %, matrix cores 22 % busy).
+// Then nothing covered a wave's exponentials at 3584 rows: with the query rows in registers a lane of head dim 128 held 238 and 80
+// accumulators, one wave per SIMD (vector ALU 45 %, matrix cores 22 % busy).  The rows are the same for the block's four
+// waves: read from LDS for every pair, they leave 184 registers and two waves per SIMD: 512 / 3584 rows 19.5 -> 16.2 /
+// 414 -> 284 us.  (Three waves, 168 registers, some of them in scratch memory: 23.5 / 443.)
 // A row's sums depend on absolute page numbers only, not on how the prompt was cut.  (They are not, bit for bit, those of
 // one wave going page by page with a maximum that always moves: one layer's output is 8e-6 apart, 2^-17 being what the
 // weights' two bf16 terms keep, and equally far from the 64-bit result.)
@@ -657,13 +659,17 @@ __global__ __launch_bounds__((kFewWaves + kFewLoaders) * 64) void prefill_few_ke
 // grid: (n_heads, ceil(G / 2)); later groups (more pages) start first.
 constexpr float kHugeScore = 0x1p29f;   // rounding a base-2 score of this size may move it by 2^5; below it by 2^4, weights stay under 2^(8 + 16)
 template <int DH>
-__global__ __launch_bounds__(256) void prefill_attn_kernel(const uint4 *__restrict__ qp, const bf16_t *__restrict__ pool,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_attn_kernel(const uint4 *__restrict__ qp, const bf16_t *__restrict__ pool,
                                                             const int32_t *__restrict__ page_table, int G, int L, int P,
                                                             int layer, int n_layers, int n_heads, int n_kv_heads, float scale,
                                                             bf16_t *__restrict__ xq_att, int nks_d)
 {
     constexpr int NKS = DH / 32, NDT = DH / 16, WAVES = 4;
-    __shared__ float part[WAVES][2][NDT][64][4];
+    // the query rows while the pages go by, the waves' outputs behind them
+    __shared__ union {
+        uint4 q[2][NKS][2][64];   // [group][32 dims][hi | lo], the same for every wave
+        float part[WAVES][2][NDT][64][4];
+    } lds;
     __shared__ float wmax[WAVES][2][16], wden[WAVES][2][16];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), slot = lane & 15, kg = lane >> 4;
     const int head = blockIdx.x, kvh = head / (n_heads / n_kv_heads);
@@ -671,14 +677,9 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(const uint4 *__restri
     const int own0 = (L >> 4) + g0;                 // the first group's own page; the second group's is the next one
     const int last_page = own0 + n_grp - 1, last_pair = last_page >> 1;
 
-    uint4 qf[2][NKS][2];
-#pragma unroll
-    for (int x = 0; x < 2; ++x) {
-        const uint4 *q = qp + ((size_t)head * G + g0 + (x < n_grp ? x : 0)) * NKS * 128;
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks)
-#pragma unroll
-            for (int hl = 0; hl < 2; ++hl) qf[x][ks][hl] = q[(ks * 2 + hl) * 64 + lane];
+    for (int i = wave; i < 2 * NKS * 2; i += WAVES) {
+        const int x = i / (2 * NKS), r = i % (2 * NKS);
+        (&lds.q[0][0][0][0])[i * 64 + lane] = qp[(((size_t)head * G + g0 + (x < n_grp ? x : 0)) * 2 * NKS + r) * 64 + lane];
     }
     // page numbers of the wave's next 64 pairs, one pair per lane; a pair's second page, if it does not exist, is the
     // first one again (its keys get weight 0)
@@ -716,6 +717,9 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(const uint4 *__restri
         load_k(pb, kf[1]);
         load_v(pa, vf[0]);
         load_v(pb, vf[1]);
+    }
+    __syncthreads();
+    if (n_pairs > 0) {
         for (int k = 0; k < n_pairs; ++k) {
             const int page0 = 2 * (wave + WAVES * k);
             // ---- scores of both groups: lane (slot, kg) has keys 4 kg + i of either page, row slot
@@ -727,8 +731,8 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(const uint4 *__restri
                     f32x4 t = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int ks = 0; ks < NKS; ++ks) {
-                        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[y][ks]), __builtin_bit_cast(bf16x8, qf[x][ks][0]), t, 0, 0, 0);
-                        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[y][ks]), __builtin_bit_cast(bf16x8, qf[x][ks][1]), t, 0, 0, 0);
+                        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[y][ks]), __builtin_bit_cast(bf16x8, lds.q[x][ks][0][lane]), t, 0, 0, 0);
+                        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[y][ks]), __builtin_bit_cast(bf16x8, lds.q[x][ks][1][lane]), t, 0, 0, 0);
                     }
                     sc[x][y] = t;
                 }
@@ -821,7 +825,7 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(const uint4 *__restri
         for (int w = 1; w < WAVES; ++w) bm = fmaxf(bm, wmax[w][x][slot]);
         const float f = __builtin_amdgcn_exp2f(m_run[x] - bm);
 #pragma unroll
-        for (int dt = 0; dt < NDT; ++dt) *reinterpret_cast<f32x4 *>(part[wave][x][dt][lane]) = o[x][dt] * f;
+        for (int dt = 0; dt < NDT; ++dt) *reinterpret_cast<f32x4 *>(lds.part[wave][x][dt][lane]) = o[x][dt] * f;
     }
     __syncthreads();
     for (int u = wave; u < 2 * NDT; u += WAVES) {
@@ -834,7 +838,7 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(const uint4 *__restri
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) {
             den = fmaf(wden[w][x][slot], __builtin_amdgcn_exp2f(wmax[w][x][slot] - bm), den);
-            v += *reinterpret_cast<const f32x4 *>(part[w][x][dt][lane]);
+            v += *reinterpret_cast<const f32x4 *>(lds.part[w][x][dt][lane]);
         }
         const int m = (g0 + x) * 16 + slot, r = m - (L & 15);
         const bool valid = r >= 0 && r < P;
