@@ -1356,6 +1356,14 @@ __device__ __forceinline__ void attn_task(AttnShared<DH> &sh, AttnKV<DH> &kv, in
     auto request = [&](AttnKV<DH> &dst, int j) __attribute__((always_inline)) {
         attn_load_kv<DH, COH>(dst, kv_head, split, L, n_new, pool, page_table, layer, n_layers, n_kv_heads, false, j);
     };
+    // The separate kernels keep the query rows of the group that they work on in LDS, where all waves read them for every page
+    // (16 registers less per lane at head dim 128).  Requested in front of the pages, which stay in flight.
+    constexpr bool kQueryLds = !COH;
+    auto share_q = [&](int rg) __attribute__((always_inline)) {
+        if (wave < NKS) q_lds[wave * 64 + lane] = qp[((size_t)(head * 4 + rg) * NKS + wave) * 64 + lane];
+        block_sync_lds();
+    };
+    if (kQueryLds) share_q(rg0);
     if (!kv.loaded) request(kv, 0);
     // The separate kernels (COH = false) go through a split's pages with ONE set of page registers, each page
     // requested when the one before it has been used: a block's own waits get longer, but at 120 instead of 154
@@ -1365,10 +1373,10 @@ __device__ __forceinline__ void attn_task(AttnShared<DH> &sh, AttnKV<DH> &kv, in
     // the query rows of the first row group: from memory, or from the copy an earlier task of this block left
     // in LDS (same head, same rows) - a block's later tasks then do not wait for memory before their first page
     uint4 qf[NKS];
-    if (q_in_lds) {
+    if (!kQueryLds && q_in_lds) {
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) qf[ks] = q_lds[ks * 64 + lane];
-    } else {
+    } else if (!kQueryLds) {
         attn_load_q<DH, COH>(qf, qp, head, rg0);
     }
     // (a task of several pages waits for loads while it goes through them, and what after_loads requests
@@ -1381,7 +1389,8 @@ __device__ __forceinline__ void attn_task(AttnShared<DH> &sh, AttnKV<DH> &kv, in
     const float scale2 = scale * 1.44269504088896f;   // scores in the base-2 domain
     for (int rg = rg0; rg * 8 < row_end; ++rg) {
         if (rg > rg0) {
-            attn_load_q<DH, COH>(qf, qp, head, rg);
+            if (kQueryLds) share_q(rg);   // (the barriers below lie between its reads and this)
+            else attn_load_q<DH, COH>(qf, qp, head, rg);
             if (kOneSet ? n_pages > 1 : n_pages > 2) request(kv, 0);   // (otherwise every page is still in its registers)
         }
         const int m = rg * 8 + (slot & 7);
@@ -1403,7 +1412,7 @@ __device__ __forceinline__ void attn_task(AttnShared<DH> &sh, AttnKV<DH> &kv, in
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks)
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, cur.kf[ks]),
-                                                              __builtin_bit_cast(bf16x8, qf[ks]), acc, 0, 0, 0);
+                                                              __builtin_bit_cast(bf16x8, kQueryLds ? q_lds[ks * 64 + lane] : qf[ks]), acc, 0, 0, 0);
             float sc[4], mx = kMasked;
             // a page wholly below the committed length is seen by every row (whole-wave branch)
             const bool all_seen = key0 + 15 < L;
@@ -1470,7 +1479,7 @@ __device__ __forceinline__ void attn_task(AttnShared<DH> &sh, AttnKV<DH> &kv, in
             if (stashed2) stash_get<DH>(*stash, 1, kv, wave, lane);
             page(kv, 2);
         }
-        if (!q_in_lds && q_lds && more_tasks && wave == 0 && rg == rg0) {   // (read by later tasks: block barriers lie in between)
+        if (!kQueryLds && !q_in_lds && q_lds && more_tasks && wave == 0 && rg == rg0) {   // (read by later tasks: block barriers lie in between)
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) q_lds[ks * 64 + lane] = qf[ks];
         }
@@ -1611,10 +1620,14 @@ __device__ __forceinline__ void attn_task(AttnShared<DH> &sh, AttnKV<DH> &kv, in
 }
 
 // Block (head, split, group of eight rows): one block for all rows of a wide window went through its pages once
-// per eight rows, one wait after the other (17 rows at 2048 positions: 31.7 us per layer, now 23.8).
+// per eight rows, one wait after the other (17 rows at 2048 positions: 31.7 us per layer, then 23.8).  What counts now is
+// how many of these chains of waits run side by side: with the query rows in LDS 80 registers suffice (three parked in
+// scratch memory in the form for several pages), three blocks per compute unit instead of two, and the last splits, of
+// three pages per wave, go first: 23.1 -> 20.0 us, 21 rows at 633 positions 11.2 -> 10.3, 13B shape, 9 rows at
+// 1101 15.2 -> 13.0 (in order of the splits 21.9, 11.0, 13.2).
 // head_counter: [group][head].   grid: (n_heads, n_splits_of(len + M), ceil(M / 8)), kFastWaves waves.
 template <int DH, bool TREE = false, int MAXP = kFastPages>
-__global__ __launch_bounds__(kFastThreads) void attn_fast_kernel(const uint4 *__restrict__ qp, const bf16_t *__restrict__ pool,
+__global__ __launch_bounds__(kFastThreads, 6) void attn_fast_kernel(const uint4 *__restrict__ qp, const bf16_t *__restrict__ pool,
                                                           const int32_t *__restrict__ page_table,
                                                           const int32_t *__restrict__ len_ptr, int M, int layer, int n_layers,
                                                           int n_heads, int n_kv_heads, int max_splits, float scale,
@@ -1623,16 +1636,18 @@ __global__ __launch_bounds__(kFastThreads) void attn_fast_kernel(const uint4 *__
                                                           const uint32_t *__restrict__ row_mask)
 {
     __shared__ AttnShared<DH> sh;
+    __shared__ uint4 q_rows[DH / 32 * 64];
     const int L = *len_ptr, row0 = 8 * (int)blockIdx.z, row_end = row0 + 8 < M ? row0 + 8 : M;
-    if (split_begin(blockIdx.y) >= L + row_end) return;
+    const int split = (int)gridDim.y - 1 - (int)blockIdx.y;
+    if (split_begin(split) >= L + row_end) return;
     AttnKV<DH> kv;
     kv.loaded = false;
     AttnBatch bt = {row0, row_end - row0, n_splits_of(L + row_end), nullptr, nullptr};
-    attn_task<DH, false, NoPrefetch, TREE ? ATTN_TREE : ATTN_CHAIN, NoPrefetch, MAXP>(sh, kv, blockIdx.x, blockIdx.y, L, qp, pool, page_table, M, layer,
+    attn_task<DH, false, NoPrefetch, TREE ? ATTN_TREE : ATTN_CHAIN, NoPrefetch, MAXP>(sh, kv, blockIdx.x, split, L, qp, pool, page_table, M, layer,
                                                                     n_layers, n_heads, n_kv_heads, max_splits, scale, part,
                                                                     head_counter + (size_t)blockIdx.z * n_heads * kCounterStride, xp_att, cls,
                                                                     NoPrefetch(), row_mask, &bt, NoPrefetch(), 1, nullptr, false, false,
-                                                                    nullptr, false, false);
+                                                                    q_rows, false, false);
 }
 
 // Several sequences' windows in one step: block (head, split, sequence) works on that sequence's rows
@@ -1646,6 +1661,7 @@ __global__ __launch_bounds__(kFastThreads) void attn_batch_kernel(const uint4 *_
                                                            int cls)
 {
     __shared__ AttnShared<DH> sh;
+    __shared__ uint4 q_rows[DH / 32 * 64];
     const SeqRef sq = seqs[blockIdx.z];
     const int L = *sq.len_ptr;
     if (split_begin(blockIdx.y) >= L + sq.n_rows) return;
@@ -1655,7 +1671,7 @@ __global__ __launch_bounds__(kFastThreads) void attn_batch_kernel(const uint4 *_
     attn_task<DH, false, NoPrefetch, ATTN_BATCH, NoPrefetch, MAXP>(sh, kv, blockIdx.x, blockIdx.y, L, qp, sq.pool, sq.page_table, M, layer, n_layers,
                                                  n_heads, n_kv_heads, max_splits, scale, part,
                                                  head_counter + (size_t)blockIdx.z * n_heads * kCounterStride, xp_att, cls,
-                                                 NoPrefetch(), nullptr, &bt, NoPrefetch(), 1, nullptr, false, false, nullptr, false, false);
+                                                 NoPrefetch(), nullptr, &bt, NoPrefetch(), 1, nullptr, false, false, q_rows, false, false);
 }
 
 // Plain decoding of many sequences (one row each): one block per (head, sequence), its wave w going through the
