@@ -445,6 +445,34 @@ StepTokens step_tokens(const int32_t *window, int n)
     return t;
 }
 
+// Where a step's LM head writes its n logits: straight into the caller's buffer when that is memory of this device that
+// takes 16-byte stores and holds them all, else into the workspace, from where they are copied (a buffer of another
+// GPU, say; one that is too short makes the copy fail, where stores would go past its end).
+float *logits_target(const anpd_model *m, float *out_logits, size_t n)
+{
+    float *own = (float *)(m->ws + m->lay.logits);
+    if (!out_logits || ((uintptr_t)out_logits & 15) != 0) return own;
+    hipPointerAttribute_t at;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&at, out_logits) != hipSuccess || hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)out_logits) != hipSuccess) {
+        (void)hipGetLastError();
+        return own;
+    }
+    const bool fits = (char *)out_logits + n * sizeof(float) <= (char *)base + size;
+    return at.type == hipMemoryTypeDevice && at.device == m->device && fits ? out_logits : own;
+}
+
+// The caller's buffer for n logits (null: none), and where the LM head writes them: looked up when its launch is due, by when
+// the device is at work on the launches in front of it (two queries of the runtime, some 2 us).
+struct LogitsTo {
+    float *out;
+    size_t n;
+    float *at;
+    float *find(const anpd_model *m) { return at = logits_target(m, out, n); }
+    bool elsewhere() const { return out && out != at; }
+};
+
 // What the last kernel of a step writes, and where.
 AcceptArgs accept_args(anpd_model *m, int32_t *len_ptr)
 {
@@ -473,7 +501,7 @@ void launch_accept(int kind, const float *logits, int V, int M, const StepTokens
 // (PIECE_CACHE) or, besides them, logits and prediction of the last row (PIECE_LAST).
 enum Piece { PIECE_NONE, PIECE_CACHE, PIECE_LAST };
 template <typename KT>
-int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int M, int mode, float *logits, hipStream_t st,
+int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int M, int mode, LogitsTo &logits_to, hipStream_t st,
                          bool tree = false, Piece piece = PIECE_NONE)
 {
     const anpd_model_cfg &c = m->cfg;
@@ -518,8 +546,10 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int 
 
     m->ev_used = 0;
     mark(m, -1, st);
-    // (the tokens by value, a window of them per launch)
-    for (int i = 0; i < M; i += c.max_window) {
+    // (the tokens by value, a window of them per launch; a step's first QKV looks its rows up itself, in 16-byte loads that an
+    // embedding table at an odd address does not get)
+    const bool embed_in_qkv = piece == PIECE_NONE && ((uintptr_t)m->embed & 15) == 0;
+    for (int i = 0; i < M && !embed_in_qkv; i += c.max_window) {
         const int n = M - i < c.max_window ? M - i : c.max_window;
         hipLaunchKernelGGL((embed_kernel<KT>), dim3(n), dim3(256), 0, st, (const KT *)m->embed, step_tokens(tokens + i, n), x + (size_t)i * d, d);
     }
@@ -530,7 +560,17 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int 
             g.W1 = m->wk[l];
             g.W2 = m->wv[l];
             g.layer = l;
-            if ((rc = launch_gen<KT, GEN_QKV>(g, (H + 2 * Hkv) * (dh / 32), st)) != ANPD_OK) return rc;
+            const int blocks = (H + 2 * Hkv) * (dh / 32);
+            if (l == 0 && embed_in_qkv) {
+                g.embed = m->embed;
+                g.x = x;
+                const StepTokens tok = step_tokens(tokens, M);
+                if (M > 16) hipLaunchKernelGGL((gemm_gen_first_kernel<KT, 2>), dim3((unsigned)blocks), dim3(512), 0, st, g, tok);
+                else hipLaunchKernelGGL((gemm_gen_first_kernel<KT, 1>), dim3((unsigned)blocks), dim3(512), 0, st, g, tok);
+                HIP_TRY(hipGetLastError());
+            } else if ((rc = launch_gen<KT, GEN_QKV>(g, blocks, st)) != ANPD_OK) {
+                return rc;
+            }
         }
         mark(m, ANPD_PROF_GEMM_QKV, st);
         for (int row0 = 0; row0 < M; row0 += L.gen_part_rows) {
@@ -563,6 +603,7 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int 
     }
     const int before = piece == PIECE_LAST ? M - 1 : 0;   // rows in front of the first whose logits are wanted
     base.M = M - before;
+    float *logits = logits_to.find(m);
     if ((rc = launch_gen_few<KT, GEN_LOGITS>(gemm(x + (size_t)before * d, d, m->lm_head, m->final_norm, logits, V), V / 16, m->n_cu, st)) != ANPD_OK) return rc;
     mark(m, ANPD_PROF_GEMM_LM_HEAD, st);
     AcceptArgs ac = accept_args(m, kv->d_len);
@@ -586,7 +627,7 @@ struct BatchLaunch {
     bool decode;   // one row per sequence and sequences enough: one block per (head, sequence)
 };
 
-int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, int mode, float *logits, hipStream_t st, bool tree = false,
+int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, int mode, LogitsTo &logits_to, hipStream_t st, bool tree = false,
                       const BatchLaunch *batch = nullptr)
 {
     const anpd_model_cfg &c = m->cfg;
@@ -725,6 +766,7 @@ int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, 
         }
         mark(m, ANPD_PROF_GEMM_DOWN, st);
     }
+    float *logits = logits_to.find(m);
     {
         FastArgs a = base;
         a.Wp = (const uint4 *)(ws + L.wp_lm);
@@ -973,7 +1015,7 @@ int32_t launch_prefill_gemm(const PrefillArgs &a, int n_cu, hipStream_t st)
 
 // All P rows at once; per layer norm -> QKV(+RoPE, cache write) -> attention -> O(+residual) -> norm ->
 // gate/up(+SwiGLU) -> down(+residual); the last row then goes through the step's LM head and argmax.
-int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const PrefillLayout &PL, float *logits, hipStream_t st)
+int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const PrefillLayout &PL, LogitsTo &logits_to, hipStream_t st)
 {
     const anpd_model_cfg &c = m->cfg;
     const Layout &L = m->lay;
@@ -1081,6 +1123,7 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
     hipLaunchKernelGGL(prefill_last_kernel, dim3((unsigned)(d / 16)), dim3(64), 0, st, x + (size_t)(r0 + P - 1) * d,
                        (const float *)(part + (size_t)(r0 + P - 1) * d), kPgSplit, (size_t)G * 16 * d, (const bf16_t *)m->final_norm, (bf16_t *)(ws + L.xp_d), (float *)(ws + L.ssp_a), kv->d_len, len + P - 1);
     mark(m, ANPD_PROF_OTHER, st);
+    float *logits = logits_to.find(m);
     {
         FastArgs a;
         std::memset(&a, 0, sizeof(a));
@@ -1104,24 +1147,6 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
     mark(m, ANPD_PROF_OTHER, st);
     HIP_TRY(hipGetLastError());
     return ANPD_OK;
-}
-
-// Where a step's LM head writes its n logits: straight into the caller's buffer when that is memory of this device that
-// takes 16-byte stores and holds them all, else into the workspace, from where they are copied (a buffer of another
-// GPU, say; one that is too short makes the copy fail, where stores would go past its end).
-float *logits_target(const anpd_model *m, float *out_logits, size_t n)
-{
-    float *own = (float *)(m->ws + m->lay.logits);
-    if (!out_logits || ((uintptr_t)out_logits & 15) != 0) return own;
-    hipPointerAttribute_t at;
-    hipDeviceptr_t base = nullptr;
-    size_t size = 0;
-    if (hipPointerGetAttributes(&at, out_logits) != hipSuccess || hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)out_logits) != hipSuccess) {
-        (void)hipGetLastError();
-        return own;
-    }
-    const bool fits = (char *)out_logits + n * sizeof(float) <= (char *)base + size;
-    return at.type == hipMemoryTypeDevice && at.device == m->device && fits ? out_logits : own;
 }
 
 // After the stream has been synchronised: did a grid barrier of the one-kernel step give up?  Then the
@@ -1514,14 +1539,14 @@ int32_t anpd_verify(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, int32
     // flag) into the pinned buffer themselves.
     const bool one_kernel = m->mega && (n_window <= 8 || (n_window <= 16 && m->mega_rows16));
     const int32_t *res = m->pin + 32;
-    float *logits = logits_target(m, out_logits, (size_t)n_window * m->cfg.vocab);
-    if (one_kernel) rc = run_step_mega(m, kv, window, n_window, mode, out_logits ? logits : nullptr, st);
+    LogitsTo logits = {out_logits, (size_t)n_window * m->cfg.vocab, nullptr};
+    if (one_kernel) rc = run_step_mega(m, kv, window, n_window, mode, out_logits ? logits.find(m) : nullptr, st);
     else if (m->mfma) rc = run_step_fast(m, kv, step_tokens(window, n_window), n_window, mode, logits, st);
     else if (m->cfg.dtype == ANPD_BF16) rc = run_step_generic<bf16_t>(m, kv, window, n_window, mode, logits, st);
     else rc = run_step_generic<float>(m, kv, window, n_window, mode, logits, st);
     if (rc != ANPD_OK) return rc;
-    if (out_logits && out_logits != logits)
-        HIP_TRY(hipMemcpyAsync(out_logits, logits, sizeof(float) * (size_t)n_window * m->cfg.vocab, hipMemcpyDeviceToDevice, st));
+    if (logits.elsewhere())
+        HIP_TRY(hipMemcpyAsync(out_logits, logits.at, sizeof(float) * (size_t)n_window * m->cfg.vocab, hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (one_kernel && barrier_gave_up(m, st)) return fail(ANPD_E_HIP, "anpd_verify: the persistent kernel timed out at a grid barrier");
     collect_marks(m);
@@ -1566,12 +1591,12 @@ int32_t anpd_verify_tree(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, 
         tm[i] = tm[parent[i]] | (1u << i);
     }
     const int32_t *res = m->pin + 32;
-    float *logits = logits_target(m, out_logits, (size_t)n_window * m->cfg.vocab);
+    LogitsTo logits = {out_logits, (size_t)n_window * m->cfg.vocab, nullptr};
     // windows of up to 8 rows: the one-kernel step in its draft-tree form (tree by value as well); otherwise one
     // launch per operation, the tree uploaded
     const bool one_kernel = m->mega && m->mega_tree && n_window <= 8;
     if (one_kernel) {
-        rc = run_step_mega(m, kv, window, n_window, ANPD_APPEND, out_logits ? logits : nullptr, st, tp);
+        rc = run_step_mega(m, kv, window, n_window, ANPD_APPEND, out_logits ? logits.find(m) : nullptr, st, tp);
     } else {
         UploadWords up;
         std::memcpy(up.w, tp, sizeof(int32_t) * 3 * ANPD_MAX_WINDOW);
@@ -1581,8 +1606,8 @@ int32_t anpd_verify_tree(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, 
         else rc = run_step_generic<float>(m, kv, window, n_window, ANPD_APPEND, logits, st, true);
     }
     if (rc != ANPD_OK) return rc;
-    if (out_logits && out_logits != logits)
-        HIP_TRY(hipMemcpyAsync(out_logits, logits, sizeof(float) * (size_t)n_window * m->cfg.vocab, hipMemcpyDeviceToDevice, st));
+    if (logits.elsewhere())
+        HIP_TRY(hipMemcpyAsync(out_logits, logits.at, sizeof(float) * (size_t)n_window * m->cfg.vocab, hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (one_kernel && barrier_gave_up(m, st)) return fail(ANPD_E_HIP, "anpd_verify_tree: the persistent kernel timed out at a grid barrier");
     collect_marks(m);
@@ -1668,13 +1693,13 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
     // value and writes the results into the pinned buffer itself; otherwise copies and the fused launches.
     const bool one_kernel = m->mega && m->mega_batch && total <= 8;
     const int32_t *res = m->pin + 256;
-    float *logits = logits_target(m, out_logits, (size_t)total * m->cfg.vocab);
+    LogitsTo logits = {out_logits, (size_t)total * m->cfg.vocab, nullptr};
     int32_t rc;
     if (one_kernel) {
         int32_t lens[8];
         for (int s = 0; s < n_seq; ++s) lens[s] = kvs[s]->len;
         MegaBatch mb = {n_seq, seqs, row_seq, lens};
-        rc = run_step_mega(m, nullptr, m->pin, total, mode, out_logits ? logits : nullptr, st, nullptr, &mb);
+        rc = run_step_mega(m, nullptr, m->pin, total, mode, out_logits ? logits.find(m) : nullptr, st, nullptr, &mb);
     } else {
         // sequence of every row, then the sequences (Layout::batch)
         static_assert(sizeof(SeqRef) % 4 == 0 && sizeof(UploadWords) == ANPD_MAX_WINDOW * (sizeof(int32_t) + sizeof(SeqRef)), "a batch's description");
@@ -1685,8 +1710,8 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
         rc = run_step_fast(m, nullptr, step_tokens(m->pin, total), total, mode, logits, st, false, &bl);
     }
     if (rc != ANPD_OK) return rc;
-    if (out_logits && out_logits != logits)
-        HIP_TRY(hipMemcpyAsync(out_logits, logits, sizeof(float) * (size_t)total * m->cfg.vocab, hipMemcpyDeviceToDevice, st));
+    if (logits.elsewhere())
+        HIP_TRY(hipMemcpyAsync(out_logits, logits.at, sizeof(float) * (size_t)total * m->cfg.vocab, hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (one_kernel && barrier_gave_up(m, st)) return fail(ANPD_E_HIP, "anpd_verify_batch: the persistent kernel timed out at a grid barrier");
     collect_marks(m);
@@ -1729,7 +1754,7 @@ int32_t anpd_prefill(anpd_model_t *m, anpd_kv_t *kv, const int32_t *tokens, int3
         auto pieces = [&]() -> int32_t {
             int32_t rc = ensure_pages(kv, len0 + n_tokens, st);
             if (rc != ANPD_OK) return rc;
-            float *logits = logits_target(m, out_logits, V);
+            LogitsTo logits = {out_logits, V, nullptr};
             for (int i = 0, n; i < n_tokens; i += n) {
                 n = n_tokens - i < m->lay.gen_rows ? n_tokens - i : m->lay.gen_rows;
                 const Piece piece = i + n < n_tokens ? PIECE_CACHE : PIECE_LAST;
@@ -1742,7 +1767,7 @@ int32_t anpd_prefill(anpd_model_t *m, anpd_kv_t *kv, const int32_t *tokens, int3
                     collect_marks(m);
                 }
             }
-            if (out_logits && out_logits != logits) HIP_TRY(hipMemcpyAsync(out_logits, logits, V * sizeof(float), hipMemcpyDeviceToDevice, st));
+            if (logits.elsewhere()) HIP_TRY(hipMemcpyAsync(out_logits, logits.at, V * sizeof(float), hipMemcpyDeviceToDevice, st));
             HIP_TRY(hipStreamSynchronize(st));
             return ANPD_OK;
         };
@@ -1769,12 +1794,12 @@ int32_t anpd_prefill(anpd_model_t *m, anpd_kv_t *kv, const int32_t *tokens, int3
     if (rc != ANPD_OK) return rc;
     char *pws = (char *)workspace;
     HIP_TRY(hipMemcpyAsync(pws + PL.tok, tokens, sizeof(int32_t) * (size_t)n_tokens, hipMemcpyHostToDevice, st));
-    float *logits = logits_target(m, out_logits, V);
+    LogitsTo logits = {out_logits, V, nullptr};
     rc = run_prefill_mfma(m, kv, n_tokens, pws, PL, logits, st);
     if (rc != ANPD_OK) return rc;
     const int32_t *res = m->pin + 32;
-    if (out_logits && out_logits != logits)
-        HIP_TRY(hipMemcpyAsync(out_logits, logits, V * sizeof(float), hipMemcpyDeviceToDevice, st));
+    if (logits.elsewhere())
+        HIP_TRY(hipMemcpyAsync(out_logits, logits.at, V * sizeof(float), hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
     collect_marks(m);
     *out_next = res[1];

@@ -312,6 +312,9 @@ struct GenArgs {
     const int32_t *page_table, *len_ptr;
     const int32_t *depth; // draft tree: a row's rotary position is length + depth (nullable)
     int layer, n_layers, n_heads, n_kv_heads, head_dim, page_tokens;
+    // first QKV of a step
+    const void *embed;    // [vocab][K]: X is the window's rows of it
+    float *x;             // [M][K], which they are written to
 };
 
 // eight weights as they lie in memory
@@ -345,8 +348,9 @@ struct Raw8<bf16_t> {
 // two layers' QKV 82 -> 74, 103 -> 92, 50 -> 48.)   An element's sums are the same in all forms.
 // grid: (features / 16, or pairs of 16; ceil(M / (16 RT)))
 enum { FEW_NO = 0, FEW_ROWS = 1, FEW_ROWS_LDS = 2 };
-template <typename WT, int MODE, int RT, int FEW = FEW_NO>
-__global__ __launch_bounds__(512, FEW && MODE != GEN_RESIDUAL ? (gen_norm(MODE) ? 6 : 8) : (sizeof(WT) == 2 && RT == 1 ? 4 : 2)) void gemm_gen_kernel(GenArgs a)
+// tok: the first QKV of a step, whose rows are looked up in the embedding table (null otherwise)
+template <typename WT, int MODE, int RT, int FEW, bool FIRST>
+__device__ __forceinline__ void gemm_gen_block(const GenArgs &a, const int32_t *tok)
 {
     constexpr int NW = gen_pairs(MODE) ? 2 : 1, S = sizeof(WT) == 2 ? 2 : 1, WAVES = 8,
                   U = (FEW && MODE != GEN_RESIDUAL) || (S == 2 && RT == 1 && MODE == GEN_QKV) ? 1 : (S == 2 && (NW == 2 || RT == 2 || MODE == GEN_LOGITS) ? 2 : 3);
@@ -375,6 +379,9 @@ __global__ __launch_bounds__(512, FEW && MODE != GEN_RESIDUAL ? (gen_norm(MODE) 
         if (NW == 2) w[NW - 1] = (const WT *)a.W1 + (size_t)(blockIdx.x * 16 + r) * K;
     }
     const WT *gain = (const WT *)a.gain;
+    const WT *row[RT];   // FIRST: the embedding of row m0 + 16 t + r
+#pragma unroll
+    for (int t = 0; t < RT; ++t) row[t] = FIRST && m0 + 16 * t + r < a.M ? (const WT *)a.embed + (size_t)tok[m0 + 16 * t + r] * K : nullptr;
     // QKV: what the epilogue of the finishing waves needs besides the sums, requested first: position -> page, angles
     int pos = 0, page = 0;
     float2 cs[4];
@@ -427,10 +434,28 @@ __global__ __launch_bounds__(512, FEW && MODE != GEN_RESIDUAL ? (gen_norm(MODE) 
                     for (int n = 0; n < NW; ++n) wv[u][s][n].load(w[n] + k);
 #pragma unroll
                     for (int t = 0; t < RT; ++t)
-                        if (m0 + 16 * t + r < a.M) load8((FEW == FEW_ROWS_LDS ? x_lds : a.X) + (size_t)(m0 + 16 * t + r) * K + k, xv[u][s][t]);
+                        if (m0 + 16 * t + r < a.M) {
+                            if (FIRST) load8(row[t] + k, xv[u][s][t]);
+                            else load8((FEW == FEW_ROWS_LDS ? x_lds : a.X) + (size_t)(m0 + 16 * t + r) * K + k, xv[u][s][t]);
+                        }
                     if (NORM) gv[u][s].load(gain + k);
                 }
             }
+        if (FIRST && blockIdx.x == 0) {   // the first block leaves the rows where the residual stream begins
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    const int k = (c0 + u * WAVES) * 32 * S + 8 * (S * kg + s);
+#pragma unroll
+                    for (int t = 0; t < RT; ++t)
+                        if (k < K && m0 + 16 * t + r < a.M) {
+                            f32x4 *x = reinterpret_cast<f32x4 *>(a.x + (size_t)(m0 + 16 * t + r) * K + k);
+                            x[0] = (f32x4){xv[u][s][t][0], xv[u][s][t][1], xv[u][s][t][2], xv[u][s][t][3]};
+                            x[1] = (f32x4){xv[u][s][t][4], xv[u][s][t][5], xv[u][s][t][6], xv[u][s][t][7]};
+                        }
+                }
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -519,6 +544,20 @@ __global__ __launch_bounds__(512, FEW && MODE != GEN_RESIDUAL ? (gen_norm(MODE) 
             }
         }
     }
+}
+
+template <typename WT, int MODE, int RT, int FEW = FEW_NO>
+__global__ __launch_bounds__(512, FEW && MODE != GEN_RESIDUAL ? (gen_norm(MODE) ? 6 : 8) : (sizeof(WT) == 2 && RT == 1 ? 4 : 2)) void gemm_gen_kernel(GenArgs a)
+{
+    gemm_gen_block<WT, MODE, RT, FEW, false>(a, nullptr);
+}
+// The first QKV of a step: its rows come from the embedding table, without a launch in front of it that copies them.  A step of
+// a small model is a chain of launches of 3-4 us: 90 -> 85 us at d 256, two layers, fp32, 5 rows.  Prompts keep the launch: their
+// pieces have up to 256 rows, whose tokens do not fit a kernel's arguments.
+template <typename WT, int RT>
+__global__ __launch_bounds__(512, sizeof(WT) == 2 && RT == 1 ? 4 : 2) void gemm_gen_first_kernel(GenArgs a, StepTokens tok)
+{
+    gemm_gen_block<WT, GEN_QKV, RT, FEW_NO, true>(a, tok.t);
 }
 
 // ------------------------------------------------------------- attention

@@ -34,3 +34,25 @@ def test_pieces_give_the_bits_of_windows(shape, path, max_window, max_positions,
     for layer in range(shape.n_layers):
         for x, y in zip(whole.read(layer, 0, capacity), parts.read(layer, 0, capacity)):
             assert torch.equal(x, y)
+
+
+# a step's first QKV takes its rows from the embedding table in 16-byte loads; a table at another address is copied by a launch
+# of its own, one element at a time.  Both give the same bits, at one row group and at two
+@pytest.mark.parametrize("shape,path", [(synth.TINY, B.GEMM_AUTO), (synth.MID_BF16, B.GEMM_DOT)])
+@pytest.mark.parametrize("rows", [1, 16, 17, 32])
+def test_embedding_table_at_any_address(shape, path, rows):
+    w = synth.make_weights(shape, 4, device="cuda")
+    table = w["embed"]
+    moved = torch.empty(table.numel() + 1, dtype=table.dtype, device="cuda")[1:].view_as(table).copy_(table)
+    assert table.data_ptr() % 16 == 0 and moved.data_ptr() % 16 == table.element_size()
+    tokens = synth.random_tokens(shape.vocab, rows, 9)
+    seen = []
+    for embed in (table, moved):
+        model = B.Model(shape, {**w, "embed": embed}, max_window=32, max_positions=64, gemm_path=path)
+        kv = B.KVCache(model, rows)
+        logits = torch.empty(rows, shape.vocab, dtype=torch.float32, device="cuda")
+        B.verify(model, kv, tokens, B.APPEND, out_logits=logits)
+        seen.append((logits, [kv.read(layer, 0, rows) for layer in range(shape.n_layers)]))
+    assert torch.equal(seen[0][0], seen[1][0])
+    for x, y in zip(seen[0][1], seen[1][1]):
+        assert torch.equal(x[0], y[0]) and torch.equal(x[1], y[1])
