@@ -240,8 +240,8 @@ int32_t anpd_verify_tree(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, 
 
 /* Several sequences in one step: their windows go through every weight matrix together, so the
  * weights are streamed once for all of them.  Measured at the 7B shape from 512 cached positions on, in
- * one-row steps: one window of up to 8 rows 1.04, of 9 to 16 rows 1.3, of 17 to 32 rows 1.5 to 1.6; sequences of one
- * row each, whose caches are all read, 8: 1.4, 16: 1.8, 32: 2.4; 8 sequences of 4 rows 1.8.  The
+ * one-row steps: one window of up to 8 rows 1.04, of 9 to 16 rows 1.3, of 17 to 32 rows 1.4 to 1.45; sequences of one
+ * row each, whose caches are all read, 8: 1.4, 16: 1.7, 32: 2.3; 8 sequences of 4 rows 1.6.  The
  * paper verifies one sequence at a time (Algorithm 1); this is the same step for n_seq independent
  * runs of it.
  *   kvs (host array of n_seq handles): one cache per sequence, all of model m, all different.

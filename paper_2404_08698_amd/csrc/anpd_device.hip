@@ -3,9 +3,9 @@
 // One step (paper, Section 3.1 "Parallel Decoding" step 2; Algorithm 1) is a
 // fixed sequence of kernel launches on the caller's stream.  The window's
 // tokens go to the kernels by value; cache length and page table, and the
-// description of a draft tree or of a batch, are read from device memory (the
-// tree and the batch are uploaded unless the step is one kernel, which takes
-// them by value as well).  The kernels write (accepted, next, predictions)
+// description of a draft tree or of a batch, are read from device memory (a
+// kernel that takes them by value writes them there, unless the step is one
+// kernel, which takes them by value itself).  The kernels write (accepted, next, predictions)
 // into pinned host memory, and the logits where the caller wants them.
 #include <hip/hip_runtime.h>
 
@@ -1593,7 +1593,7 @@ int32_t anpd_verify_tree(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, 
     const int32_t *res = m->pin + 32;
     LogitsTo logits = {out_logits, (size_t)n_window * m->cfg.vocab, nullptr};
     // windows of up to 8 rows: the one-kernel step in its draft-tree form (tree by value as well); otherwise one
-    // launch per operation, the tree uploaded
+    // launch per operation, the tree written to device memory by a kernel in front
     const bool one_kernel = m->mega && m->mega_tree && n_window <= 8;
     if (one_kernel) {
         rc = run_step_mega(m, kv, window, n_window, ANPD_APPEND, out_logits ? logits.find(m) : nullptr, st, tp);

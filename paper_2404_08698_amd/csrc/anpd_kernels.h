@@ -293,7 +293,7 @@ __global__ __launch_bounds__(256) void embed_kernel(const WT *__restrict__ E, St
 // the block sums x^2 of its rows beside it, 1 / rms scales the result), and so are rotary embedding and cache
 // write, residual add and SwiGLU.  One layer is five launches where one per operation took eleven, and a launch
 // takes 3-4 us instead of 11 (dot products with a butterfly over the lanes per output: 40 us at 32 rows, which
-// it took eight at a time).
+// it took eight at a time).  The first QKV of a step looks its rows up in the embedding table as well.
 enum { GEN_PLAIN = 0, GEN_QKV = 1, GEN_RESIDUAL = 2, GEN_GATE_UP = 3, GEN_LOGITS = 4 };
 __host__ __device__ constexpr bool gen_norm(int mode) { return mode == GEN_QKV || mode == GEN_GATE_UP || mode == GEN_LOGITS; }
 __host__ __device__ constexpr bool gen_pairs(int mode) { return mode == GEN_QKV || mode == GEN_GATE_UP; }
