@@ -567,7 +567,8 @@ __global__ __launch_bounds__(512, sizeof(WT) == 2 && RT == 1 ? 4 : 2) void gemm_
 // keys, computes for each row the split's score maximum, sum of exponentials and unnormalised weighted V sum on
 // the fp32 matrix cores; the last block of a (head, row group) merges the splits of its rows in increasing
 // order.  Row r sees keys 0..len + r; keys it must not see get
-// weight exactly 0, so a row's numbers do not depend on M.
+// weight exactly 0 and, where their V is not finite, take no part at all, so a row's numbers do not depend on M or on the
+// rows behind it.
 // A long window is gone through in launches of at most part_rows rows, of which this one takes those from row0 on.
 // part: outputs [head][split][part_rows][DH], then (maximum, denominator) [head][split][part_rows][2].
 // counter: [row group][head], a 256-byte line each, zero between calls.
@@ -637,12 +638,14 @@ __global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ q, 
     }
     const f32x4 s = ((sq[0] + sq[1]) + (sq[2] + sq[3])) + ((sq[4] + sq[5]) + (sq[6] + sq[7]));
     const uint32_t vis = row_mask && m < M ? row_mask[m] : 0u;
+    // whether row `row`, whose mask is `mask`, sees key `key`
+    auto sees = [&](int row, uint32_t mask, int key) __attribute__((always_inline)) {
+        return row_mask ? key < L || (key - L < 32 && ((mask >> (key - L)) & 1u)) : key <= L + row;
+    };
     float p[4], mx = kMasked;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int key = key0 + 4 * kg + i;
-        const bool sees = row_mask ? key < L || (key - L < 32 && ((vis >> (key - L)) & 1u)) : key <= L + m;
-        p[i] = m < M && sees ? s[i] * scale : kMasked;
+        p[i] = m < M && sees(m, vis, key0 + 4 * kg + i) ? s[i] * scale : kMasked;
         mx = fmaxf(mx, p[i]);
     }
     mx = rows_max(mx);
@@ -659,12 +662,29 @@ __global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ q, 
     den = rows_sum(den);
     if (kg == 0) wden[wave][r] = den;
     // ---- weighted V: lane (r, kg) has dimensions 16 c + 4 kg .. + 4 of row m
+    // A weight of 0 does not keep out what is not finite.  Where a key that some row must not see has such a V, the rows
+    // are taken one at a time, each over the keys that it sees.
+    bool apart = false;
+    if (key0 + 15 > L + (row_mask ? 0 : m0)) {
+        float z = 0.f;
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        f32x4 o[4];
+        for (int c = 0; c < NC; ++c)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c][i], p[i], (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-        *reinterpret_cast<f32x4 *>(red[wave][c][lane]) = (o[0] + o[1]) + (o[2] + o[3]);
+            for (int i = 0; i < 4; ++i) z = fmaf(vf[c][i], 0.f, z);
+        apart = __builtin_amdgcn_ballot_w64(z != 0.f) != 0;
+    }
+    for (int q = apart ? 0 : 15; q < 16; ++q) {
+        const uint32_t vis_q = (uint32_t)__builtin_amdgcn_readlane((int)vis, q);   // (lane q has row m0 + q)
+        bool seen[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) seen[i] = !apart || sees(m0 + q, vis_q, key0 + 4 * kg + i);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            f32x4 o[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(seen[i] ? vf[c][i] : 0.f, p[i], (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            if (!apart || r == q) *reinterpret_cast<f32x4 *>(red[wave][c][lane]) = (o[0] + o[1]) + (o[2] + o[3]);
+        }
     }
     __syncthreads();
     const size_t slot0 = ((size_t)head * max_splits) * part_rows, stride = (size_t)part_rows;   // rows of (head, split 0); rows per split

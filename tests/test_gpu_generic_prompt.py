@@ -56,3 +56,21 @@ def test_embedding_table_at_any_address(shape, path, rows):
     assert torch.equal(seen[0][0], seen[1][0])
     for x, y in zip(seen[0][1], seen[1][1]):
         assert torch.equal(x[0], y[0]) and torch.equal(x[1], y[1])
+
+
+# a row whose keys and values are not finite: the first of a row group, inside one, the last of a piece's keys that a wave holds;
+# one window of a prompt before it or a whole one in its piece, one launch of attention per piece or several
+@pytest.mark.parametrize("shape,path,max_window,max_positions", [(synth.TINY, B.GEMM_AUTO, 5, 400), (synth.TINY, B.GEMM_AUTO, 32, 20000),
+                                                                 (synth.MID_GQA, B.GEMM_DOT, 8, 400)])
+@pytest.mark.parametrize("at", [1, 16, 40, 47, 63, 64, 90])
+def test_a_row_that_is_not_finite_leaves_the_rows_before_it_alone(shape, path, max_window, max_positions, at):
+    w = synth.make_weights(shape, 3, device="cuda")
+    w["embed"][7] = float("nan")
+    model = B.Model(shape, w, max_window=max_window, max_positions=max_positions, gemm_path=path)
+    prompt = [t if t != 7 else 8 for t in synth.random_tokens(shape.vocab, 100, 11)]
+    whole, before = B.KVCache(model, 128), B.KVCache(model, 128)
+    B.prefill(model, whole, prompt[:at] + [7] + prompt[at + 1:])
+    B.prefill(model, before, prompt[:at])
+    for layer in range(shape.n_layers):
+        for x, y in zip(whole.read(layer, 0, at), before.read(layer, 0, at)):
+            assert torch.equal(x, y), layer   # (NaN equals nothing)
