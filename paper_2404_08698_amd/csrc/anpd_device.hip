@@ -603,6 +603,7 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int 
     }
     const int before = piece == PIECE_LAST ? M - 1 : 0;   // rows in front of the first whose logits are wanted
     base.M = M - before;
+    HIP_TRY(hipGetLastError());   // (of the launches so far: the lookup clears it)
     float *logits = logits_to.find(m);
     if ((rc = launch_gen_few<KT, GEN_LOGITS>(gemm(x + (size_t)before * d, d, m->lm_head, m->final_norm, logits, V), V / 16, m->n_cu, st)) != ANPD_OK) return rc;
     mark(m, ANPD_PROF_GEMM_LM_HEAD, st);
@@ -766,6 +767,7 @@ int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, 
         }
         mark(m, ANPD_PROF_GEMM_DOWN, st);
     }
+    HIP_TRY(hipGetLastError());   // (of the launches so far: the lookup clears it)
     float *logits = logits_to.find(m);
     {
         FastArgs a = base;
@@ -1123,6 +1125,7 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
     hipLaunchKernelGGL(prefill_last_kernel, dim3((unsigned)(d / 16)), dim3(64), 0, st, x + (size_t)(r0 + P - 1) * d,
                        (const float *)(part + (size_t)(r0 + P - 1) * d), kPgSplit, (size_t)G * 16 * d, (const bf16_t *)m->final_norm, (bf16_t *)(ws + L.xp_d), (float *)(ws + L.ssp_a), kv->d_len, len + P - 1);
     mark(m, ANPD_PROF_OTHER, st);
+    HIP_TRY(hipGetLastError());   // (of the launches so far: the lookup clears it)
     float *logits = logits_to.find(m);
     {
         FastArgs a;

@@ -150,6 +150,30 @@ def test_a_prompt_in_windows_that_fails_half_way_leaves_the_cache_as_it_was(stub
     in_child(stub, "child_failing_prompt", dtype, path)
 
 
+def child_failing_launch(dtype, path):
+    """Every launch of a step and of a prompt fails once while the logits go to memory that the runtime does not know (the query of
+    it fails, too, and leaves an error of its own): the call says so."""
+    h = Host(dtype=dtype, path=int(path))
+    kv = h.cache(256)
+    unknown = C.create_string_buffer(20 * 512 * 4 + 16)
+    out = (C.addressof(unknown) + 15) // 16 * 16
+    for call in (lambda: h.verify(kv, 20, out), lambda: h.prefill(kv, 33, out)):
+        h.stub.stub_forget()
+        h.ok(call())
+        for nth in range(1, h.stub.stub_launches() + 1):
+            h.ok(h.L.anpd_kv_truncate(kv, 0, None))
+            h.stub.hipGetLastError()
+            h.stub.stub_fail_launch(nth)
+            assert call() == h.B.E_HIP, (nth, h.names())
+        h.stub.hipGetLastError()
+        h.ok(h.L.anpd_kv_truncate(kv, 0, None))
+
+
+@pytest.mark.parametrize("dtype,path", [("bf16", 4), ("bf16", 1), ("f32", 0)])
+def test_a_launch_that_fails_in_front_of_the_lookup_of_the_logits_buffer_is_reported(stub, dtype, path):
+    in_child(stub, "child_failing_launch", dtype, path)
+
+
 def child_route(lengths, heads, kv_heads, dh, expected):
     lengths, heads, dh = [int(x) for x in lengths.split(",")], int(heads), int(dh)
     h = Host(d=heads * dh, heads=heads, dh=dh, kv_heads=int(kv_heads), max_positions=4200)
