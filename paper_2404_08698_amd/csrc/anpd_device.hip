@@ -546,11 +546,11 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int 
 
     m->ev_used = 0;
     mark(m, -1, st);
-    // (the tokens by value, a window of them per launch; a step's first QKV looks its rows up itself, in 16-byte loads that an
+    // (the tokens by value, as many per launch as its arguments take; a step's first QKV looks its rows up itself, in 16-byte loads that an
     // embedding table at an odd address does not get)
     const bool embed_in_qkv = piece == PIECE_NONE && ((uintptr_t)m->embed & 15) == 0;
-    for (int i = 0; i < M && !embed_in_qkv; i += c.max_window) {
-        const int n = M - i < c.max_window ? M - i : c.max_window;
+    for (int i = 0; i < M && !embed_in_qkv; i += kMaxRows) {
+        const int n = M - i < kMaxRows ? M - i : kMaxRows;
         hipLaunchKernelGGL((embed_kernel<KT>), dim3(n), dim3(256), 0, st, (const KT *)m->embed, step_tokens(tokens + i, n), x + (size_t)i * d, d);
     }
     mark(m, ANPD_PROF_OTHER, st);

@@ -101,8 +101,7 @@ def child_logits(dtype, path):
         h.ok(h.L.anpd_kv_truncate(kv, 0, None))
         direct = h.memory(size)
         h.ok(call(direct))
-        if int(path) == h.B.GEMM_MFMA_LAUNCHES or rows > 1:   # (a prompt on the generic path copies its last row)
-            assert h.logits_of_argmax() == direct
+        assert h.logits_of_argmax() == direct
         for other in (h.memory(size, offset=4), h.memory(size, device=1)):    # not for wide stores; another GPU's
             h.ok(h.L.anpd_kv_truncate(kv, 0, None))
             h.ok(call(other))
@@ -119,35 +118,37 @@ def test_logits_go_straight_to_a_buffer_that_holds_them_only(stub, dtype, path):
     in_child(stub, "child_logits", dtype, path)
 
 
-def child_failing_prompt(dtype, path):
-    """Every launch of a prompt of three windows fails once; the copy of its logits fails, too."""
-    h = Host(dtype=dtype, path=int(path), max_window=16)
-    kv = h.cache(256, 20)
+def child_failing_prompt(dtype, path, max_window):
+    """Every launch of a prompt of three pieces fails once; the copy of its logits fails, too."""
+    h = Host(dtype=dtype, path=int(path), max_window=int(max_window), max_positions=700)
+    kv = h.cache(700, 20)
     d_len = C.c_int32.from_address(h.length_at[kv.value])
 
     def unchanged():
         h.stub.hipGetLastError()
         assert h.L.anpd_kv_length(kv) == 20 and d_len.value == 20
     h.stub.stub_forget()
-    h.ok(h.prefill(kv, 40))
+    h.ok(h.prefill(kv, 600))
     launches = h.stub.stub_launches()
-    assert sum("embed_kernel" in n for n in h.names()) == 3 and h.L.anpd_kv_length(kv) == 60
+    # pieces of 256, 256 and 88 rows, whatever the window; 32 tokens per launch of the embedding
+    assert sum("advance_length" in n for n in h.names()) == 2 and h.L.anpd_kv_length(kv) == 620
+    assert sum("embed_kernel" in n for n in h.names()) == 8 + 8 + 3
     for nth in range(1, launches + 1):
         h.ok(h.L.anpd_kv_truncate(kv, 20, None))
-        d_len.value = 36        # as the first window leaves it (the stand-in runs no kernel)
+        d_len.value = 276       # as the first piece leaves it (the stand-in runs no kernel)
         h.stub.stub_fail_launch(nth)
-        assert h.prefill(kv, 40) == h.B.E_HIP
+        assert h.prefill(kv, 600) == h.B.E_HIP
         unchanged()
-    d_len.value = 60
-    assert h.prefill(kv, 40, h.memory(512 * 4 - 4)) == h.B.E_HIP
+    d_len.value = 620
+    assert h.prefill(kv, 600, h.memory(512 * 4 - 4)) == h.B.E_HIP
     unchanged()
-    h.ok(h.prefill(kv, 40))
-    assert h.L.anpd_kv_length(kv) == 60
+    h.ok(h.prefill(kv, 600))
+    assert h.L.anpd_kv_length(kv) == 620
 
 
-@pytest.mark.parametrize("dtype,path", [("f32", 0), ("bf16", 1)])
-def test_a_prompt_in_windows_that_fails_half_way_leaves_the_cache_as_it_was(stub, dtype, path):
-    in_child(stub, "child_failing_prompt", dtype, path)
+@pytest.mark.parametrize("dtype,path,max_window", [("f32", 0, 16), ("f32", 0, 1), ("bf16", 1, 16)])
+def test_a_prompt_in_pieces_that_fails_half_way_leaves_the_cache_as_it_was(stub, dtype, path, max_window):
+    in_child(stub, "child_failing_prompt", dtype, path, max_window)
 
 
 def child_failing_launch(dtype, path):
