@@ -292,10 +292,10 @@ int32_t launch_wide(const FastArgs &a, int blocks, hipStream_t st)
     return launch_lds(gemm_wide_kernel<T, D, EPI>, attr_set, blocks, kFastThreads, (size_t)4 * kFastWaves * 4 * 256 * sizeof(float), a, st);
 }
 template <int NT, int EPI>
-int32_t launch_tile(const FastArgs &a, int waves, hipStream_t st)
+int32_t launch_tile(const FastArgs &a, int waves, int n_cu, hipStream_t st)
 {
     static bool attr_set = false;
-    return launch_lds(gemm_tile_kernel<NT, EPI>, attr_set, (a.n_tiles + waves - 1) / waves, (waves + 1) * 64, tile_lds_bytes(NT), a, st);
+    return launch_lds(gemm_tile_kernel<NT, EPI>, attr_set, a.n_tiles < n_cu ? a.n_tiles : n_cu, (waves + 1) * 64, tile_lds_bytes(NT), a, st);
 }
 
 template <int EPI>
@@ -319,9 +319,9 @@ int32_t launch_fast(FastArgs &a, int n_cu, bool force_stream, hipStream_t st)
         else hipLaunchKernelGGL((gemm_stream_kernel<2, EPI>), grid, block, smem, st, a);
     } else {
         // windows of 9..32 rows: a tile per wave where one round of blocks takes them all; else (LM heads) blocks of a
-        // contiguous range of tiles, in as few passes over the operand as the accumulators allow
+        // contiguous range of tiles, in as few passes over the operand as the accumulators allow.
         const int per_block = (a.n_tiles + n_cu - 1) / n_cu;
-        if (per_block <= kTileWaves) return a.cls == 32 ? launch_tile<4, EPI>(a, per_block, st) : launch_tile<2, EPI>(a, per_block, st);
+        if (per_block <= kTileWaves) return a.cls == 32 ? launch_tile<4, EPI>(a, per_block, n_cu, st) : launch_tile<2, EPI>(a, per_block, n_cu, st);
         if (a.cls == 16) {
             static bool attr_set = false;
             return launch_lds(gemm_group_kernel<2, 8, EPI>, attr_set, n_cu, kFastThreads, (size_t)8 * kFastWaves * 2 * 256 * sizeof(float), a, st);

@@ -52,6 +52,7 @@ void stub_forget(void) { g_launches.clear(); g_syncs = 0; }
 int stub_launches(void) { return (int)g_launches.size(); }
 int stub_syncs(void) { return g_syncs; }
 const char *stub_name(int i) { return g_launches[(size_t)i].name.c_str(); }
+unsigned stub_blocks(int i) { const dim3 &g = g_launches[(size_t)i].grid; return g.x * g.y * g.z; }
 void *stub_arg0(int i) { return g_launches[(size_t)i].arg0[0]; }
 
 // ---- what the compiler's host code calls

@@ -175,6 +175,25 @@ def test_a_launch_that_fails_in_front_of_the_lookup_of_the_logits_buffer_is_repo
     in_child(stub, "child_failing_launch", dtype, path)
 
 
+def child_tile_blocks():
+    """A tile per wave: every compute unit gets a block, as long as there are tiles (257 tiles were 129 blocks of two)."""
+    h = Host()
+    n_tiles = [1, 3, 255, 256, 257, 300, 512, 513, 960, 1376, 1791, 1792]
+    for rows in (9, 17):
+        for n in n_tiles:
+            if rows <= 16 and n <= 256:     # (another kernel's)
+                continue
+            h.stub.stub_forget()
+            x, w, y, ws = h.memory(4096), h.memory(4096), h.memory(4096), h.memory(16384)
+            h.ok(h.L.anpd_linear(x, w, y, rows, 16 * n, 64, h.B.BF16, h.B.GEMM_MFMA, ws, 16384, None))
+            at = [i for i, k in enumerate(h.names()) if "gemm_tile_kernel" in k]
+            assert len(at) == 1 and h.stub.stub_blocks(at[0]) == min(n, 256), (rows, n, h.names())
+
+
+def test_tiles_of_a_wide_window_are_spread_over_all_compute_units(stub):
+    in_child(stub, "child_tile_blocks")
+
+
 def child_route(lengths, heads, kv_heads, dh, expected):
     lengths, heads, dh = [int(x) for x in lengths.split(",")], int(heads), int(dh)
     h = Host(d=heads * dh, heads=heads, dh=dh, kv_heads=int(kv_heads), max_positions=4200)
