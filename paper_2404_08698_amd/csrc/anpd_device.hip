@@ -291,11 +291,11 @@ int32_t launch_wide(const FastArgs &a, int blocks, hipStream_t st)
     static bool attr_set = false;
     return launch_lds(gemm_wide_kernel<T, D, EPI>, attr_set, blocks, kFastThreads, (size_t)4 * kFastWaves * 4 * 256 * sizeof(float), a, st);
 }
-template <int NT, int EPI>
+template <int NT, int WAVES, int EPI>
 int32_t launch_tile(const FastArgs &a, int waves, int n_cu, hipStream_t st)
 {
     static bool attr_set = false;
-    return launch_lds(gemm_tile_kernel<NT, EPI>, attr_set, a.n_tiles < n_cu ? a.n_tiles : n_cu, (waves + 1) * 64, tile_lds_bytes(NT), a, st);
+    return launch_lds(gemm_tile_kernel<NT, WAVES, EPI>, attr_set, a.n_tiles < n_cu ? a.n_tiles : n_cu, (waves + 1) * 64, tile_lds_bytes(NT), a, st);
 }
 
 template <int EPI>
@@ -320,8 +320,13 @@ int32_t launch_fast(FastArgs &a, int n_cu, bool force_stream, hipStream_t st)
     } else {
         // windows of 9..32 rows: a tile per wave where one round of blocks takes them all; else (LM heads) blocks of a
         // contiguous range of tiles, in as few passes over the operand as the accumulators allow.
+        // (17..32 rows, at most a tile per compute unit: eight waves of a block on it took, traced, 512 features of K 4096 /
+        // 11008 / 13824 15.1 / 30.9 / 36.0 us; one wave with 16 k-steps in flight 13.6 / 30.1 / 37.6, with 32 13.0 / 28.6 / 35.9;
+        // 4096 features 16.4 / 34.4 / 40.3, 14.7 / 33.2 / 40.9, 14.7 / 32.3 / 39.6.  K that does not fill the longer ring has
+        // nothing of it: K = 256 5.5 -> 5.9, K = 1024 5.3 -> 5.2.)
         const int per_block = (a.n_tiles + n_cu - 1) / n_cu;
-        if (per_block <= kTileWaves) return a.cls == 32 ? launch_tile<4, EPI>(a, per_block, n_cu, st) : launch_tile<2, EPI>(a, per_block, n_cu, st);
+        if (per_block == 1 && a.cls == 32 && a.nks >= tile_depth(4, 1)) return launch_tile<4, 1, EPI>(a, 1, n_cu, st);
+        if (per_block <= kTileWaves) return a.cls == 32 ? launch_tile<4, kTileWaves, EPI>(a, per_block, n_cu, st) : launch_tile<2, kTileWaves, EPI>(a, per_block, n_cu, st);
         if (a.cls == 16) {
             static bool attr_set = false;
             return launch_lds(gemm_group_kernel<2, 8, EPI>, attr_set, n_cu, kFastThreads, (size_t)8 * kFastWaves * 2 * 256 * sizeof(float), a, st);

@@ -837,13 +837,14 @@ __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t buffer, uint4
 constexpr int kTileChunk = kFastWaves;   // k-steps per buffer of the operand: one of every class
 constexpr int kTileBufs = 3;
 constexpr int kTileWaves = 7;   // most tiles per block
-// weight fragments in flight per wave: what the registers hold beside the sums
-__host__ __device__ constexpr int tile_depth(int NT) { return NT == 2 ? 32 : 16; }
+// Weight fragments in flight per wave: what the registers hold beside the sums, of which a block of one tile (WAVES = 1), with a
+// SIMD to itself, has twice as many.
+__host__ __device__ constexpr int tile_depth(int NT, int WAVES) { return NT == 2 || WAVES == 1 ? 32 : 16; }
 __host__ __device__ constexpr size_t tile_lds_bytes(int NT) { return (size_t)kTileBufs * kTileChunk * NT * 1024 + 64 * 32 * 4; }
-template <int NT, int EPI>
-__global__ __launch_bounds__((kTileWaves + 1) * 64) void gemm_tile_kernel(FastArgs a)
+template <int NT, int WAVES, int EPI>
+__global__ __launch_bounds__((WAVES + 1) * 64) void gemm_tile_kernel(FastArgs a)
 {
-    constexpr int D = tile_depth(NT), DX = kTileChunk, NB = kTileBufs, UNITS = DX * NT;
+    constexpr int D = tile_depth(NT, WAVES), DX = kTileChunk, NB = kTileBufs, UNITS = DX * NT;
     extern __shared__ uint4 xs[];   // [NB][DX][NT][64], then the norm's group sums [64][32]
     __shared__ float rinv[32];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = (int)(blockDim.x >> 6) - 1;

@@ -176,18 +176,20 @@ def test_a_launch_that_fails_in_front_of_the_lookup_of_the_logits_buffer_is_repo
 
 
 def child_tile_blocks():
-    """A tile per wave: every compute unit gets a block, as long as there are tiles (257 tiles were 129 blocks of two)."""
+    """A tile per wave: every compute unit gets a block, as long as there are tiles (257 tiles were 129 blocks of two); a wave
+    that is alone on its compute unit has a longer ring if K fills it."""
     h = Host()
     n_tiles = [1, 3, 255, 256, 257, 300, 512, 513, 960, 1376, 1791, 1792]
-    for rows in (9, 17):
+    x, w, y, ws = (h.memory(n) for n in (4096, 4096, 4096, 1 << 18))
+    for rows, k in ((9, 64), (17, 64), (17, 992), (17, 1000), (32, 1024)):
         for n in n_tiles:
             if rows <= 16 and n <= 256:     # (another kernel's)
                 continue
             h.stub.stub_forget()
-            x, w, y, ws = h.memory(4096), h.memory(4096), h.memory(4096), h.memory(16384)
-            h.ok(h.L.anpd_linear(x, w, y, rows, 16 * n, 64, h.B.BF16, h.B.GEMM_MFMA, ws, 16384, None))
-            at = [i for i, k in enumerate(h.names()) if "gemm_tile_kernel" in k]
+            h.ok(h.L.anpd_linear(x, w, y, rows, 16 * n, k, h.B.BF16, h.B.GEMM_MFMA, ws, 1 << 18, None))
+            at = [i for i, name in enumerate(h.names()) if "gemm_tile_kernel" in name]
             assert len(at) == 1 and h.stub.stub_blocks(at[0]) == min(n, 256), (rows, n, h.names())
+            assert ("gemm_tile_kernelILi4ELi1E" in h.names()[at[0]]) == (n <= 256 and k > 992), (rows, n, k)
 
 
 def test_tiles_of_a_wide_window_are_spread_over_all_compute_units(stub):
