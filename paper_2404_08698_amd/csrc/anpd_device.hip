@@ -1081,12 +1081,18 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
             if ((rc = launch_prefill_gemm<EPI_QKV>(a, m->n_cu, st)) != ANPD_OK) return rc;
         }
         mark(m, ANPD_PROF_GEMM_QKV, st);
-        if (dh == 128)
-            hipLaunchKernelGGL((prefill_attn_kernel<128>), dim3((unsigned)H, (unsigned)((G + 1) / 2)), dim3(256), 0, st, (const uint4 *)qp,
-                               (const bf16_t *)kv->pool, kv->d_table, G, len, P, l, c.n_layers, H, kv_heads_of(c), scale, xq_att, nks_d);
-        else
-            hipLaunchKernelGGL((prefill_attn_kernel<64>), dim3((unsigned)H, (unsigned)((G + 1) / 2)), dim3(256), 0, st, (const uint4 *)qp,
-                               (const bf16_t *)kv->pool, kv->d_table, G, len, P, l, c.n_layers, H, kv_heads_of(c), scale, xq_att, nks_d);
+        {
+            const dim3 grid((unsigned)H, (unsigned)((G + 1) / 2));
+            // query rows in LDS where that brings one more block to a compute unit, else in registers (see the kernel)
+            const bool shared = (long long)H * ((G + 1) / 2) > (dh == 128 ? 1 : 2) * m->n_cu;
+#define ANPD_ATTN_P(DH_, Q_)                                                                                                      \
+    hipLaunchKernelGGL((prefill_attn_kernel<DH_, Q_>), grid, dim3(256), 0, st, (const uint4 *)qp, (const bf16_t *)kv->pool, kv->d_table, G, \
+                       len, P, l, c.n_layers, H, kv_heads_of(c), scale, xq_att, nks_d)
+            if (dh == 128) { if (shared) ANPD_ATTN_P(128, true); else ANPD_ATTN_P(128, false); }
+            else if (shared) ANPD_ATTN_P(64, true);
+            else ANPD_ATTN_P(64, false);
+#undef ANPD_ATTN_P
+        }
         mark(m, ANPD_PROF_ATTN, st);
         {
             PrefillArgs a = base;

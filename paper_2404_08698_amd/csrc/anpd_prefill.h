@@ -649,8 +649,11 @@ __global__ __launch_bounds__((kFewWaves + kFewLoaders) * 64) void prefill_few_ke
 // 7B shape, 512 / 3584 rows: 35 -> 21 / 489 -> 409 us per layer; 205 rows behind 777, 32 heads over 2 key / value heads: 63 -> 19.
 // Then nothing covered a wave's exponentials at 3584 rows: with the query rows in registers a lane of head dim 128 held 238 and 80
 // accumulators, one wave per SIMD (vector ALU 45 %, matrix cores 22 % busy).  The rows are the same for the block's four
-// waves: read from LDS for every pair, they leave 184 registers and two waves per SIMD: 512 / 3584 rows 19.5 -> 16.2 /
-// 414 -> 284 us.  (Three waves, 168 registers, some of them in scratch memory: 23.5 / 443.)
+// waves: read from LDS for every pair (QLDS), they leave 184 registers and two waves per SIMD: 512 / 3584 rows 19.5 -> 16.2 /
+// 414 -> 284 us.  (Three waves, 168 registers, some of them in scratch memory: 23.5 / 443.)  Where the blocks are too few for
+// that second wave the reads are all that is left of it, and the rows stay in registers: 128 rows, LDS / registers 7.9 / 6.7 us,
+// 256 rows, 256 blocks, 9.8 / 9.0, 320 rows behind 1000, 320 blocks, 28 / 36.  At head dim 64 two blocks fit a compute unit with the
+// rows in registers (188): 32 heads, 272 / 512 rows, 7.0 / 6.4, 10.3 / 9.9, 600 behind 1000, 608 blocks, 27.0 / 37.2.
 // A row's sums depend on absolute page numbers only, not on how the prompt was cut.  (They are not, bit for bit, those of
 // one wave going page by page with a maximum that always moves: one layer's output is 8e-6 apart, 2^-17 being what the
 // weights' two bf16 terms keep, and equally far from the 64-bit result.)
@@ -658,8 +661,8 @@ __global__ __launch_bounds__((kFewWaves + kFewLoaders) * 64) void prefill_few_ke
 // multiplied by 0, as in a step, V of later pages is not.
 // grid: (n_heads, ceil(G / 2)); later groups (more pages) start first.
 constexpr float kHugeScore = 0x1p29f;   // rounding a base-2 score of this size may move it by 2^5; below it by 2^4, weights stay under 2^(8 + 16)
-template <int DH>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_attn_kernel(const uint4 *__restrict__ qp, const bf16_t *__restrict__ pool,
+template <int DH, bool QLDS>
+__global__ __launch_bounds__(256, QLDS ? 2 : 1) void prefill_attn_kernel(const uint4 *__restrict__ qp, const bf16_t *__restrict__ pool,
                                                             const int32_t *__restrict__ page_table, int G, int L, int P,
                                                             int layer, int n_layers, int n_heads, int n_kv_heads, float scale,
                                                             bf16_t *__restrict__ xq_att, int nks_d)
@@ -677,9 +680,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int own0 = (L >> 4) + g0;                 // the first group's own page; the second group's is the next one
     const int last_page = own0 + n_grp - 1, last_pair = last_page >> 1;
 
-    for (int i = wave; i < 2 * NKS * 2; i += WAVES) {
-        const int x = i / (2 * NKS), r = i % (2 * NKS);
-        (&lds.q[0][0][0][0])[i * 64 + lane] = qp[(((size_t)head * G + g0 + (x < n_grp ? x : 0)) * 2 * NKS + r) * 64 + lane];
+    uint4 qf[2][NKS][2];   // (the query rows in registers)
+    if (QLDS) {
+        for (int i = wave; i < 2 * NKS * 2; i += WAVES) {
+            const int x = i / (2 * NKS), r = i % (2 * NKS);
+            (&lds.q[0][0][0][0])[i * 64 + lane] = qp[(((size_t)head * G + g0 + (x < n_grp ? x : 0)) * 2 * NKS + r) * 64 + lane];
+        }
+    } else {
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const uint4 *q = qp + ((size_t)head * G + g0 + (x < n_grp ? x : 0)) * NKS * 128;
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+                for (int hl = 0; hl < 2; ++hl) qf[x][ks][hl] = q[(ks * 2 + hl) * 64 + lane];
+        }
     }
     // page numbers of the wave's next 64 pairs, one pair per lane; a pair's second page, if it does not exist, is the
     // first one again (its keys get weight 0)
@@ -718,7 +733,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         load_v(pa, vf[0]);
         load_v(pb, vf[1]);
     }
-    __syncthreads();
+    if (QLDS) __syncthreads();
     if (n_pairs > 0) {
         for (int k = 0; k < n_pairs; ++k) {
             const int page0 = 2 * (wave + WAVES * k);
@@ -730,10 +745,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 for (int y = 0; y < 2; ++y) {
                     f32x4 t = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int ks = 0; ks < NKS; ++ks) {
-                        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[y][ks]), __builtin_bit_cast(bf16x8, lds.q[x][ks][0][lane]), t, 0, 0, 0);
-                        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[y][ks]), __builtin_bit_cast(bf16x8, lds.q[x][ks][1][lane]), t, 0, 0, 0);
-                    }
+                    for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+                        for (int hl = 0; hl < 2; ++hl)
+                            t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[y][ks]),
+                                                                        __builtin_bit_cast(bf16x8, QLDS ? lds.q[x][ks][hl][lane] : qf[x][ks][hl]), t, 0, 0, 0);
                     sc[x][y] = t;
                 }
             if (((k + 1) & 63) == 0) fetch_ids(k + 1);

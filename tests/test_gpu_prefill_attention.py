@@ -87,3 +87,27 @@ def test_a_key_with_a_nan_has_weight_zero_and_a_huge_one_its_weight_as_in_a_step
         B.verify(model, step, prompt[lo:lo + 8], B.APPEND, out_logits=ref)
     assert torch.isfinite(ref[-1]).all()
     assert (got - ref[-1]).abs().max().item() < 2e-2   # (as in the comparison with windows above)
+
+
+# query rows in LDS where the blocks (heads x pairs of row groups) are more than one per compute unit, two at head dim 64, in registers otherwise: a prompt whose
+# blocks are, at a page's start and inside one, against pieces of it whose blocks are not, and one of the last size that has them in registers
+@pytest.mark.parametrize("shape,rows,piece", [(synth.RING_BF16, 513, 512), (synth.RING_BF16, 600, 256), (synth.TINY_BF16, 4097, 4096), (synth.TINY_BF16, 4200, 1300)],
+                         ids=["dh128_first", "dh128", "dh64_first", "dh64"])
+@pytest.mark.parametrize("before", [0, 21])
+def test_query_rows_in_lds_and_in_registers_give_the_same_bits(shape, rows, piece, before):
+    w = synth.make_weights(shape, 3, device="cuda")
+    model = B.Model(shape, w, max_window=8, max_positions=before + rows)
+    prompt = synth.random_tokens(shape.vocab, before + rows, 11)
+    one, cut = (B.KVCache(model, before + rows) for _ in range(2))
+    logits = [torch.empty(shape.vocab, dtype=torch.float32, device="cuda") for _ in range(2)]
+    for kv in (one, cut):
+        if before:
+            B.prefill(model, kv, prompt[:before])
+    B.prefill(model, one, prompt[before:], out_logits=logits[0])
+    piece -= before % 16    # (so that its groups are as many)
+    for lo in range(before, before + rows, piece):
+        B.prefill(model, cut, prompt[lo:min(lo + piece, before + rows)], out_logits=logits[1])
+    assert torch.equal(logits[0], logits[1])
+    for layer in range(shape.n_layers):
+        for x, y in zip(one.read(layer, 0, before + rows), cut.read(layer, 0, before + rows)):
+            assert torch.equal(x, y)

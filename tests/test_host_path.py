@@ -196,6 +196,24 @@ def test_tiles_of_a_wide_window_are_spread_over_all_compute_units(stub):
     in_child(stub, "child_tile_blocks")
 
 
+def child_prompt_attention(heads, dh, length, rows, shared):
+    h = Host(d=int(heads) * int(dh), heads=int(heads), dh=int(dh), max_positions=4200)
+    kv = h.cache(4200, int(length))
+    h.stub.stub_forget()
+    h.ok(h.prefill(kv, int(rows)))
+    taken = {n for n in h.names() if "prefill_attn_kernel" in n}
+    assert len(taken) == 1 and f"prefill_attn_kernelILi{dh}ELb{shared}E" in taken.pop(), h.names()
+
+
+# blocks: heads x pairs of row groups; up to one per compute unit, two at head dim 64, have their query rows in registers
+@pytest.mark.parametrize("heads,dh,length,rows,shared", [
+    (32, 128, 0, 1, 0), (32, 128, 0, 256, 0), (32, 128, 0, 257, 1), (32, 128, 15, 241, 0), (32, 128, 15, 242, 1), (40, 128, 777, 182, 0),
+    (40, 128, 777, 205, 1), (4, 64, 0, 4096, 0), (4, 64, 0, 4097, 1),
+])
+def test_query_rows_of_a_prompt_lie_where_its_blocks_gain_by_it(stub, heads, dh, length, rows, shared):
+    in_child(stub, "child_prompt_attention", heads, dh, length, rows, shared)
+
+
 def child_route(lengths, heads, kv_heads, dh, expected):
     lengths, heads, dh = [int(x) for x in lengths.split(",")], int(heads), int(dh)
     h = Host(d=heads * dh, heads=heads, dh=dh, kv_heads=int(kv_heads), max_positions=4200)
