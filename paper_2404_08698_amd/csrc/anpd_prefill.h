@@ -183,18 +183,22 @@ __device__ __forceinline__ void prefill_epilogue(const PrefillArgs &a, int tile,
         // gate rows are in the lower half of the wave, the matching up rows in the upper half: two swaps give either half
         // both rows of two of the four features (each lane all four, with half of the lanes' work thrown away, and
         // the rows exchanged through LDS: see the kernel's comment)
-        float act[2];
+        float q[2], up[2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(y[i]), __float_as_uint(y[i + 2]), false, false);
-            const float g = __uint_as_float(p[0]), up = __uint_as_float(p[1]);
-            act[i] = g / (1.0f + expf(-g)) * up;
+            const float g = __uint_as_float(p[0]);
+            q[i] = g / (1.0f + expf(-g));
+            up[i] = __uint_as_float(p[1]);
         }
         if (valid) {
             const int k = tile * 8 + 4 * (kg & 1) + 2 * (kg >> 1);
-            const uint32_t hi = pack_bf16(act[0], act[1]);
+            const uint32_t hi = pack_bf16(q[0] * up[0], q[1] * up[1]);
             *reinterpret_cast<uint32_t *>(a.out + xq_offset(a.out_nks, m, k, 0)) = hi;
-            *reinterpret_cast<uint32_t *>(a.out + xq_offset(a.out_nks, m, k, 1)) = pack_lo(act[0], act[1], hi);
+            // (the product's rest in the fused form, by name: left to itself the compiler fuses or does not, by the code around
+            // it, and the forms' bits must agree)
+            *reinterpret_cast<uint32_t *>(a.out + xq_offset(a.out_nks, m, k, 1)) =
+                pack_bf16(fmaf(q[0], up[0], -__uint_as_float(hi << 16)), fmaf(q[1], up[1], -__uint_as_float(hi & 0xffff0000u)));
         }
     }
 }

@@ -214,6 +214,35 @@ def test_query_rows_of_a_prompt_lie_where_its_blocks_gain_by_it(stub, heads, dh,
     in_child(stub, "child_prompt_attention", heads, dh, length, rows, shared)
 
 
+def child_prompt_forms(heads, ffn, before, rows, expected, cuts):
+    import re
+    h = Host(d=128 * int(heads), heads=int(heads), dh=128, ffn=int(ffn), vocab=1024, max_positions=1700)
+    kv = h.cache(1700)
+    epilogue = {"1": "qkv", "2": "residual", "3": "gate_up"}
+
+    def forms(lo, hi):
+        h.ok(h.L.anpd_kv_truncate(kv, lo, None))
+        h.stub.stub_forget()
+        h.ok(h.prefill(kv, hi - lo))
+        found = [re.search(r"prefill_(gemm|narrow|mixed|few)_kernelILi(\d)E((?:Li\d+E)*)", k) for k in h.names()]
+        return {" ".join((m[1], epilogue[m[2]], *re.findall(r"\d+", m[3]))) for m in found if m}
+    whole = forms(int(before), int(before) + int(rows))
+    assert {f for f in whole if f.startswith(("narrow", "mixed"))} == set(expected.split(",")), whole
+    cuts = [int(x) for x in cuts.split(",")]
+    for lo, hi in zip(cuts, cuts[1:]):
+        assert all(f.startswith("few") for f in forms(lo, hi)), (lo, hi)
+
+
+def test_prompts_of_wide_models_take_the_forms_they_are_tested_for(stub):
+    """In one piece the forms that the GPU test of wide models lists, in its pieces none of them."""
+    import test_gpu_prefill_forms as G
+    for (name, rows), expected in G.CASES.items():
+        shape = G.SHAPES[name]
+        cuts = G.pieces(G.BEFORE + rows)
+        in_child(stub, "child_prompt_forms", shape.n_heads, shape.d_ffn, G.BEFORE, rows, ",".join(sorted(expected)),
+                 ",".join(str(lo) for lo, _ in cuts) + f",{cuts[-1][1]}")
+
+
 def child_route(lengths, heads, kv_heads, dh, expected):
     lengths, heads, dh = [int(x) for x in lengths.split(",")], int(heads), int(dh)
     h = Host(d=heads * dh, heads=heads, dh=dh, kv_heads=int(kv_heads), max_positions=4200)
