@@ -1,5 +1,6 @@
-"""The prompt GEMMs of a few rows: pieces of one row to 128, on either side of every row group and of every form's limit,
-leave bit for bit what the prompt in one piece does (its rows in the wide blocks): an element's sums do not depend on the form."""
+"""The prompt GEMMs with a tile per wave: pieces of one row to 128, on either side of every row group and of the numbers of row
+groups per block, leave bit for bit what the prompt in one piece does (its rows in the wide blocks; a small model's, in the same
+form): an element's sums do not depend on the form.  The forms that only wide models take: test_gpu_prefill_forms.py."""
 import pytest
 import torch
 

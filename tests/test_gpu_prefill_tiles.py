@@ -1,5 +1,5 @@
 """The prompt GEMM's block widths: a prompt long enough to be cut into wider blocks gives, bit for bit, what the same
-prompt gives in pieces that take the narrowest ones (an element's sums do not depend on the width)."""
+prompt gives in pieces, whose GEMMs have a tile per wave (an element's sums do not depend on the form)."""
 import pytest
 import torch
 
@@ -18,7 +18,7 @@ def model():
 # gate / up of this shape on 256 compute units: 2, 3, 4, 5 and 6 weight fragments per wave, ragged last row groups;
 # the down projection's K = 6144 splits into 4 x 48 k-steps, an odd piece length leaves odd row counts
 @pytest.mark.parametrize("rows", [129, 250, 385, 640, 767, 1001])
-def test_every_block_width_gives_the_bits_of_the_narrowest(model, rows):
+def test_every_block_width_gives_the_bits_of_a_tile_per_wave(model, rows):
     shape = synth.RING_BF16
     prompt = synth.random_tokens(shape.vocab, rows, 11)
     whole, parts = B.KVCache(model, 1100), B.KVCache(model, 1100)
