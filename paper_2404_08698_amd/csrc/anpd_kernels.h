@@ -760,7 +760,7 @@ __global__ void advance_length_kernel(int32_t *__restrict__ len_ptr, int n)
 
 // ------------------------------------------- argmax + acceptance + commit
 //
-// Block r finds argmax(logits[r]) (lowest index among equal maxima); the last block to finish decides what is accepted,
+// Block r finds argmax(logits[r]) (lowest index among equal maxima; a NaN is none); the last block to finish decides what is accepted,
 // advances the cache length and writes the result.  KIND:
 //   chain: Algorithm 1's rule: a = longest prefix with window[i + 1] == pred[i], next = pred[a], length += before + 1 + a
 //     (rejected rows are simply left beyond the length and overwritten later; before: rows of the same prompt piece
@@ -812,7 +812,7 @@ __global__ __launch_bounds__(1024) void argmax_accept_kernel(const float *__rest
             if (i0 + 1024 * u >= V / 4) break;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (v[u][j] > best || besti == 0x7fffffff) { best = v[u][j]; besti = 4 * (i0 + 1024 * u) + j; }
+                if (v[u][j] > best) { best = v[u][j]; besti = 4 * (i0 + 1024 * u) + j; }   // (never a NaN)
         }
     }
 #pragma unroll
@@ -826,6 +826,7 @@ __global__ __launch_bounds__(1024) void argmax_accept_kernel(const float *__rest
     if (threadIdx.x == 0) {
         for (int w = 1; w < 16; ++w)
             if (bv[w] > best || (bv[w] == best && bi[w] < besti)) { best = bv[w]; besti = bi[w]; }
+        if (besti == 0x7fffffff) besti = 0;   // nothing above -infinity
         st_agent(a.result + 2 + r, (int32_t)besti);
         wait_stores();
         last = __hip_atomic_fetch_add(a.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(M - 1);

@@ -103,3 +103,20 @@ def test_windows_of_a_few_rows_have_the_bits_of_sixteen(shape):
         rows[n] = torch.empty(n, shape.vocab, dtype=torch.float32, device="cuda")
         B.verify(model, kv, win[:n], B.APPEND, out_logits=rows[n])
         assert torch.equal(rows[n], rows[16][:n]), n
+
+
+# tokens whose logits are NaN: the first, one that is the first a thread reads, in it and behind it, the first of a wave, every
+# fourth (the first of every thread), all but one, all
+@pytest.mark.parametrize("shape,path", [(synth.TINY, B.GEMM_AUTO), (synth.MID_BF16, B.GEMM_MFMA_LAUNCHES)])
+@pytest.mark.parametrize("bad", [[0], [4], [5], [256], range(0, 1024, 4), [i for i in range(2048) if i != 700], range(2048)],
+                         ids=["0", "4", "5", "256", "fourths", "all_but_one", "all"])
+def test_a_nan_among_the_logits_hides_no_other(shape, path, bad):
+    w = synth.make_weights(shape, 4, device="cuda")
+    bad = [i for i in bad if i < shape.vocab]
+    w["lm_head"][bad] = float("nan")
+    model = B.Model(shape, w, max_window=32, max_positions=64, gemm_path=path)
+    kv = B.KVCache(model, 32)
+    logits = torch.empty(32, shape.vocab, dtype=torch.float32, device="cuda")
+    preds = B.verify(model, kv, synth.random_tokens(shape.vocab, 32, 9), B.APPEND, want_predicts=True, out_logits=logits)[2]
+    assert torch.equal(torch.isnan(logits).any(0).nonzero().flatten().cpu(), torch.tensor(bad))
+    assert preds == torch.nan_to_num(logits, nan=-float("inf")).argmax(-1).tolist()
