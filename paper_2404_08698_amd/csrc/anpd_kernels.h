@@ -666,24 +666,34 @@ __global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ q, 
     // are taken one at a time, each over the keys that it sees.
     bool apart = false;
     if (key0 + 15 > L + (row_mask ? 0 : m0)) {
-        float z = 0.f;
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) z = fmaf(vf[c][i], 0.f, z);
-        apart = __builtin_amdgcn_ballot_w64(z != 0.f) != 0;
-    }
-    for (int q = apart ? 0 : 15; q < 16; ++q) {
-        const uint32_t vis_q = (uint32_t)__builtin_amdgcn_readlane((int)vis, q);   // (lane q has row m0 + q)
-        bool seen[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) seen[i] = !apart || sees(m0 + q, vis_q, key0 + 4 * kg + i);
+        float z[2] = {0.f, 0.f};   // not finite if a value is not (or a product of two is beyond fp32: no harm)
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            f32x4 o[4];
+            z[0] = fmaf(vf[c][0], vf[c][1], z[0]);
+            z[1] = fmaf(vf[c][2], vf[c][3], z[1]);
+        }
+        apart = __builtin_amdgcn_ballot_w64(!(fabsf(z[0]) + fabsf(z[1]) < INFINITY)) != 0;
+    }
+    auto weigh = [&](int c, const bool *seen) __attribute__((always_inline)) {
+        f32x4 o[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(seen[i] ? vf[c][i] : 0.f, p[i], (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-            if (!apart || r == q) *reinterpret_cast<f32x4 *>(red[wave][c][lane]) = (o[0] + o[1]) + (o[2] + o[3]);
+        for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(!seen || seen[i] ? vf[c][i] : 0.f, p[i], (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        return (o[0] + o[1]) + (o[2] + o[3]);
+    };
+    if (!apart) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) *reinterpret_cast<f32x4 *>(red[wave][c][lane]) = weigh(c, nullptr);
+    } else {
+        for (int q = 0; q < 16; ++q) {
+            const uint32_t vis_q = (uint32_t)__builtin_amdgcn_readlane((int)vis, q);   // (lane q has row m0 + q)
+            bool seen[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) seen[i] = sees(m0 + q, vis_q, key0 + 4 * kg + i);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const f32x4 o = weigh(c, seen);
+                if (r == q) *reinterpret_cast<f32x4 *>(red[wave][c][lane]) = o;
+            }
         }
     }
     __syncthreads();
