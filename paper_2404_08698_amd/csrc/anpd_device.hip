@@ -291,11 +291,18 @@ int32_t launch_wide(const FastArgs &a, int blocks, hipStream_t st)
     static bool attr_set = false;
     return launch_lds(gemm_wide_kernel<T, D, EPI>, attr_set, blocks, kFastThreads, (size_t)4 * kFastWaves * 4 * 256 * sizeof(float), a, st);
 }
+// waves: most tiles per block.  Up to four, the tiles are dealt evenly over all compute units: with blocks of as many tiles as go in,
+// up to half of the compute units had none (257 tiles in 129 blocks).  From five on 9 in 10 have one all the same, the
+// stream of weights is as fast, and fewer blocks read the operand.  9 / 17 rows, K 4096 / 11008, full blocks -> even, us:
+// 257 tiles 13.2 -> 12.3 / 15.7 -> 15.2, 30.0 -> 28.2 / 36.3 -> 34.5; 700 18.1 -> 17.4 / 20.1 -> 20.0, 42.0 -> 40.4 / 49.6 -> 47.8;
+// 960 24.3 -> 22.6 / 28.6 -> 24.9, 54.9 -> 54.9 / 61.5 -> 61.8; 1376 30.6 -> 31.7 / 33.2 -> 32.8, 77.1 -> 77.3 / 83.1 -> 81.7,
+// and as gate/up of a 17-row step 35.4 -> 36.1.
 template <int NT, int WAVES, int EPI>
 int32_t launch_tile(const FastArgs &a, int waves, int n_cu, hipStream_t st)
 {
     static bool attr_set = false;
-    return launch_lds(gemm_tile_kernel<NT, WAVES, EPI>, attr_set, a.n_tiles < n_cu ? a.n_tiles : n_cu, (waves + 1) * 64, tile_lds_bytes(NT), a, st);
+    const int blocks = waves > 4 ? (a.n_tiles + waves - 1) / waves : (a.n_tiles < n_cu ? a.n_tiles : n_cu);
+    return launch_lds(gemm_tile_kernel<NT, WAVES, EPI>, attr_set, blocks, (waves + 1) * 64, tile_lds_bytes(NT), a, st);
 }
 
 template <int EPI>

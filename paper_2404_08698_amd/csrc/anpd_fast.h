@@ -829,11 +829,9 @@ __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t buffer, uint4
 // 7B, 17 rows, 8 layers (traced; before: grouped and wide form): QKV 26.2 -> 23.9 us, gate/up 42.3 -> 35.5 (5.1 TB/s);
 // 8192 x 4096 alone, 16 rows, 20.5 -> 17.3.  What is left: HBM at 5.3 TB/s where the same loads from the memory-side
 // cache run at 6.3, and start and end of a launch.
-// The tiles are dealt evenly, so that every compute unit has a block (blocks of ceil(n_tiles / compute units) tiles left 16 to
-// 127 of 256 without one: 4112 x 4096, 9 / 17 rows 13.2 -> 12.3 / 15.7 -> 15.2 us, 15360 x 4096 24.5 -> 22.5 / 28.4 -> 24.9).
 // Tried: rings of 24 and 32 k-steps (no change), one class after the other, whose sums take a quarter of the registers (weights
 // in pieces of 1 KB: QKV 32, gate/up 43).
-// blockDim: 64 x (most tiles per block + 1).  grid: one block per compute unit, or per tile if there are fewer.
+// blockDim: 64 x (most tiles per block + 1).  grid: blocks that share the tiles evenly (launch_tile says how many).
 constexpr int kTileChunk = kFastWaves;   // k-steps per buffer of the operand: one of every class
 constexpr int kTileBufs = 3;
 constexpr int kTileWaves = 7;   // most tiles per block
@@ -899,8 +897,10 @@ __global__ __launch_bounds__((WAVES + 1) * 64) void gemm_tile_kernel(FastArgs a)
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (the last requests, of nothing; rinv)
         return;
     }
-    const int first = (int)(((long long)blockIdx.x * a.n_tiles) / gridDim.x), tile = first + wave;
-    const bool have = tile < (int)(((long long)(blockIdx.x + 1) * a.n_tiles) / gridDim.x);
+    // (the first blocks have one tile more than the rest)
+    const int n_blocks = (int)gridDim.x, b = (int)blockIdx.x, base = (int)((unsigned)a.n_tiles / (unsigned)n_blocks), more = a.n_tiles - base * n_blocks;
+    const int tile = b * base + (b < more ? b : more) + wave;
+    const bool have = wave < base + (b < more);
     __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.Wp + (size_t)(have ? tile : 0) * nks * 64), 0,
                                                                   have ? nks * 1024 : 0, 0x00020000);
     u32x4_t w[D];

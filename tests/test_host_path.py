@@ -176,23 +176,23 @@ def test_a_launch_that_fails_in_front_of_the_lookup_of_the_logits_buffer_is_repo
 
 
 def child_tile_blocks():
-    """A tile per wave: every compute unit gets a block, as long as there are tiles (257 tiles were 129 blocks of two); a wave
-    that is alone on its compute unit has a longer ring if K fills it."""
+    """A tile per wave: up to four tiles per block every compute unit gets one, as long as there are tiles (257 tiles were 129 blocks of
+    two), from five on the blocks are full; a wave that is alone on its compute unit has a longer ring if K fills it."""
     h = Host()
-    n_tiles = [1, 3, 255, 256, 257, 300, 512, 513, 960, 1376, 1791, 1792]
+    blocks = {1: 1, 3: 3, 255: 255, 256: 256, 257: 256, 300: 256, 512: 256, 513: 256, 960: 256, 1024: 256, 1025: 205, 1376: 230, 1791: 256, 1792: 256}
     x, w, y, ws = (h.memory(n) for n in (4096, 4096, 4096, 1 << 18))
     for rows, k in ((9, 64), (17, 64), (17, 992), (17, 1000), (32, 1024)):
-        for n in n_tiles:
+        for n in blocks:
             if rows <= 16 and n <= 256:     # (another kernel's)
                 continue
             h.stub.stub_forget()
             h.ok(h.L.anpd_linear(x, w, y, rows, 16 * n, k, h.B.BF16, h.B.GEMM_MFMA, ws, 1 << 18, None))
             at = [i for i, name in enumerate(h.names()) if "gemm_tile_kernel" in name]
-            assert len(at) == 1 and h.stub.stub_blocks(at[0]) == min(n, 256), (rows, n, h.names())
+            assert len(at) == 1 and h.stub.stub_blocks(at[0]) == blocks[n], (rows, n, h.names())
             assert ("gemm_tile_kernelILi4ELi1E" in h.names()[at[0]]) == (n <= 256 and k > 992), (rows, n, k)
 
 
-def test_tiles_of_a_wide_window_are_spread_over_all_compute_units(stub):
+def test_tiles_of_a_wide_window_are_spread_over_the_compute_units(stub):
     in_child(stub, "child_tile_blocks")
 
 
