@@ -313,6 +313,9 @@ __device__ __forceinline__ void prefill_finish(const PrefillArgs &a, int f0, int
 // until the queue had taken them (gate/up of 512 rows 141.5 -> 139.4 us, of 128 rows 87 -> 83).  One block barrier
 // per k-step: it publishes the stage whose loads every wave has just waited for and frees the stage that every
 // wave has just finished reading.
+// (Figures here and in launch_prefill_gemm are of the kernel alone, repeated, before every load had its own place in the ring,
+// which took 1 to 3 % off; between the others of a prompt, traced, gate/up took 153 us at 512 rows where it took 135.5 alone, 934 at
+// 3584 where it took 921.)
 // What is left (gate/up of 512 rows, one round of 232 blocks, 135.5 us): 0.93 us per k-step, of which the MFMAs
 // alone would take 0.66 at the clock that the power limit leaves them (0.79 without the loads into LDS, 0.83
 // without the reads; 0.79 with a third of the chip at work, and no faster without the reads: what they cost is
@@ -344,12 +347,13 @@ __device__ __forceinline__ void wait_loads_and_meet()
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-// WF: waves side by side along the features (2 along the rows).  Fragments per stage, loads per wave and stage, stages
-// of the ring, bytes of LDS (a stage's fragments; one place for the loads of nothing that make every wave's number even)
+// WF: waves side by side along the features (2 along the rows).  Fragments per stage, loads per wave and stage, places per
+// stage (every load has one, also those of nothing that make every wave's number even), stages of the ring, bytes of LDS
 __host__ __device__ constexpr int pg_units(int TN, int WF) { return WF * TN + 16; }
 __host__ __device__ constexpr int pg_loads(int TN, int WF) { return (pg_units(TN, WF) + 2 * WF - 1) / (2 * WF); }
+__host__ __device__ constexpr int pg_places(int TN, int WF) { return pg_loads(TN, WF) * 2 * WF; }
 __host__ __device__ constexpr int pg_stages(int WF) { return WF == 4 ? 4 : 3; }
-__host__ __device__ constexpr size_t pg_lds_bytes(int TN, int WF) { return ((size_t)pg_stages(WF) * pg_units(TN, WF) + (pg_units(TN, WF) % (2 * WF) != 0)) * 1024; }
+__host__ __device__ constexpr size_t pg_lds_bytes(int TN, int WF) { return (size_t)pg_stages(WF) * pg_places(TN, WF) * 1024; }
 
 // calls f with 0, 1, ... as compile-time constants
 template <int... I, typename F>
@@ -368,8 +372,8 @@ struct PgFrags {
 template <int EPI, int TN, int WF>
 __device__ __forceinline__ void prefill_gemm_block(const PrefillArgs &a, int block, int n_blocks, int tile0, int tile_end)
 {
-    constexpr int kUnits = pg_units(TN, WF), kLoads = pg_loads(TN, WF), kStages = pg_stages(WF);
-    extern __shared__ uint4 ring[];   // [kStages][kUnits][64], [64]
+    constexpr int kUnits = pg_units(TN, WF), kLoads = pg_loads(TN, WF), kPlaces = pg_places(TN, WF), kStages = pg_stages(WF);
+    extern __shared__ uint4 ring[];   // [kStages][kPlaces][64]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wf = wave % WF, wr = wave / WF;
     const int n_br = (a.G + 7) / 8;
@@ -414,14 +418,16 @@ __device__ __forceinline__ void prefill_gemm_block(const PrefillArgs &a, int blo
             ustride[j] = 2048;
         }
     }
-    // stage `slot` of the ring <- k-step `it` (past the end: zeros, nothing fetched)
-    auto request_one = [&](int j, int it, int slot) __attribute__((always_inline)) {
-        const int u = kLoads * wave + j;
-        load_to_lds(rs[j], ring + (size_t)(u < kUnits ? slot * kUnits + u : kStages * kUnits) * 64, uoff[j] + it * ustride[j] + lane * 16);
+    // the stage that begins with place `stage` of the ring <- k-step `it` (past the end: zeros, nothing fetched)
+    // (one place for all loads of nothing instead of one each had a choice per load and a product per stage in the loop, scalar
+    // instructions that showed at short k-steps: TN = 2, QKV of 144 rows 59.3 -> 55.8 us, 13B 72.7 -> 69.4, O and down of 3584
+    // rows, TN = 4, 382 -> 373)
+    auto request_one = [&](int j, int it, int stage) __attribute__((always_inline)) {
+        load_to_lds(rs[j], ring + (size_t)(stage + kLoads * wave + j) * 64, uoff[j] + it * ustride[j] + lane * 16);
     };
-    auto request = [&](int it, int slot) __attribute__((always_inline)) {
+    auto request = [&](int it, int stage) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j) request_one(j, it, slot);
+        for (int j = 0; j < kLoads; ++j) request_one(j, it, stage);
     };
 
     f32x4 acc[TN][kPfTM];
@@ -454,19 +460,19 @@ __device__ __forceinline__ void prefill_gemm_block(const PrefillArgs &a, int blo
         acc[t][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.w[t]),
                                                             __builtin_bit_cast(bf16x8, j < 4 * TN ? f.xh[g] : f.xl[g]), acc[t][g], 0, 0, 0);
     };
-    // The reads of the next k-step's fragments from stage `slot`, one every few MFMAs of this one's, the last
+    // The reads of the next k-step's fragments from stage `stage`, one every few MFMAs of this one's, the last
     // some MFMAs before the end: issued in one go they would fill the LDS queue and hold up every wave's MFMAs
     // until they are through.
-    auto interleave = [&](const Frags &cur, Frags &next, int slot, int ahead, int free_slot) __attribute__((always_inline)) {
+    auto interleave = [&](const Frags &cur, Frags &next, int stage, int ahead, int free_stage) __attribute__((always_inline)) {
         constexpr int NR = TN + 8, NM = 8 * TN, SPAN = NM * 85 / 100;
-        const uint32_t sbase = lds_base + (uint32_t)slot * (kUnits * 1024);
+        const uint32_t sbase = lds_base + (uint32_t)stage * 1024;
         const uint32_t aw = sbase + (uint32_t)(TN * wf) * 1024, ax = sbase + (uint32_t)(WF * TN + 8 * wr) * 1024;
         auto part = [&](auto index) __attribute__((always_inline)) {
             constexpr int i = decltype(index)::value;
             read_one(index, next, aw, ax);
 #pragma unroll
             for (int j = 0; j < kLoads; ++j)
-                if (j * NR / kLoads == i) request_one(j, ahead, free_slot);
+                if (j * NR / kLoads == i) request_one(j, ahead, free_stage);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = i * SPAN / NR; j < (i + 1 == NR ? NM : (i + 1) * SPAN / NR); ++j) mma_one(cur, j);
@@ -477,16 +483,16 @@ __device__ __forceinline__ void prefill_gemm_block(const PrefillArgs &a, int blo
     // One k-step: `cur` holds its fragments.  This wave's loads of k-step it + 1 have landed when at most the
     // kStages - 2 younger stages are outstanding; after the barrier every wave's have, and every wave has its
     // fragments of k-step it in registers, so that slot is free for k-step it + kStages.
-    int slot = 0;   // of k-step it
+    int stage = 0;   // of k-step it: its first place
     auto step = [&](const Frags &cur, Frags &next, int it) __attribute__((always_inline)) {
         wait_loads_and_meet<(kStages - 2) * kLoads>();
-        const int free_slot = slot;
-        slot = slot + 1 == kStages ? 0 : slot + 1;
-        interleave(cur, next, slot, it + kStages, free_slot);
+        const int free_stage = stage;
+        stage = stage == (kStages - 1) * kPlaces ? 0 : stage + kPlaces;
+        interleave(cur, next, stage, it + kStages, free_stage);
         wait_reads(next);
     };
 #pragma unroll
-    for (int s = 0; s < kStages; ++s) request(s, s);
+    for (int s = 0; s < kStages; ++s) request(s, s * kPlaces);
     Frags fa, fb;
     wait_loads_and_meet<(kStages - 1) * kLoads>();
     index_each(std::make_integer_sequence<int, TN + 8>{}, [&](auto... index) __attribute__((always_inline)) {
