@@ -567,6 +567,7 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int 
     }
     mark(m, ANPD_PROF_OTHER, st);
     for (int l = 0; l < c.n_layers; ++l) {
+        const bool last = piece != PIECE_NONE && l > 0 && l + 1 == c.n_layers;
         {
             GenArgs g = gemm(x, d, m->wq[l], m->attn_norm[l], q, d);
             g.W1 = m->wk[l];
@@ -585,7 +586,11 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int 
             }
         }
         mark(m, ANPD_PROF_GEMM_QKV, st);
-        for (int row0 = 0; row0 < M; row0 += L.gen_part_rows) {
+        // (a piece of a prompt: behind the last layer's keys and values only the row whose logits are wanted goes on, with its row group)
+        if (last && piece == PIECE_CACHE) break;
+        const int first = last ? (M - 1) / 16 * 16 : 0;
+        base.M = M - first;
+        for (int row0 = first; row0 < M; row0 += L.gen_part_rows) {
             const int end = M - row0 < L.gen_part_rows ? M : row0 + L.gen_part_rows;
             const dim3 grid((unsigned)H, (unsigned)((kv->len + end + kAttnSplit - 1) / kAttnSplit), (unsigned)((end - row0 + 15) / 16));
 #define ANPD_ATTN_G(DH_)                                                                                                          \
@@ -596,15 +601,15 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int 
 #undef ANPD_ATTN_G
         }
         mark(m, ANPD_PROF_ATTN, st);
-        if ((rc = launch_gen_few<KT, GEN_RESIDUAL>(gemm(att, d, m->wo[l], nullptr, x, d), d / 16, m->n_cu, st)) != ANPD_OK) return rc;
+        if ((rc = launch_gen_few<KT, GEN_RESIDUAL>(gemm(att + (size_t)first * d, d, m->wo[l], nullptr, x + (size_t)first * d, d), d / 16, m->n_cu, st)) != ANPD_OK) return rc;
         mark(m, ANPD_PROF_GEMM_O, st);
         {
-            GenArgs g = gemm(x, d, m->w_gate[l], m->ffn_norm[l], act, F);
+            GenArgs g = gemm(x + (size_t)first * d, d, m->w_gate[l], m->ffn_norm[l], act + (size_t)first * F, F);
             g.W1 = m->w_up[l];
             if ((rc = launch_gen<KT, GEN_GATE_UP>(g, F / 16, st)) != ANPD_OK) return rc;
         }
         mark(m, ANPD_PROF_GEMM_GATE_UP, st);
-        if ((rc = launch_gen_few<KT, GEN_RESIDUAL>(gemm(act, F, m->w_down[l], nullptr, x, d), d / 16, m->n_cu, st)) != ANPD_OK) return rc;
+        if ((rc = launch_gen_few<KT, GEN_RESIDUAL>(gemm(act + (size_t)first * F, F, m->w_down[l], nullptr, x + (size_t)first * d, d), d / 16, m->n_cu, st)) != ANPD_OK) return rc;
         mark(m, ANPD_PROF_GEMM_DOWN, st);
     }
     if (piece == PIECE_CACHE) {
@@ -974,12 +979,13 @@ double blocks_end(long long n_a, double ta, long long n_b, double tb, int n_cu)
 template <int EPI>
 int32_t launch_prefill_gemm(const PrefillArgs &a, int n_cu, hipStream_t st)
 {
-    auto cols = [&](int tiles) { return (long long)((a.n_tiles + tiles - 1) / tiles) * a.S; };
+    const int n_tiles = a.n_tiles - a.tile0, G = a.G - a.g0;
+    auto cols = [&](int tiles) { return (long long)((n_tiles + tiles - 1) / tiles) * a.S; };
     // A few row groups: a tile per wave and as many waves per block as one round of blocks takes, if there is one:
     // 64 TN features x 128 rows -> this, QKV of 16 / 32 / 64 / 128 rows 45 -> 17, 45 -> 19, 46 -> 20, 46 -> 27; gate/up
     // of 16 / 32 / 64 rows 48 -> 27, 48 -> 28, 49 -> 31; down 33 -> 16, 33 -> 17, 34 -> 19.  (In two rounds it loses what
     // it gains: gate/up of 128 rows 50 -> 50, down 35 -> 32 against 28 for the narrow form.)
-    const int tg = a.G == 1 ? 1 : 2, n_br2 = (a.G + tg - 1) / tg;
+    const int tg = G == 1 ? 1 : 2, n_br2 = (G + tg - 1) / tg;
     for (int waves = 3; waves <= kFewWaves; ++waves) {
         const long long blocks = cols(waves) * n_br2;
         if (blocks > n_cu) continue;
@@ -989,13 +995,13 @@ int32_t launch_prefill_gemm(const PrefillArgs &a, int n_cu, hipStream_t st)
     // Up to 128 rows: half as wide, of four waves, where that is at most one block per compute unit: gate/up 50 -> 47,
     // down 35 -> 28 (they read half as much again per MFMA, which more rows would feel: two per compute unit, gate/up
     // of 512 rows 136 -> 153).
-    if (a.G <= 8 && cols(4) <= n_cu) return launch_prefill_narrow<EPI, 2>(a, cols(4), st);
-    if (a.G <= 8 && cols(6) <= n_cu) return launch_prefill_narrow<EPI, 3>(a, cols(6), st);
+    if (G <= 8 && cols(4) <= n_cu) return launch_prefill_narrow<EPI, 2>(a, cols(4), st);
+    if (G <= 8 && cols(6) <= n_cu) return launch_prefill_narrow<EPI, 3>(a, cols(6), st);
     // Blocks of 64 TN features: wider ones read less per MFMA, narrower ones leave fewer compute units idle in the
     // last round (512 rows: 6 for gate/up, 3 for QKV, 4 for O and down).  Where the widest take some rounds and a
     // piece of one, the piece in narrower blocks: gate/up of 768 / 1800 / 3584 rows 218 -> 205, 518 -> 481, 964 -> 921,
     // QKV of 3584 538 -> 511, down of 1800 278 -> 259.
-    const int n_br = (a.G + 7) / 8;
+    const int n_br = (G + 7) / 8;
     int best = 0, best_b = 0, best_cols = 0;
     double least = 0;
     for (int tn = 6; tn >= 2; --tn) {
@@ -1005,17 +1011,17 @@ int32_t launch_prefill_gemm(const PrefillArgs &a, int n_cu, hipStream_t st)
     const long long rounds = cols(24) * n_br / n_cu;
     for (long long r = rounds; r >= 1 && r >= rounds - 1; --r) {
         const int wide = (int)(r * n_cu / ((long long)n_br * a.S));   // columns of the widest blocks
-        if (wide < 1 || wide * 24 >= a.n_tiles) continue;
+        if (wide < 1 || wide * 24 >= n_tiles) continue;
         for (int tb = 4; tb >= 3; --tb) {
-            const long long n_b = (long long)((a.n_tiles - wide * 24 + 4 * tb - 1) / (4 * tb)) * a.S * n_br;
+            const long long n_b = (long long)((n_tiles - wide * 24 + 4 * tb - 1) / (4 * tb)) * a.S * n_br;
             const double t = blocks_end((long long)wide * a.S * n_br, kPgBlock[6], n_b, kPgBlock[tb], n_cu);
             if (t < 0.98 * least) { least = t; best_b = tb; best_cols = wide; }
         }
     }
     if (best_b) {
         const int n_a = best_cols * a.S * n_br, tiles_a = best_cols * 24;
-        const long long blocks = n_a + (long long)((a.n_tiles - tiles_a + 4 * best_b - 1) / (4 * best_b)) * a.S * n_br;
-        return best_b == 4 ? launch_prefill_mixed<EPI, 4>(a, n_a, tiles_a, blocks, st) : launch_prefill_mixed<EPI, 3>(a, n_a, tiles_a, blocks, st);
+        const long long blocks = n_a + (long long)((n_tiles - tiles_a + 4 * best_b - 1) / (4 * best_b)) * a.S * n_br;
+        return best_b == 4 ? launch_prefill_mixed<EPI, 4>(a, n_a, a.tile0 + tiles_a, blocks, st) : launch_prefill_mixed<EPI, 3>(a, n_a, a.tile0 + tiles_a, blocks, st);
     }
     const long long blocks = cols(4 * best) * n_br;
     switch (best) {
@@ -1066,18 +1072,23 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
     mark(m, -1, st);
     // columns F .. 32 * nks_f of the down projection's operand meet zero weights: they must not hold NaN patterns
     if (F % 32 != 0) HIP_TRY(hipMemsetAsync(xq_f, 0, (size_t)G * nks_f * 2048, st));
-    auto norm = [&](const bf16_t *gain, bool embed) {
+    auto norm = [&](const bf16_t *gain, bool embed, int g0) {
 #define ANPD_NORM(EMBED_, NV_)                                                                                              \
-    hipLaunchKernelGGL((prefill_norm_kernel<EMBED_, NV_>), dim3((unsigned)((G + 7) / 8 * 128)), dim3(256), 0, st, (const bf16_t *)m->embed, tok, x, \
-                       (const float *)part, gain, xq, nks_d, d, G, len, P, inv_d, c.rms_eps)
+    hipLaunchKernelGGL((prefill_norm_kernel<EMBED_, NV_>), dim3((unsigned)((G - g0 + 7) / 8 * 128)), dim3(256), 0, st, (const bf16_t *)m->embed, tok, x, \
+                       (const float *)part, gain, xq, nks_d, d, g0, G, len, P, inv_d, c.rms_eps)
         if (d <= 4096) { if (embed) ANPD_NORM(true, 4); else ANPD_NORM(false, 4); }
         else if (embed) ANPD_NORM(true, 8);
         else ANPD_NORM(false, 8);
 #undef ANPD_NORM
     };
-    norm((const bf16_t *)m->attn_norm[0], true);
+    norm((const bf16_t *)m->attn_norm[0], true, 0);
     mark(m, ANPD_PROF_OTHER, st);
     for (int l = 0; l < c.n_layers; ++l) {
+        // Behind the last layer's keys and values only the last row is wanted, so everything from its queries on works on that row's
+        // group alone (4 layers, 205 / 512 / 3584 rows 1116 -> 1028 us (ChatGLM3 shape), 1546 -> 1369, 10641 -> 8811; a layer's GEMMs
+        // and attention are then 0.11 ms whatever the rows: of 32 layers it saves the better part of one).  A model of one layer, which
+        // serves to run the kernels' forms on all rows, does without.
+        const int g0 = l > 0 && l + 1 == c.n_layers ? G - 1 : 0;
         {
             PrefillArgs a = base;
             a.Wp = (const uint4 *)(ws + L.wp_qkv[(size_t)l]);
@@ -1085,15 +1096,24 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
             a.nks = nks_d;
             a.n_tiles = (d + 2 * kv_dim_of(c)) / 16;
             a.layer = l;
+            // ... its queries as a launch of their own from 257 rows on, where that is less than the other rows' queries: 256 / 384 / 512
+            // / 1800 rows, one layer, in one launch -> two, 7B shape 250 -> 260, 277 -> 271, 295 -> 291, 572 -> 505 us; 13B 302 -> 313,
+            // 333 -> 326, 367 -> 357, 764 -> 639; ChatGLM3 269 -> 272, 286 -> 281, 316 -> 294, 465 -> 389.
+            if (g0 >= 16) {
+                PrefillArgs q = a;
+                q.n_tiles = a.tile0 = d / 16;
+                q.g0 = g0;
+                if ((rc = launch_prefill_gemm<EPI_QKV>(q, m->n_cu, st)) != ANPD_OK) return rc;
+            }
             if ((rc = launch_prefill_gemm<EPI_QKV>(a, m->n_cu, st)) != ANPD_OK) return rc;
         }
         mark(m, ANPD_PROF_GEMM_QKV, st);
         {
-            const dim3 grid((unsigned)H, (unsigned)((G + 1) / 2));
+            const dim3 grid((unsigned)H, (unsigned)((G - g0 + 1) / 2));
             // query rows in LDS where that brings one more block to a compute unit, else in registers (see the kernel)
-            const bool shared = (long long)H * ((G + 1) / 2) > (dh == 128 ? 1 : 2) * m->n_cu;
+            const bool shared = (long long)grid.x * grid.y > (dh == 128 ? 1 : 2) * m->n_cu;
 #define ANPD_ATTN_P(DH_, Q_)                                                                                                      \
-    hipLaunchKernelGGL((prefill_attn_kernel<DH_, Q_>), grid, dim3(256), 0, st, (const uint4 *)qp, (const bf16_t *)kv->pool, kv->d_table, G, \
+    hipLaunchKernelGGL((prefill_attn_kernel<DH_, Q_>), grid, dim3(256), 0, st, (const uint4 *)qp, (const bf16_t *)kv->pool, kv->d_table, g0, G, \
                        len, P, l, c.n_layers, H, kv_heads_of(c), scale, xq_att, nks_d)
             if (dh == 128) { if (shared) ANPD_ATTN_P(128, true); else ANPD_ATTN_P(128, false); }
             else if (shared) ANPD_ATTN_P(64, true);
@@ -1107,11 +1127,12 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
             a.Xq = (const uint4 *)xq_att;
             a.nks = nks_d;
             a.n_tiles = d / 16;
+            a.g0 = g0;
             a.S = kPgSplit;
             if ((rc = launch_prefill_gemm<EPI_RESIDUAL>(a, m->n_cu, st)) != ANPD_OK) return rc;
         }
         mark(m, ANPD_PROF_GEMM_O, st);
-        norm((const bf16_t *)m->ffn_norm[l], false);
+        norm((const bf16_t *)m->ffn_norm[l], false, g0);
         mark(m, ANPD_PROF_OTHER, st);
         {
             PrefillArgs a = base;
@@ -1119,6 +1140,7 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
             a.Xq = (const uint4 *)xq;
             a.nks = nks_d;
             a.n_tiles = F / 8;
+            a.g0 = g0;
             a.out = xq_f;
             a.out_nks = nks_f;
             if ((rc = launch_prefill_gemm<EPI_GATE_UP>(a, m->n_cu, st)) != ANPD_OK) return rc;
@@ -1130,12 +1152,13 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
             a.Xq = (const uint4 *)xq_f;
             a.nks = nks_f;
             a.n_tiles = d / 16;
+            a.g0 = g0;
             a.S = kPgSplit;
             if ((rc = launch_prefill_gemm<EPI_RESIDUAL>(a, m->n_cu, st)) != ANPD_OK) return rc;
         }
         mark(m, ANPD_PROF_GEMM_DOWN, st);
         if (l + 1 < c.n_layers) {
-            norm((const bf16_t *)m->attn_norm[(size_t)l + 1], false);
+            norm((const bf16_t *)m->attn_norm[(size_t)l + 1], false, 0);
             mark(m, ANPD_PROF_OTHER, st);
         }
     }

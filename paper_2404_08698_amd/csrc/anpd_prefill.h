@@ -38,6 +38,7 @@ struct PrefillArgs {
     const uint4 *Wp;      // packed weights [n_tiles][nks][64]
     const uint4 *Xq;      // activation operand [G][nks][2][64]
     int nks, n_tiles, G;
+    int tile0, g0;        // first tile, first row group wanted (the last layer's rows in front of it feed nothing)
     int L, P;             // cache length before the call, prompt rows
     int S;                // K splits (1 except RESIDUAL)
     // RESIDUAL
@@ -99,15 +100,15 @@ __device__ __forceinline__ f32x4 widen4(uint2 b)
 // with the numbering below, 512 rows of the 7B shape 16.9 -> 13.3 us, 3584 rows 110 -> 83).  NV: 1024-column pieces of a row (d <= 1024 NV).
 // The rows of a group write 8-byte pieces of the same lines of the operand: blocks are dealt to the eight XCDs in
 // turn, and a group's sixteen blocks are numbered to land on one, whose L2 puts the lines together.
-// grid: 128 ceil(G / 8) blocks (one per row) of 256 threads.
+// grid: 128 ceil((G - g0) / 8) blocks (one per row, from group g0 on) of 256 threads.
 template <bool EMBED, int NV>
 __global__ __launch_bounds__(256) void prefill_norm_kernel(const bf16_t *__restrict__ E, const int32_t *__restrict__ tok,
                                                             float *__restrict__ x, const float *__restrict__ part,
                                                             const bf16_t *__restrict__ gain, bf16_t *__restrict__ xq, int nks,
-                                                            int d, int G, int L, int P, float inv_d, float eps)
+                                                            int d, int g0, int G, int L, int P, float inv_d, float eps)
 {
     __shared__ float red[4];
-    const int grp = (int)(blockIdx.x & 7) + 8 * (int)(blockIdx.x >> 7);
+    const int grp = g0 + (int)(blockIdx.x & 7) + 8 * (int)(blockIdx.x >> 7);
     if (grp >= G) return;
     const int m = 16 * grp + (int)((blockIdx.x >> 3) & 15), r = m - (L & 15);
     const bool valid = r >= 0 && r < P;
@@ -330,7 +331,7 @@ __device__ __forceinline__ void prefill_finish(const PrefillArgs &a, int f0, int
 // residual stream, in split order, by the norm kernel that follows.  S is
 // fixed by the matrix, never by the number of rows: a row's sums are formed
 // in the same order whatever else is in the batch.
-// grid: ceil(n_tiles / (4 TN)) * S * ceil(G / 8) blocks; rows run fastest, so
+// grid: ceil((n_tiles - tile0) / (4 TN)) * S * ceil((G - g0) / 8) blocks; rows run fastest, so
 // consecutive blocks share a weight range.
 template <int OFF>
 __device__ __forceinline__ u32x4_t lds_read16(uint32_t addr)
@@ -376,7 +377,7 @@ __device__ __forceinline__ void prefill_gemm_block(const PrefillArgs &a, int blo
     extern __shared__ uint4 ring[];   // [kStages][kPlaces][64]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wf = wave % WF, wr = wave / WF;
-    const int n_br = (a.G + 7) / 8;
+    const int n_br = (a.G - a.g0 + 7) / 8;
     // Blocks are dealt to the 8 XCDs in turn, and each XCD has its own L2.  Give XCD x a contiguous
     // range of the (weights, rows) order, so that the blocks sharing a weight range, and the row
     // blocks they all stream in step, meet in one L2 instead of being fetched into several.
@@ -389,7 +390,7 @@ __device__ __forceinline__ void prefill_gemm_block(const PrefillArgs &a, int blo
     const int br = id % n_br;
     id /= n_br;
     const int sp = id % a.S, bt = id / a.S;
-    const int F0 = tile0 + bt * WF * TN, G0 = br * 8;
+    const int F0 = tile0 + bt * WF * TN, G0 = a.g0 + br * 8;
     const int nks = a.nks;
     const int ks0 = (int)((long long)sp * nks / a.S), n_it = (int)((long long)(sp + 1) * nks / a.S) - ks0;
 
@@ -512,19 +513,19 @@ __device__ __forceinline__ void prefill_gemm_block(const PrefillArgs &a, int blo
 template <int EPI, int TN>
 __global__ __launch_bounds__(kPgThreads) void prefill_gemm_kernel(PrefillArgs a)
 {
-    prefill_gemm_block<EPI, TN, 4>(a, blockIdx.x, gridDim.x, 0, a.n_tiles);
+    prefill_gemm_block<EPI, TN, 4>(a, blockIdx.x, gridDim.x, a.tile0, a.n_tiles);
 }
 // half as wide, four waves
 template <int EPI, int TN>
 __global__ __launch_bounds__(256, 2) void prefill_narrow_kernel(PrefillArgs a)
 {
-    prefill_gemm_block<EPI, TN, 2>(a, blockIdx.x, gridDim.x, 0, a.n_tiles);
+    prefill_gemm_block<EPI, TN, 2>(a, blockIdx.x, gridDim.x, a.tile0, a.n_tiles);
 }
-// the tiles [0, tiles_a) in blocks of TA, n_a of them, the rest in blocks of TB
+// the tiles up to tiles_a in blocks of TA, n_a of them, the rest in blocks of TB
 template <int EPI, int TA, int TB>
 __global__ __launch_bounds__(kPgThreads) void prefill_mixed_kernel(PrefillArgs a, int n_a, int tiles_a)
 {
-    if ((int)blockIdx.x < n_a) prefill_gemm_block<EPI, TA, 4>(a, blockIdx.x, n_a, 0, tiles_a);
+    if ((int)blockIdx.x < n_a) prefill_gemm_block<EPI, TA, 4>(a, blockIdx.x, n_a, a.tile0, tiles_a);
     else prefill_gemm_block<EPI, TB, 4>(a, (int)blockIdx.x - n_a, (int)gridDim.x - n_a, tiles_a, a.n_tiles);
 }
 
@@ -556,7 +557,7 @@ __global__ __launch_bounds__((kFewWaves + kFewLoaders) * 64) void prefill_few_ke
     constexpr int D = kFewDepth, DX = kFewChunk, NB = kFewBufs, UNITS = few_units(TG);
     extern __shared__ uint4 xs[];   // [NB][DX][TG][hi | lo][64]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = (int)(blockDim.x >> 6) - kFewLoaders;
-    const int n_br = (a.G + TG - 1) / TG;
+    const int n_br = (a.G - a.g0 + TG - 1) / TG;
     int id;
     {
         const int n = (int)gridDim.x, per = (n + 7) / 8, rem = n % 8;
@@ -566,7 +567,7 @@ __global__ __launch_bounds__((kFewWaves + kFewLoaders) * 64) void prefill_few_ke
     const int br = id % n_br;
     id /= n_br;
     const int sp = id % a.S, bt = id / a.S;
-    const int G0 = br * TG, nks = a.nks;
+    const int G0 = a.g0 + br * TG, nks = a.nks;
     const int ks0 = (int)((long long)sp * nks / a.S), n_it = (int)((long long)(sp + 1) * nks / a.S) - ks0;
     const int n_chunks = (n_it + DX - 1) / DX;
     if (wave >= n_waves) {
@@ -594,7 +595,7 @@ __global__ __launch_bounds__((kFewWaves + kFewLoaders) * 64) void prefill_few_ke
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         return;
     }
-    const int tile = bt * n_waves + wave;
+    const int tile = a.tile0 + bt * n_waves + wave;
     const bool have = tile < a.n_tiles;
     __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.Wp + ((size_t)(have ? tile : 0) * nks + ks0) * 64), 0,
                                                                   have ? n_it * 1024 : 0, 0x00020000);
@@ -669,11 +670,11 @@ __global__ __launch_bounds__((kFewWaves + kFewLoaders) * 64) void prefill_few_ke
 // weights' two bf16 terms keep, and equally far from the 64-bit result.)
 // Scores of any size are right (see kHugeScore).  What is not finite: a key whose score is NaN has weight 0; V of keys on a row's own page that the row must not see is
 // multiplied by 0, as in a step, V of later pages is not.
-// grid: (n_heads, ceil(G / 2)); later groups (more pages) start first.
+// grid: (n_heads, ceil((G - first) / 2)): row groups from `first` on; later groups (more pages) start first.
 constexpr float kHugeScore = 0x1p29f;   // rounding a base-2 score of this size may move it by 2^5; below it by 2^4, weights stay under 2^(8 + 16)
 template <int DH, bool QLDS>
 __global__ __launch_bounds__(256, QLDS ? 2 : 1) void prefill_attn_kernel(const uint4 *__restrict__ qp, const bf16_t *__restrict__ pool,
-                                                            const int32_t *__restrict__ page_table, int G, int L, int P,
+                                                            const int32_t *__restrict__ page_table, int first, int G, int L, int P,
                                                             int layer, int n_layers, int n_heads, int n_kv_heads, float scale,
                                                             bf16_t *__restrict__ xq_att, int nks_d)
 {
@@ -686,7 +687,7 @@ __global__ __launch_bounds__(256, QLDS ? 2 : 1) void prefill_attn_kernel(const u
     __shared__ float wmax[WAVES][2][16], wden[WAVES][2][16];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), slot = lane & 15, kg = lane >> 4;
     const int head = blockIdx.x, kvh = head / (n_heads / n_kv_heads);
-    const int g0 = 2 * ((int)gridDim.y - 1 - (int)blockIdx.y), n_grp = G - g0 < 2 ? G - g0 : 2;
+    const int g0 = first + 2 * ((int)gridDim.y - 1 - (int)blockIdx.y), n_grp = G - g0 < 2 ? G - g0 : 2;
     const int own0 = (L >> 4) + g0;                 // the first group's own page; the second group's is the next one
     const int last_page = own0 + n_grp - 1, last_pair = last_page >> 1;
 
