@@ -20,6 +20,7 @@
 #include "anpd_fast.h"
 #include "anpd_mega.h"
 #include "anpd_prefill.h"
+#include "anpd_small.h"
 
 using namespace anpd;
 
@@ -36,6 +37,33 @@ size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 int kv_heads_of(const anpd_model_cfg &c) { return c.n_kv_heads > 0 ? c.n_kv_heads : c.n_heads; }
 int kv_dim_of(const anpd_model_cfg &c) { return kv_heads_of(c) * c.head_dim; }
 
+// Work items of a phase beyond the first 32, which is what an XCD's compute units hold at a time, in rounds of 32.
+int small_rounds(int items) { return (items + 31) / 32 - 1; }
+// Whether a window of so many rows and splits of the keys goes through a model as one launch on one XCD (anpd_small.h): as long as a
+// layer's phases take no more than one round besides the five that they are, and the LM head no more than one per layer.
+// us, separate launches -> one, 5 rows (d 256, FFN 688, vocabulary 1024): 2 layers, 128 cached positions 102 -> 84, 500 103 -> 91, 1000
+// 106 -> 105 (an extra round more per layer; 2000 112 -> 135); 8 layers 258 -> 199; 17 rows at 128 / 500 121 -> 104 / 122 -> 130
+// (the second with two extra rounds); d 384, FFN 1024 at 128 / 500 109 -> 107 / 110 -> 120 (two, three); d 512 114 -> 130;
+// vocabulary 32000 117 -> 237.
+bool small_step(const anpd_model_cfg &c, int rows, int splits)
+{
+    const int rt = rows > 16 ? 2 : 1;
+    const int extra = small_rounds((c.n_heads + 2 * (c.n_kv_heads > 0 ? c.n_kv_heads : c.n_heads)) * (c.head_dim / 32)) + small_rounds(c.n_heads * splits * rt) +
+                      2 * small_rounds(c.d_model / 16) + small_rounds(c.d_ffn / 16);
+    return rows <= kMaxRows && splits <= 8 && extra <= 1 && small_rounds(c.vocab / 16) <= c.n_layers;
+}
+bool small_model(const anpd_model_cfg &c) { return c.dtype == ANPD_F32 && c.gemm_path == ANPD_GEMM_AUTO && small_step(c, 1, 1); }
+
+constexpr int kSmallLine = 64;   // words
+// most items of a phase that such a step may have
+size_t small_items(const anpd_model_cfg &c)
+{
+    const size_t qkv = (size_t)(c.n_heads + 2 * kv_heads_of(c)) * (size_t)(c.head_dim / 32), lm = (size_t)c.vocab / 16, ffn = (size_t)c.d_ffn / 16;
+    size_t most = 256;
+    for (size_t n : {qkv, lm, ffn, (size_t)c.d_model / 16}) most = 2 * n > most ? 2 * n : most;
+    return (most + 63) / 64 * 64;
+}
+
 struct Layout {  // byte offsets into the model workspace
     size_t rope_tab, tree, batch, result, counter, gen_ctr, x, qkv, att, a, logits, part;
     // fast path: packed operands, partial sums of squares, packed weights
@@ -43,6 +71,8 @@ struct Layout {  // byte offsets into the model workspace
     size_t xp_layers, xp_stride;   // the one-kernel step's operands (bytes; stride between the layers' sets in bf16 elements: 0, one set)
     std::vector<size_t> wp_qkv, wp_o, wp_gu, wp_down;
     int max_splits;
+    size_t small_ctr, small_layers;   // the one launch of a small model: two item counters, a word for completed launches, the items' flags; its layers' pointers
+    int small_stride;   // flags per phase
     int gen_rows, gen_part_rows;   // generic path: most rows that go through a layer together, and of those through attention
 };
 
@@ -110,6 +140,14 @@ Layout make_layout(const anpd_model_cfg *c)
     }
     const size_t GR = (size_t)L.gen_rows;
     L.gen_ctr = take((size_t)c->n_heads * ((L.gen_part_rows + 15) / 16) * 64 * sizeof(uint32_t));
+    L.small_ctr = L.small_layers = 0;
+    L.small_stride = 0;
+    if (small_model(*c)) {
+        // (counters: a line each)
+        L.small_stride = (int)small_items(*c);
+        L.small_ctr = take((3 * kSmallLine + (size_t)(5 * c->n_layers + 1) * L.small_stride) * sizeof(uint32_t));
+        L.small_layers = take((size_t)c->n_layers * sizeof(GenLayer));
+    }
     L.x = take(GR * d * 4);
     L.qkv = take(GR * d * 4);
     L.att = take(GR * d * 4);
@@ -190,6 +228,8 @@ struct anpd_model {
     bool plain_launch;    // launch the one-kernel step without the cooperative-launch API (profiling aid)
     int32_t spin_limit;   // polls before a grid-barrier wait gives up
     uint32_t bar_epoch;
+    int xcd;               // where the one launch of a small model runs (-1: it is not used)
+    uint32_t small_launches, small_launch;   // those that have to be completed by now; number of the last one, which its flags are set to
     uint32_t ready_epoch;  // QKV phases run by the one-kernel step so far
     const void *embed, *final_norm, *lm_head;
     std::vector<const void *> attn_norm, wq, wk, wv, wo, ffn_norm, w_gate, w_up, w_down;
@@ -593,9 +633,9 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int 
         for (int row0 = first; row0 < M; row0 += L.gen_part_rows) {
             const int end = M - row0 < L.gen_part_rows ? M : row0 + L.gen_part_rows;
             const dim3 grid((unsigned)H, (unsigned)((kv->len + end + kAttnSplit - 1) / kAttnSplit), (unsigned)((end - row0 + 15) / 16));
-#define ANPD_ATTN_G(DH_)                                                                                                          \
-    hipLaunchKernelGGL((attn_kernel<KT, DH_>), grid, dim3(256), 0, st, q, d, pool, kv->d_table, kv->d_len, end, l, c.n_layers, H, Hkv, \
-                       c.page_tokens, row0, L.gen_part_rows, L.max_splits, scale, part, attn_ctr, att, t_mask)
+            const GenAttnArgs ga = {q, d, kv->pool, kv->d_table, kv->d_len, end, l, c.n_layers, H, Hkv, c.page_tokens, row0, L.gen_part_rows,
+                                    L.max_splits, dh, scale, part, attn_ctr, att, t_mask};
+#define ANPD_ATTN_G(DH_) hipLaunchKernelGGL((attn_kernel<KT, DH_>), grid, dim3(256), 0, st, ga)
             if (dh == 128) ANPD_ATTN_G(128);
             else ANPD_ATTN_G(64);
 #undef ANPD_ATTN_G
@@ -635,6 +675,93 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int 
     mark(m, ANPD_PROF_OTHER, st);
     HIP_TRY(hipGetLastError());
     return ANPD_OK;
+}
+
+// The same step or piece as one launch, if the model is small (anpd_small.h) and the call allows it; *ran says whether.
+int32_t run_step_small(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int M, int mode, LogitsTo &logits_to, hipStream_t st, bool tree, Piece piece,
+                       bool *ran)
+{
+    const anpd_model_cfg &c = m->cfg;
+    const Layout &L = m->lay;
+    *ran = false;
+    const int splits = (kv->len + M + kAttnSplit - 1) / kAttnSplit, rt = M > 16 ? 2 : 1;
+    if (m->xcd < 0 || !small_step(c, M, splits) || M > L.gen_part_rows || piece == PIECE_CACHE || ((uintptr_t)m->embed & 15) != 0) return ANPD_OK;
+    char *ws = m->ws;
+    const int d = c.d_model, F = c.d_ffn, V = c.vocab, H = c.n_heads, Hkv = kv_heads_of(c);
+    SmallArgs g;
+    std::memset(&g, 0, sizeof(g));
+    g.gen.eps = c.rms_eps;
+    g.gen.rope = (const float2 *)(ws + L.rope_tab);
+    g.gen.pool = kv->pool;
+    g.gen.page_table = kv->d_table;
+    g.gen.len_ptr = kv->d_len;
+    int32_t *t_parent = (int32_t *)(ws + L.tree);
+    g.gen.depth = tree ? t_parent + ANPD_MAX_WINDOW : nullptr;
+    g.gen.n_layers = c.n_layers;
+    g.gen.n_heads = H;
+    g.gen.n_kv_heads = Hkv;
+    g.gen.head_dim = c.head_dim;
+    g.gen.page_tokens = c.page_tokens;
+    g.gen.embed = m->embed;
+    g.gen.x = g.x = (float *)(ws + L.x);
+    g.attn = {(float *)(ws + L.qkv), d, kv->pool, kv->d_table, kv->d_len, M, 0, c.n_layers, H, Hkv, c.page_tokens, 0, L.gen_part_rows, L.max_splits,
+              c.head_dim, 1.0f / sqrtf((float)c.head_dim), (float *)(ws + L.part), (uint32_t *)(ws + L.gen_ctr), (float *)(ws + L.att),
+              tree ? (const uint32_t *)(t_parent + 2 * ANPD_MAX_WINDOW) : nullptr};
+    g.act = (float *)(ws + L.a);
+    g.logits = logits_to.find(m);
+    g.layers = (const GenLayer *)(ws + L.small_layers);
+    g.final_norm = m->final_norm;
+    g.lm_head = m->lm_head;
+    g.d = d;
+    g.ffn = F;
+    g.vocab = V;
+    g.M = M;
+    g.splits = splits;
+    g.out0 = piece == PIECE_LAST ? M - 1 : 0;
+    g.n_out = M - g.out0;
+    g.tree = tree;
+    g.mode = mode;
+    uint32_t *words = (uint32_t *)(ws + L.small_ctr);
+    const uint32_t launch = m->small_launch + 1 ? m->small_launch + 1 : 1;   // (never 0, which is what the flags begin with)
+    g.ticket = words + (m->small_launches & 1) * kSmallLine;
+    g.other = words + (1 - (m->small_launches & 1)) * kSmallLine;
+    g.flags = words + 3 * kSmallLine;
+    g.stride = L.small_stride;
+    g.launch = launch;
+    g.xcd = m->xcd;
+    g.error = m->pin_dev + 100;
+    g.spin_limit = m->spin_limit;
+    g.accept = accept_args(m, kv->d_len);
+    g.accept.before = g.out0;
+    g.accept.parent = t_parent;
+    g.accept.depth = t_parent + ANPD_MAX_WINDOW;
+    g.accept.launches = words + 2 * kSmallLine;
+    g.accept.host_launches = (uint32_t *)m->pin_dev + 102;
+    g.tok = step_tokens(tokens, M);
+    m->ev_used = 0;
+    mark(m, -1, st);
+#define ANPD_SMALL(DH_, RT_) hipLaunchKernelGGL((small_step_kernel<DH_, RT_>), dim3(kSmallBlocks), dim3(512), 0, st, g)
+    if (c.head_dim == 128) { if (rt == 2) ANPD_SMALL(128, 2); else ANPD_SMALL(128, 1); }
+    else if (rt == 2) ANPD_SMALL(64, 2);
+    else ANPD_SMALL(64, 1);
+#undef ANPD_SMALL
+    HIP_TRY(hipGetLastError());
+    m->small_launch = launch;
+    m->small_launches += 1;
+    mark(m, ANPD_PROF_STEP, st);
+    *ran = true;
+    return ANPD_OK;
+}
+
+// A step or a piece of a model on the caller's weights.
+int32_t run_step_weights(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int M, int mode, LogitsTo &logits, hipStream_t st, bool tree = false,
+                         Piece piece = PIECE_NONE)
+{
+    if (m->cfg.dtype == ANPD_BF16) return run_step_generic<bf16_t>(m, kv, tokens, M, mode, logits, st, tree, piece);
+    bool ran;
+    const int32_t rc = run_step_small(m, kv, tokens, M, mode, logits, st, tree, piece, &ran);
+    if (rc != ANPD_OK || ran) return rc;
+    return run_step_generic<float>(m, kv, tokens, M, mode, logits, st, tree, piece);
 }
 
 // The fused bf16 step: per layer QKV(+norm, RoPE, cache write) -> attention -> combine -> O(+residual)
@@ -1193,12 +1320,28 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
     return ANPD_OK;
 }
 
+// After the stream has been synchronised: was there a launch of the small model's kernel of which no block ran where it was to run, so
+// that nothing was done?  Then steps are separate launches from here on.
+bool small_missed(anpd_model *m)
+{
+    if (m->xcd < 0 || (uint32_t)m->pin[102] == m->small_launches) return false;
+    m->xcd = -1;
+    return true;
+}
+
 // After the stream has been synchronised: did a grid barrier of the one-kernel step give up?  Then the
 // counters are no longer in step: start them over.
 bool barrier_gave_up(anpd_model *m, hipStream_t st)
 {
     if (m->pin[100] == 0) return false;
     m->pin[100] = 0;
+    if (!m->mfma) {
+        (void)hipMemsetAsync(m->ws + m->lay.small_ctr, 0, 2 * kSmallLine * sizeof(uint32_t), st);
+        (void)hipMemsetAsync(m->ws + m->lay.gen_ctr, 0, (size_t)m->cfg.n_heads * ((m->lay.gen_part_rows + 15) / 16) * 64 * sizeof(uint32_t), st);
+        (void)hipStreamSynchronize(st);
+        m->small_launches = (uint32_t)m->pin[102];
+        return true;
+    }
     (void)hipMemsetAsync(m->ws + m->lay.bar, 0, kBarStride * 9 * sizeof(uint32_t) + (size_t)m->cfg.n_heads * kCounterStride * sizeof(uint32_t), st);
     (void)hipStreamSynchronize(st);
     m->bar_epoch = 0;
@@ -1300,6 +1443,8 @@ int32_t anpd_model_create(const anpd_model_cfg *cfg, const anpd_weights *w, void
     m->mega_grid = 0;
     m->bar_epoch = 0;
     m->ready_epoch = 0;
+    m->xcd = -1;
+    m->small_launches = m->small_launch = 0;
     m->spin_limit = 1 << 21;
     // ANPD_MEGA_PLAIN_LAUNCH=1: an ordinary launch of the same grid.  Only for profilers that cannot
     // cope with the cooperative queue; all blocks are resident only if nothing else runs on the device
@@ -1368,6 +1513,21 @@ int32_t anpd_model_create(const anpd_model_cfg *cfg, const anpd_weights *w, void
             if (prc == ANPD_OK) prc = launch_pack(m->w_down[l], nullptr, nullptr, m->ws + lay.wp_down[(size_t)l], PACK_PLAIN, d / 16, F, d, dh, kvd, st);
         }
         if (prc == ANPD_OK) prc = launch_pack(m->lm_head, nullptr, nullptr, m->ws + lay.wp_lm, PACK_PLAIN, cfg->vocab / 16, d, d, dh, kvd, st);
+    }
+    if (e == hipSuccess && small_model(*cfg)) {
+        // where blocks of such a grid run: the XCD with the most of them
+        uint32_t *count = (uint32_t *)(m->ws + lay.small_ctr), seen[16];
+        std::vector<GenLayer> tab(nl);
+        for (size_t l = 0; l < nl; ++l)
+            tab[l] = {m->attn_norm[l], m->wq[l], m->wk[l], m->wv[l], m->wo[l], m->ffn_norm[l], m->w_gate[l], m->w_up[l], m->w_down[l]};
+        e = hipMemcpyAsync(m->ws + lay.small_layers, tab.data(), nl * sizeof(GenLayer), hipMemcpyHostToDevice, st);
+        hipLaunchKernelGGL(xcd_census_kernel, dim3(kSmallBlocks), dim3(512), 0, st, count);
+        if (e == hipSuccess) e = hipGetLastError();
+        if (e == hipSuccess) e = hipMemcpyAsync(seen, count, sizeof(seen), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipMemsetAsync(count, 0, sizeof(seen), st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        for (int i = 0; e == hipSuccess && i < 16; ++i)
+            if (seen[i] >= 16 && (m->xcd < 0 || seen[i] > seen[m->xcd])) m->xcd = i;
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess || prc != ANPD_OK) {
@@ -1586,13 +1746,13 @@ int32_t anpd_verify(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, int32
     LogitsTo logits = {out_logits, (size_t)n_window * m->cfg.vocab, nullptr};
     if (one_kernel) rc = run_step_mega(m, kv, window, n_window, mode, out_logits ? logits.find(m) : nullptr, st);
     else if (m->mfma) rc = run_step_fast(m, kv, step_tokens(window, n_window), n_window, mode, logits, st);
-    else if (m->cfg.dtype == ANPD_BF16) rc = run_step_generic<bf16_t>(m, kv, window, n_window, mode, logits, st);
-    else rc = run_step_generic<float>(m, kv, window, n_window, mode, logits, st);
+    else rc = run_step_weights(m, kv, window, n_window, mode, logits, st);
     if (rc != ANPD_OK) return rc;
     if (logits.elsewhere())
         HIP_TRY(hipMemcpyAsync(out_logits, logits.at, sizeof(float) * (size_t)n_window * m->cfg.vocab, hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
-    if (one_kernel && barrier_gave_up(m, st)) return fail(ANPD_E_HIP, "anpd_verify: the persistent kernel timed out at a grid barrier");
+    if (barrier_gave_up(m, st)) return fail(ANPD_E_HIP, "anpd_verify: the persistent kernel timed out at a grid barrier");
+    if (small_missed(m)) return anpd_verify(m, kv, window, n_window, mode, out_accepted, out_next, out_predicts, out_logits, stream);
     collect_marks(m);
     *out_accepted = res[0];
     *out_next = res[1];
@@ -1646,14 +1806,14 @@ int32_t anpd_verify_tree(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, 
         std::memcpy(up.w, tp, sizeof(int32_t) * 3 * ANPD_MAX_WINDOW);
         hipLaunchKernelGGL(upload_kernel, dim3(1), dim3(kUploadWords), 0, st, (uint32_t *)(m->ws + m->lay.tree), up, 3 * ANPD_MAX_WINDOW);
         if (m->mfma) rc = run_step_fast(m, kv, step_tokens(window, n_window), n_window, ANPD_APPEND, logits, st, true);
-        else if (m->cfg.dtype == ANPD_BF16) rc = run_step_generic<bf16_t>(m, kv, window, n_window, ANPD_APPEND, logits, st, true);
-        else rc = run_step_generic<float>(m, kv, window, n_window, ANPD_APPEND, logits, st, true);
+        else rc = run_step_weights(m, kv, window, n_window, ANPD_APPEND, logits, st, true);
     }
     if (rc != ANPD_OK) return rc;
     if (logits.elsewhere())
         HIP_TRY(hipMemcpyAsync(out_logits, logits.at, sizeof(float) * (size_t)n_window * m->cfg.vocab, hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
-    if (one_kernel && barrier_gave_up(m, st)) return fail(ANPD_E_HIP, "anpd_verify_tree: the persistent kernel timed out at a grid barrier");
+    if (barrier_gave_up(m, st)) return fail(ANPD_E_HIP, "anpd_verify_tree: the persistent kernel timed out at a grid barrier");
+    if (small_missed(m)) return anpd_verify_tree(m, kv, window, parent, n_window, out_accepted, out_next, out_path, out_predicts, out_logits, stream);
     collect_marks(m);
     *out_accepted = res[0];
     *out_next = res[1];
@@ -1802,8 +1962,7 @@ int32_t anpd_prefill(anpd_model_t *m, anpd_kv_t *kv, const int32_t *tokens, int3
             for (int i = 0, n; i < n_tokens; i += n) {
                 n = n_tokens - i < m->lay.gen_rows ? n_tokens - i : m->lay.gen_rows;
                 const Piece piece = i + n < n_tokens ? PIECE_CACHE : PIECE_LAST;
-                rc = m->cfg.dtype == ANPD_BF16 ? run_step_generic<bf16_t>(m, kv, tokens + i, n, ANPD_APPEND, logits, st, false, piece)
-                                               : run_step_generic<float>(m, kv, tokens + i, n, ANPD_APPEND, logits, st, false, piece);
+                rc = run_step_weights(m, kv, tokens + i, n, ANPD_APPEND, logits, st, false, piece);
                 if (rc != ANPD_OK) return rc;
                 kv->len += n;
                 if (m->prof) {
@@ -1813,9 +1972,11 @@ int32_t anpd_prefill(anpd_model_t *m, anpd_kv_t *kv, const int32_t *tokens, int3
             }
             if (logits.elsewhere()) HIP_TRY(hipMemcpyAsync(out_logits, logits.at, V * sizeof(float), hipMemcpyDeviceToDevice, st));
             HIP_TRY(hipStreamSynchronize(st));
-            return ANPD_OK;
+            return barrier_gave_up(m, st) ? fail(ANPD_E_HIP, "anpd_prefill: a wait inside the kernel timed out") : ANPD_OK;
         };
-        if (const int32_t rc = pieces(); rc != ANPD_OK) {
+        int32_t rc = pieces();
+        const bool missed = rc == ANPD_OK && small_missed(m);
+        if (rc != ANPD_OK || missed) {
             // some pieces may have run, some not: the cache is what it was, on the host and on the device
             (void)hipStreamSynchronize(st);
             kv->len = len0;
@@ -1823,7 +1984,7 @@ int32_t anpd_prefill(anpd_model_t *m, anpd_kv_t *kv, const int32_t *tokens, int3
             (void)hipMemcpyAsync(kv->d_len, kv->pin, sizeof(int32_t), hipMemcpyHostToDevice, st);
             (void)hipStreamSynchronize(st);
             release_pages(kv, len0);
-            return rc;
+            return missed ? anpd_prefill(m, kv, tokens, n_tokens, out_next, out_logits, workspace, workspace_bytes, stream) : rc;
         }
         *out_next = m->pin[33];
         return ANPD_OK;

@@ -152,6 +152,12 @@ __device__ __forceinline__ uint4 ld16_at(const uint4 *base, uint32_t idx)
     u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(wave_buffer(base), (int)(idx * 16u), 0, kAuxCoherent);
     return make_uint4(v.x, v.y, v.z, v.w);
 }
+// 16 bytes that a block of the same launch on the same XCD has stored: past the vector cache, from the L2 that the two share
+constexpr int kAuxNear = 16;  // sc1
+__device__ __forceinline__ u32x4_t ld16_near(const void *base, uint32_t byte)
+{
+    return __builtin_amdgcn_raw_buffer_load_b128(wave_buffer(base), (int)byte, 0, kAuxNear);
+}
 template <bool COH>
 __device__ __forceinline__ uint2 ld8_at(const uint2 *base, uint32_t idx)
 {
@@ -348,35 +354,97 @@ struct Raw8<bf16_t> {
 // two layers' QKV 82 -> 74, 103 -> 92, 50 -> 48.)   An element's sums are the same in all forms.
 // grid: (features / 16, or pairs of 16; ceil(M / (16 RT)))
 enum { FEW_NO = 0, FEW_ROWS = 1, FEW_ROWS_LDS = 2 };
-// tok: the first QKV of a step, whose rows are looked up in the embedding table (null otherwise)
-template <typename WT, int MODE, int RT, int FEW, bool FIRST>
-__device__ __forceinline__ void gemm_gen_block(const GenArgs &a, const int32_t *tok)
+struct GenAttnArgs {
+    const float *q;
+    int q_stride;
+    const void *pool;
+    const int32_t *page_table, *len_ptr;
+    int M, layer, n_layers, n_heads, n_kv_heads, page_tokens, row0, part_rows, max_splits, head_dim;
+    float scale;
+    float *part;
+    uint32_t *counter;
+    float *att;
+    const uint32_t *row_mask;   // draft tree: nullable
+};
+// Block (bx, by) of such a grid.  tok: the first QKV of a step, whose rows are looked up in the embedding table (null otherwise).
+// ONE: what the block reads of X comes from blocks of the same launch on the same XCD (read past the vector cache, from
+// their L2); the first weights are requested, then `wait` says that X is there.  Every wave calls it once.  ONE_U: chunks in flight then.
+// SPLITS > 0 (with ONE): X is attention's output, merged here from the partial results of up to that many splits.
+template <int MODE, int RT>
+struct GenShared {
+    float red[8][gen_pairs(MODE) ? 2 : 1][RT][64][4];
+    float ssq[8][RT][16];
+};
+// Columns k .. k + 7 of attention's output of row `row`: the splits' partial results, which blocks of the same launch on the same XCD have
+// stored, merged in increasing order, as attn_gen_block does.
+template <int SPLITS>
+__device__ __forceinline__ void gen_merge8(const GenAttnArgs &a, int len, int row, int k, f32x4 &lo, f32x4 &hi)
+{
+    const int dh = a.head_dim, head = k / dh, e = k - head * dh, ns = (len + row) / kAttnSplit + 1;
+    const uint32_t slot0 = (uint32_t)(head * a.max_splits) * (uint32_t)a.part_rows + (uint32_t)(row - a.row0), stride = (uint32_t)a.part_rows;
+    const float *ps = a.part + (size_t)a.n_heads * a.max_splits * a.part_rows * dh;
+    f32x4 v0[SPLITS], v1[SPLITS];
+    u32x2_t st[SPLITS];
+#pragma unroll
+    for (int s = 0; s < SPLITS; ++s) {
+        const uint32_t at = slot0 + (uint32_t)(s < ns ? s : 0) * stride;
+        v0[s] = __builtin_bit_cast(f32x4, ld16_near(a.part, (at * (uint32_t)dh + (uint32_t)e) * 4u));
+        v1[s] = __builtin_bit_cast(f32x4, ld16_near(a.part, (at * (uint32_t)dh + (uint32_t)e + 4u) * 4u));
+        st[s] = __builtin_amdgcn_raw_buffer_load_b64(wave_buffer(ps), (int)(at * 8u), 0, kAuxNear);
+    }
+    float g = kMasked;
+#pragma unroll
+    for (int s = 0; s < SPLITS; ++s) g = fmaxf(g, __uint_as_float(st[s][0]));   // (a split beyond the last is the first again)
+    float dn = 0.f;
+    lo = hi = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < SPLITS; ++s) {
+        if (s >= ns) continue;
+        const float wgt = expf(__uint_as_float(st[s][0]) - g);
+        dn = fmaf(wgt, __uint_as_float(st[s][1]), dn);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            lo[i] = fmaf(wgt, v0[s][i], lo[i]);
+            hi[i] = fmaf(wgt, v1[s][i], hi[i]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { lo[i] /= dn; hi[i] /= dn; }
+}
+struct NoWait {
+    __device__ __forceinline__ void operator()() const {}
+    __device__ __forceinline__ void publish() const {}   // called by every wave before the block meets again
+};
+template <typename WT, int MODE, int RT, int FEW, bool FIRST, bool ONE = false, int ONE_U = 1, int SPLITS = 0, typename Wait = NoWait>
+__device__ __forceinline__ void gemm_gen_block(const GenArgs &a, const int32_t *tok, int bx, int by, GenShared<MODE, RT> &sh, const Wait &wait = Wait(),
+                                               const GenAttnArgs *parts = nullptr)
 {
     constexpr int NW = gen_pairs(MODE) ? 2 : 1, S = sizeof(WT) == 2 ? 2 : 1, WAVES = 8,
-                  U = (FEW && MODE != GEN_RESIDUAL) || (S == 2 && RT == 1 && MODE == GEN_QKV) ? 1 : (S == 2 && (NW == 2 || RT == 2 || MODE == GEN_LOGITS) ? 2 : 3);
+                  U = ONE ? ONE_U : (FEW && MODE != GEN_RESIDUAL) || (S == 2 && RT == 1 && MODE == GEN_QKV) ? 1 : (S == 2 && (NW == 2 || RT == 2 || MODE == GEN_LOGITS) ? 2 : 3);
     static_assert(FEW == FEW_NO || RT == 1, "one row tile");
     extern __shared__ float x_lds[];   // FEW_ROWS_LDS: [M][K]
     constexpr bool NORM = gen_norm(MODE);
-    __shared__ float red[WAVES][NW][RT][64][4];
-    __shared__ float ssq[WAVES][RT][16];
+    auto &red = sh.red;
+    auto &ssq = sh.ssq;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 15, kg = lane >> 4;
-    const int K = a.K, m0 = blockIdx.y * 16 * RT;
+    const int K = a.K, m0 = by * 16 * RT;
 
     // the weight rows of this block's tiles
     const WT *w[NW];
     int sect = 0, head = 0, i0 = 0;   // QKV: q | k | v, its head, the pair's first dimension
     if (MODE == GEN_QKV) {
         const int half = a.head_dim / 2, per_head = half / 16;
-        head = blockIdx.x / per_head;
-        i0 = 16 * (blockIdx.x - head * per_head);
+        head = bx / per_head;
+        i0 = 16 * (bx - head * per_head);
         sect = head < a.n_heads ? 0 : (head < a.n_heads + a.n_kv_heads ? 1 : 2);
         head -= sect == 0 ? 0 : (sect == 1 ? a.n_heads : a.n_heads + a.n_kv_heads);
-        const WT *W = (const WT *)(sect == 0 ? a.W0 : (sect == 1 ? a.W1 : a.W2)) + (size_t)(head * a.head_dim + i0 + r) * K;
+        const void *wq = a.W0, *wk = a.W1, *wv = a.W2;   // (values: a choice among the arguments' places would put them all into scratch memory)
+        const WT *W = (const WT *)(sect == 0 ? wq : (sect == 1 ? wk : wv)) + (size_t)(head * a.head_dim + i0 + r) * K;
         w[0] = W;
         w[NW - 1] = W + (size_t)half * K;
     } else {
-        w[0] = (const WT *)a.W0 + (size_t)(blockIdx.x * 16 + r) * K;
-        if (NW == 2) w[NW - 1] = (const WT *)a.W1 + (size_t)(blockIdx.x * 16 + r) * K;
+        w[0] = (const WT *)a.W0 + (size_t)(bx * 16 + r) * K;
+        if (NW == 2) w[NW - 1] = (const WT *)a.W1 + (size_t)(bx * 16 + r) * K;
     }
     const WT *gain = (const WT *)a.gain;
     const WT *row[RT];   // FIRST: the embedding of row m0 + 16 t + r
@@ -413,7 +481,9 @@ __device__ __forceinline__ void gemm_gen_block(const GenArgs &a, const int32_t *
         for (int i = 4 * (int)threadIdx.x; i < a.M * K; i += 4 * 512) *reinterpret_cast<float4 *>(x_lds + i) = *reinterpret_cast<const float4 *>(a.X + i);
         __syncthreads();
     }
-    for (int c0 = wave; c0 * 32 * S < K; c0 += WAVES * U) {
+    f32x4 old = {0.f, 0.f, 0.f, 0.f};   // (ONE, RESIDUAL)
+    const int len = SPLITS > 0 ? *parts->len_ptr : 0;
+    for (int c0 = wave; c0 * 32 * S < K || (ONE && c0 == wave); c0 += WAVES * U) {
         Raw8<WT> wv[U][S][NW];
         Raw8<WT> gv[U][S];
         float xv[U][S][RT][8];
@@ -436,12 +506,40 @@ __device__ __forceinline__ void gemm_gen_block(const GenArgs &a, const int32_t *
                     for (int t = 0; t < RT; ++t)
                         if (m0 + 16 * t + r < a.M) {
                             if (FIRST) load8(row[t] + k, xv[u][s][t]);
-                            else load8((FEW == FEW_ROWS_LDS ? x_lds : a.X) + (size_t)(m0 + 16 * t + r) * K + k, xv[u][s][t]);
+                            else if (!ONE) load8((FEW == FEW_ROWS_LDS ? x_lds : a.X) + (size_t)(m0 + 16 * t + r) * K + k, xv[u][s][t]);
                         }
                     if (NORM) gv[u][s].load(gain + k);
                 }
             }
-        if (FIRST && blockIdx.x == 0) {   // the first block leaves the rows where the residual stream begins
+        if constexpr (ONE) {
+            if (c0 == wave) {
+                wait();
+                const int t = wave, m = m0 + 16 * t + r;
+                if (MODE == GEN_RESIDUAL && t < RT && m < a.M)
+                    old = __builtin_bit_cast(f32x4, ld16_near(a.Y, (uint32_t)(m * a.ldy + bx * 16 + 4 * kg) * 4u));
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    const int k = (c0 + u * WAVES) * 32 * S + 8 * (S * kg + s);
+#pragma unroll
+                    for (int t = 0; t < RT; ++t)
+                        if (!FIRST && k < K && m0 + 16 * t + r < a.M) {
+                            f32x4 lo, hi;
+                            if constexpr (SPLITS > 0) {
+                                gen_merge8<SPLITS>(*parts, len, m0 + 16 * t + r, k, lo, hi);
+                            } else {
+                                const uint32_t at = ((uint32_t)(m0 + 16 * t + r) * (uint32_t)K + (uint32_t)k) * 4u;
+                                lo = __builtin_bit_cast(f32x4, ld16_near(a.X, at));
+                                hi = __builtin_bit_cast(f32x4, ld16_near(a.X, at + 16u));
+                            }
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) { xv[u][s][t][i] = lo[i]; xv[u][s][t][4 + i] = hi[i]; }
+                        }
+                }
+        }
+        if (FIRST && bx == 0) {   // the first block leaves the rows where the residual stream begins
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -486,6 +584,7 @@ __device__ __forceinline__ void gemm_gen_block(const GenArgs &a, const int32_t *
             *reinterpret_cast<f32x4 *>(red[wave][n][t][lane]) = s;
         }
     }
+    wait.publish();
     __syncthreads();
     if (wave >= RT) return;
     // wave t finishes row tile t: lane (m, kg) has features 4 kg .. 4 kg + 3 of row m0 + 16 t + m
@@ -508,14 +607,14 @@ __device__ __forceinline__ void gemm_gen_block(const GenArgs &a, const int32_t *
         for (int n = 0; n < NW; ++n) y[n] = y[n] * rinv;
     }
     if (m >= a.M) return;
-    const int f = blockIdx.x * 16 + 4 * kg;   // (all but QKV)
+    const int f = bx * 16 + 4 * kg;   // (all but QKV)
     if (MODE == GEN_PLAIN || MODE == GEN_LOGITS) {
         // (the caller's buffer need not be aligned for wide stores)
 #pragma unroll
         for (int i = 0; i < 4; ++i) a.Y[(size_t)m * a.ldy + f + i] = y[0][i];
     } else if (MODE == GEN_RESIDUAL) {
         f32x4 *x = reinterpret_cast<f32x4 *>(a.Y + (size_t)m * a.ldy + f);
-        *x = *x + y[0];
+        *x = (ONE ? old : *x) + y[0];
     } else if (MODE == GEN_GATE_UP) {
         f32x4 o;
 #pragma unroll
@@ -549,7 +648,8 @@ __device__ __forceinline__ void gemm_gen_block(const GenArgs &a, const int32_t *
 template <typename WT, int MODE, int RT, int FEW = FEW_NO>
 __global__ __launch_bounds__(512, FEW && MODE != GEN_RESIDUAL ? (gen_norm(MODE) ? 6 : 8) : (sizeof(WT) == 2 && RT == 1 ? 4 : 2)) void gemm_gen_kernel(GenArgs a)
 {
-    gemm_gen_block<WT, MODE, RT, FEW, false>(a, nullptr);
+    __shared__ GenShared<MODE, RT> sh;
+    gemm_gen_block<WT, MODE, RT, FEW, false>(a, nullptr, blockIdx.x, blockIdx.y, sh);
 }
 // The first QKV of a step: its rows come from the embedding table, without a launch in front of it that copies them.  A step of
 // a small model is a chain of launches of 3-4 us: 67.7 -> 65.5 us of kernels (traced) and one launch less at d 256, two layers,
@@ -558,7 +658,8 @@ __global__ __launch_bounds__(512, FEW && MODE != GEN_RESIDUAL ? (gen_norm(MODE) 
 template <typename WT, int RT>
 __global__ __launch_bounds__(512, sizeof(WT) == 2 && RT == 1 ? 4 : 2) void gemm_gen_first_kernel(GenArgs a, StepTokens tok)
 {
-    gemm_gen_block<WT, GEN_QKV, RT, FEW_NO, true>(a, tok.t);
+    __shared__ GenShared<GEN_QKV, RT> sh;
+    gemm_gen_block<WT, GEN_QKV, RT, FEW_NO, true>(a, tok.t, blockIdx.x, blockIdx.y, sh);
 }
 
 // ------------------------------------------------------------- attention
@@ -574,24 +675,35 @@ __global__ __launch_bounds__(512, sizeof(WT) == 2 && RT == 1 ? 4 : 2) void gemm_
 // part: outputs [head][split][part_rows][DH], then (maximum, denominator) [head][split][part_rows][2].
 // counter: [row group][head], a 256-byte line each, zero between calls.
 // grid: (n_heads, n_splits, row groups), 4 waves.
-template <typename KT, int DH>
-__global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ q, int q_stride, const KT *__restrict__ pool,
-                                                    const int32_t *__restrict__ page_table,
-                                                    const int32_t *__restrict__ len_ptr, int M, int layer, int n_layers,
-                                                    int n_heads, int n_kv_heads, int page_tokens, int row0, int part_rows,
-                                                    int max_splits, float scale, float *__restrict__ part,
-                                                    uint32_t *__restrict__ counter, float *__restrict__ att,
-                                                    const uint32_t *__restrict__ row_mask /* draft tree: nullable */)
+template <int DH>
+struct GenAttnShared {
+    float red[kAttnSplit / 16][DH / 16][64][4];
+    float wmax[kAttnSplit / 16][16], wden[kAttnSplit / 16][16];
+    bool last;
+};
+// Block (head, split, group).  ONE: as in gemm_gen_block, eight waves, of which four have keys; those of earlier steps are requested
+// before `wait`.
+// merge: by the last block; else the partial results are what it leaves.
+template <typename KT, int DH, bool ONE = false, typename Wait = NoWait>
+__device__ __forceinline__ void attn_gen_block(const GenAttnArgs &a, int head, int split, int group, GenAttnShared<DH> &sh, const Wait &wait = Wait(), bool merge = true)
 {
     constexpr int NC = DH / 16, WAVES = kAttnSplit / 16;
-    __shared__ float red[WAVES][NC][64][4];
-    __shared__ float wmax[WAVES][16], wden[WAVES][16];
-    __shared__ bool last;
-    const int head = blockIdx.x, split = blockIdx.y, m0 = row0 + 16 * blockIdx.z;
+    auto &red = sh.red;
+    auto &wmax = sh.wmax;
+    auto &wden = sh.wden;
+    const KT *pool = (const KT *)a.pool;
+    const int32_t *page_table = a.page_table;
+    const uint32_t *row_mask = a.row_mask;
+    const int M = a.M, layer = a.layer, n_layers = a.n_layers, n_heads = a.n_heads, n_kv_heads = a.n_kv_heads, page_tokens = a.page_tokens;
+    const int row0 = a.row0, m0 = row0 + 16 * group;
     const int kvh = head / (n_heads / n_kv_heads);   // the key / value head this query head reads
-    const int L = *len_ptr;
+    const int L = *a.len_ptr;
     const int n_splits = (L + (m0 + 16 < M ? m0 + 16 : M) + kAttnSplit - 1) / kAttnSplit;
-    if (split >= n_splits) return;  // no row of the group sees a key of this split
+    if (split >= n_splits) {  // no row of the group sees a key of this split
+        wait();
+        wait.publish();
+        return;
+    }
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 15, kg = lane >> 4;
     const int key0 = split * kAttnSplit + 16 * wave, m = m0 + r;
 
@@ -602,32 +714,50 @@ __global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ q, 
     for (int c = 0; c < NC; ++c)
 #pragma unroll
         for (int i = 0; i < 4; ++i) { kf[c][i] = 0.f; qf[c][i] = 0.f; vf[c][i] = 0.f; }
-    if (m < M) {
-        const float *qr = q + (size_t)m * q_stride + head * DH + 4 * kg;
+    // the wave's keys' pages, then keys lo .. hi - 1
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    int page_k = 0;
+    i32x4 page_v = {0, 0, 0, 0};
+    if (key0 + r < L + M) page_k = page_table[(key0 + r) / page_tokens];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (key0 + 4 * kg + i < L + M) page_v[i] = page_table[(key0 + 4 * kg + i) / page_tokens];
+    auto load_kv = [&](int lo, int hi) __attribute__((always_inline)) {
+        if (key0 + r >= lo && key0 + r < hi) {
+            const KT *kr = pool + kv_offset(page_k, layer, n_layers, 0, kvh, n_kv_heads, (key0 + r) % page_tokens, page_tokens, DH) + 4 * kg;
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) kf[c][i] = load_f32(kr, (size_t)(16 * c + i));
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int key = key0 + 4 * kg + i;
+            if (key >= lo && key < hi) {
+                const KT *vr = pool + kv_offset(page_v[i], layer, n_layers, 1, kvh, n_kv_heads, key % page_tokens, page_tokens, DH) + r;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) vf[c][i] = load_f32(vr, (size_t)(16 * c));
+            }
+        }
+    };
+    const bool mine = !ONE || wave < WAVES;   // (a block of the one launch has more waves than this needs)
+    if (ONE) {
+        if (mine) load_kv(0, L);
+        wait();
+    }
+    if (mine && m < M) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            const f32x4 v = *reinterpret_cast<const f32x4 *>(qr + 16 * c);
+            const size_t at = (size_t)m * a.q_stride + head * DH + 4 * kg + 16 * c;
+            f32x4 v;
+            if (ONE) v = __builtin_bit_cast(f32x4, ld16_near(a.q, (uint32_t)at * 4u));
+            else v = *reinterpret_cast<const f32x4 *>(a.q + at);
 #pragma unroll
             for (int i = 0; i < 4; ++i) qf[c][i] = v[i];
         }
     }
-    if (key0 + r < L + M) {
-        const int key = key0 + r;
-        const KT *kr = pool + kv_offset(page_table[key / page_tokens], layer, n_layers, 0, kvh, n_kv_heads, key % page_tokens, page_tokens, DH) + 4 * kg;
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) kf[c][i] = load_f32(kr, (size_t)(16 * c + i));
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int key = key0 + 4 * kg + i;
-        if (key < L + M) {
-            const KT *vr = pool + kv_offset(page_table[key / page_tokens], layer, n_layers, 1, kvh, n_kv_heads, key % page_tokens, page_tokens, DH) + r;
-#pragma unroll
-            for (int c = 0; c < NC; ++c) vf[c][i] = load_f32(vr, (size_t)(16 * c));
-        }
-    }
+    if (mine) load_kv(ONE ? L : 0, L + M);
+    wait.publish();
     // ---- scores: lane (r, kg) has keys key0 + 4 kg + i of row m
     // (eight chains, as in the GEMM)
     f32x4 sq[8];
@@ -646,11 +776,11 @@ __global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ q, 
     float p[4], mx = kMasked;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        p[i] = m < M && sees(m, vis, key0 + 4 * kg + i) ? s[i] * scale : kMasked;
+        p[i] = m < M && sees(m, vis, key0 + 4 * kg + i) ? s[i] * a.scale : kMasked;
         mx = fmaxf(mx, p[i]);
     }
     mx = rows_max(mx);
-    if (kg == 0) wmax[wave][r] = mx;
+    if (mine && kg == 0) wmax[wave][r] = mx;
     __syncthreads();
     float bm = wmax[0][r], den = 0.f;
 #pragma unroll
@@ -661,7 +791,7 @@ __global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ q, 
         den += p[i];
     }
     den = rows_sum(den);
-    if (kg == 0) wden[wave][r] = den;
+    if (mine && kg == 0) wden[wave][r] = den;
     // ---- weighted V: lane (r, kg) has dimensions 16 c + 4 kg .. + 4 of row m
     // A weight of 0 does not keep out what is not finite.  Where a key that some row must not see has such a V, the rows
     // are taken one at a time, each over the keys that it sees.
@@ -681,7 +811,8 @@ __global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ q, 
         for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(!seen || seen[i] ? vf[c][i] : 0.f, p[i], (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
         return (o[0] + o[1]) + (o[2] + o[3]);
     };
-    if (!apart) {
+    if (!mine) {
+    } else if (!apart) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) *reinterpret_cast<f32x4 *>(red[wave][c][lane]) = weigh(c, nullptr);
     } else {
@@ -698,31 +829,32 @@ __global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ q, 
         }
     }
     __syncthreads();
-    const size_t slot0 = ((size_t)head * max_splits) * part_rows, stride = (size_t)part_rows;   // rows of (head, split 0); rows per split
-    float *po = part, *ps = part + (size_t)n_heads * max_splits * part_rows * DH;
-    for (int c = wave; c < NC; c += WAVES) {
+    const size_t slot0 = ((size_t)head * a.max_splits) * a.part_rows, stride = (size_t)a.part_rows;   // rows of (head, split 0); rows per split
+    float *po = a.part, *ps = a.part + (size_t)n_heads * a.max_splits * a.part_rows * DH;
+    for (int c = wave; c < NC; c += ONE ? 2 * WAVES : WAVES) {
         f32x4 o = *reinterpret_cast<const f32x4 *>(red[0][c][lane]);
 #pragma unroll
         for (int v = 1; v < WAVES; ++v) o += *reinterpret_cast<const f32x4 *>(red[v][c][lane]);
-        if (m < M) stc16<true>(po + (slot0 + split * stride + (m - row0)) * DH + 16 * c + 4 * kg, o);
+        if (m < M) stc16<!ONE>(po + (slot0 + split * stride + (m - row0)) * DH + 16 * c + 4 * kg, o);
     }
     if (wave == 0 && kg == 0 && m < M) {
         float d = wden[0][r];
 #pragma unroll
         for (int v = 1; v < WAVES; ++v) d += wden[v][r];
-        stc8<true>(ps + (slot0 + split * stride + (m - row0)) * 2, make_uint2(__float_as_uint(bm), __float_as_uint(d)));
+        stc8<!ONE>(ps + (slot0 + split * stride + (m - row0)) * 2, make_uint2(__float_as_uint(bm), __float_as_uint(d)));
     }
+    if (ONE && !merge) return;
     // ---- the last block of this head and row group merges the splits
     wait_stores();
     __syncthreads();
-    uint32_t *ctr = counter + ((size_t)blockIdx.z * n_heads + head) * 64;
+    uint32_t *ctr = a.counter + ((size_t)group * n_heads + head) * 64;
     if (threadIdx.x == 0)
-        last = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == (uint32_t)n_splits;
+        sh.last = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == (uint32_t)n_splits;
     __syncthreads();
-    if (!last) return;
+    if (!sh.last) return;
     if (threadIdx.x == 0) st_agent(ctr, 0u);
     constexpr int SB = 8, DQ = DH / 4;
-    for (int idx = threadIdx.x; idx < 16 * DQ; idx += 256) {
+    for (int idx = threadIdx.x; idx < 16 * DQ; idx += ONE ? 512 : 256) {
         const int row = m0 + idx / DQ, e4 = idx % DQ;
         if (row >= M) continue;
         const int ns = (L + row) / kAttnSplit + 1;   // splits that hold keys this row may see
@@ -759,8 +891,14 @@ __global__ __launch_bounds__(256) void attn_kernel(const float *__restrict__ q, 
             }
         }
         o[0] /= dn; o[1] /= dn; o[2] /= dn; o[3] /= dn;
-        *reinterpret_cast<f32x4 *>(att + (size_t)row * n_heads * DH + head * DH + 4 * e4) = o;
+        *reinterpret_cast<f32x4 *>(a.att + (size_t)row * n_heads * DH + head * DH + 4 * e4) = o;
     }
+}
+template <typename KT, int DH>
+__global__ __launch_bounds__(256) void attn_kernel(GenAttnArgs a)
+{
+    __shared__ GenAttnShared<DH> sh;
+    attn_gen_block<KT, DH>(a, blockIdx.x, blockIdx.y, blockIdx.z, sh);
 }
 
 // Appends n rows to the cache's length: a window of a prompt of which only the cache entries are wanted.
@@ -800,30 +938,36 @@ struct AcceptArgs {
     const SeqRef *seqs;               // batch
     int n_seq;
     int32_t *host_batch;
+    uint32_t *launches, *host_launches;   // the one launch of a small model: completed ones, here and in pinned host memory
 };
-template <int KIND>
-__global__ __launch_bounds__(1024) void argmax_accept_kernel(const float *__restrict__ logits, int V, int M, StepTokens window,
-                                                              int mode, AcceptArgs a)
+struct AcceptShared {
+    float bv[16];
+    int bi[16];
+    bool last;
+};
+// window: the rows' tokens.  Returns whether this block applied the rules.
+template <int KIND, int THREADS>
+__device__ __forceinline__ bool argmax_accept_block(const float *__restrict__ logits, int V, int M, const int32_t *window, int mode, const AcceptArgs &a,
+                                                    int r, AcceptShared &sh)
 {
-    __shared__ float bv[16];
-    __shared__ int bi[16];
-    __shared__ bool last;
-    const int r = blockIdx.x;
+    auto &bv = sh.bv;
+    auto &bi = sh.bi;
+    auto &last = sh.last;
     const f32x4 *row = reinterpret_cast<const f32x4 *>(logits + (size_t)r * V);   // (V is a multiple of 16, logits are 16-byte aligned)
     float best = -INFINITY;
     int besti = 0x7fffffff;
     constexpr int U = 8;
-    for (int i0 = threadIdx.x; i0 < V / 4; i0 += 1024 * U) {
+    for (int i0 = threadIdx.x; i0 < V / 4; i0 += THREADS * U) {
         f32x4 v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (i0 + 1024 * u < V / 4) v[u] = row[i0 + 1024 * u];
+            if (i0 + THREADS * u < V / 4) v[u] = row[i0 + THREADS * u];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (i0 + 1024 * u >= V / 4) break;
+            if (i0 + THREADS * u >= V / 4) break;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (v[u][j] > best) { best = v[u][j]; besti = 4 * (i0 + 1024 * u) + j; }   // (never a NaN)
+                if (v[u][j] > best) { best = v[u][j]; besti = 4 * (i0 + THREADS * u) + j; }   // (never a NaN)
         }
     }
 #pragma unroll
@@ -835,7 +979,7 @@ __global__ __launch_bounds__(1024) void argmax_accept_kernel(const float *__rest
     if ((threadIdx.x & 63) == 0) { bv[threadIdx.x >> 6] = best; bi[threadIdx.x >> 6] = besti; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < 16; ++w)
+        for (int w = 1; w < THREADS / 64; ++w)
             if (bv[w] > best || (bv[w] == best && bi[w] < besti)) { best = bv[w]; besti = bi[w]; }
         if (besti == 0x7fffffff) besti = 0;   // nothing above -infinity
         st_agent(a.result + 2 + r, (int32_t)besti);
@@ -844,12 +988,13 @@ __global__ __launch_bounds__(1024) void argmax_accept_kernel(const float *__rest
         st_system(a.host_result + 2 + r, (int32_t)besti);   // (after the counter: its way to the host is long)
     }
     __syncthreads();
-    if (!last || threadIdx.x >= 64) return;
+    if (!last) return false;
+    if (threadIdx.x >= 64) return true;
     const int lane = threadIdx.x;
     const int32_t pred = ld_agent(a.result + 2 + (lane < M ? lane : 0));
     if (KIND == ACCEPT_CHAIN || KIND == ACCEPT_BATCH) {
         // bit m: the token of row m + 1 is not the prediction made at row m
-        const unsigned long long wrong = __builtin_amdgcn_ballot_w64(lane + 1 < M && window.t[lane + 1 < M ? lane + 1 : 0] != pred);
+        const unsigned long long wrong = __builtin_amdgcn_ballot_w64(lane + 1 < M && window[lane + 1 < M ? lane + 1 : 0] != pred);
         constexpr bool seq = KIND == ACCEPT_BATCH;
         const bool mine = lane < (seq ? a.n_seq : 1);
         const int r0 = seq && mine ? a.seqs[lane].row0 : 0, n = seq ? (mine ? a.seqs[lane].n_rows : 1) : M;
@@ -871,7 +1016,7 @@ __global__ __launch_bounds__(1024) void argmax_accept_kernel(const float *__rest
         const int p = lane > 0 && lane < M ? a.parent[lane] : 0, depth = lane < M ? a.depth[lane] : 0;
         // whether this row's token is the prediction made at its parent
         const int32_t at_parent = __shfl(pred, p, kWave);
-        const unsigned long long right = __builtin_amdgcn_ballot_w64(lane > 0 && lane < M && window.t[lane < M ? lane : 0] == at_parent);
+        const unsigned long long right = __builtin_amdgcn_ballot_w64(lane > 0 && lane < M && window[lane < M ? lane : 0] == at_parent);
         unsigned long long ok = 1ull;
         int best_row = 0, best_depth = 0;
         for (int q = 1; q < M; ++q) {
@@ -898,6 +1043,14 @@ __global__ __launch_bounds__(1024) void argmax_accept_kernel(const float *__rest
         }
     }
     if (lane == 0) st_agent(a.counter, 0u);
+    return true;
+}
+template <int KIND>
+__global__ __launch_bounds__(1024) void argmax_accept_kernel(const float *__restrict__ logits, int V, int M, StepTokens window,
+                                                              int mode, AcceptArgs a)
+{
+    __shared__ AcceptShared sh;
+    argmax_accept_block<KIND, 1024>(logits, V, M, window.t, mode, a, blockIdx.x, sh);
 }
 
 // Generic-layout counterpart of kvf_compact_kernel.   grid: n_layers * 2 * n_heads blocks.

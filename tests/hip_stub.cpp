@@ -40,6 +40,8 @@ hipError_t launch(const void *f, dim3 grid, dim3 block, void **args)
 {
     if (g_fail_at > 0 && --g_fail_at == 0) return error(hipErrorLaunchFailure);
     g_launches.push_back({g_names[f], grid, block, {*(void **)args[0]}});
+    // (the one kernel whose answer the library looks at: how many blocks run on each XCD, here all that there are on the third)
+    if (std::getenv("STUB_XCD_BLOCKS") && g_names[f].find("xcd_census") != std::string::npos) (*(unsigned **)args[0])[2] = std::atoi(std::getenv("STUB_XCD_BLOCKS"));
     return hipSuccess;
 }
 }  // namespace

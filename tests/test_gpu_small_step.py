@@ -1,0 +1,96 @@
+"""A small fp32 model's step in one launch leaves, bit for bit, what the separate launches leave: logits, results, cache."""
+import dataclasses
+
+import pytest
+import torch
+
+from paper_2404_08698_amd import binding as B
+from paper_2404_08698_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+T = synth.TINY
+SHAPES = {
+    "tiny": T, "one_layer": dataclasses.replace(T, n_layers=1), "grouped": synth.TINY_MQA,
+    # K of half a round of the eight waves, and of two and three rounds; no tile of the feed-forward layer left over, one
+    "d128": dataclasses.replace(T, n_layers=3, d_model=128, n_heads=2, d_ffn=512, vocab=512),
+    "d320": dataclasses.replace(T, d_model=320, n_heads=5, d_ffn=512, vocab=528),
+    "head128": dataclasses.replace(T, d_model=256, n_heads=2, head_dim=128, d_ffn=528),
+}
+
+
+@pytest.fixture(scope="module")
+def pairs():
+    made = {}
+
+    def get(name):
+        if name not in made:
+            made.clear()
+            w = synth.make_weights(SHAPES[name], 6, device="cuda")
+            made[name] = [B.Model(SHAPES[name], w, max_window=32, max_positions=600, gemm_path=p) for p in (B.GEMM_AUTO, B.GEMM_DOT)]
+        return made[name]
+    yield get
+    made.clear()
+
+
+def one_launch(model):
+    p = model.profile_read()
+    return p["steps"] == p["intervals"]["step"] > 0
+
+
+# key splits (of 64): one, up to four, which O's blocks merge, five and eight; the window's rows on either side of a split; row
+# tiles of one and two.  Repeated: flags and counters of the launch before are there.
+@pytest.mark.parametrize("name", sorted(SHAPES))
+@pytest.mark.parametrize("length,rows", [(0, 1), (59, 5), (60, 5), (128, 16), (128, 17), (200, 32), (239, 17), (251, 5), (252, 5), (300, 1), (496, 16)])
+def test_a_step_has_the_bits_of_separate_launches(pairs, name, length, rows):
+    shape = SHAPES[name]
+    tokens = synth.random_tokens(shape.vocab, length + rows, 21)
+    seen = []
+    for model in pairs(name):
+        kv = B.KVCache(model, length + rows)
+        if length:
+            B.prefill(model, kv, tokens[:length])
+        runs = []
+        model.profile(True)
+        for mode in (B.VERIFY, B.APPEND, B.APPEND):
+            kv.truncate(length)
+            logits = torch.zeros(rows, shape.vocab, dtype=torch.float32, device="cuda")
+            done = B.verify(model, kv, tokens[length:], mode, out_logits=logits)
+            runs.append((logits, done, kv.length, [kv.read(layer, 0, kv.length) for layer in range(shape.n_layers)]))
+        seen.append((runs, one_launch(model)))
+        model.profile(False)
+    assert seen[0][1] and not seen[1][1]
+    for (la, da, na, ka), (lb, db, nb, kb) in zip(seen[0][0], seen[1][0]):
+        assert torch.equal(la, lb) and da == db and na == nb
+        for x, y in zip(ka, kb):
+            assert torch.equal(x[0], y[0]) and torch.equal(x[1], y[1])
+
+
+# a tree whose accepted path (what the model itself says, as second child of every row) has to be moved in the cache; a short prompt
+def test_trees_and_short_prompts(pairs):
+    shape, length = SHAPES["tiny"], 70
+    tokens = synth.random_tokens(shape.vocab, length + 1, 22)
+    seen = []
+    for model in pairs("tiny"):
+        kv = B.KVCache(model, 200)
+        first = B.prefill(model, kv, tokens[:30])
+        B.prefill(model, kv, tokens[30:length])
+        window, parents = [tokens[length]], [-1]
+        chain = [tokens[length]]
+        for _ in range(3):
+            kv.truncate(length)
+            chain.append(B.verify(model, kv, chain, B.APPEND)[1])
+        at = 0
+        for t in chain[1:]:
+            window += [(t + 1) % shape.vocab, t]
+            parents += [at, at]
+            at = len(window) - 1
+        kv.truncate(length)
+        logits = torch.zeros(len(window), shape.vocab, dtype=torch.float32, device="cuda")
+        done = B.verify_tree(model, kv, window, parents, out_logits=logits)
+        assert done[0] == 3
+        seen.append((first, done, logits, kv.length, [kv.read(layer, 0, kv.length) for layer in range(shape.n_layers)]))
+    a, b = seen
+    assert a[0] == b[0] and a[1] == b[1] and torch.equal(a[2], b[2]) and a[3] == b[3] == length + 4
+    for x, y in zip(a[4], b[4]):
+        assert torch.equal(x[0], y[0]) and torch.equal(x[1], y[1])

@@ -1,0 +1,65 @@
+"""Host side of a small fp32 model's step in one launch, on the stand-in for the HIP runtime: which calls take it, and what happens
+when no block ran on the XCD that it was meant for (on the stand-in none does): the step is separate launches, then and later."""
+import os
+import sys
+
+import pytest
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+from test_host_path import Host, in_child, stub  # noqa: E402,F401
+
+
+def run(stub, name, *args, blocks=32):
+    os.environ["STUB_XCD_BLOCKS"] = str(blocks)
+    try:
+        import subprocess
+        r = subprocess.run([sys.executable, os.path.abspath(__file__), name, *map(str, args)], capture_output=True, text=True, timeout=120,
+                           env=dict(os.environ, ANPD_HIP_STUB=stub, PYTHONPATH=os.path.dirname(os.path.dirname(os.path.abspath(__file__)))))
+    finally:
+        del os.environ["STUB_XCD_BLOCKS"]
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def child_route(d, heads, dh, ffn, vocab, path, length, rows, taken):
+    h = Host(d=int(d), heads=int(heads), dh=int(dh), ffn=int(ffn), vocab=int(vocab), dtype="f32", path=int(path), layers=2, max_positions=1200)
+    kv = h.cache(1200, int(length))
+    h.stub.stub_forget()
+    h.ok(h.verify(kv, int(rows), None))
+    assert ("small_step_kernel" in h.names()[0]) == bool(int(taken)), h.names()
+    # (taken: it did nothing)  the separate launches did the step, and do the next one
+    assert any("attn_kernel" in n for n in h.names()) and h.L.anpd_kv_length(kv) == int(length) + 1
+    h.stub.stub_forget()
+    h.ok(h.verify(kv, int(rows), None))
+    assert not any("small_step_kernel" in n for n in h.names()), h.names()
+
+
+# the tiny decoder at either end of its range (splits of 64 keys: eight; 17 rows and more count twice), a wider one, a larger
+# vocabulary, separate launches asked for, too few blocks on any XCD
+@pytest.mark.parametrize("d,heads,dh,ffn,vocab,path,length,rows,taken,blocks", [
+    (256, 4, 64, 688, 1024, 0, 128, 5, 1, 32), (256, 4, 64, 688, 1024, 0, 0, 1, 1, 32), (256, 4, 64, 688, 1024, 0, 507, 5, 1, 32),
+    (256, 4, 64, 688, 1024, 0, 508, 5, 0, 32), (256, 4, 64, 688, 1024, 0, 128, 32, 1, 32), (256, 4, 64, 688, 1024, 0, 239, 17, 1, 32),
+    (256, 4, 64, 688, 1024, 0, 240, 17, 0, 32), (512, 8, 64, 1408, 1024, 0, 128, 5, 0, 32), (256, 4, 64, 688, 32000, 0, 128, 5, 0, 32),
+    (256, 4, 64, 688, 1024, 1, 128, 5, 0, 32), (256, 4, 64, 688, 1024, 0, 128, 5, 0, 15),
+])
+def test_which_steps_are_one_launch_and_what_a_step_that_was_not_done_becomes(stub, d, heads, dh, ffn, vocab, path, length, rows, taken, blocks):
+    run(stub, "child_route", d, heads, dh, ffn, vocab, path, length, rows, taken, blocks=blocks)
+
+
+def child_prompt():
+    """A prompt whose last piece is small: its first pieces are launches, the last one's launch does nothing, and the prompt starts over."""
+    import ctypes as C
+    h = Host(dtype="f32", ffn=688, vocab=1024, layers=2, max_positions=700)
+    kv = h.cache(700, 20)
+    h.stub.stub_forget()
+    h.ok(h.prefill(kv, 261))
+    names = h.names()
+    assert sum("small_step_kernel" in n for n in names) == 1 and sum("advance_length" in n for n in names) == 2 and h.L.anpd_kv_length(kv) == 281
+    assert C.c_int32.from_address(h.length_at[kv.value]).value == 20      # (as it was before the second run, which the stand-in does not make)
+
+
+def test_a_prompt_that_was_not_done_starts_over(stub):
+    run(stub, "child_prompt")
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[1]](*sys.argv[2:])
