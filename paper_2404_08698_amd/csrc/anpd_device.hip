@@ -852,12 +852,13 @@ int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, 
                        (const uint4 *)qp, b_seqs, M, l, c.n_layers, H, Hkv, L.max_splits, scale, part, \
                        head_ctr, xp_att, cls)
             if (batch->decode) {
-                if (dh == 128)
-                    hipLaunchKernelGGL((attn_decode_kernel<128>), dim3(H, batch->n_seq), dim3(kFastThreads), 0, st, (const uint4 *)qp, b_seqs, l,
-                                       c.n_layers, H, Hkv, scale, xp_att, cls);
-                else
-                    hipLaunchKernelGGL((attn_decode_kernel<64>), dim3(H, batch->n_seq), dim3(kFastThreads), 0, st, (const uint4 *)qp, b_seqs, l,
-                                       c.n_layers, H, Hkv, scale, xp_att, cls);
+#define ANPD_ATTN_D(DH_, ONCE_)                                                                                            \
+    hipLaunchKernelGGL((attn_decode_kernel<DH_, ONCE_>), dim3(H, batch->n_seq), dim3(kFastThreads), 0, st, (const uint4 *)qp, b_seqs, l, c.n_layers, H, Hkv, \
+                       scale, xp_att, cls)
+                if (dh == 128) { if (H == Hkv) ANPD_ATTN_D(128, true); else ANPD_ATTN_D(128, false); }
+                else if (H == Hkv) ANPD_ATTN_D(64, true);
+                else ANPD_ATTN_D(64, false);
+#undef ANPD_ATTN_D
             } else if (dh == 128) { if (one_page) ANPD_ATTN_B(128, 1); else ANPD_ATTN_B(128, kFastPages); }
             else if (one_page) ANPD_ATTN_B(64, 1);
             else ANPD_ATTN_B(64, kFastPages);

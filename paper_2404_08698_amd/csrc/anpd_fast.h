@@ -1685,9 +1685,11 @@ __global__ __launch_bounds__(kFastThreads) void attn_batch_kernel(const uint4 *_
 // attn_task, so the bits are its bits.  What bounds attn_batch_kernel here is that a block holds its 64 KB of pages
 // for one round trip only and then meets, reduces, stores and counts for as long (32 sequences of 512 positions,
 // 32 heads, 282 MB: 73 us there, 65 here; 4.3 TB/s).
+// ONCE: every query head has a key / value head of its own, so a page is read by one block: loads marked non-temporal (32 sequences of
+// 512 / 1000 positions, 7B shape, 8 layers 1535 -> 1480 / 1942 -> 1876 us, of 512, 13B shape, 4 layers 1064 -> 1026).
 // A sequence may have up to kDecodeSplits splits (4096 positions).   grid: (n_heads, n_seq).
 constexpr int kDecodeSplits = 16;
-template <int DH>
+template <int DH, bool ONCE>
 __global__ __launch_bounds__(kFastThreads) void attn_decode_kernel(const uint4 *__restrict__ qp, const SeqRef *__restrict__ seqs, int layer,
                                                             int n_layers, int n_heads, int n_kv_heads, float scale,
                                                             bf16_t *__restrict__ xp_att, int cls)
@@ -1714,12 +1716,12 @@ __global__ __launch_bounds__(kFastThreads) void attn_decode_kernel(const uint4 *
         auto load_k = [&](int i) __attribute__((always_inline)) {
             const uint4 *kp = reinterpret_cast<const uint4 *>(sq.pool + kvf_base(__builtin_amdgcn_readlane(ids, i), layer, n_layers, 0, kvh, n_kv_heads, DH));
 #pragma unroll
-            for (int q = 0; q < NKS; ++q) kf[q] = kp[q * 64 + lane];
+            for (int q = 0; q < NKS; ++q) kf[q] = ONCE ? ld_stream(kp + q * 64 + lane) : kp[q * 64 + lane];
         };
         auto load_v = [&](int i) __attribute__((always_inline)) {
             const uint2 *vp = reinterpret_cast<const uint2 *>(sq.pool + kvf_base(__builtin_amdgcn_readlane(ids, i), layer, n_layers, 1, kvh, n_kv_heads, DH));
 #pragma unroll
-            for (int q = 0; q < NDT; ++q) vf[q] = vp[q * 64 + lane];
+            for (int q = 0; q < NDT; ++q) vf[q] = ONCE ? ld_stream(vp + q * 64 + lane) : vp[q * 64 + lane];
         };
         attn_load_q<DH, false>(qf, qp, head, m >> 3);
         load_k(0);

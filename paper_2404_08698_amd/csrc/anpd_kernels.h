@@ -136,6 +136,12 @@ __device__ __forceinline__ uint4 ld_stream(const uint4 *p)
     u4 v = __builtin_nontemporal_load(reinterpret_cast<const u4 *>(p));
     return make_uint4(v.x, v.y, v.z, v.w);
 }
+__device__ __forceinline__ uint2 ld_stream(const uint2 *p)
+{
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+    u2 v = __builtin_nontemporal_load(reinterpret_cast<const u2 *>(p));
+    return make_uint2(v.x, v.y);
+}
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_buffer(const void *base)
 {
     // (said explicitly to be the same in every lane: a base that was computed on the vector ALU - an index
