@@ -52,7 +52,9 @@ enum { ANPD_VERIFY = 0, ANPD_APPEND = 1 };          /* anpd_verify modes */
  * registers; both MFMA forms give bit-identical results.  With MFMA, a window runs as ONE
  * persistent kernel per step when the model allows it: up to 16 rows for d_model <= 4096, up to
  * 8 rows for d_model <= 5120 (draft trees and several sequences: up to 8 rows, d_model <= 4096);
- * MFMA_LAUNCHES (model option) keeps the same arithmetic as one launch per operation. */
+ * MFMA_LAUNCHES (model option) keeps the same arithmetic as one launch per operation.  AUTO (bf16) takes the faster
+ * of the two: launches below d_model 2048 and for most windows of 9 rows and more.  AUTO (f32) is DOT, with the steps
+ * of small models in one launch; same arithmetic, bit-identical results. */
 enum { ANPD_GEMM_AUTO = 0, ANPD_GEMM_DOT = 1, ANPD_GEMM_MFMA = 2, ANPD_GEMM_MFMA_STREAM = 3,
        ANPD_GEMM_MFMA_LAUNCHES = 4 };
 

@@ -1321,6 +1321,21 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
     return ANPD_OK;
 }
 
+// Left to itself (AUTO) a model below d 2048 takes separate launches: what the one kernel hides in longer phases, the first weights of
+// the next one, is not worth its barriers there.  us, one kernel -> launches, 8 layers unless said: d 256, 2 layers, 1 / 8 rows at 200
+// positions 120 -> 86, 123 -> 87, tree of 7 rows 126 -> 93, 2 sequences x 4 rows 146 -> 114, 8 x 1 258 -> 222; d 512 326 -> 235; d 1024
+// 357 -> 298, 8 x 1 512 -> 445; d 1920 425 -> 392, at 1500 positions 454 -> 437 (d 2048 434 -> 408, d 3072 537 -> 584).
+bool launches_preferred(const anpd_model_cfg &c) { return c.gemm_path == ANPD_GEMM_AUTO && c.d_model < 2048; }
+// Windows of 9 to 16 rows, whose GEMMs have a tile per wave as separate launches: the one kernel is the faster form only where few
+// key / value heads leave attention's launch little to do.  us, 8 layers, 9 rows at 64 / 512 / 2048 / 4000 positions, one kernel ->
+// launches: 7B shape 892 -> 846, 893 -> 858, 998 -> 917, 1038 -> 1018; d 3072 691 -> 621, 687 -> 624, 799 -> 686, 824 -> 727; d 2048
+// 547 -> 449, 550 -> 451, 605 -> 490, 616 -> 522; ChatGLM3 shape 961 -> 951, 948 -> 963, 1043 -> 1010, 1052 -> 1045 (16 rows 970 -> 969,
+// 959 -> 982, 1054 -> 1027, 1066 -> 1067).
+bool one_kernel_rows16(const anpd_model &m, int positions)
+{
+    return m.cfg.gemm_path != ANPD_GEMM_AUTO || (m.cfg.d_model > 3072 && kv_heads_of(m.cfg) < m.cfg.n_heads && n_splits_of(positions) <= kSmallSplits);
+}
+
 // After the stream has been synchronised: was there a launch of the small model's kernel of which no block ran where it was to run, so
 // that nothing was done?  Then steps are separate launches from here on.
 bool small_missed(anpd_model *m)
@@ -1456,7 +1471,7 @@ int32_t anpd_model_create(const anpd_model_cfg *cfg, const anpd_weights *w, void
     }
     m->mega_rows16 = false;
     m->mega_kc = (cfg->d_model + 31) / 32 <= 2 * kChunk * kFastWaves ? kChunk : 10;
-    if (e == hipSuccess && m->mfma && cfg->gemm_path != ANPD_GEMM_MFMA_LAUNCHES && (cfg->d_model + 31) / 32 <= 2 * 10 * kFastWaves) {
+    if (e == hipSuccess && m->mfma && cfg->gemm_path != ANPD_GEMM_MFMA_LAUNCHES && !launches_preferred(*cfg) && (cfg->d_model + 31) / 32 <= 2 * 10 * kFastWaves) {
         // the persistent step needs every block resident at once: one block per compute unit
         int per_cu = 0;
         hipError_t oe;
@@ -1742,7 +1757,7 @@ int32_t anpd_verify(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, int32
     if (rc != ANPD_OK) return rc;
     // The window goes to the kernels by value, and they write the result (and the persistent kernel its error
     // flag) into the pinned buffer themselves.
-    const bool one_kernel = m->mega && (n_window <= 8 || (n_window <= 16 && m->mega_rows16));
+    const bool one_kernel = m->mega && (n_window <= 8 || (n_window <= 16 && m->mega_rows16 && one_kernel_rows16(*m, kv->len + n_window)));
     const int32_t *res = m->pin + 32;
     LogitsTo logits = {out_logits, (size_t)n_window * m->cfg.vocab, nullptr};
     if (one_kernel) rc = run_step_mega(m, kv, window, n_window, mode, out_logits ? logits.find(m) : nullptr, st);
