@@ -847,10 +847,11 @@ int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, 
         mark(m, ANPD_PROF_GEMM_QKV, st);
         // (n_splits <= kSmallSplits: every split of the step has one page per wave: the leaner instantiation)
         if (batch) {
-#define ANPD_ATTN_B(DH_, MAXP_)                                                                                            \
-    hipLaunchKernelGGL((attn_batch_kernel<DH_, MAXP_>), dim3(H, n_splits, batch->n_seq), dim3(kFastThreads), 0, st,      \
+#define ANPD_ATTN_B(DH_, MAXP_, ONCE_)                                                                                     \
+    hipLaunchKernelGGL((attn_batch_kernel<DH_, MAXP_, ONCE_>), dim3(H, n_splits, batch->n_seq), dim3(kFastThreads), 0, st, \
                        (const uint4 *)qp, b_seqs, M, l, c.n_layers, H, Hkv, L.max_splits, scale, part, \
                        head_ctr, xp_att, cls)
+#define ANPD_ATTN_O(DH_, MAXP_) do { if (H == Hkv) ANPD_ATTN_B(DH_, MAXP_, true); else ANPD_ATTN_B(DH_, MAXP_, false); } while (0)
             if (batch->decode) {
 #define ANPD_ATTN_D(DH_, ONCE_)                                                                                            \
     hipLaunchKernelGGL((attn_decode_kernel<DH_, ONCE_>), dim3(H, batch->n_seq), dim3(kFastThreads), 0, st, (const uint4 *)qp, b_seqs, l, c.n_layers, H, Hkv, \
@@ -859,9 +860,10 @@ int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, 
                 else if (H == Hkv) ANPD_ATTN_D(64, true);
                 else ANPD_ATTN_D(64, false);
 #undef ANPD_ATTN_D
-            } else if (dh == 128) { if (one_page) ANPD_ATTN_B(128, 1); else ANPD_ATTN_B(128, kFastPages); }
-            else if (one_page) ANPD_ATTN_B(64, 1);
-            else ANPD_ATTN_B(64, kFastPages);
+            } else if (dh == 128) { if (one_page) ANPD_ATTN_O(128, 1); else ANPD_ATTN_O(128, kFastPages); }
+            else if (one_page) ANPD_ATTN_O(64, 1);
+            else ANPD_ATTN_O(64, kFastPages);
+#undef ANPD_ATTN_O
 #undef ANPD_ATTN_B
         } else {
 #define ANPD_ATTN(DH_, TREE_, MAXP_)                                                                                       \

@@ -1225,7 +1225,7 @@ __device__ __forceinline__ AttnPageIds attn_page_ids(int split, int L, int M, co
     }
     return ids;
 }
-template <int DH, bool COH>
+template <int DH, bool COH, bool ONCE = false>
 __device__ __forceinline__ void attn_load_kv(AttnKV<DH> &kv, int head, int split, int L, int M,
                                              const bf16_t *__restrict__ pool, const int32_t *__restrict__ page_table,
                                              int layer, int n_layers, int n_heads, bool only_old, int j = 0,
@@ -1245,9 +1245,9 @@ __device__ __forceinline__ void attn_load_kv(AttnKV<DH> &kv, int head, int split
         const uint4 *kp = reinterpret_cast<const uint4 *>(pool + kvf_base(page, layer, n_layers, 0, head, n_heads, DH));
         const uint2 *vp = reinterpret_cast<const uint2 *>(pool + kvf_base(page, layer, n_layers, 1, head, n_heads, DH));
 #pragma unroll
-        for (int i = 0; i < NKS; ++i) kv.kf[i] = ld16_at<COH>(kp, (uint32_t)(i * 64 + lane));
+        for (int i = 0; i < NKS; ++i) kv.kf[i] = ONCE ? ld_stream(kp + i * 64 + lane) : ld16_at<COH>(kp, (uint32_t)(i * 64 + lane));
 #pragma unroll
-        for (int i = 0; i < NDT; ++i) kv.vf[i] = ld8_at<COH>(vp, (uint32_t)(i * 64 + lane));
+        for (int i = 0; i < NDT; ++i) kv.vf[i] = ONCE ? ld_stream(vp + i * 64 + lane) : ld8_at<COH>(vp, (uint32_t)(i * 64 + lane));
         kv.loaded = true;
     }
 }
@@ -1329,7 +1329,7 @@ struct AttnBatch {
 // split_begin(kSmallSplits), so the code for further pages - a second set of page registers among it - is left
 // out: the separate kernels then fit two blocks on a compute unit instead of one).
 template <int DH, bool COH = false, typename AfterLoads = NoPrefetch, int MODE = ATTN_CHAIN, typename AfterValues = NoPrefetch,
-          int MAXP = kFastPages>
+          int MAXP = kFastPages, bool ONCE = false>
 __device__ __forceinline__ void attn_task(AttnShared<DH> &sh, AttnKV<DH> &kv, int head, int split, int L,
                                           const uint4 *__restrict__ qp, const bf16_t *__restrict__ pool,
                                           const int32_t *__restrict__ page_table, int M, int layer, int n_layers, int n_heads,
@@ -1357,7 +1357,7 @@ __device__ __forceinline__ void attn_task(AttnShared<DH> &sh, AttnKV<DH> &kv, in
     AttnKV<DH> kvb;
     kvb.loaded = false;
     auto request = [&](AttnKV<DH> &dst, int j) __attribute__((always_inline)) {
-        attn_load_kv<DH, COH>(dst, kv_head, split, L, n_new, pool, page_table, layer, n_layers, n_kv_heads, false, j);
+        attn_load_kv<DH, COH, ONCE>(dst, kv_head, split, L, n_new, pool, page_table, layer, n_layers, n_kv_heads, false, j);
     };
     // The separate kernels keep the query rows of the group that they work on in LDS, where all waves read them for every page
     // (16 registers less per lane at head dim 128), and there before the first page is requested.  (Put there behind the
@@ -1656,8 +1656,9 @@ __global__ __launch_bounds__(kFastThreads, 6) void attn_fast_kernel(const uint4 
 
 // Several sequences' windows in one step: block (head, split, sequence) works on that sequence's rows
 // against that sequence's cache; the last block of a (head, sequence) merges them.
+// ONCE: as in attn_decode_kernel (7B shape, 8 layers, 16 sequences x 2 rows of 512 positions 1296 -> 1270 us, 8 x 4 of 1000 1282 -> 1265).
 // head_counter: [sequence][head].   grid: (n_heads, largest number of splits of any sequence, n_seq).
-template <int DH, int MAXP = kFastPages>
+template <int DH, int MAXP, bool ONCE>
 __global__ __launch_bounds__(kFastThreads) void attn_batch_kernel(const uint4 *__restrict__ qp, const SeqRef *__restrict__ seqs,
                                                            int M, int layer, int n_layers, int n_heads, int n_kv_heads, int max_splits,
                                                            float scale, float *__restrict__ part,
@@ -1672,7 +1673,7 @@ __global__ __launch_bounds__(kFastThreads) void attn_batch_kernel(const uint4 *_
     AttnKV<DH> kv;
     kv.loaded = false;
     AttnBatch bt = {sq.row0, sq.n_rows, n_splits_of(L + sq.n_rows), nullptr, nullptr};
-    attn_task<DH, false, NoPrefetch, ATTN_BATCH, NoPrefetch, MAXP>(sh, kv, blockIdx.x, blockIdx.y, L, qp, sq.pool, sq.page_table, M, layer, n_layers,
+    attn_task<DH, false, NoPrefetch, ATTN_BATCH, NoPrefetch, MAXP, ONCE>(sh, kv, blockIdx.x, blockIdx.y, L, qp, sq.pool, sq.page_table, M, layer, n_layers,
                                                  n_heads, n_kv_heads, max_splits, scale, part,
                                                  head_counter + (size_t)blockIdx.z * n_heads * kCounterStride, xp_att, cls,
                                                  NoPrefetch(), nullptr, &bt, NoPrefetch(), 1, nullptr, false, false, q_rows, false, false);
