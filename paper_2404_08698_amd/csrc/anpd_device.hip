@@ -1353,7 +1353,8 @@ bool barrier_gave_up(anpd_model *m, hipStream_t st)
 {
     if (m->pin[100] == 0) return false;
     m->pin[100] = 0;
-    if (!m->mfma) {
+    if (!m->mfma) {   // (the one launch of a small model: nothing else on this path waits)
+        if (m->lay.small_stride == 0) return true;
         (void)hipMemsetAsync(m->ws + m->lay.small_ctr, 0, 2 * kSmallLine * sizeof(uint32_t), st);
         (void)hipMemsetAsync(m->ws + m->lay.gen_ctr, 0, (size_t)m->cfg.n_heads * ((m->lay.gen_part_rows + 15) / 16) * 64 * sizeof(uint32_t), st);
         (void)hipStreamSynchronize(st);
