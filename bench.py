@@ -279,8 +279,8 @@ def main() -> int:
     # cycle's, whatever --steps is.
     from paper_2404_08698_amd import ablation
     adaptive = args.workload == "long7b"
-    # The adaptive policy's longest draft: 16 rows is the widest window the one-kernel step holds, and a 17th row
-    # costs half a step more (separate launches), which one more draft token never earns back.
+    # The adaptive policy's longest draft: chosen when 16 rows was the widest window that AUTO ran in one kernel and a 17th
+    # row cost half a step more than one more draft token earns; kept, so that the workload's figures compare.
     K_adapt = min(K, 15)
     stream = synth.markov_stream(shape.vocab, wl["prompt"] + 48 * SCRIPT_CYCLE * (K + 1), wl["p_copy"], wl["span"][0], wl["span"][1],
                                  wl["seed"])
