@@ -590,6 +590,9 @@ __device__ __forceinline__ void gemm_gen_block(const GenArgs &a, const int32_t *
             *reinterpret_cast<f32x4 *>(red[wave][n][t][lane]) = s;
         }
     }
+    // (the one launch: the item's flag stands for the rows that every wave has stored above; the waves that set it wait for their own stores
+    // only.  By now a wave's loads have long returned: only the first block waits at all)
+    if (ONE && FIRST) wait_stores();
     wait.publish();
     __syncthreads();
     if (wave >= RT) return;

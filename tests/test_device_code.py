@@ -111,3 +111,55 @@ def test_split_gemm_requests_its_operand_around_the_first_weights(kernels):
     barrier = next(i for i, c in enumerate(code) if c[1] == "s_barrier")
     loads = ["x" if c[2].endswith("lds") else "w" for c in code[:barrier] if c[1].startswith("buffer_load")]
     assert "".join(loads) == "x" * 8 + "w" * 16 + "x" * 8
+
+
+def _unordered(code):
+    """Pairs (store, barrier): the second half of a row's eight columns of the residual stream is stored and the block meets behind its
+    sums (16 bytes at a time, to LDS), on some path through the kernel, without a wait for all stores behind the products.  (One in front
+    of them is the compiler's, for the operands it is about to use, and may leave out what came later.)"""
+    index = {address: i for i, (address, _, _) in enumerate(code)}
+    seen, todo, bad = set(), [(0, None, False, False)], set()
+    while todo:
+        i, store, sums, waited = todo.pop()
+        while i < len(code) and (i, store, sums, waited) not in seen:
+            seen.add((i, store, sums, waited))
+            address, name, operands = code[i]
+            if name == "global_store_dwordx4" and operands.endswith("off offset:16"):
+                store, sums, waited = hex(address), False, False
+            elif name == "ds_write_b128":
+                sums = True
+            elif name == "s_waitcnt" and "vmcnt(0)" in operands:
+                waited = True
+            elif name.startswith("v_mfma"):
+                waited = False
+            elif name == "s_barrier" and sums:
+                if store and not waited:
+                    bad.add((store, hex(address)))
+                store = None
+            if name == "s_endpgm":
+                break
+            if name.startswith(("s_cbranch", "s_branch")):
+                jump = int(operands.split()[0])
+                todo.append((index[address + 4 + 4 * (jump - (0x10000 if jump >= 0x8000 else 0))], store, sums, waited))
+                if name == "s_branch":
+                    break
+            i += 1
+    return sorted(bad)
+
+
+def test_small_step_meets_behind_the_rows_that_it_stores(kernels):
+    """The flag of the first QKV item, set by one or two of its waves, stands for the residual stream that all eight have stored."""
+    mine = {k: v for k, v in kernels.items() if "small_step_kernel" in k}
+    assert len(mine) == 4
+    for k, code in mine.items():
+        assert sum(n == "global_store_dwordx4" and o.endswith("off offset:16") for _, n, o in code) >= 1, k
+        assert not _unordered(code), k
+
+
+def test_a_store_that_a_barrier_does_not_wait_for_is_seen():
+    store, sums, wait, meet = (0, "global_store_dwordx4", "v[8:9], v[4:7], off offset:16"), (8, "ds_write_b128", "v2, v[4:7]"), (16, "s_waitcnt", "vmcnt(0)"), (20, "s_barrier", "")
+    assert not _unordered([store, sums, wait, meet, (24, "s_endpgm", "")])
+    assert not _unordered([store, wait, sums, meet, (24, "s_endpgm", "")])
+    assert _unordered([store, sums, (16, "s_waitcnt", "lgkmcnt(0)"), meet, (24, "s_endpgm", "")])
+    assert _unordered([store, wait, (18, "v_mfma_f32_16x16x4_f32", "v[0:3], v1, v2, v[0:3]"), sums, meet, (24, "s_endpgm", "")])
+    assert _unordered([store, sums, (12, "s_cbranch_execz", "1"), wait, meet, (24, "s_endpgm", "")])
