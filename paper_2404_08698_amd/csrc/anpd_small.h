@@ -108,7 +108,7 @@ __global__ __launch_bounds__(512, 2) void small_step_kernel(SmallArgs /* read wh
     const bool merged = g->splits <= kSmallMerge;
     auto draw = [&]() __attribute__((always_inline)) {   // (lane 0's)
         int t = 0;
-        if (lane == 0) t = (int)__hip_atomic_fetch_add(g->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (lane == 0) t = (int)__hip_atomic_fetch_add(g->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return t;
     };
     if (wave == 7) {
