@@ -740,12 +740,17 @@ int32_t run_step_small(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int M,
     g.tok = step_tokens(tokens, M);
     m->ev_used = 0;
     mark(m, -1, st);
-#define ANPD_SMALL(DH_, RT_) hipLaunchKernelGGL((small_step_kernel<DH_, RT_>), dim3(kSmallBlocks), dim3(512), 0, st, g)
-    if (c.head_dim == 128) { if (rt == 2) ANPD_SMALL(128, 2); else ANPD_SMALL(128, 1); }
-    else if (rt == 2) ANPD_SMALL(64, 2);
-    else ANPD_SMALL(64, 1);
-#undef ANPD_SMALL
+    const void *kernel = c.head_dim == 128 ? (rt == 2 ? (const void *)small_step_kernel<128, 2> : (const void *)small_step_kernel<128, 1>)
+                                           : (rt == 2 ? (const void *)small_step_kernel<64, 2> : (const void *)small_step_kernel<64, 1>);
+    void *args[] = {&g};
+    // (errors left behind by someone else are reported with nothing launched: behind the launch they would be taken for its own)
     HIP_TRY(hipGetLastError());
+    const hipError_t e = hipLaunchKernel(kernel, dim3(kSmallBlocks), dim3(512), args, 0, st);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(ANPD_E_HIP, "the one launch of a small model's step: %s", hipGetErrorString(e));
+    }
+    // (whatever is said later: it runs, and counts itself)
     m->small_launch = launch;
     m->small_launches += 1;
     mark(m, ANPD_PROF_STEP, st);

@@ -18,6 +18,7 @@ std::vector<Launch> g_launches;
 struct { dim3 grid, block; size_t shared; hipStream_t stream; } g_config;
 int g_fail_at = 0, g_syncs = 0;
 hipError_t g_last = hipSuccess;
+int *g_pin = nullptr;     // a model's pinned memory, where the one launch of a small model counts itself
 
 std::map<char *, Range>::iterator range_of(const void *p)
 {
@@ -42,6 +43,8 @@ hipError_t launch(const void *f, dim3 grid, dim3 block, void **args)
     g_launches.push_back({g_names[f], grid, block, {*(void **)args[0]}});
     // (the one kernel whose answer the library looks at: how many blocks run on each XCD, here all that there are on the third)
     if (std::getenv("STUB_XCD_BLOCKS") && g_names[f].find("xcd_census") != std::string::npos) (*(unsigned **)args[0])[2] = std::atoi(std::getenv("STUB_XCD_BLOCKS"));
+    // (... and the one that counts itself there, if it is to run here)
+    if (std::getenv("STUB_SMALL_RUNS") && g_names[f].find("small_step") != std::string::npos) ++g_pin[102];
     return hipSuccess;
 }
 }  // namespace
@@ -51,6 +54,7 @@ extern "C" {
 void stub_memory(void *p, size_t n, int device) { g_memory[(char *)p] = {n, device}; }
 void stub_fail_launch(int nth) { g_fail_at = nth; }       // the nth launch from here on fails (0: none)
 void stub_forget(void) { g_launches.clear(); g_syncs = 0; }
+void stub_leave_error(void) { g_last = hipErrorInvalidValue; }   // as a call elsewhere in the thread leaves it
 int stub_launches(void) { return (int)g_launches.size(); }
 int stub_syncs(void) { return g_syncs; }
 const char *stub_name(int i) { return g_launches[(size_t)i].name.c_str(); }
@@ -80,7 +84,12 @@ hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 256; 
 hipError_t hipGetSymbolAddress(void **, const void *) { return error(hipErrorInvalidSymbol); }
 const char *hipGetErrorString(hipError_t) { return "stub error"; }
 hipError_t hipGetLastError(void) { hipError_t e = g_last; g_last = hipSuccess; return e; }
-hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = std::calloc(1, n); return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned)
+{
+    *p = std::calloc(1, n);
+    if (n == 1024 * sizeof(int)) g_pin = (int *)*p;
+    return hipSuccess;
+}
 hipError_t hipHostFree(void *p) { std::free(p); return hipSuccess; }
 hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned) { *d = h; return hipSuccess; }
 hipError_t hipMemset(void *p, int v, size_t n) { std::memset(p, v, n); return hipSuccess; }

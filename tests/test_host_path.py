@@ -86,6 +86,11 @@ class Host:
         acc, nxt = C.c_int32(), C.c_int32()
         return self.L.anpd_verify(self.model, kv, (C.c_int32 * n)(*range(n)), n, self.B.APPEND, C.byref(acc), C.byref(nxt), None, out, None)
 
+    def verify_tree(self, kv, n, out):
+        acc, nxt, row = C.c_int32(), C.c_int32(), C.c_int32 * n
+        return self.L.anpd_verify_tree(self.model, kv, row(*range(n)), row(-1, *[i // 2 for i in range(n - 1)]), n, C.byref(acc), C.byref(nxt),
+                                       None, None, out, None)
+
     def prefill(self, kv, n, out=None):
         nxt = C.c_int32()
         nb = self.L.anpd_prefill_workspace_bytes(self.model, n)

@@ -1,5 +1,6 @@
 """Host side of a small fp32 model's step in one launch, on the stand-in for the HIP runtime: which calls take it, and what happens
-when no block ran on the XCD that it was meant for (on the stand-in none does): the step is separate launches, then and later."""
+when no block ran on the XCD that it was meant for (on the stand-in none does, unless told to): the step is separate launches, then
+and later; and that no error is lost or taken for another's."""
 import os
 import sys
 
@@ -9,12 +10,12 @@ sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 from test_host_path import Host, in_child, stub  # noqa: E402,F401
 
 
-def run(stub, name, *args, blocks=32):
+def run(stub, name, *args, blocks=32, env=()):
     os.environ["STUB_XCD_BLOCKS"] = str(blocks)
     try:
         import subprocess
         r = subprocess.run([sys.executable, os.path.abspath(__file__), name, *map(str, args)], capture_output=True, text=True, timeout=120,
-                           env=dict(os.environ, ANPD_HIP_STUB=stub, PYTHONPATH=os.path.dirname(os.path.dirname(os.path.abspath(__file__)))))
+                           env=dict(os.environ, ANPD_HIP_STUB=stub, PYTHONPATH=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), **dict(env)))
     finally:
         del os.environ["STUB_XCD_BLOCKS"]
     assert r.returncode == 0, r.stdout + r.stderr
@@ -59,6 +60,35 @@ def child_prompt():
 
 def test_a_prompt_that_was_not_done_starts_over(stub):
     run(stub, "child_prompt")
+
+
+def calls_in_one_launch(h, kv, out):
+    return ((lambda: h.verify(kv, 5, out)), (lambda: h.verify_tree(kv, 5, out)), (lambda: h.prefill(kv, 20, out)))
+
+
+def only_small(h):
+    steps = [n for n in h.names() if "upload" not in n]
+    return len(steps) == 1 and "small_step_kernel" in steps[0]
+
+
+def child_pending_error():
+    """An error that a call elsewhere left behind is reported and nothing is launched; the next call is a step like any other."""
+    h = Host(dtype="f32", ffn=688, vocab=1024, layers=2, max_positions=300)
+    kv = h.cache(300, 20)
+    for call in calls_in_one_launch(h, kv, None):
+        for _ in range(3):
+            h.stub.stub_leave_error()
+            h.stub.stub_forget()
+            assert call() == h.B.E_HIP and not any("small_step_kernel" in n for n in h.names()), h.names()
+            h.ok(h.L.anpd_kv_truncate(kv, 20, None))
+            h.stub.stub_forget()
+            h.ok(call())
+            assert only_small(h), h.names()
+            h.ok(h.L.anpd_kv_truncate(kv, 20, None))
+
+
+def test_an_error_from_elsewhere_does_not_cost_the_count_of_launches(stub):
+    run(stub, "child_pending_error", env={"STUB_SMALL_RUNS": "1"})
 
 
 if __name__ == "__main__":
