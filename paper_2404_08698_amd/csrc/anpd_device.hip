@@ -686,6 +686,9 @@ int32_t run_step_small(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int M,
     *ran = false;
     const int splits = (kv->len + M + kAttnSplit - 1) / kAttnSplit, rt = M > 16 ? 2 : 1;
     if (m->xcd < 0 || !small_step(c, M, splits) || M > L.gen_part_rows || piece == PIECE_CACHE || ((uintptr_t)m->embed & 15) != 0) return ANPD_OK;
+    // (errors of launches in front, or left behind by someone else, are reported with nothing launched: the lookup of the logits' buffer
+    // would clear them, and behind the launch they would be taken for its own)
+    HIP_TRY(hipGetLastError());
     char *ws = m->ws;
     const int d = c.d_model, F = c.d_ffn, V = c.vocab, H = c.n_heads, Hkv = kv_heads_of(c);
     SmallArgs g;
@@ -743,8 +746,6 @@ int32_t run_step_small(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int M,
     const void *kernel = c.head_dim == 128 ? (rt == 2 ? (const void *)small_step_kernel<128, 2> : (const void *)small_step_kernel<128, 1>)
                                            : (rt == 2 ? (const void *)small_step_kernel<64, 2> : (const void *)small_step_kernel<64, 1>);
     void *args[] = {&g};
-    // (errors left behind by someone else are reported with nothing launched: behind the launch they would be taken for its own)
-    HIP_TRY(hipGetLastError());
     const hipError_t e = hipLaunchKernel(kernel, dim3(kSmallBlocks), dim3(512), args, 0, st);
     if (e != hipSuccess) {
         (void)hipGetLastError();

@@ -91,5 +91,31 @@ def test_an_error_from_elsewhere_does_not_cost_the_count_of_launches(stub):
     run(stub, "child_pending_error", env={"STUB_SMALL_RUNS": "1"})
 
 
+def child_lost_launch():
+    """Every launch of a call fails once, while the logits go to memory that the runtime does not know (the query of it fails, too, and
+    clears what was there): the call says so, and the next one is a step like any other."""
+    import ctypes as C
+    h = Host(dtype="f32", ffn=688, vocab=1024, layers=2, max_positions=300)
+    kv = h.cache(300, 20)
+    unknown = C.create_string_buffer(20 * 1024 * 4 + 16)
+    for call in calls_in_one_launch(h, kv, (C.addressof(unknown) + 15) // 16 * 16):
+        h.stub.stub_forget()
+        h.ok(call())
+        assert only_small(h), h.names()
+        for nth in range(1, h.stub.stub_launches() + 1):
+            h.ok(h.L.anpd_kv_truncate(kv, 20, None))
+            h.stub.stub_fail_launch(nth)
+            assert call() == h.B.E_HIP, (nth, h.names())
+            h.ok(h.L.anpd_kv_truncate(kv, 20, None))
+            h.stub.stub_forget()
+            h.ok(call())
+            assert only_small(h), (nth, h.names())
+        h.ok(h.L.anpd_kv_truncate(kv, 20, None))
+
+
+def test_a_launch_that_fails_is_reported_by_the_call_it_belongs_to(stub):
+    run(stub, "child_lost_launch", env={"STUB_SMALL_RUNS": "1"})
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](*sys.argv[2:])
