@@ -1333,7 +1333,8 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
 // the next one, is not worth its barriers there.  us, one kernel -> launches, 8 layers unless said: d 256, 2 layers, 1 / 8 rows at 200
 // positions 120 -> 86, 123 -> 87, tree of 7 rows 126 -> 93, 2 sequences x 4 rows 146 -> 114, 8 x 1 258 -> 222; d 512 326 -> 235; d 1024
 // 357 -> 298, 8 x 1 512 -> 445; d 1920 425 -> 392, at 1500 positions 454 -> 437 (d 2048 434 -> 408, d 3072 537 -> 584).
-bool launches_preferred(const anpd_model_cfg &c) { return c.gemm_path == ANPD_GEMM_AUTO && c.d_model < 2048; }
+bool one_kernel_asked(const anpd_model &m) { return m.cfg.gemm_path != ANPD_GEMM_AUTO || m.trace; }   // by name, or by a trace of its barriers
+bool one_kernel_taken(const anpd_model &m) { return m.mega && (one_kernel_asked(m) || m.cfg.d_model >= 2048); }
 // Windows of 9 to 16 rows, whose GEMMs have a tile per wave as separate launches: the one kernel is the faster form only where few
 // key / value heads leave attention's launch little to do.  us, 8 layers, 9 rows at 64 / 512 / 2048 / 4000 positions, one kernel ->
 // launches: 7B shape 892 -> 846, 893 -> 858, 998 -> 917, 1038 -> 1018; d 3072 691 -> 621, 687 -> 624, 799 -> 686, 824 -> 727; d 2048
@@ -1341,7 +1342,7 @@ bool launches_preferred(const anpd_model_cfg &c) { return c.gemm_path == ANPD_GE
 // 959 -> 982, 1054 -> 1027, 1066 -> 1067).
 bool one_kernel_rows16(const anpd_model &m, int positions)
 {
-    return m.cfg.gemm_path != ANPD_GEMM_AUTO || (m.cfg.d_model > 3072 && kv_heads_of(m.cfg) < m.cfg.n_heads && n_splits_of(positions) <= kSmallSplits);
+    return one_kernel_asked(m) || (m.cfg.d_model > 3072 && kv_heads_of(m.cfg) < m.cfg.n_heads && n_splits_of(positions) <= kSmallSplits);
 }
 
 // After the stream has been synchronised: was there a launch of the small model's kernel of which no block ran where it was to run, so
@@ -1480,7 +1481,7 @@ int32_t anpd_model_create(const anpd_model_cfg *cfg, const anpd_weights *w, void
     }
     m->mega_rows16 = false;
     m->mega_kc = (cfg->d_model + 31) / 32 <= 2 * kChunk * kFastWaves ? kChunk : 10;
-    if (e == hipSuccess && m->mfma && cfg->gemm_path != ANPD_GEMM_MFMA_LAUNCHES && !launches_preferred(*cfg) && (cfg->d_model + 31) / 32 <= 2 * 10 * kFastWaves) {
+    if (e == hipSuccess && m->mfma && cfg->gemm_path != ANPD_GEMM_MFMA_LAUNCHES && (cfg->d_model + 31) / 32 <= 2 * 10 * kFastWaves) {
         // the persistent step needs every block resident at once: one block per compute unit
         int per_cu = 0;
         hipError_t oe;
@@ -1766,7 +1767,7 @@ int32_t anpd_verify(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, int32
     if (rc != ANPD_OK) return rc;
     // The window goes to the kernels by value, and they write the result (and the persistent kernel its error
     // flag) into the pinned buffer themselves.
-    const bool one_kernel = m->mega && (n_window <= 8 || (n_window <= 16 && m->mega_rows16 && one_kernel_rows16(*m, kv->len + n_window)));
+    const bool one_kernel = one_kernel_taken(*m) && (n_window <= 8 || (n_window <= 16 && m->mega_rows16 && one_kernel_rows16(*m, kv->len + n_window)));
     const int32_t *res = m->pin + 32;
     LogitsTo logits = {out_logits, (size_t)n_window * m->cfg.vocab, nullptr};
     if (one_kernel) rc = run_step_mega(m, kv, window, n_window, mode, out_logits ? logits.find(m) : nullptr, st);
@@ -1823,7 +1824,7 @@ int32_t anpd_verify_tree(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, 
     LogitsTo logits = {out_logits, (size_t)n_window * m->cfg.vocab, nullptr};
     // windows of up to 8 rows: the one-kernel step in its draft-tree form (tree by value as well); otherwise one
     // launch per operation, the tree written to device memory by a kernel in front
-    const bool one_kernel = m->mega && m->mega_tree && n_window <= 8;
+    const bool one_kernel = one_kernel_taken(*m) && m->mega_tree && n_window <= 8;
     if (one_kernel) {
         rc = run_step_mega(m, kv, window, n_window, ANPD_APPEND, out_logits ? logits.find(m) : nullptr, st, tp);
     } else {
@@ -1920,7 +1921,7 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
     bl.decode = total == n_seq && bl.grid_splits <= kDecodeSplits && filled && even;
     // At most 8 rows in all (decoding batches, short windows): the persistent kernel takes the sequences by
     // value and writes the results into the pinned buffer itself; otherwise copies and the fused launches.
-    const bool one_kernel = m->mega && m->mega_batch && total <= 8;
+    const bool one_kernel = one_kernel_taken(*m) && m->mega_batch && total <= 8;
     const int32_t *res = m->pin + 256;
     LogitsTo logits = {out_logits, (size_t)total * m->cfg.vocab, nullptr};
     int32_t rc;

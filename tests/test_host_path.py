@@ -282,5 +282,32 @@ def test_the_batches_meant_for_the_many_sequences_kernel_take_it(stub):
             in_child(stub, "child_route", ",".join(str(x + step) for x in lengths), shape.n_heads, shape.kv_heads, shape.head_dim, "attn_decode")
 
 
+def child_trace(d, heads, rows):
+    """While its barriers are traced a step is the one kernel, also where AUTO takes launches; and none is refused that can be one."""
+    d, rows = int(d), int(rows)
+    h = Host(d=d, heads=int(heads), dh=d // int(heads), max_positions=128)
+    kv, kv2 = h.cache(128, 20), h.cache(128, 30)
+    one, half = C.POINTER(C.c_int32), (C.c_int32 * 2)(0, 1)
+
+    def batch():
+        return h.L.anpd_verify_batch(h.model, (C.c_void_p * 2)(kv, kv2), 2, (one * 2)(C.cast(half, one), C.cast(half, one)), (C.c_int32 * 2)(2, 2),
+                                     h.B.VERIFY, (C.c_int32 * 2)(), (C.c_int32 * 2)(), None, None)
+    calls = [lambda: h.verify(kv, rows, None)] + ([lambda: h.verify_tree(kv, rows, None), batch] if rows <= 8 else [])
+    grid = h.L.anpd_model_trace(h.model, None, 0)
+    assert grid == 256
+    buffer = h.memory(grid * 1024 * 8)
+    for traced in (0, 1, 0):
+        h.ok(h.L.anpd_model_trace(h.model, buffer if traced else None, grid * 1024 * 8 if traced else 0))
+        for call in calls:
+            h.stub.stub_forget()
+            h.ok(call())
+            assert ["verify_mega" in n for n in h.names()].count(True) == traced, (traced, h.names())
+
+
+@pytest.mark.parametrize("d,heads,rows", [(256, 4, 5), (256, 4, 16), (1920, 30, 8), (2048, 16, 9)])
+def test_a_traced_step_is_the_one_kernel(stub, d, heads, rows):
+    in_child(stub, "child_trace", d, heads, rows)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](*sys.argv[2:])
