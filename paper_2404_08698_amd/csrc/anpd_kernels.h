@@ -955,7 +955,9 @@ struct AcceptShared {
     bool last;
 };
 // window: the rows' tokens.  Returns whether this block applied the rules.
-template <int KIND, int THREADS>
+// ONE: the logits come from blocks of the same launch on the same XCD (as in gemm_gen_block).  The caller's buffer may share its first and
+// last line with something that was read before they were written, weights say, which this block's vector cache may still hold.
+template <int KIND, int THREADS, bool ONE = false>
 __device__ __forceinline__ bool argmax_accept_block(const float *__restrict__ logits, int V, int M, const int32_t *window, int mode, const AcceptArgs &a,
                                                     int r, AcceptShared &sh)
 {
@@ -970,7 +972,7 @@ __device__ __forceinline__ bool argmax_accept_block(const float *__restrict__ lo
         f32x4 v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (i0 + THREADS * u < V / 4) v[u] = row[i0 + THREADS * u];
+            if (i0 + THREADS * u < V / 4) v[u] = ONE ? __builtin_bit_cast(f32x4, ld16_near(row, (uint32_t)(i0 + THREADS * u) * 16u)) : row[i0 + THREADS * u];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (i0 + THREADS * u >= V / 4) break;

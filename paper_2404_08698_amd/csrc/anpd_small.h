@@ -213,8 +213,8 @@ __global__ __launch_bounds__(512, 2) void small_step_kernel(SmallArgs /* read wh
             const AcceptArgs ac = {g->accept.result, g->accept.host_result, g->accept.len_ptr, g->accept.counter, g->accept.before, g->accept.parent, g->accept.depth,
                                    nullptr, 0, nullptr, g->accept.launches, g->accept.host_launches};
             const int32_t *tok = (const int32_t *)g->tok.t + g->out0;
-            const bool rules = g->tree ? argmax_accept_block<ACCEPT_TREE, 512>(g->logits, g->vocab, g->n_out, tok, g->mode, ac, i, sh.accept)
-                                       : argmax_accept_block<ACCEPT_CHAIN, 512>(g->logits, g->vocab, g->n_out, tok, g->mode, ac, i, sh.accept);
+            const bool rules = g->tree ? argmax_accept_block<ACCEPT_TREE, 512, true>(g->logits, g->vocab, g->n_out, tok, g->mode, ac, i, sh.accept)
+                                       : argmax_accept_block<ACCEPT_CHAIN, 512, true>(g->logits, g->vocab, g->n_out, tok, g->mode, ac, i, sh.accept);
             if (rules && g->tree) {
                 // the accepted path's keys and values to consecutive slots (kv_compact_kernel's rule)
                 wait_stores();

@@ -94,3 +94,31 @@ def test_trees_and_short_prompts(pairs):
     assert a[0] == b[0] and a[1] == b[1] and torch.equal(a[2], b[2]) and a[3] == b[3] == length + 4
     for x, y in zip(a[4], b[4]):
         assert torch.equal(x[0], y[0]) and torch.equal(x[1], y[1])
+
+
+# logits between weights, sharing their first and last line with them (a caller that packs its buffers to 64 bytes): the predictions are
+# those of the logits that are there, also where a block that looks for them has read those weights before
+def test_logits_that_share_lines_with_weights(pairs):
+    shape, rows = SHAPES["tiny"], 5
+    w = {k: list(v) if isinstance(v, list) else v for k, v in pairs("tiny")[0].weights.items()}
+    n_lm, n_out, d = w["lm_head"].numel(), rows * shape.vocab, shape.d_model
+    arena = torch.zeros(n_lm + n_out + d + 64, dtype=torch.float32, device="cuda")
+    base = (-arena.data_ptr() // 4) % 32 + 16       # half a line of 128 bytes
+    lm, out, norm = arena[base:base + n_lm], arena[base + n_lm:base + n_lm + n_out], arena[base + n_lm + n_out:base + n_lm + n_out + d]
+    lm.copy_(w["lm_head"].flatten())
+    norm.copy_(w["final_norm"])
+    lm, out = lm.view(shape.vocab, d), out.view(rows, shape.vocab)
+    assert out.data_ptr() % 128 == 64 and norm.data_ptr() % 128 == 64
+    lm[0] *= 20.0        # one of these is the largest logit of nearly every row
+    lm[-1] *= 20.0
+    w["lm_head"], w["final_norm"] = lm, norm
+    model = B.Model(shape, w, max_window=8, max_positions=64)
+    kv = B.KVCache(model, 64)
+    model.profile(True)
+    seen = set()
+    for i in range(400):
+        kv.truncate(20)
+        _, _, preds = B.verify(model, kv, synth.random_tokens(shape.vocab, rows, 1000 + i), B.APPEND, want_predicts=True, out_logits=out)
+        assert preds == out.argmax(1).tolist(), i
+        seen |= set(preds)
+    assert one_launch(model) and {0, shape.vocab - 1} <= seen
