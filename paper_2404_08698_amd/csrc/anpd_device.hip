@@ -40,17 +40,20 @@ int kv_dim_of(const anpd_model_cfg &c) { return kv_heads_of(c) * c.head_dim; }
 // Work items of a phase beyond the first 32, which is what an XCD's compute units hold at a time, in rounds of 32.
 int small_rounds(int items) { return (items + 31) / 32 - 1; }
 // Whether a window of so many rows and splits of the keys goes through a model as one launch on one XCD (anpd_small.h): as long as a
-// layer's phases take no more than one round besides the five that they are, and the LM head no more than one per layer.
-// us, separate launches -> one, 5 rows (d 256, FFN 688, vocabulary 1024): 2 layers, 128 cached positions 102 -> 84, 500 103 -> 91, 1000
-// 106 -> 105 (an extra round more per layer; 2000 112 -> 135); 8 layers 258 -> 199; 17 rows at 128 / 500 121 -> 104 / 122 -> 130
-// (the second with two extra rounds); d 384, FFN 1024 at 128 / 500 109 -> 107 / 110 -> 120 (two, three); d 512 114 -> 130;
-// vocabulary 32000 117 -> 237.
+// layer's phases take no round besides the five that they are (one more up to d 384, 320 beyond 16 rows, where a round is short) and the LM
+// head no more than one per layer.
+// us of a step with the truncation in front of it, separate launches -> one; 5 rows at 128 positions, 2 layers, vocabulary 1024 unless said:
+// d 256, FFN 688 97 -> 82, at 450 (one extra round) 97 -> 86, 32 rows 120 -> 108, 8 layers 255 -> 197, with vocabulary 4608 (eight more for
+// the LM head) 260 -> 220.  d 320, FFN 1024 (one) 103 -> 97, 32 rows 131 -> 128.  d 384, FFN 512 (one) 99 -> 93; 8 layers, vocabulary
+// 4608, 16 / 17 / 32 rows at 8 positions 287 -> 275, 341 -> 342, 354 -> 365.  d 448, FFN 512, one key / value head (none) 100 -> 90, seven
+// (one) 101 -> 99, 17 rows at 8 positions 121 -> 124.  d 512, FFN 512, two key / value heads (none) 100 -> 94, eight (one) 101 -> 104, 32 rows
+// at 8 positions 125 -> 138.  Two rounds: d 256, 17 rows at 500 122 -> 130; more for the LM head: vocabulary 32000 117 -> 237.
 bool small_step(const anpd_model_cfg &c, int rows, int splits)
 {
     const int rt = rows > 16 ? 2 : 1;
     const int extra = small_rounds((c.n_heads + 2 * (c.n_kv_heads > 0 ? c.n_kv_heads : c.n_heads)) * (c.head_dim / 32)) + small_rounds(c.n_heads * splits * rt) +
                       2 * small_rounds(c.d_model / 16) + small_rounds(c.d_ffn / 16);
-    return rows <= kMaxRows && splits <= 8 && extra <= 1 && small_rounds(c.vocab / 16) <= c.n_layers;
+    return rows <= kMaxRows && splits <= 8 && extra <= (c.d_model <= (rt == 1 ? 384 : 320) ? 1 : 0) && small_rounds(c.vocab / 16) <= c.n_layers;
 }
 bool small_model(const anpd_model_cfg &c) { return c.dtype == ANPD_F32 && c.gemm_path == ANPD_GEMM_AUTO && small_step(c, 1, 1); }
 

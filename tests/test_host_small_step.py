@@ -21,8 +21,9 @@ def run(stub, name, *args, blocks=32, env=()):
     assert r.returncode == 0, r.stdout + r.stderr
 
 
-def child_route(d, heads, dh, ffn, vocab, path, length, rows, taken):
-    h = Host(d=int(d), heads=int(heads), dh=int(dh), ffn=int(ffn), vocab=int(vocab), dtype="f32", path=int(path), layers=2, max_positions=1200)
+def child_route(d, heads, dh, ffn, vocab, path, length, rows, taken, kv_heads=0):
+    h = Host(d=int(d), heads=int(heads), dh=int(dh), ffn=int(ffn), vocab=int(vocab), dtype="f32", path=int(path), layers=2, max_positions=1200,
+             kv_heads=int(kv_heads))
     kv = h.cache(1200, int(length))
     h.stub.stub_forget()
     h.ok(h.verify(kv, int(rows), None))
@@ -44,6 +45,16 @@ def child_route(d, heads, dh, ffn, vocab, path, length, rows, taken):
 ])
 def test_which_steps_are_one_launch_and_what_a_step_that_was_not_done_becomes(stub, d, heads, dh, ffn, vocab, path, length, rows, taken, blocks):
     run(stub, "child_route", d, heads, dh, ffn, vocab, path, length, rows, taken, blocks=blocks)
+
+
+# an extra round of work items in a layer: up to d 384, 320 beyond 16 rows (more keys, more features, more key / value heads than 32 blocks take)
+@pytest.mark.parametrize("d,heads,dh,ffn,kv_heads,length,rows,taken", [
+    (320, 5, 64, 1024, 0, 128, 32, 1), (384, 6, 64, 512, 0, 128, 16, 1), (384, 6, 64, 512, 0, 8, 17, 0), (448, 7, 64, 512, 1, 128, 5, 1),
+    (448, 7, 64, 512, 0, 128, 5, 0), (512, 8, 64, 512, 2, 128, 16, 1), (512, 8, 64, 512, 2, 251, 5, 1), (512, 8, 64, 512, 2, 252, 5, 0),
+    (512, 8, 64, 512, 2, 128, 17, 0), (512, 8, 64, 512, 0, 128, 5, 0), (512, 8, 64, 528, 2, 128, 5, 0), (512, 4, 128, 512, 2, 450, 16, 1),
+])
+def test_an_extra_round_where_rounds_are_short(stub, d, heads, dh, ffn, kv_heads, length, rows, taken):
+    run(stub, "child_route", d, heads, dh, ffn, 1024, 0, length, rows, taken, kv_heads)
 
 
 def child_prompt():
