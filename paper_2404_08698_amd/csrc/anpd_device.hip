@@ -1333,16 +1333,22 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
 }
 
 // Left to itself (AUTO) a model below d 2048 takes separate launches: what the one kernel hides in longer phases, the first weights of
-// the next one, is not worth its barriers there.  us, one kernel -> launches, 8 layers unless said: d 256, 2 layers, 1 / 8 rows at 200
-// positions 120 -> 86, 123 -> 87, tree of 7 rows 126 -> 93, 2 sequences x 4 rows 146 -> 114, 8 x 1 258 -> 222; d 512 326 -> 235; d 1024
-// 357 -> 298, 8 x 1 512 -> 445; d 1920 425 -> 392, at 1500 positions 454 -> 437 (d 2048 434 -> 408, d 3072 537 -> 584).
+// the next one, is not worth its barriers there.  us, one kernel -> launches, 8 layers, 1 row at 512 / 2048 / 4000 positions: d 1024 357 -> 303,
+// 388 -> 334, 391 -> 337; d 1536 385 -> 343, 417 -> 379, 421 -> 389; d 1920 414 -> 385, 445 -> 425, 452 -> 436 (8 rows within 1 % of that;
+// tree of 7 rows / 2 sequences x 4 rows at 512: d 1024 367 -> 310 / 388 -> 334, d 1920 429 -> 410 / 454 -> 439).  d 256, 2 layers, 1 / 8 rows at
+// 200 120 -> 86, 123 -> 87.  Further up the two forms are close, and such models keep the one kernel, though it is the slower form up to
+// d 2304: d 2048 421 -> 405, 457 -> 447, 467 -> 456; d 2304 444 -> 435, 479 -> 481, 534 -> 506; d 2432 467 -> 472, 498 -> 509, 556 -> 538; d 2560
+// 472 -> 476, 507 -> 521, 563 -> 552; d 3072 521 -> 565, 594 -> 612, 616 -> 646 (grouped heads 1 to 3 % to the launches' side of these).
 bool one_kernel_asked(const anpd_model &m) { return m.cfg.gemm_path != ANPD_GEMM_AUTO || m.trace; }   // by name, or by a trace of its barriers
 bool one_kernel_taken(const anpd_model &m) { return m.mega && (one_kernel_asked(m) || m.cfg.d_model >= 2048); }
-// Windows of 9 to 16 rows, whose GEMMs have a tile per wave as separate launches: the one kernel is the faster form only where few
-// key / value heads leave attention's launch little to do.  us, 8 layers, 9 rows at 64 / 512 / 2048 / 4000 positions, one kernel ->
-// launches: 7B shape 892 -> 846, 893 -> 858, 998 -> 917, 1038 -> 1018; d 3072 691 -> 621, 687 -> 624, 799 -> 686, 824 -> 727; d 2048
-// 547 -> 449, 550 -> 451, 605 -> 490, 616 -> 522; ChatGLM3 shape 961 -> 951, 948 -> 963, 1043 -> 1010, 1052 -> 1045 (16 rows 970 -> 969,
-// 959 -> 982, 1054 -> 1027, 1066 -> 1067).
+// Windows of 9 to 16 rows, whose GEMMs have a tile per wave as separate launches: those are the faster form, us, one kernel -> launches, 8
+// layers, 9 rows at 64 / 512 / 1000 / 2048 / 4000 positions: 7B shape 883 -> 839, 884 -> 852, 894 -> 868, 988 -> 908, 1029 -> 1005; d 3072
+// 666 -> 600, 661 -> 603, 663 -> 621, 772 -> 671, 798 -> 709 (eight key / value heads 657 -> 603, 656 -> 609, 654 -> 624, 758 -> 670, 765 -> 698);
+// d 2048 529 -> 435, 532 -> 436, 536 -> 441, 585 -> 481, 595 -> 513.  Where key / value heads are few, d is above 3072 and the positions are
+// no more than 1024, attention's launch has little to do and the two are level, which is where the one kernel stays: ChatGLM3 shape 955 -> 931,
+// 943 -> 941, 953 -> 948 (16 rows 964 -> 953, 954 -> 967, 964 -> 977); d 4096 with four of them 915 -> 882, 905 -> 894, 910 -> 905 (924 -> 899,
+// 915 -> 912, 923 -> 925), with eight 929 -> 899, 925 -> 910, 928 -> 923 (938 -> 919, 936 -> 934, 938 -> 946); beyond, at 2048 / 4000, ChatGLM3 shape
+// 1036 -> 989, 1043 -> 1020, eight 1024 -> 962, 1043 -> 1055 (16 rows 1034 -> 984, 1056 -> 1083).
 bool one_kernel_rows16(const anpd_model &m, int positions)
 {
     return one_kernel_asked(m) || (m.cfg.d_model > 3072 && kv_heads_of(m.cfg) < m.cfg.n_heads && n_splits_of(positions) <= kSmallSplits);
