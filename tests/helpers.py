@@ -44,3 +44,9 @@ def seed_kv_both(shape, dec, kv, n_tokens, seed):
         kv.write(layer, 0, k.float().cuda().contiguous(), v.float().cuda().contiguous())
     dec.set_length(n_tokens)
     kv.truncate(n_tokens)
+
+
+def ran_as_one_kernel(model):
+    """Whether every step since model.profile(True) was one launch."""
+    p = model.profile_read()
+    return p["intervals"]["step"] == p["steps"] > 0

@@ -7,7 +7,7 @@ import torch
 from oracle import decoder as od
 from paper_2404_08698_amd import binding as B
 from paper_2404_08698_amd import synth
-from helpers import TOL, gpu_logits, to_cuda
+from helpers import TOL, gpu_logits, ran_as_one_kernel, to_cuda
 
 pytestmark = pytest.mark.gpu
 
@@ -83,12 +83,12 @@ def test_thirty_two_sequences_decoding_one_token_each():
 
 
 def test_eight_rows_or_fewer_run_in_the_persistent_kernel_with_the_same_bits():
-    """Batches of at most 8 rows take the one-kernel form of the step; a model built for separate launches
-    takes the fused launches.  Same results, bit for bit, over several decoding steps with lengths that
+    """Batches of at most 8 rows in the one-kernel form of the step, which is asked for by name (a model of this width takes separate
+    launches when left to itself); a model built for separate launches takes the fused launches.  Same results, bit for bit, over several decoding steps with lengths that
     cross a page and an attention split."""
     shape = synth.MID_BF16
     w = synth.make_weights(shape, 55, device="cuda")
-    one = B.Model(shape, w, max_window=8, max_positions=400)
+    one = B.Model(shape, w, max_window=8, max_positions=400, gemm_path=B.GEMM_MFMA)
     many = B.Model(shape, w, max_window=8, max_positions=400, gemm_path=B.GEMM_MFMA_LAUNCHES)
     lengths = [125, 15, 260, 1, 127, 64, 31, 200]
     state = []
@@ -100,6 +100,7 @@ def test_eight_rows_or_fewer_run_in_the_persistent_kernel_with_the_same_bits():
             kvs.append(kv)
         state.append((model, kvs, cur))
     assert state[0][2] == state[1][2]
+    one.profile(True)
     bufs = [torch.empty(8, shape.vocab, dtype=torch.float32, device="cuda") for _ in range(2)]
     for step in range(5):
         outs = []
@@ -116,6 +117,7 @@ def test_eight_rows_or_fewer_run_in_the_persistent_kernel_with_the_same_bits():
         res = B.verify_batch(model, kvs[:3], wins, out_logits=buf)
         state[state.index((model, kvs, cur))] = (model, kvs, res)
     assert state[0][2] == state[1][2] and torch.equal(bufs[0], bufs[1])
+    assert ran_as_one_kernel(one)
     for layer in range(shape.n_layers):
         for a, b, n in zip(state[0][1], state[1][1], lengths):
             ka, va = a.read(layer, 0, a.length)

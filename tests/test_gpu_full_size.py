@@ -10,7 +10,7 @@ from oracle import anpd as oanpd
 from oracle import decoder as od
 from paper_2404_08698_amd import binding as B
 from paper_2404_08698_amd import synth
-from helpers import TOL, top2_gap
+from helpers import TOL, ran_as_one_kernel, top2_gap
 
 pytestmark = pytest.mark.gpu
 
@@ -89,9 +89,12 @@ def test_llama7b_step_in_the_bench_configuration():
     dec.set_length(L + 1)
     _check_cache_rows(shape, dec, kv, L, 1, (0, shape.n_layers // 2, shape.n_layers - 1))
 
-    # windows of 9 and 16 rows (one kernel, two operand fragments) and of 17 (separate launches, four):
-    # against the oracle, row for row the bits of the widest window, and 9 / 16 rows also against the
-    # one-launch-per-operation path
+    # windows of 9, 16 and 17 rows (separate launches): against the oracle, row for row the bits of the widest window; 9 and 16
+    # rows also in the one kernel (two operand fragments), which is asked for by name, against the one-launch-per-operation path
+    model_k = B.Model(shape, w, max_window=32, max_positions=L + 64, gemm_path=B.GEMM_MFMA)
+    kv_k = B.KVCache(model_k, L + 64)
+    _seed_both(shape, dec, [kv_k], L, seed=7)
+    model_k.profile(True)
     wide = synth.random_tokens(shape.vocab, 17, 21)
     dec.set_length(L)
     ref = dec.forward(wide)
@@ -112,6 +115,10 @@ def test_llama7b_step_in_the_bench_configuration():
             kv_l.truncate(L)
             _, _, preds_l, got_l = _step_logits(model_l, kv_l, wide[:M])
             assert torch.equal(got, got_l) and preds == preds_l, M
+            kv_k.truncate(L)
+            _, _, preds_k, got_k = _step_logits(model_k, kv_k, wide[:M])
+            assert torch.equal(got_k, got_l) and preds_k == preds_l, M
+    assert ran_as_one_kernel(model_k)
 
 
 def test_llama13b_step_at_full_depth():
@@ -153,20 +160,24 @@ def test_llama13b_step_at_full_depth():
 
 def test_llama7b_long_context_in_permuted_pages():
     """The long-context workload's own shape: 7B, 3584 cached positions in 16-token pages handed out in a
-    scrambled order, windows of 17 rows (its k + 1; separate launches), 16 and 9 (one kernel, two operand
-    fragments), 8 and 1 (one kernel).  Every size against the oracle; rows agree bit for bit across sizes."""
+    scrambled order, windows of 17 rows (its k + 1; separate launches), 16 and 9 (separate launches, and the one kernel
+    with two operand fragments, asked for by name), 8 and 1 (one kernel).  Every size against the oracle; rows agree bit for bit
+    across sizes and forms."""
     shape = synth.LLAMA_7B
     L = 3584
     w = synth.make_weights(shape, 2, device="cuda")
     model = B.Model(shape, w, max_window=32, max_positions=L + 64)
-    kv = B.KVCache(model, L + 64)
+    model_k = B.Model(shape, w, max_window=16, max_positions=L + 64, gemm_path=B.GEMM_MFMA)
+    kv, kv_k = B.KVCache(model, L + 64), B.KVCache(model_k, L + 64)
     n = kv.num_pages
-    kv.set_page_order([(37 * i + 11) % n for i in range(n)])
+    for cache in (kv, kv_k):
+        cache.set_page_order([(37 * i + 11) % n for i in range(n)])
     w_host = {k_: ([t.cpu() for t in v] if isinstance(v, list) else v.cpu()) for k_, v in w.items()}
     dec = od.Decoder(shape, w_host, L + 64)
-    _seed_both(shape, dec, [kv], L, seed=9)
+    _seed_both(shape, dec, [kv, kv_k], L, seed=9)
     window = synth.random_tokens(shape.vocab, 17, 13)
     ref = dec.forward(window)
+    model_k.profile(True)
     full = None
     for M in (17, 16, 9, 8, 1):
         kv.truncate(L)
@@ -181,6 +192,10 @@ def test_llama7b_long_context_in_permuted_pages():
             full = got
         else:
             assert torch.equal(got, full[:M]), M
+        if M in (16, 9):
+            kv_k.truncate(L)
+            assert torch.equal(_step_logits(model_k, kv_k, window[:M])[3], got), M
+    assert ran_as_one_kernel(model_k)
     dec.set_length(L + 1)
     _check_cache_rows(shape, dec, kv, L, 1, (0, shape.n_layers - 1))
 
@@ -361,7 +376,7 @@ def test_phases_of_one_two_and_three_items_per_block():
 
 
 def test_two_fragment_windows_repeat_their_bits_after_other_steps():
-    """Windows of 9 to 15 rows run the one-kernel step with two operand fragments of which the second is partly
+    """Windows of 9 to 15 rows, in the one-kernel step (asked for by name), have two operand fragments of which the second is partly
     filled.  Their bits must not depend on what ran before: every repetition, after a 17-row step (separate
     launches) or a 16-row step (the same kernel) on the same model, equals the one-launch-per-operation path.
     (A step that read its LDS copy of the operand before the copy had arrived got one tile in some ten
@@ -369,7 +384,7 @@ def test_two_fragment_windows_repeat_their_bits_after_other_steps():
     shape = synth.LLAMA_7B
     L = 512
     w = synth.make_weights(shape, 2, device="cuda")
-    model = B.Model(shape, w, max_window=32, max_positions=L + 64)
+    model = B.Model(shape, w, max_window=32, max_positions=L + 64, gemm_path=B.GEMM_MFMA)
     model_l = B.Model(shape, w, max_window=32, max_positions=L + 64, gemm_path=B.GEMM_MFMA_LAUNCHES)
     kv, kv_l = B.KVCache(model, L + 64), B.KVCache(model_l, L + 64)
     for layer in range(shape.n_layers):
@@ -389,5 +404,7 @@ def test_two_fragment_windows_repeat_their_bits_after_other_steps():
         want = run(model_l, kv_l, M)
         for it in range(24):
             run(model, kv, 17 if it % 2 == 0 else 16)
+            model.profile(True)
             got = run(model, kv, M)
-            assert torch.equal(got, want), (M, it)
+            assert torch.equal(got, want) and ran_as_one_kernel(model), (M, it)
+            model.profile(False)

@@ -11,7 +11,7 @@ from oracle import decoder as od
 from oracle import anpd as oanpd
 from paper_2404_08698_amd import binding as B
 from paper_2404_08698_amd import synth
-from helpers import TOL, gpu_logits, make_pair, seed_kv_both, top2_gap
+from helpers import TOL, gpu_logits, make_pair, ran_as_one_kernel, seed_kv_both, top2_gap
 
 pytestmark = pytest.mark.gpu
 
@@ -58,16 +58,18 @@ def test_windows_of_every_class_match_the_oracle(shape_name, tol):
 def test_one_kernel_step_equals_one_launch_per_operation(shape_name):
     shape = getattr(synth, shape_name)
     w = synth.make_weights(shape, 45, device="cuda")
-    model = B.Model(shape, w, max_window=8, max_positions=300)
+    model = B.Model(shape, w, max_window=8, max_positions=300, gemm_path=B.GEMM_MFMA)
     model_l = B.Model(shape, w, max_window=8, max_positions=300, gemm_path=B.GEMM_MFMA_LAUNCHES)
     kv, kv_l = B.KVCache(model, 300), B.KVCache(model_l, 300)
     prompt = synth.markov_stream(shape.vocab, 140, 0.3, 4, 12, 12)
     assert B.prefill(model, kv, prompt) == B.prefill(model_l, kv_l, prompt)
+    model.profile(True)
     for M in (1, 5, 8):
         window = synth.random_tokens(shape.vocab, M, 60 + M)
         a1, n1, p1, l1 = gpu_logits(model, kv, window)
         a2, n2, p2, l2 = gpu_logits(model_l, kv_l, window)
         assert (a1, n1, p1) == (a2, n2, p2) and np.array_equal(l1, l2)
+    assert ran_as_one_kernel(model)
 
 
 @pytest.mark.parametrize("shape_name,tol", SHAPES)

@@ -9,7 +9,7 @@ from oracle import anpd as oanpd
 from oracle import decoder as od
 from paper_2404_08698_amd import binding as B
 from paper_2404_08698_amd import synth
-from helpers import TOL, gpu_logits, make_pair, top2_gap
+from helpers import TOL, gpu_logits, make_pair, ran_as_one_kernel, top2_gap
 
 pytestmark = pytest.mark.gpu
 
@@ -25,12 +25,12 @@ def _tree_logits(model, kv, window, parent):
     return a, nxt, path, preds, buf.cpu().numpy().astype(np.float64)
 
 
-@pytest.mark.parametrize("rows", [11, 8])   # 8 rows: the one-kernel step in its draft-tree form (bf16 shapes)
+@pytest.mark.parametrize("rows", [11, 8])   # 8 rows: the one-kernel step in its draft-tree form (bf16 shapes; asked for by name)
 @pytest.mark.parametrize("shape_name,tol", [("TINY", "f32"), ("TINY_BF16", "bf16"), ("MID_BF16", "bf16")])
 def test_tree_rows_match_their_linear_windows(shape_name, tol, rows):
     shape = getattr(synth, shape_name)
     L = 45   # not a multiple of the page size
-    dec, model, kv = make_pair(shape, 31, 160)
+    dec, model, kv = make_pair(shape, 31, 160, gemm_path=B.GEMM_MFMA if tol == "bf16" else B.GEMM_AUTO)
     prompt = synth.markov_stream(shape.vocab, L, 0.3, 4, 12, 9)
     dec.prefill(prompt)
     B.prefill(model, kv, prompt)
@@ -50,7 +50,9 @@ def test_tree_rows_match_their_linear_windows(shape_name, tol, rows):
         window = [root, g[0], wrong(g[1]), wrong(g[0]), g[0], g[1], g[2], wrong(g[3])]
         parent = [-1,   0,    1,           0,           0,    4,    5,    6]
     ref = _oracle_tree_logits(dec, window, parent)
+    model.profile(True)
     a, nxt, path, preds, got = _tree_logits(model, kv, window, parent)
+    assert tol != "bf16" or ran_as_one_kernel(model) == (rows == 8)
     err = float(np.max(np.abs(got - ref)))
     assert err < TOL[tol], err
     clear = all(top2_gap(ref[r]) > TOL[tol] for r in range(len(window)))
@@ -78,10 +80,11 @@ def test_tree_rows_match_their_linear_windows(shape_name, tol, rows):
     assert float(np.max(np.abs(have - want))) < TOL[tol]
 
 
-def test_a_chain_is_bit_identical_to_the_linear_step():
+@pytest.mark.parametrize("path", [B.GEMM_AUTO, B.GEMM_MFMA])   # separate launches; the one kernel up to 8 rows (16 in a chain)
+def test_a_chain_is_bit_identical_to_the_linear_step(path):
     shape = synth.MID_BF16
     w = synth.make_weights(shape, 32, device="cuda")
-    model = B.Model(shape, w, max_window=32, max_positions=200)
+    model = B.Model(shape, w, max_window=32, max_positions=200, gemm_path=path)
     kv_a, kv_b = B.KVCache(model, 200), B.KVCache(model, 200)
     prompt = synth.markov_stream(shape.vocab, 70, 0.3, 4, 12, 10)
     c = B.prefill(model, kv_a, prompt)
@@ -91,8 +94,8 @@ def test_a_chain_is_bit_identical_to_the_linear_step():
         kv_a.truncate(70)
         kv_b.truncate(70)
         a1, n1, p1, lin = gpu_logits(model, kv_a, window)
-        a2, n2, path, p2, tree = _tree_logits(model, kv_b, window, list(range(-1, n - 1)))
-        assert (a1, n1, p1) == (a2, n2, p2) and path == list(range(a2 + 1))
+        a2, n2, rows, p2, tree = _tree_logits(model, kv_b, window, list(range(-1, n - 1)))
+        assert (a1, n1, p1) == (a2, n2, p2) and rows == list(range(a2 + 1))
         assert np.array_equal(lin, tree)
         assert kv_a.length == kv_b.length
         for layer in range(shape.n_layers):
