@@ -1786,7 +1786,7 @@ int32_t anpd_verify(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, int32
     if (logits.elsewhere())
         HIP_TRY(hipMemcpyAsync(out_logits, logits.at, sizeof(float) * (size_t)n_window * m->cfg.vocab, hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
-    if (barrier_gave_up(m, st)) return fail(ANPD_E_HIP, "anpd_verify: the persistent kernel timed out at a grid barrier");
+    if (barrier_gave_up(m, st)) return fail(ANPD_E_HIP, "anpd_verify: a wait inside the step's kernel timed out");
     if (small_missed(m)) return anpd_verify(m, kv, window, n_window, mode, out_accepted, out_next, out_predicts, out_logits, stream);
     collect_marks(m);
     *out_accepted = res[0];
@@ -1847,7 +1847,7 @@ int32_t anpd_verify_tree(anpd_model_t *m, anpd_kv_t *kv, const int32_t *window, 
     if (logits.elsewhere())
         HIP_TRY(hipMemcpyAsync(out_logits, logits.at, sizeof(float) * (size_t)n_window * m->cfg.vocab, hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
-    if (barrier_gave_up(m, st)) return fail(ANPD_E_HIP, "anpd_verify_tree: the persistent kernel timed out at a grid barrier");
+    if (barrier_gave_up(m, st)) return fail(ANPD_E_HIP, "anpd_verify_tree: a wait inside the step's kernel timed out");
     if (small_missed(m)) return anpd_verify_tree(m, kv, window, parent, n_window, out_accepted, out_next, out_path, out_predicts, out_logits, stream);
     collect_marks(m);
     *out_accepted = res[0];
@@ -1952,7 +1952,7 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
     if (logits.elsewhere())
         HIP_TRY(hipMemcpyAsync(out_logits, logits.at, sizeof(float) * (size_t)total * m->cfg.vocab, hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
-    if (one_kernel && barrier_gave_up(m, st)) return fail(ANPD_E_HIP, "anpd_verify_batch: the persistent kernel timed out at a grid barrier");
+    if (one_kernel && barrier_gave_up(m, st)) return fail(ANPD_E_HIP, "anpd_verify_batch: a wait inside the step's kernel timed out");
     collect_marks(m);
     for (int s = 0; s < n_seq; ++s) {
         out_accepted[s] = res[2 * s];
@@ -2007,7 +2007,7 @@ int32_t anpd_prefill(anpd_model_t *m, anpd_kv_t *kv, const int32_t *tokens, int3
             }
             if (logits.elsewhere()) HIP_TRY(hipMemcpyAsync(out_logits, logits.at, V * sizeof(float), hipMemcpyDeviceToDevice, st));
             HIP_TRY(hipStreamSynchronize(st));
-            return barrier_gave_up(m, st) ? fail(ANPD_E_HIP, "anpd_prefill: a wait inside the kernel timed out") : ANPD_OK;
+            return barrier_gave_up(m, st) ? fail(ANPD_E_HIP, "anpd_prefill: a wait inside the step's kernel timed out") : ANPD_OK;
         };
         int32_t rc = pieces();
         const bool missed = rc == ANPD_OK && small_missed(m);

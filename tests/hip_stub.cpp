@@ -18,7 +18,8 @@ std::vector<Launch> g_launches;
 struct { dim3 grid, block; size_t shared; hipStream_t stream; } g_config;
 int g_fail_at = 0, g_syncs = 0;
 hipError_t g_last = hipSuccess;
-int *g_pin = nullptr;     // a model's pinned memory, where the one launch of a small model counts itself
+int *g_pin = nullptr;     // a model's pinned memory, where the one launch of a small model counts itself and says that a wait was given up
+bool g_give_up = false;   // whether the next one says so
 
 std::map<char *, Range>::iterator range_of(const void *p)
 {
@@ -44,7 +45,11 @@ hipError_t launch(const void *f, dim3 grid, dim3 block, void **args)
     // (the one kernel whose answer the library looks at: how many blocks run on each XCD, here all that there are on the third)
     if (std::getenv("STUB_XCD_BLOCKS") && g_names[f].find("xcd_census") != std::string::npos) (*(unsigned **)args[0])[2] = std::atoi(std::getenv("STUB_XCD_BLOCKS"));
     // (... and the one that counts itself there, if it is to run here)
-    if (std::getenv("STUB_SMALL_RUNS") && g_names[f].find("small_step") != std::string::npos) ++g_pin[102];
+    if (std::getenv("STUB_SMALL_RUNS") && g_names[f].find("small_step") != std::string::npos) {
+        ++g_pin[102];
+        if (g_give_up) g_pin[100] = 1;
+        g_give_up = false;
+    }
     return hipSuccess;
 }
 }  // namespace
@@ -55,6 +60,7 @@ void stub_memory(void *p, size_t n, int device) { g_memory[(char *)p] = {n, devi
 void stub_fail_launch(int nth) { g_fail_at = nth; }       // the nth launch from here on fails (0: none)
 void stub_forget(void) { g_launches.clear(); g_syncs = 0; }
 void stub_leave_error(void) { g_last = hipErrorInvalidValue; }   // as a call elsewhere in the thread leaves it
+void stub_give_up(void) { g_give_up = true; }
 int stub_launches(void) { return (int)g_launches.size(); }
 int stub_syncs(void) { return g_syncs; }
 const char *stub_name(int i) { return g_launches[(size_t)i].name.c_str(); }

@@ -122,3 +122,49 @@ def test_logits_that_share_lines_with_weights(pairs):
         assert preds == out.argmax(1).tolist(), i
         seen |= set(preds)
     assert one_launch(model) and {0, shape.vocab - 1} <= seen
+
+
+# A wait inside the launch gives up at once (its limit is set from the host; all items are still worked off, in order): the call says so, and
+# the next one, in one launch again, has the bits of a fresh step.  Keys of two splits, merged by O's blocks, and of five, merged by the
+# last of attention's.
+@pytest.mark.parametrize("length", [70, 300])
+@pytest.mark.parametrize("what", ["window", "tree", "prompt"])
+def test_a_wait_that_gives_up_is_reported_and_the_next_step_is_correct(pairs, what, length):
+    shape, model = SHAPES["tiny"], pairs("tiny")[0]
+    rows = 16 if what == "prompt" else 7
+    tokens = synth.random_tokens(shape.vocab, length + rows, 23)
+    kv = B.KVCache(model, length + rows)
+    B.prefill(model, kv, tokens[:length])
+    logits = torch.zeros(1 if what == "prompt" else rows, shape.vocab, dtype=torch.float32, device="cuda")
+
+    def call():
+        if what == "window":
+            return B.verify(model, kv, tokens[length:], B.APPEND, want_predicts=True, out_logits=logits)
+        if what == "tree":
+            return B.verify_tree(model, kv, tokens[length:], [-1, 0, 1, 0, 3, 4, 0], want_predicts=True, out_logits=logits)
+        return B.prefill(model, kv, tokens[length:], out_logits=logits[0])
+
+    def fresh():
+        logits.zero_()
+        model.profile(True)
+        done = call()
+        assert one_launch(model)
+        kept = done, logits.clone(), kv.length, [kv.read(layer, 0, kv.length) for layer in range(shape.n_layers)]
+        kv.truncate(length)
+        return kept
+
+    want = fresh()
+    for _ in range(3):
+        model.set_barrier_spin_limit(1)
+        try:
+            with pytest.raises(B.AnpdError) as e:
+                call()
+        finally:
+            model.set_barrier_spin_limit(0)
+        assert e.value.code == B.E_HIP and kv.length == length
+        kv.truncate(length)
+        for _ in range(2):
+            got = fresh()
+            assert got[0] == want[0] and torch.equal(got[1], want[1]) and got[2] == want[2]
+            for x, y in zip(got[3], want[3]):
+                assert torch.equal(x[0], y[0]) and torch.equal(x[1], y[1])

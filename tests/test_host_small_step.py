@@ -128,5 +128,25 @@ def test_a_launch_that_fails_is_reported_by_the_call_it_belongs_to(stub):
     run(stub, "child_lost_launch", env={"STUB_SMALL_RUNS": "1"})
 
 
+def child_gave_up():
+    """A wait inside the launch that is given up: the call says so, once, and the calls behind it are steps in one launch like any other."""
+    h = Host(dtype="f32", ffn=688, vocab=1024, layers=2, max_positions=300)
+    kv = h.cache(300, 20)
+    for call in calls_in_one_launch(h, kv, None):
+        for _ in range(3):
+            h.stub.stub_give_up()
+            assert call() == h.B.E_HIP and h.L.anpd_kv_length(kv) == 20
+            for _ in range(2):
+                h.ok(h.L.anpd_kv_truncate(kv, 20, None))
+                h.stub.stub_forget()
+                h.ok(call())
+                assert only_small(h), h.names()
+            h.ok(h.L.anpd_kv_truncate(kv, 20, None))
+
+
+def test_a_wait_that_was_given_up_is_reported_once(stub):
+    run(stub, "child_gave_up", env={"STUB_SMALL_RUNS": "1"})
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](*sys.argv[2:])
