@@ -610,7 +610,7 @@ int32_t run_step_generic(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int 
     }
     mark(m, ANPD_PROF_OTHER, st);
     for (int l = 0; l < c.n_layers; ++l) {
-        const bool last = piece != PIECE_NONE && l > 0 && l + 1 == c.n_layers;
+        const bool last = piece != PIECE_NONE && l + 1 == c.n_layers;
         {
             GenArgs g = gemm(x, d, m->wq[l], m->attn_norm[l], q, d);
             g.W1 = m->wk[l];
@@ -1225,9 +1225,8 @@ int32_t run_prefill_mfma(anpd_model *m, anpd_kv *kv, int P, char *pws, const Pre
     for (int l = 0; l < c.n_layers; ++l) {
         // Behind the last layer's keys and values only the last row is wanted, so everything from its queries on works on that row's
         // group alone (4 layers, 205 / 512 / 3584 rows 1116 -> 1028 us (ChatGLM3 shape), 1546 -> 1369, 10641 -> 8811; a layer's GEMMs
-        // and attention are then 0.11 ms whatever the rows: of 32 layers it saves the better part of one).  A model of one layer, which
-        // serves to run the kernels' forms on all rows, does without.
-        const int g0 = l > 0 && l + 1 == c.n_layers ? G - 1 : 0;
+        // and attention are then 0.11 ms whatever the rows: of 32 layers it saves the better part of one).
+        const int g0 = l + 1 == c.n_layers ? G - 1 : 0;
         {
             PrefillArgs a = base;
             a.Wp = (const uint4 *)(ws + L.wp_qkv[(size_t)l]);

@@ -10,7 +10,8 @@ from paper_2404_08698_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = {"bf16": dataclasses.replace(synth.TINY_BF16, n_layers=3), "f32": dataclasses.replace(synth.TINY, n_layers=3)}
+SHAPES = {"bf16": dataclasses.replace(synth.TINY_BF16, n_layers=3), "f32": dataclasses.replace(synth.TINY, n_layers=3),
+          "bf16_one_layer": dataclasses.replace(synth.TINY_BF16, n_layers=1), "f32_one_layer": dataclasses.replace(synth.TINY, n_layers=1)}
 
 
 # rows behind `before` cached ones: one row group and two, either side of the 16 groups from which the queries are a launch of their

@@ -202,12 +202,13 @@ def test_tiles_of_a_wide_window_are_spread_over_the_compute_units(stub):
 
 
 def child_prompt_attention(heads, dh, length, rows, shared):
-    h = Host(d=int(heads) * int(dh), heads=int(heads), dh=int(dh), max_positions=4200)
+    h = Host(d=int(heads) * int(dh), heads=int(heads), dh=int(dh), max_positions=4200, layers=2)
     kv = h.cache(4200, int(length))
     h.stub.stub_forget()
     h.ok(h.prefill(kv, int(rows)))
-    taken = {n for n in h.names() if "prefill_attn_kernel" in n}
-    assert len(taken) == 1 and f"prefill_attn_kernelILi{dh}ELb{shared}E" in taken.pop(), h.names()
+    first, last = [n for n in h.names() if "prefill_attn_kernel" in n]
+    assert f"prefill_attn_kernelILi{dh}ELb{shared}E" in first, h.names()
+    assert f"prefill_attn_kernelILi{dh}ELb0E" in last, h.names()     # (one row group)
 
 
 # blocks: heads x pairs of row groups; up to one per compute unit, two at head dim 64, have their query rows in registers
@@ -219,9 +220,27 @@ def test_query_rows_of_a_prompt_lie_where_its_blocks_gain_by_it(stub, heads, dh,
     in_child(stub, "child_prompt_attention", heads, dh, length, rows, shared)
 
 
+def child_last_layer(dtype, layers, rows):
+    """Blocks of attention in each layer of a prompt: all row groups, in the last layer one."""
+    h = Host(dtype=dtype, layers=int(layers), max_positions=400)
+    kv = h.cache(400)
+    h.stub.stub_forget()
+    h.ok(h.prefill(kv, int(rows)))
+    blocks = [h.stub.stub_blocks(i) for i, n in enumerate(h.names()) if "attn_kernel" in n]
+    groups, splits = -(-int(rows) // 16), -(-int(rows) // 64)
+    whole, last = (4 * -(-groups // 2), 4) if dtype == "bf16" else (4 * splits * groups, 4 * splits)
+    assert blocks == [whole] * (int(layers) - 1) + [last], blocks
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("layers", [1, 2, 3])
+def test_a_prompt_leaves_the_last_layer_with_one_row_group(stub, dtype, layers):
+    in_child(stub, "child_last_layer", dtype, layers, 200)
+
+
 def child_prompt_forms(heads, ffn, before, rows, expected, cuts):
     import re
-    h = Host(d=128 * int(heads), heads=int(heads), dh=128, ffn=int(ffn), vocab=1024, max_positions=1700)
+    h = Host(d=128 * int(heads), heads=int(heads), dh=128, ffn=int(ffn), vocab=1024, max_positions=1700, layers=2)
     kv = h.cache(1700)
     epilogue = {"1": "qkv", "2": "residual", "3": "gate_up"}
 
@@ -229,8 +248,9 @@ def child_prompt_forms(heads, ffn, before, rows, expected, cuts):
         h.ok(h.L.anpd_kv_truncate(kv, lo, None))
         h.stub.stub_forget()
         h.ok(h.prefill(kv, hi - lo))
-        found = [re.search(r"prefill_(gemm|narrow|mixed|few)_kernelILi(\d)E((?:Li\d+E)*)", k) for k in h.names()]
-        return {" ".join((m[1], epilogue[m[2]], *re.findall(r"\d+", m[3]))) for m in found if m}
+        found = [m for m in (re.search(r"prefill_(gemm|narrow|mixed|few)_kernelILi(\d)E((?:Li\d+E)*)", k) for k in h.names()) if m]
+        layer2 = [i for i, m in enumerate(found) if epilogue[m[2]] == "qkv"][1]      # (the last one: a row group alone behind its keys and values)
+        return {" ".join((m[1], epilogue[m[2]], *re.findall(r"\d+", m[3]))) for m in found[:layer2]}
     whole = forms(int(before), int(before) + int(rows))
     assert {f for f in whole if f.startswith(("narrow", "mixed"))} == set(expected.split(",")), whole
     cuts = [int(x) for x in cuts.split(",")]
