@@ -779,7 +779,19 @@ int32_t run_step_weights(anpd_model *m, anpd_kv *kv, const int32_t *tokens, int 
 struct BatchLaunch {
     int n_seq, grid_splits /* splits of the longest sequence */;
     bool decode;   // one row per sequence and sequences enough: one block per (head, sequence)
+    bool stream;   // keys and values are loaded as a stream
 };
+// Keys and values of a batch are loaded as a stream (non-temporal) where one block reads each and where they are more than the memory-side
+// cache keeps until the next step (256 MB; the line is at 384).  us, ordinary loads -> stream, by what a step reads of them in all
+// its layers: 7B shape, 8 layers, 8 sequences x 4 rows of 128 positions (159 MB) 975 -> 1001, 32 x 1 of 32 (159) 1033 -> 1052, of 64 (294) 1068 ->
+// 1077, of 128 (562) 1132 -> 1125, of 500 (2122) 1420 -> 1384, of 1000 1835 -> 1753, 16 x 2 of 1000 (2122) 1472 -> 1423; 32 layers, 32 x 1 of 500
+// 5582 -> 5359; two layers, 8 x 4 of 500 (137) 305 -> 312, 32 x 1 of 256 (275) 363 -> 364, of 500 (531) 413 -> 406; 13B shape, 8 layers, 16 x 1 of 128
+// (351) 1391 -> 1393, 4 x 8 of 500 (359) 1387 -> 1387, 32 x 1 of 128 (703) 1520 -> 1511; d 2048, 8 x 4 of 500 (275) 595 -> 604; d 512, 32 x 1 of 500
+// (265) 399 -> 404, of 1000 (527) 484 -> 465.
+bool batch_streams(const anpd_model_cfg &c, long long positions)
+{
+    return kv_heads_of(c) == c.n_heads && positions * c.n_layers * kv_dim_of(c) * 4 > 384ll << 20;
+}
 
 int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, int mode, LogitsTo &logits_to, hipStream_t st, bool tree = false,
                       const BatchLaunch *batch = nullptr)
@@ -856,17 +868,17 @@ int32_t run_step_fast(anpd_model *m, anpd_kv *kv, const StepTokens &tok, int M, 
         mark(m, ANPD_PROF_GEMM_QKV, st);
         // (n_splits <= kSmallSplits: every split of the step has one page per wave: the leaner instantiation)
         if (batch) {
-#define ANPD_ATTN_B(DH_, MAXP_, ONCE_)                                                                                     \
-    hipLaunchKernelGGL((attn_batch_kernel<DH_, MAXP_, ONCE_>), dim3(H, n_splits, batch->n_seq), dim3(kFastThreads), 0, st, \
+#define ANPD_ATTN_B(DH_, MAXP_, STREAM_)                                                                                     \
+    hipLaunchKernelGGL((attn_batch_kernel<DH_, MAXP_, STREAM_>), dim3(H, n_splits, batch->n_seq), dim3(kFastThreads), 0, st, \
                        (const uint4 *)qp, b_seqs, M, l, c.n_layers, H, Hkv, L.max_splits, scale, part, \
                        head_ctr, xp_att, cls)
-#define ANPD_ATTN_O(DH_, MAXP_) do { if (H == Hkv) ANPD_ATTN_B(DH_, MAXP_, true); else ANPD_ATTN_B(DH_, MAXP_, false); } while (0)
+#define ANPD_ATTN_O(DH_, MAXP_) do { if (batch->stream) ANPD_ATTN_B(DH_, MAXP_, true); else ANPD_ATTN_B(DH_, MAXP_, false); } while (0)
             if (batch->decode) {
-#define ANPD_ATTN_D(DH_, ONCE_)                                                                                            \
-    hipLaunchKernelGGL((attn_decode_kernel<DH_, ONCE_>), dim3(H, batch->n_seq), dim3(kFastThreads), 0, st, (const uint4 *)qp, b_seqs, l, c.n_layers, H, Hkv, \
+#define ANPD_ATTN_D(DH_, STREAM_)                                                                                            \
+    hipLaunchKernelGGL((attn_decode_kernel<DH_, STREAM_>), dim3(H, batch->n_seq), dim3(kFastThreads), 0, st, (const uint4 *)qp, b_seqs, l, c.n_layers, H, Hkv, \
                        scale, xp_att, cls)
-                if (dh == 128) { if (H == Hkv) ANPD_ATTN_D(128, true); else ANPD_ATTN_D(128, false); }
-                else if (H == Hkv) ANPD_ATTN_D(64, true);
+                if (dh == 128) { if (batch->stream) ANPD_ATTN_D(128, true); else ANPD_ATTN_D(128, false); }
+                else if (batch->stream) ANPD_ATTN_D(64, true);
                 else ANPD_ATTN_D(64, false);
 #undef ANPD_ATTN_D
             } else if (dh == 128) { if (one_page) ANPD_ATTN_O(128, 1); else ANPD_ATTN_O(128, kFastPages); }
@@ -1892,8 +1904,9 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
     // joint window, sequence of every row, sequences
     int32_t *row_seq = m->pin + 384;
     SeqRef *seqs = (SeqRef *)(m->pin + 512);
-    BatchLaunch bl = {n_seq, 0, false};
+    BatchLaunch bl = {n_seq, 0, false, false};
     int row = 0;
+    long long positions = 0;
     long long pages = 0, longest = 0;   // that one wave of attn_decode_kernel goes through: of all sequences, of the longest
     for (int s = 0; s < n_seq; ++s) {
         anpd_kv *kv = kvs[s];
@@ -1904,6 +1917,7 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
         seqs[s].n_rows = n_windows[s];
         const int splits = n_splits_of(kv->len + n_windows[s]);
         if (splits > bl.grid_splits) bl.grid_splits = splits;
+        positions += kv->len + n_windows[s];
         const long long walk = kv->len / (16 * kFastWaves) + 1;
         pages += walk;
         if (walk > longest) longest = walk;
@@ -1927,6 +1941,7 @@ int32_t anpd_verify_batch(anpd_model_t *m, anpd_kv_t *const *kvs, int32_t n_seq,
     const bool filled = (long long)n_seq * m->cfg.n_heads >= (bl.grid_splits <= kSmallSplits ? 2 : 3) * m->n_cu;
     const bool even = 3 * pages * m->cfg.n_heads >= (kv_heads_of(m->cfg) < m->cfg.n_heads ? 3 : 4) * longest * m->n_cu;
     bl.decode = total == n_seq && bl.grid_splits <= kDecodeSplits && filled && even;
+    bl.stream = batch_streams(m->cfg, positions);
     // At most 8 rows in all (decoding batches, short windows): the persistent kernel takes the sequences by
     // value and writes the results into the pinned buffer itself; otherwise copies and the fused launches.
     const bool one_kernel = one_kernel_taken(*m) && m->mega_batch && total <= 8;

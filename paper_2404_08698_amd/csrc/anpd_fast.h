@@ -1656,7 +1656,7 @@ __global__ __launch_bounds__(kFastThreads, 6) void attn_fast_kernel(const uint4 
 
 // Several sequences' windows in one step: block (head, split, sequence) works on that sequence's rows
 // against that sequence's cache; the last block of a (head, sequence) merges them.
-// ONCE: as in attn_decode_kernel (7B shape, 8 layers, 16 sequences x 2 rows of 512 positions 1296 -> 1270 us, 8 x 4 of 1000 1282 -> 1265).
+// ONCE: as in attn_decode_kernel (7B shape, 8 layers, 16 sequences x 2 rows of 500 / 1000 positions 1224 -> 1204, 1472 -> 1423 us).
 // head_counter: [sequence][head].   grid: (n_heads, largest number of splits of any sequence, n_seq).
 template <int DH, int MAXP, bool ONCE>
 __global__ __launch_bounds__(kFastThreads) void attn_batch_kernel(const uint4 *__restrict__ qp, const SeqRef *__restrict__ seqs,
@@ -1687,7 +1687,8 @@ __global__ __launch_bounds__(kFastThreads) void attn_batch_kernel(const uint4 *_
 // for one round trip only and then meets, reduces, stores and counts for as long (32 sequences of 512 positions,
 // 32 heads, 282 MB: 73 us there, 65 here; 4.3 TB/s).
 // ONCE: every query head has a key / value head of its own, so a page is read by one block: loads marked non-temporal (32 sequences of
-// 512 / 1000 positions, 7B shape, 8 layers 1535 -> 1480 / 1942 -> 1876 us, of 512, 13B shape, 4 layers 1064 -> 1026).
+// 500 / 1000 positions, 7B shape, 8 layers 1420 -> 1384 / 1835 -> 1753 us, 13B shape 1854 -> 1800 / 2367 -> 2254).  Where the memory-side
+// cache would have kept the pages until the next step they are the slower loads: see the rule where the kernel is launched.
 // A sequence may have up to kDecodeSplits splits (4096 positions).   grid: (n_heads, n_seq).
 constexpr int kDecodeSplits = 16;
 template <int DH, bool ONCE>

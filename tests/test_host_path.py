@@ -268,18 +268,20 @@ def test_prompts_of_wide_models_take_the_forms_they_are_tested_for(stub):
                  ",".join(str(lo) for lo, _ in cuts) + f",{cuts[-1][1]}")
 
 
-def child_route(lengths, heads, kv_heads, dh, expected):
-    lengths, heads, dh = [int(x) for x in lengths.split(",")], int(heads), int(dh)
-    h = Host(d=heads * dh, heads=heads, dh=dh, kv_heads=int(kv_heads), max_positions=4200)
+def child_route(lengths, heads, kv_heads, dh, expected, rows=1, layers=1, stream=""):
+    lengths, heads, dh, rows, layers = [int(x) for x in lengths.split(",")], int(heads), int(dh), int(rows), int(layers)
+    h = Host(d=heads * dh, heads=heads, dh=dh, kv_heads=int(kv_heads), max_positions=4200, layers=layers)
     n = len(lengths)
     kvs = [h.cache(x + 8, x) for x in lengths]
     one = C.POINTER(C.c_int32)
-    rows = [(C.c_int32 * 1)(i) for i in range(n)]
+    windows = [(C.c_int32 * rows)(*range(i, i + rows)) for i in range(n)]
     h.stub.stub_forget()
-    h.ok(h.L.anpd_verify_batch(h.model, (C.c_void_p * n)(*kvs), n, (one * n)(*[C.cast(r, one) for r in rows]), (C.c_int32 * n)(*[1] * n),
+    h.ok(h.L.anpd_verify_batch(h.model, (C.c_void_p * n)(*kvs), n, (one * n)(*[C.cast(r, one) for r in windows]), (C.c_int32 * n)(*[rows] * n),
                                h.B.VERIFY, (C.c_int32 * n)(), (C.c_int32 * n)(), None, None))
     taken = {k for k in ("attn_decode", "attn_batch", "verify_mega") if any(k in name for name in h.names())}
     assert taken == {expected}, taken
+    if stream:   # the kernels' last argument: whether keys and values are loaded as a stream
+        assert all(f"Lb{stream}EEE" in name for name in h.names() if expected in name), [k for k in h.names() if expected in k]
 
 
 # heads, key / value heads, cached tokens: enough blocks, too few, one long sequence among short ones, in between
@@ -300,6 +302,21 @@ def test_the_batches_meant_for_the_many_sequences_kernel_take_it(stub):
     for shape, lengths in G.DECODE:
         for step in (0, 1):
             in_child(stub, "child_route", ",".join(str(x + step) for x in lengths), shape.n_heads, shape.kv_heads, shape.head_dim, "attn_decode")
+
+
+# keys and values of a step in all its layers, bytes: up to 384 MiB (what the memory-side cache may keep until the next step) ordinary loads,
+# beyond a stream; with grouped heads, where several blocks read a page, ordinary loads whatever they are
+@pytest.mark.parametrize("heads,kv_heads,dh,layers,lengths,rows,route,stream", [
+    (32, 32, 64, 1, [1535] * 32, 1, "attn_decode", 0), (32, 32, 64, 1, [1535] * 31 + [1536], 1, "attn_decode", 1),
+    (32, 32, 64, 4, [383] * 32, 1, "attn_decode", 0), (32, 32, 64, 4, [383] * 31 + [384], 1, "attn_decode", 1),
+    (16, 16, 128, 3, [1022] * 16, 2, "attn_batch", 0), (16, 16, 128, 3, [1022] * 15 + [1023], 2, "attn_batch", 1),
+    (32, 32, 128, 3, [1532] * 8, 4, "attn_batch", 1), (32, 32, 128, 2, [1532] * 8, 4, "attn_batch", 0), (32, 16, 64, 8, [2000] * 32, 1, "attn_decode", 0),
+    (32, 16, 64, 8, [2000] * 16, 2, "attn_batch", 0),
+])
+def test_keys_and_values_of_a_batch_are_a_stream_where_no_cache_keeps_them(stub, heads, kv_heads, dh, layers, lengths, rows, route, stream):
+    per_position = 4 * layers * kv_heads * dh
+    assert stream == (kv_heads == heads and per_position * sum(n + rows for n in lengths) > 384 << 20)
+    in_child(stub, "child_route", ",".join(map(str, lengths)), heads, kv_heads, dh, route, rows, layers, stream)
 
 
 def child_trace(d, heads, rows):
