@@ -163,3 +163,14 @@ def test_a_store_that_a_barrier_does_not_wait_for_is_seen():
     assert _unordered([store, sums, (16, "s_waitcnt", "lgkmcnt(0)"), meet, (24, "s_endpgm", "")])
     assert _unordered([store, wait, (18, "v_mfma_f32_16x16x4_f32", "v[0:3], v1, v2, v[0:3]"), sums, meet, (24, "s_endpgm", "")])
     assert _unordered([store, sums, (12, "s_cbranch_execz", "1"), wait, meet, (24, "s_endpgm", "")])
+
+
+def test_generic_attention_waits_once_in_front_of_its_keys_and_values(kernels):
+    """The pages of a wave's keys come together; the loads behind them are all on their way before the first product waits."""
+    mine = {k: v for k, v in kernels.items() if re.search(r"\d+attn_kernelIf", k)}
+    assert len(mine) == 2
+    for k, code in mine.items():
+        first = next(i for i, c in enumerate(code) if c[1].startswith("global_load"))
+        product = next(i for i, c in enumerate(code) if c[1].startswith("v_mfma"))
+        last = max(i for i, c in enumerate(code[:product]) if c[1].startswith("global_load"))
+        assert sum(n == "s_waitcnt" and "vmcnt" in o for _, n, o in code[first:last]) == 1, k
