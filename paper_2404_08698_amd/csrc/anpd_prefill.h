@@ -558,12 +558,11 @@ __global__ __launch_bounds__((kFewWaves + kFewLoaders) * 64) void prefill_few_ke
     extern __shared__ uint4 xs[];   // [NB][DX][TG][hi | lo][64]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = (int)(blockDim.x >> 6) - kFewLoaders;
     const int n_br = (a.G - a.g0 + TG - 1) / TG;
-    int id;
-    {
-        const int n = (int)gridDim.x, per = (n + 7) / 8, rem = n % 8;
-        const int xcd = (int)blockIdx.x % 8, j = (int)blockIdx.x / 8;
-        id = (rem == 0 || xcd < rem ? xcd * per : rem * per + (xcd - rem) * (per - 1)) + j;
-    }
+    // (prefill_gemm_block's numbering without a branch: behind one, the other arguments are requested only when the grid's size is there, a
+    // round trip later.  By rocprofv3, d 1536, QKV / O and down / gate/up of 16 rows 8.3 -> 8.15, 5.6 -> 5.25, 8.8 -> 8.55 us, of 32 10.5 -> 10.1, 6.3 ->
+    // 6.1, 10.9 -> 10.5)
+    const int rem = (int)gridDim.x % 8, xcd = (int)blockIdx.x % 8;
+    int id = xcd * ((int)gridDim.x / 8) + (xcd < rem ? xcd : rem) + (int)blockIdx.x / 8;
     const int br = id % n_br;
     id /= n_br;
     const int sp = id % a.S, bt = id / a.S;

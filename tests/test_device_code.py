@@ -174,3 +174,12 @@ def test_generic_attention_waits_once_in_front_of_its_keys_and_values(kernels):
         product = next(i for i, c in enumerate(code) if c[1].startswith("v_mfma"))
         last = max(i for i, c in enumerate(code[:product]) if c[1].startswith("global_load"))
         assert sum(n == "s_waitcnt" and "vmcnt" in o for _, n, o in code[first:last]) == 1, k
+
+
+def test_gemm_of_few_rows_requests_its_arguments_together(kernels):
+    """One round trip for the grid's size and the arguments that a block finds its tiles and rows with."""
+    mine = {k: v for k, v in kernels.items() if "prefill_few_kernel" in k}
+    assert len(mine) == 9
+    for k, code in mine.items():
+        division = next(i for i, c in enumerate(code) if c[1].startswith("v_rcp_iflag"))
+        assert sum(n == "s_waitcnt" for _, n, _ in code[:division]) == 1, k
