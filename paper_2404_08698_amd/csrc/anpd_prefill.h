@@ -56,6 +56,17 @@ struct PrefillArgs {
     int n_kv_heads;
 };
 
+// Blocks are dealt to the 8 XCDs in turn, and each XCD has its own L2.  Give XCD x a contiguous
+// range of the (weights, rows) order, so that the blocks sharing a weight range, and the row
+// blocks they all stream in step, meet in one L2 instead of being fetched into several.
+// (Without a branch: behind one, the compiler requests the other arguments only when the grid's size is there, a round trip later.  By rocprofv3,
+// d 1536, QKV / O and down / gate/up of 16 rows 8.3 -> 8.15, 5.6 -> 5.25, 8.8 -> 8.55 us, of 32 10.5 -> 10.1, 6.3 -> 6.1, 10.9 -> 10.5.)
+__device__ __forceinline__ int xcd_order(int block, int n_blocks)
+{
+    const int xcd = block % 8, rem = n_blocks % 8;
+    return xcd * (n_blocks / 8) + (xcd < rem ? xcd : rem) + block / 8;
+}
+
 __host__ __device__ __forceinline__ size_t xq_offset(int nks, int m, int k, int lo)
 {
     return ((((size_t)(m >> 4) * nks + (k >> 5)) * 2 + lo) * 64 + (size_t)((k >> 3) & 3) * 16 + (m & 15)) * 8 + (k & 7);
@@ -378,15 +389,7 @@ __device__ __forceinline__ void prefill_gemm_block(const PrefillArgs &a, int blo
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wf = wave % WF, wr = wave / WF;
     const int n_br = (a.G - a.g0 + 7) / 8;
-    // Blocks are dealt to the 8 XCDs in turn, and each XCD has its own L2.  Give XCD x a contiguous
-    // range of the (weights, rows) order, so that the blocks sharing a weight range, and the row
-    // blocks they all stream in step, meet in one L2 instead of being fetched into several.
-    int id;
-    {
-        const int n = n_blocks, per = (n + 7) / 8, rem = n % 8;
-        const int xcd = block % 8, j = block / 8;
-        id = (rem == 0 || xcd < rem ? xcd * per : rem * per + (xcd - rem) * (per - 1)) + j;
-    }
+    int id = xcd_order(block, n_blocks);
     const int br = id % n_br;
     id /= n_br;
     const int sp = id % a.S, bt = id / a.S;
@@ -558,11 +561,7 @@ __global__ __launch_bounds__((kFewWaves + kFewLoaders) * 64) void prefill_few_ke
     extern __shared__ uint4 xs[];   // [NB][DX][TG][hi | lo][64]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = (int)(blockDim.x >> 6) - kFewLoaders;
     const int n_br = (a.G - a.g0 + TG - 1) / TG;
-    // (prefill_gemm_block's numbering without a branch: behind one, the other arguments are requested only when the grid's size is there, a
-    // round trip later.  By rocprofv3, d 1536, QKV / O and down / gate/up of 16 rows 8.3 -> 8.15, 5.6 -> 5.25, 8.8 -> 8.55 us, of 32 10.5 -> 10.1, 6.3 ->
-    // 6.1, 10.9 -> 10.5)
-    const int rem = (int)gridDim.x % 8, xcd = (int)blockIdx.x % 8;
-    int id = xcd * ((int)gridDim.x / 8) + (xcd < rem ? xcd : rem) + (int)blockIdx.x / 8;
+    int id = xcd_order((int)blockIdx.x, (int)gridDim.x);
     const int br = id % n_br;
     id /= n_br;
     const int sp = id % a.S, bt = id / a.S;

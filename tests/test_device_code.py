@@ -176,10 +176,11 @@ def test_generic_attention_waits_once_in_front_of_its_keys_and_values(kernels):
         assert sum(n == "s_waitcnt" and "vmcnt" in o for _, n, o in code[first:last]) == 1, k
 
 
-def test_gemm_of_few_rows_requests_its_arguments_together(kernels):
+@pytest.mark.parametrize("name,count", [("prefill_few_kernel", 9), ("prefill_gemm_kernel", 15), ("prefill_narrow_kernel", 6)])
+def test_prompt_gemms_request_their_arguments_together(kernels, name, count):
     """One round trip for the grid's size and the arguments that a block finds its tiles and rows with."""
-    mine = {k: v for k, v in kernels.items() if "prefill_few_kernel" in k}
-    assert len(mine) == 9
+    mine = {k: v for k, v in kernels.items() if name in k}
+    assert len(mine) == count
     for k, code in mine.items():
         division = next(i for i, c in enumerate(code) if c[1].startswith("v_rcp_iflag"))
         assert sum(n == "s_waitcnt" for _, n, _ in code[:division]) == 1, k
