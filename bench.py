@@ -36,7 +36,7 @@ TRAFFIC_SOURCE = "profiles/verify_step_hbm_traffic_by_workload.md"
 TRAFFIC_FROM_PROFILE = {
     "llama7b": ("one kernel", 13.779371e9 + 0.030687e9),
     "glm6b": ("one kernel", 12.316147e9 + 0.022917e9),
-    "long7b": ("one kernel", 0.85 * (15.467586e9 + 0.035323e9) + 0.15 * (16.154998e9 + 0.422860e9)),   # 85 % of the steps up to 8 rows, 15 % at 16
+    "long7b": ("one kernel", 15.467586e9 + 0.035323e9),   # its steps of up to 8 rows; those of 16 are separate launches
     "llama13b": ("gemm launches", 26.3642e9 + 0.0732e9),
 }
 
