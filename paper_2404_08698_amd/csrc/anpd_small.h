@@ -11,9 +11,9 @@
 // phase, the last of 16 to 43 items was seen 1.6 us after its stores).  Progress does not depend on which blocks run, or how many:
 // items are handed out in order, an item waits for earlier ones only, and those are held by blocks that run.  If no block at
 // all runs on that XCD, nothing is done, which the host sees by the count of completed launches.
-// Two layers, d 256, 5 rows at 128 positions: 85.2 -> 70.6 us per call, 50 of them in the kernel: 11 phases of 3 to 5 us, each the hand-over
-// (0.4 to 0.6), reading the activations (0.4; O, which merges attention's splits meanwhile, 1.6), the products (0.3 to 0.8), the
-// exchange in LDS and the epilogue (0.3 to 0.8).  Tried: two blocks per compute unit (the same; 128 registers, 15 in scratch
+// Two layers, d 256, 5 rows at 128 positions: 84.5 -> 65.8 us per call, 48 of them in the kernel: 12 phases of 2.3 to 6.3 us, each the hand-over
+// (0.2 to 0.6) and an item's own work behind it (1.5 to 2.6: reading the activations, O merging attention's splits meanwhile, products, exchange in LDS,
+// epilogue), that twice in gate/up and the LM head, which have more items than there are blocks.  Tried: two blocks per compute unit (the same; 128 registers, 15 in scratch
 // memory), the next item drawn at this one's start (held while this one waits: 76 us).
 #pragma once
 #include "anpd_kernels.h"
