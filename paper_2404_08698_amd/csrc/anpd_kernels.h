@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace anpd {
 
 typedef uint16_t bf16_t;  // bfloat16 storage
@@ -732,13 +734,22 @@ __device__ __forceinline__ void attn_gen_block(const GenAttnArgs &a, int head, i
 #pragma unroll
     for (int i = 0; i < 4; ++i) page_v[i] = page_of(key0 + 4 * kg + i);
     asm volatile("" : "+v"(page_k), "+v"(page_v[0]), "+v"(page_v[1]), "+v"(page_v[2]), "+v"(page_v[3]));
-    auto load_kv = [&](int lo, int hi) __attribute__((always_inline)) {
+    // (ONE: the window's own, which other blocks of the launch have stored, past the vector cache, as all that crosses blocks)
+    static_assert(!ONE || sizeof(KT) == 4, "ONE: fp32 caches");
+    auto load_kv = [&](int lo, int hi, auto own) __attribute__((always_inline)) {
+        constexpr bool past = ONE && decltype(own)::value;
         if (key0 + r >= lo && key0 + r < hi) {
             const KT *kr = pool + kv_offset(page_k, layer, n_layers, 0, kvh, n_kv_heads, (key0 + r) % page_tokens, page_tokens, DH) + 4 * kg;
 #pragma unroll
-            for (int c = 0; c < NC; ++c)
+            for (int c = 0; c < NC; ++c) {
+                if (past) {
+                    const uint4 v = ldc16<true>(reinterpret_cast<const uint4 *>(kr + 16 * c));
+                    kf[c][0] = __uint_as_float(v.x); kf[c][1] = __uint_as_float(v.y); kf[c][2] = __uint_as_float(v.z); kf[c][3] = __uint_as_float(v.w);
+                    continue;
+                }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) kf[c][i] = load_f32(kr, (size_t)(16 * c + i));
+            }
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -746,13 +757,13 @@ __device__ __forceinline__ void attn_gen_block(const GenAttnArgs &a, int head, i
             if (key >= lo && key < hi) {
                 const KT *vr = pool + kv_offset(page_v[i], layer, n_layers, 1, kvh, n_kv_heads, key % page_tokens, page_tokens, DH) + r;
 #pragma unroll
-                for (int c = 0; c < NC; ++c) vf[c][i] = load_f32(vr, (size_t)(16 * c));
+                for (int c = 0; c < NC; ++c) vf[c][i] = past ? ldc<true>(reinterpret_cast<const float *>(vr) + 16 * c) : load_f32(vr, (size_t)(16 * c));
             }
         }
     };
     const bool mine = !ONE || wave < WAVES;   // (a block of the one launch has more waves than this needs)
     if (ONE) {
-        if (mine) load_kv(0, L);
+        if (mine) load_kv(0, L, std::false_type());
         wait();
     }
     if (mine && m < M) {
@@ -766,7 +777,7 @@ __device__ __forceinline__ void attn_gen_block(const GenAttnArgs &a, int head, i
             for (int i = 0; i < 4; ++i) qf[c][i] = v[i];
         }
     }
-    if (mine) load_kv(ONE ? L : 0, L + M);
+    if (mine) load_kv(ONE ? L : 0, L + M, std::true_type());
     wait.publish();
     // ---- scores: lane (r, kg) has keys key0 + 4 kg + i of row m
     // (eight chains, as in the GEMM)

@@ -228,7 +228,7 @@ __global__ __launch_bounds__(512, 2) void small_step_kernel(SmallArgs /* read wh
                     for (int e = threadIdx.x; e < n_layers * 2 * hkv * DH; e += 512) {
                         const int b = e / DH, head = b % hkv, kv = (b / hkv) & 1, layer = b / (2 * hkv);
                         pool[kv_offset(to, layer, n_layers, kv, head, hkv, dst % pt, pt, DH) + e % DH] =
-                            pool[kv_offset(from, layer, n_layers, kv, head, hkv, src % pt, pt, DH) + e % DH];
+                            ldc<true>(pool + kv_offset(from, layer, n_layers, kv, head, hkv, src % pt, pt, DH) + e % DH);
                     }
                 }
             }

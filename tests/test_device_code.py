@@ -156,6 +156,17 @@ def test_small_step_meets_behind_the_rows_that_it_stores(kernels):
         assert not _unordered(code), k
 
 
+def test_small_step_reads_the_windows_keys_and_values_past_the_vector_cache(kernels):
+    """Other blocks of the launch have stored them, so none may come from a line that the compute unit holds: per 16 dimensions a lane has
+    four numbers of one key, in pieces of 8 bytes, and one of four values each."""
+    mine = {k: v for k, v in kernels.items() if "small_step_kernel" in k}
+    assert len(mine) == 4
+    for k, code in mine.items():
+        chunks = int(re.search(r"small_step_kernelILi(\d+)E", k).group(1)) // 16
+        past = [n for _, n, o in code if n.startswith("global_load") and "sc1" in o]
+        assert past.count("global_load_dwordx2") >= 2 * chunks and past.count("global_load_dword") >= 4 * chunks, (k, len(past))
+
+
 def test_a_store_that_a_barrier_does_not_wait_for_is_seen():
     store, sums, wait, meet = (0, "global_store_dwordx4", "v[8:9], v[4:7], off offset:16"), (8, "ds_write_b128", "v2, v[4:7]"), (16, "s_waitcnt", "vmcnt(0)"), (20, "s_barrier", "")
     assert not _unordered([store, sums, wait, meet, (24, "s_endpgm", "")])
